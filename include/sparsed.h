@@ -158,6 +158,21 @@ sparsed_status sparsed_select_pattern(const sparsed_tensor* q, const sparsed_ten
                                       const sparsed_exec* ex);
 
 /*
+ * The switch step in one call (Algorithm 1 nests the selection under the full-attention branch): the dense
+ * attention of sparsed_attn_dense and, from the same q and k, the pattern of sparsed_select_pattern. For bf16 inputs
+ * the attention kernel leaves the pooled scores itself (its softmax already forms every block's row sums), so
+ * Q K^T and the exponentials are computed once instead of twice; for fp32 it is the two calls in turn. Same outputs
+ * as the two calls up to fp32 summation order. Arguments and limits are those of the two calls; ex->lse_out and
+ * ex->pooled_out are optional, ex->lse_in is ignored. Needs ex->workspace; sparsed_select_workspace_bytes()
+ * always suffices.
+ */
+sparsed_status sparsed_attn_dense_select(const sparsed_tensor* q, const sparsed_tensor* k,
+                                         const sparsed_tensor* v, sparsed_tensor* out,
+                                         int32_t block_q, int32_t block_k, double rho,
+                                         sparsed_block_index* out_block_index,
+                                         const sparsed_exec* ex);
+
+/*
  * sparsed_select_pattern for callers that cannot allocate device memory or bring a workspace
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * selection, same kernels and results, with the scratch (row statistics + pooled scores) in a

@@ -25,7 +25,7 @@ EXPORTS = [
     "sparsed_status_string", "sparsed_last_error", "sparsed_version",
     "sparsed_index_fill_window", "sparsed_index_window_entries", "sparsed_probe_mfma_bf16", "sparsed_probe_valu_f32", "sparsed_probe_mix_bf16",
     "sparsed_select_pattern_isolated_tokens", "sparsed_select_tokens_workspace_bytes",
-    "sparsed_select_pattern_static", "sparsed_select_workspace_min_bytes",
+    "sparsed_select_pattern_static", "sparsed_select_workspace_min_bytes", "sparsed_attn_dense_select",
 ]
 
 
@@ -71,6 +71,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     T, I, E = ctypes.POINTER(_Tensor), ctypes.POINTER(_BlockIndex), ctypes.POINTER(_Exec)
     lib.sparsed_attn_dense.argtypes = [T, T, T, T, E]
     lib.sparsed_attn_dense.restype = ctypes.c_int
+    lib.sparsed_attn_dense_select.argtypes = [T, T, T, T, ctypes.c_int32, ctypes.c_int32, ctypes.c_double, I, E]
+    lib.sparsed_attn_dense_select.restype = ctypes.c_int
     lib.sparsed_select_pattern.argtypes = [T, T, ctypes.c_int32, ctypes.c_int32, ctypes.c_double, I, E]
     lib.sparsed_select_pattern.restype = ctypes.c_int
     lib.sparsed_select_pattern_static.argtypes = [T, T, ctypes.c_int32, ctypes.c_int32, ctypes.c_double, I, E]
@@ -270,6 +272,38 @@ def select_pattern(q, k, block_q: int, block_k: int, rho: float, lse_in=None, wo
                    index: Optional[BlockIndex] = None, stream=None, seq_lens: Optional[torch.Tensor] = None) -> BlockIndex:
     """sparsed_select_pattern: pooled post-softmax scores + per-row top-k -> CSR block index."""
     return _select(q, k, block_q, block_k, rho, None, lse_in, workspace, pooled_out, index, stream, seq_lens=seq_lens)
+
+
+def attn_dense_select(q, k, v, block_q: int, block_k: int, rho: float, out: Optional[torch.Tensor] = None, lse_out=None,
+                      workspace=None, pooled_out=None, index: Optional[BlockIndex] = None, stream=None,
+                      seq_lens: Optional[torch.Tensor] = None):
+    """sparsed_attn_dense_select: the dense step and the pattern selected from its q, k in one call. Returns (out, index)."""
+    lib = load_library()
+    B, H, L, D = q.shape
+    nqb, nkb = -(-L // block_q), -(-L // block_k)
+    if out is None:
+        out = torch.empty_like(q)
+    if index is None:
+        keep = kept_blocks(rho, nkb)
+        index = BlockIndex(torch.empty(B, H, nqb + 1, dtype=torch.int32, device=q.device),
+                           torch.empty(B, H, max(nqb * keep, 1), dtype=torch.int32, device=q.device), block_q, block_k, nkb)
+    if workspace is None:
+        workspace = torch.empty(select_workspace_bytes(q, block_q, block_k), dtype=torch.uint8, device=q.device)
+    if pooled_out is not None and (pooled_out.dtype != torch.float32 or not pooled_out.is_contiguous()
+                                   or pooled_out.numel() != B * H * nqb * nkb):
+        raise ValueError("pooled_out must be contiguous fp32 [B, Hq, nqb, nkb]")
+    if lse_out is not None and (lse_out.dtype != torch.float32 or not lse_out.is_contiguous() or lse_out.numel() != B * H * L):
+        raise ValueError("lse_out must be contiguous fp32 [B, Hq, L]")
+    if stream is not None and int(stream.cuda_stream) != int(torch.cuda.current_stream(q.device).cuda_stream):
+        for t in (workspace, index.row_ptr, index.col_idx):   # as in select_pattern
+            t.record_stream(stream)
+    ex = _Exec(_stream_ptr(stream), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+               lse_out.data_ptr() if lse_out is not None else None, None,
+               pooled_out.data_ptr() if pooled_out is not None else None, _seq_lens_ptr(seq_lens, B))
+    tq, tk, tv, to, ci = _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"), index._c()
+    _check(lib.sparsed_attn_dense_select(ctypes.byref(tq), ctypes.byref(tk), ctypes.byref(tv), ctypes.byref(to), block_q, block_k,
+                                         float(rho), ctypes.byref(ci), ctypes.byref(ex)))
+    return out, index
 
 
 STATIC_SCRATCH_BYTES = 32 << 20

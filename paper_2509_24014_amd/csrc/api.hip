@@ -353,6 +353,84 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   return SPARSED_OK;
 }
 
+// Dense attention and the pattern of one key range from the same q, k. bf16: the attention kernel leaves the pooled
+// scores; fp32: dense with its log-sum-exp, then selection with it.
+sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v, sparsed_tensor* out,
+                                 int32_t bq, int32_t bk, double rho, sparsed_block_index* ix, const sparsed_exec* ex) {
+  sparsed_status st;
+  if ((st = check_tensor(q, "q")) || (st = check_tensor(k, "k")) || (st = check_tensor(v, "v")) || (st = check_tensor(out, "out")))
+    return st;
+  if ((st = check_qk(q, k, "k")) || (st = check_qk(q, v, "v")) || (st = check_out(q, out))) return st;
+  if (k->H != v->H) return fail(SPARSED_ERR_SHAPE, "k has %d heads, v has %d", k->H, v->H);
+  if ((st = check_blocks(q, bq, bk))) return st;
+  if (!(rho > 0.0) || !(rho <= 1.0)) return fail(SPARSED_ERR_RANGE, "rho %g outside (0, 1]", rho);
+  if ((st = check_index_shape(ix, q))) return st;
+  if (ix->block_q != bq || ix->block_k != bk) return fail(SPARSED_ERR_INDEX, "block index blocks %dx%d differ from %dx%d", ix->block_q, ix->block_k, bq, bk);
+  const int nqb = ix->nqb, nkb = ix->nkb;
+  if (nkb > 8192) return fail(SPARSED_ERR_UNSUPPORTED, "more than 8192 key blocks per row (%d)", nkb);
+  const int keep = sparsed_kept_blocks(rho, nkb);
+  if ((int64_t)ix->cap_per_head < (int64_t)nqb * keep)
+    return fail(SPARSED_ERR_INDEX, "cap_per_head %d < nqb*k = %lld", ix->cap_per_head, (long long)nqb * keep);
+
+  char* ws = nullptr;
+  if (q->dtype != SPARSED_BF16) {
+    if ((st = caller_workspace(ex, select_ws_bytes(q->B, q->H, q->L, nqb, nkb), "dense step with selection", &ws))) return st;
+    sparsed_exec step = *ex;
+    if (!step.lse_out) step.lse_out = reinterpret_cast<float*>(ws);  // where the selection would put its own statistics
+    step.lse_in = step.lse_out;
+    if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step))) return st;
+    return select_impl(q, k, bq, bk, rho, 0, false, ix, &step);
+  }
+  const DensePoolShape sh = dense_pool_shape(q->B, q->H, q->L, bk);
+  const size_t apool_bytes = align256((size_t)q->B * q->H * nqb * nkb * sizeof(float));
+  const size_t need = apool_bytes + (size_t)sh.groups * sh.rows * sh.slab_cols * sizeof(float);
+  if ((st = caller_workspace(ex, need, "dense step with selection", &ws))) return st;
+  AttnArgs a{};
+  a.q = targ(q);
+  a.k = targ(k);
+  a.v = targ(v);
+  a.o = out->data;
+  a.o_sb = out->stride_b;
+  a.o_sh = out->stride_h;
+  a.o_sl = out->stride_l;
+  a.lse = ex->lse_out;
+  a.B = q->B;
+  a.Hq = q->H;
+  a.Hkv = k->H;
+  a.L = q->L;
+  a.seq_lens = ex->seq_lens;
+  a.scale_log2 = scale_log2(q->D);
+  a.nqb = nqb;
+  a.nkb = nkb;
+  a.block_q = bq;
+  a.block_k = bk;
+  a.apool = ex->pooled_out ? ex->pooled_out : reinterpret_cast<float*>(ws);
+  a.slab = reinterpret_cast<float*>(ws + apool_bytes);
+  hipError_t e = launch_attn_bf16_dense_pool(q->D, a, stream_of(ex));
+  if (e != hipSuccess) return hip_fail(e, "dense attention with pooling launch");
+  TopkArgs t{};
+  t.apool = a.apool;
+  t.row_ptr = ix->row_ptr;
+  t.col_idx = ix->col_idx;
+  t.rows = q->B * q->H * nqb;
+  t.nqb = nqb;
+  t.nkb = nkb;
+  t.split = nkb;
+  t.keep_lo = keep;
+  t.cap_per_head = ix->cap_per_head;
+  t.seq_lens = ex->seq_lens;
+  t.heads_per_batch = q->H;
+  t.block_q = bq;
+  t.block_k = bk;
+  t.L = q->L;
+  t.rho = rho;
+  t.straddle = -1;
+  t.boundary = -1;
+  e = launch_topk(t, stream_of(ex));
+  if (e != hipSuccess) return hip_fail(e, "top-k launch");
+  return SPARSED_OK;
+}
+
 // The three machine probes share one shape: check the arguments, take 512 KiB of the caller's workspace, run a short
 // warm-up launch and a timed launch of `iters` iterations on the stream, return the timed launch's milliseconds.
 template <typename Launch>
@@ -389,6 +467,12 @@ extern "C" {
 sparsed_status sparsed_attn_dense(const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v, sparsed_tensor* out,
                                   const sparsed_exec* ex) {
   return attention(Mode::kDense, q, k, v, nullptr, out, ex);
+}
+
+sparsed_status sparsed_attn_dense_select(const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v, sparsed_tensor* out,
+                                         int32_t block_q, int32_t block_k, double rho, sparsed_block_index* out_block_index,
+                                         const sparsed_exec* ex) {
+  return dense_select_impl(q, k, v, out, block_q, block_k, rho, out_block_index, ex);
 }
 
 sparsed_status sparsed_attn_sparse(const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v,

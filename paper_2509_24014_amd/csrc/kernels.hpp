@@ -25,6 +25,10 @@ struct AttnArgs {
   int32_t nqb, cap_per_head, block_k;
   int32_t n_qtiles;        // query tiles per head = ceil(L / rows per work-group)
   float scale_log2;        // log2(e) / sqrt(D)
+  // kDensePool only (nqb and block_k then describe the pooled blocks)
+  float* slab;             // scratch: one slab of (rows per work-group) x slab_cols floats per work-group of the launch
+  float* apool;            // [B, Hq, nqb, nkb] pooled scores
+  int32_t slab_cols, nkb, block_q;
 };
 
 // Arguments of the pooled-score kernels (Section 3.3: A' = avgpool(A, block)). The keys pooled are
@@ -96,7 +100,7 @@ struct WindowArgs {
   int32_t sink_blocks;  // leading key blocks that are always visible
 };
 
-enum class Mode : int { kDense = 0, kSparse = 1, kStats = 2 };
+enum class Mode : int { kDense = 0, kSparse = 1, kStats = 2, kDensePool = 3 };
 
 // Launchers. Each returns the HIP error of the launch. block_q selects the work-group shape for
 // the sparse and pooled kernels; dense and stats pick their own query tile from L.
@@ -104,6 +108,15 @@ hipError_t launch_attn_bf16(Mode mode, int D, int block_q, AttnArgs a, hipStream
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s);
 // bf16 sparse attention for query blocks of 32 or 64 rows (two waves per 32 rows, keys of a tile split between them)
 hipError_t launch_attn_bf16_splitk(int D, int block_q, const AttnArgs& a, hipStream_t s);
+// The dense call that also pools (bf16): shape of its launch for q [B, Hq, L, .] and blocks of block_q x block_k, and the
+// launch itself (a.slab of groups * rows * slab_cols floats, a.apool, a.nqb, a.nkb, a.block_q, a.block_k set by the caller).
+struct DensePoolShape {
+  int rows;       // query rows per work-group: a multiple of every block_q
+  int groups;     // persistent work-groups
+  int slab_cols;  // columns of a work-group's slab
+};
+DensePoolShape dense_pool_shape(int B, int Hq, int L, int block_k);
+hipError_t launch_attn_bf16_dense_pool(int D, AttnArgs a, hipStream_t s);
 hipError_t launch_pool_bf16(int D, int block_q, const PoolArgs& a, hipStream_t s);
 hipError_t launch_pool_f32(int D, int block_q, const PoolArgs& a, hipStream_t s);
 // Pooled scores of bf16 inputs in one pass over the keys (no row statistics needed): `groups` persistent work-groups,

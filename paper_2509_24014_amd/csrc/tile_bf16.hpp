@@ -32,6 +32,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4v;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 constexpr int kTileK = 64;  // keys per K/V tile of the bf16 kernels (a listed key block is half a tile, one tile or two)
@@ -56,6 +57,20 @@ __device__ __forceinline__ float pair_sum(float x) {
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
+// Sum of one value per lane over aligned groups of 8, 16 or 32 lanes with DPP row operations (no LDS traffic); the total
+// ends up in the last lane of each group.
+__device__ __forceinline__ float lane_group_sum_to_last(float x, int lanes) {
+#define SPARSED_DPP_ADD(CTRL, ROWS) \
+  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, true));
+  SPARSED_DPP_ADD(0x111, 0xf)                 // row_shr:1
+  SPARSED_DPP_ADD(0x112, 0xf)                 // row_shr:2
+  SPARSED_DPP_ADD(0x114, 0xf)                 // row_shr:4
+  if (lanes > 8) SPARSED_DPP_ADD(0x118, 0xf)  // row_shr:8
+  if (lanes > 16) SPARSED_DPP_ADD(0x142, 0xa) // row_bcast:15
+#undef SPARSED_DPP_ADD
   return x;
 }
 

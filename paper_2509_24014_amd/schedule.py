@@ -16,7 +16,7 @@ class SparseDLayer:
 
     ``step(q, k, v, t)`` runs step ``t`` (0-based) of a ``T``-step schedule:
     steps ``0 .. n_dense-1`` use full attention; at step ``n_dense-1`` the pattern is selected
-    from that step's Q, K (reusing the dense call's row log-sum-exp); steps ``>= n_dense`` use
+    from that step's Q, K (in the dense call itself, or reusing its row log-sum-exp); steps ``>= n_dense`` use
     sparse attention with the stored pattern.
 
     Two switches reproduce the paper's ablation rows (Table 2) on the same kernels:
@@ -36,12 +36,15 @@ class SparseDLayer:
         self._lse = None
         self._workspace = None
 
-    def _select(self, q, k, lse):
+    def _scratch(self, q):
         if self._workspace is None:
             need = binding.select_workspace_bytes(q, self.block_q, self.block_k)
             self._workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        return self._workspace
+
+    def _select(self, q, k, lse):
         self.index = binding.select_pattern(q, k, self.block_q, self.block_k, self.rho, lse_in=lse,
-                                            workspace=self._workspace, index=self.index)
+                                            workspace=self._scratch(q), index=self.index)
         self.calls["select"] += 1
 
     def step(self, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, t: int, out: Optional[torch.Tensor] = None):
@@ -51,6 +54,13 @@ class SparseDLayer:
             self._select(q, k, None)  # no dense call at this step: selection runs its own statistics pass
         if t < self.n_dense:
             switch = t == self.n_dense - 1
+            if switch and q.is_cuda and q.dtype == torch.bfloat16:
+                # bf16: the dense kernel leaves the pooled scores the selection ranks, one Q K^T for both
+                out, self.index = binding.attn_dense_select(q, k, v, self.block_q, self.block_k, self.rho, out=out,
+                                                            workspace=self._scratch(q), index=self.index)
+                self.calls["dense"] += 1
+                self.calls["select"] += 1
+                return out
             if switch and self._lse is None:
                 self._lse = torch.empty(q.shape[0], q.shape[1], q.shape[2], dtype=torch.float32, device=q.device)
             out = binding.attn_dense(q, k, v, out=out, lse_out=self._lse if switch else None)
