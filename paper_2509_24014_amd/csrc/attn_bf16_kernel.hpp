@@ -37,11 +37,15 @@ namespace sparsed {
 // block and divided by the entries that exist. Work-groups are persistent, so the slabs are bounded by the chip, not
 // by the sequence. The alternative, pooling as a pass of its own with the row log-sum-exp handed over, computes
 // Q K^T and every exponential a second time and is bound by the vector unit (16 fma, 16 exp2 and 16 adds for 8 matrix
-// instructions). @MEASURED@
+// instructions). Dense + pooling + top-k, 32 heads of 128, pass of its own against this: 4k (64 x 64) 365 -> 237 us,
+// 64k (128 x 64) 85.2 -> 54.9 ms, 2.5 % above the dense call alone.
+// What it needs in registers (the block sum in progress and one held back) is what the 256 of a lane leave over once
+// the lane number and the kernel's arguments are not kept across the tile loop (fresh_lane, fresh_kernel_args); with
+// them kept a spill reload sits in every sub-step, waits for the copies in flight and costs 12 % (62.1 ms).
 template <int D, int NQ, int NW, Mode MODE, int KB = kTileK>
 __global__ __launch_bounds__(NW * 64)
     __attribute__((amdgpu_waves_per_eu((NQ == 1 && NW >= 4) ? (MODE == Mode::kStats ? 4 : 2) : 1,
-                                       (NQ == 1 && NW >= 4) ? (MODE == Mode::kStats ? 4 : 2) : 1))) void attn_bf16_kernel(const AttnArgs a) {
+                                       (NQ == 1 && NW >= 4) ? (MODE == Mode::kStats ? 4 : 2) : 1))) void attn_bf16_kernel(const AttnArgs) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
   constexpr bool kPool = MODE == Mode::kDensePool;
   static_assert(!kPool || NQ == 1, "pooling parks one row per lane");
@@ -59,15 +63,16 @@ __global__ __launch_bounds__(NW * 64)
   __shared__ __attribute__((aligned(1024))) char vbuf1[kVBytes];
   __shared__ __attribute__((aligned(16))) float inv_z[kPool ? QT : 1];  // kPool: 1 / Z_r of the group's rows
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it in a scalar register
-  const int g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: keep it in a scalar register
 
   // kPool: persistent work-groups (group i takes the ids i, i + gridDim.x, ...; the grid is a multiple of the 8 XCDs
   // or covers every id, so an XCD keeps its contiguous range); otherwise one id per work-group
-  const int n_units = kPool ? a.B * a.Hq * a.n_qtiles : (int)gridDim.x;
   int unit = blockIdx.x;
+  int n_units = (int)gridDim.x;
   do {
+  const KernelArgs<AttnArgs>& a = fresh_kernel_args<AttnArgs>();
+  const int lane = fresh_lane();
+  if (kPool) n_units = a.B * a.Hq * a.n_qtiles;
   const int lid = xcd_remap(unit, n_units);
   const int qt = lid % a.n_qtiles;
   const int bh = lid / a.n_qtiles;
@@ -205,7 +210,7 @@ __global__ __launch_bounds__(NW * 64)
       vdma.issue(vrsrc, ub * v_tile_bytes, dst, wave);
     }
   };
-  int lane_tail = lane;
+  int lane_tail = 0;  // the tail loop's own copy of the lane number
 
   const float c = a.scale_log2;
 
@@ -220,7 +225,7 @@ __global__ __launch_bounds__(NW * 64)
   // masked: apply `valid`, the number of keys of this sub-tile that exist (32 or more = all, 0 or less =
   // none: a phantom tile or the empty half of a partial last block). Unmasked steps skip the 16 selects.
   auto mask_sub = [&](f32x16(&s)[NQ], int valid) {
-    const int mine = valid - 8 * g;  // register x of lane (j, g) holds key 16*(x/8) + 8*g + x%8 of the sub-tile
+    const int mine = valid - 8 * (fresh_lane() >> 5);  // register x of lane (j, g) holds key 16*(x/8) + 8*g + x%8 of the sub-tile
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
@@ -278,8 +283,7 @@ __global__ __launch_bounds__(NW * 64)
   float carry = 0.f, hold = 0.f;
   const __amdgpu_buffer_rsrc_t slab_rsrc = make_rsrc(kPool ? (const void*)slab : (const void*)kbase, kPool ? (int64_t)QT * a.slab_cols * 4 : 0);
   auto park_store = [&](int col, float v) {
-    int ln = lane;  // the lane's offset is worked out at each store: the main loop has no register to keep it in
-    asm volatile("" : "+v"(ln));
+    const int ln = fresh_lane();  // the main loop has no register to keep the offset in
     const int off = 4 * ((KB == 2 * kTileK ? 0 : (ln >> 5) * QT) + (ln & 31));
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), slab_rsrc, off, (col * QT + wave * 32) * 4, 0);
   };
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(NW * 64)
         const int cols = KB == kTileK / 2 ? 2 * tiles_done : KB == kTileK ? tiles_done & ~1 : tiles_done >> 1;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // this wave's parked sums have been written
         if (alpha < 1.0f)  // (not for a NaN: the row is lost anyway)
-          for (int J = g; J < cols; J += 2) slab[(int64_t)J * QT + wave * 32 + (lane & 31)] *= alpha;
+          for (int J = fresh_lane() >> 5; J < cols; J += 2) slab[(int64_t)J * QT + wave * 32 + (fresh_lane() & 31)] *= alpha;
       }
     }
     exp_sub(s, p, part);
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(NW * 64)
     if (kHasV) pv_sub<D, NQ, false>(vb_this, 0, vaddr, p_even, o);                                 \
     softmax_sub(s_odd, p_odd, part, (MASKED), valid_odd);                                          \
     sched_substep_interleave<D, NQ, kHasV>();                                                      \
-    if (overflowed(part)) re_reference(s_odd, p_odd, part, (T));                                   \
+    if (__builtin_expect(overflowed(part), 0)) re_reference(s_odd, p_odd, part, (T));              \
     SPARSED_ADD_PART                                                                               \
     if (kPool) park_tile((P), (MASKED), (T), part[0]);                                             \
     __builtin_amdgcn_sched_barrier(0);                                                             \
@@ -372,7 +376,7 @@ __global__ __launch_bounds__(NW * 64)
     if (kHasV) pv_sub<D, NQ, false>(vb_this, 1, vaddr, p_odd, o);                                  \
     softmax_sub(s_even, p_even, part, (MASKED), valid_even);                                       \
     sched_substep_interleave<D, NQ, kHasV>();                                                      \
-    if (overflowed(part)) re_reference(s_even, p_even, part, (T) + 1);                             \
+    if (__builtin_expect(overflowed(part), 0)) re_reference(s_even, p_even, part, (T) + 1);        \
     SPARSED_ADD_PART                                                                               \
     if (kPool) carry = part[0];                                                                    \
     blk0 = blk1;                                                                                   \
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(NW * 64)
       SPARSED_TILE_STEP(0, false, t);
       t += 1;
     }
-    asm volatile("" : "+v"(lane_tail));
+    lane_tail = fresh_lane();
     for (; t < n; ++t) {
       if (t & 1) {
         SPARSED_TILE_STEP(1, true, t);
@@ -444,16 +448,16 @@ __global__ __launch_bounds__(NW * 64)
   static_assert(32 * kRowBytes * 2 <= kKBytes && (!kHasV || 32 * kRowBytes * 2 <= kVBytes), "two waves share one buffer");
   // (The lane-derived values of this part are worked out afresh from an opaque copy of the lane number, so that
   // none of them is kept in a register, or spilled, across the tile loop.)
-  int lane_e = lane;
-  asm volatile("" : "+v"(lane_e));
+  const int lane_e = fresh_lane();
+  const KernelArgs<AttnArgs>& ae = fresh_kernel_args<AttnArgs>();
   const int je = lane_e & 31, ge = lane_e >> 5;
   char* const stage = ((wave >> 1) == 0 ? kbuf0 : (wave >> 1) == 1 ? kbuf1 : (wave >> 1) == 2 ? vbuf0 : vbuf1) + (wave & 1) * (32 * kRowBytes);
 #pragma unroll
   for (int nq = 0; nq < NQ; ++nq) {
     const float ltot = pair_sum(lsum[nq]);
     const int row = row0 + nq * 32 + je;
-    if (a.lse != nullptr && ge == 0 && row < L)
-      a.lse[(int64_t)bh * a.L + row] = (M[nq] + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+    if (ae.lse != nullptr && ge == 0 && row < L)
+      ae.lse[(int64_t)bh * ae.L + row] = (M[nq] + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
     if (kPool && ge == 0) inv_z[wave * 32 + je] = row < L ? 1.0f / ltot : 0.f;
     if (kHasV) {
       const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
@@ -469,13 +473,13 @@ __global__ __launch_bounds__(NW * 64)
           // columns 32*dt + 8*q4 + 4*g .. +3 of row j: slot 4*dt + q4, half g
           *reinterpret_cast<u32x2*>(stage + je * kRowBytes + (((4 * dt + q4) ^ (je & (kSlots - 1))) << 4) + 8 * ge) = w;
         }
-      __bf16* const obase = static_cast<__bf16*>(a.o) + b * a.o_sb + h * a.o_sh;
+      __bf16* const obase = static_cast<__bf16*>(ae.o) + b * ae.o_sb + h * ae.o_sh;
 #pragma unroll
       for (int it = 0; it < 32 / kRowsPerStore; ++it) {
         const int r = it * kRowsPerStore + lane_e / kSlots, slot = lane_e % kSlots;
         const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * kRowBytes + ((slot ^ (r & (kSlots - 1))) << 4));
         const int grow = row0 + nq * 32 + r;
-        if (grow < L) *reinterpret_cast<u32x4*>(obase + (int64_t)grow * a.o_sl + slot * 8) = w;  // partial last query tile: rows past L are dropped
+        if (grow < L) *reinterpret_cast<u32x4*>(obase + (int64_t)grow * ae.o_sl + slot * 8) = w;  // partial last query tile: rows past L are dropped
       }
     }
   }
@@ -486,11 +490,11 @@ __global__ __launch_bounds__(NW * 64)
     constexpr int kLanes = QT / 4, kCols = 64 / kLanes, kUnroll = 4;  // lanes per column, columns per wave load
     const int li = lane_e % kLanes, sub_col = lane_e / kLanes;
     const f32x4v w = *reinterpret_cast<const f32x4v*>(&inv_z[4 * li]);
-    const int bq = a.block_q;
+    const int bq = ae.block_q;
     const int I = qt * (QT / bq) + 4 * li / bq;
     const int rows_here = L - I * bq < bq ? L - I * bq : bq;
     const bool writes = (4 * li + 4) % bq == 0 && rows_here > 0;  // the last lane of a query block that exists
-    float* const arow = a.apool + ((int64_t)bh * a.nqb + I) * a.nkb;
+    float* const arow = ae.apool + ((int64_t)bh * ae.nqb + I) * ae.nkb;
     const int nkb_here = (L + KB - 1) / KB;
     for (int J0 = wave * (kCols * kUnroll); J0 < nkb_here; J0 += NW * kCols * kUnroll) {
       f32x4v e[kUnroll];

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(RW >= 
     logits_sub<D, 1, false>(kb_next, kh, kaddr, qf, S_NEXT);                                       \
     softmax_half(S_CUR, part, (MASKED), valid);                                                    \
     sched_substep_interleave<D, 1, false>();                                                       \
-    if (__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0) re_reference(S_CUR, part);          \
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0, 0)) re_reference(S_CUR, part);  \
     lsum += part;                                                                                  \
     __builtin_amdgcn_sched_barrier(0);                                                             \
     pv_sub<D, 1, true>(vb_this, kh, vaddr, p, o);                                                  \

@@ -159,7 +159,7 @@ void pool1p_bf16_kernel(const PoolArgs a) {
     auto expsum_sub = [&](f32x16(&s)[1], const bool masked, int valid) {
       if (masked) mask_sub(s, valid);
       float part = exp_sum(s);
-      if (__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0) {  // wave-uniform, practically never taken
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0, 0)) {  // wave-uniform, practically never taken
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");           // this wave's slab stores are complete
         re_reference(s, sub / kSubPerBlock);
         part = exp_sum(s);

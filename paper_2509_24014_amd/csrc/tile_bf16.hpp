@@ -60,6 +60,25 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// The lane number, worked out anew at every call (two vector instructions) so that it need not be kept in a register
+// across a loop that has none to spare.
+__device__ __forceinline__ int fresh_lane() {
+  uint32_t zero = 0;
+  asm volatile("" : "+s"(zero));
+  return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
+// The kernel's argument struct (its only argument), read from the argument segment at the point of the call. Reading
+// it again where it is used late keeps two dozen scalars from living, or being spilled into vector registers, in between.
+template <typename Args>
+using KernelArgs = const __attribute__((address_space(4))) Args;
+template <typename Args>
+__device__ __forceinline__ KernelArgs<Args>& fresh_kernel_args() {
+  auto p = (KernelArgs<Args>*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
 // Sum of one value per lane over aligned groups of 8, 16 or 32 lanes with DPP row operations (no LDS traffic); the total
 // ends up in the last lane of each group.
 __device__ __forceinline__ float lane_group_sum_to_last(float x, int lanes) {
