@@ -1,24 +1,36 @@
 // fp32 flash-attention forward for gfx950: dense (Eq. 1), block-sparse (Eq. 3 / Eq. 4) and the
 // statistics-only pass. fp32 inputs, fp32 matrix cores (32x32x2), fp32 softmax, fp32 output:
-// this is the path held to 1e-5 against the fp64 reference, not the throughput path.
+// this is the path held to 1e-5 against the fp64 reference.
 //
-// One work-group of NW waves owns 32*NW query rows of one (batch, head); each wave owns 32 rows.
-// Keys are walked in 32-key tiles staged through LDS (single buffer, two barriers per tile).
+// One work-group owns 32 query rows of one (batch, head); its KW waves share the rows and split the keys: wave w takes
+// the 32-key tiles w, w + KW, ... of the list with its own running maximum, sum and output accumulator, and the parts
+// are merged once, through LDS, at the end. The waves need nothing from each other in between (K and V are loaded
+// straight into registers, see tile_f32.hpp), so the tile loop has no barrier, and a short sequence still spreads over
+// many waves. A fragment of the next tile is requested as soon as the fragment it replaces has been used: every load
+// has a whole tile of matrix work (8192 cycles at head dim 128) to arrive.
+//
+// Bound: the fp32 matrix rate (157 TFLOP/s nominal). 8 heads of 2000 x 128: dense 440 -> 167 us (98 TFLOP/s), sparse
+// (64 x 64 blocks, 20 % kept) 122 -> 50 us; 2 heads of 256 x 64: dense 33 -> 12 us, sparse 18 -> 8 us. (Before: tiles staged
+// through LDS by all waves, two barriers per tile, one LDS read per matrix instruction and operand, rows not split.)
 #include "kernels.hpp"
 #include "tile_f32.hpp"
 
 namespace sparsed {
 
-template <int D, int NW, Mode MODE>
-__global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnArgs a) {
-  constexpr int NT = NW * 64;
-  constexpr int QT = 32 * NW;
+template <int D, int KW, Mode MODE>
+__global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnArgs a) {
+  constexpr int NT = KW * 64;
   constexpr bool kHasV = MODE != Mode::kStats;
-  using T = TileF32<D>;
-  __shared__ __attribute__((aligned(16))) float klds[T::kKFloats];
-  __shared__ __attribute__((aligned(16))) float vlds[kHasV ? T::kVFloats : 4];
+  constexpr int kChunks = D / 8, kV = D / 32;
+  using VRow = typename SlabF32<D>::VRow;
+  // The query fragments ([chunk][lane], 16 bytes each) and, once the keys are done, the waves' accumulators
+  // ([wave][row][32 pieces of D/32 columns], piece i of row j at position i ^ j so that neither side has bank conflicts).
+  constexpr int kQBytes = kChunks * 64 * 16, kAccBytes = kHasV ? KW * 32 * D * 4 : 16;
+  __shared__ __attribute__((aligned(16))) char lds[kQBytes > kAccBytes ? kQBytes : kAccBytes];
+  __shared__ float stat_m[KW][32], stat_l[KW][32];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 31, g = lane >> 5;
 
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
@@ -31,60 +43,85 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnArgs a) {
     const int len = a.seq_lens[b];
     L = len < a.L ? len : a.L;
   }
-  if (qt * QT >= L) return;  // a query tile wholly past the end (uniform over the work-group)
+  const int row0 = qt * 32;
+  if (row0 >= L) return;  // a query tile wholly past the end (uniform over the work-group)
 
-  const float* qbase = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
-  const float* kbase = static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh;
-  const float* vbase = kHasV ? static_cast<const float*>(a.v.ptr) + b * a.v.sb + hk * a.v.sh : nullptr;
-  const int row0 = qt * QT + wave * 32;
+  const SlabF32<D> ks{reinterpret_cast<const char*>(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh), (uint32_t)(a.k.sl * 4), L};
+  const SlabF32<D> vs{reinterpret_cast<const char*>(kHasV ? static_cast<const float*>(a.v.ptr) + b * a.v.sb + hk * a.v.sh : nullptr),
+                      (uint32_t)(a.v.sl * 4), L};
 
-  const int tiles_per_block = (MODE == Mode::kSparse) ? a.block_k / kTileKF : 1;
-  int n_tiles;
+  // tiles of the list: every 32 keys (dense), or those of the listed key blocks
+  const int tile_shift = (MODE == Mode::kSparse) ? (a.block_k == 128 ? 2 : a.block_k == 64 ? 1 : 0) : 0;
+  int n;
   const int32_t* cols = nullptr;
   if (MODE == Mode::kSparse) {
-    const int32_t* rp = a.row_ptr + (int64_t)bh * (a.nqb + 1) + qt;
+    const int32_t* rp = a.row_ptr + (int64_t)bh * (a.nqb + 1) + row0 / a.block_q;
     const int beg = rp[0], end = rp[1];
-    n_tiles = (end - beg) * tiles_per_block;
+    n = (end - beg) << tile_shift;
     cols = a.col_idx + (int64_t)bh * a.cap_per_head + beg;
   } else {
-    n_tiles = (L + kTileKF - 1) / kTileKF;
+    n = (L + kTileKF - 1) / kTileKF;
+  }
+  int opaque_zero;  // keeps the list reads on the vector path: a scalar load would share its counter with the LDS reads
+  asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
+  auto first_key = [&](int t) -> int {  // of tile t of the list; past the end: of the last one (a harmless repeat)
+    const int u = t < n ? t : n - 1;
+    if (MODE != Mode::kSparse) return u * kTileKF;
+    return cols[(u >> tile_shift) + opaque_zero] * a.block_k + (u & ((1 << tile_shift) - 1)) * kTileKF;
+  };
+
+  {  // query fragments into LDS: lane (j, g) of chunk c holds columns 8c + 4g .. + 3 of row j
+    const int row = row0 + j < L ? row0 + j : L - 1;
+    const float* qrow = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh + (int64_t)row * a.q.sl + 4 * g;
+    for (int c = wave; c < kChunks; c += KW)
+      *reinterpret_cast<f32x4*>(lds + (c * 64 + lane) * 16) = *reinterpret_cast<const f32x4*>(qrow + 8 * c);
   }
 
-  QFragF32<D> qf;
-  qf.load(qbase, row0, L, a.q.sl, lane);
-
   float M = -1e30f, lsum = 0.f;
-  f32x16 o[D / 32];
+  f32x16 o[kV];
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
     for (int x = 0; x < 16; ++x) o[dt][x] = 0.f;
-
+  f32x4 kf[kChunks];
+  VRow vf[16];
   const float c = a.scale_log2;
-  for (int t = 0; t < n_tiles; ++t) {
-    int key0;
-    if (MODE == Mode::kSparse) {
-      const int blk = __builtin_amdgcn_readfirstlane(cols[t / tiles_per_block]);
-      key0 = blk * a.block_k + (t % tiles_per_block) * kTileKF;
-    } else {
-      key0 = t * kTileKF;
-    }
-    // keys of this tile that exist: fewer than 32 only at the end of a sequence whose length is not a
-    // multiple of the tile; a tile wholly past the end (the later tiles of a partial key block) is skipped
-    const int valid = L - key0 < kTileKF ? L - key0 : kTileKF;
-    if (valid <= 0) continue;  // uniform over the work-group
-    __syncthreads();  // everyone is done reading the previous tile
-    T::template stage<NT>(kbase + (int64_t)key0 * a.k.sl, a.k.sl, klds, T::kKStride, tid, valid);
-    if (kHasV) T::template stage<NT>(vbase + (int64_t)key0 * a.v.sl, a.v.sl, vlds, D, tid, valid);
-    __syncthreads();
 
-    f32x16 s = logits_tile_f32<D>(klds, qf, lane);
+  int t = wave, key = 0, key_next = 0;
+  if (t < n) {
+    key = __builtin_amdgcn_readfirstlane(first_key(t));
+    key_next = __builtin_amdgcn_readfirstlane(first_key(t + KW));
+    const uint32_t off = ks.row_offset(key + j) + 16 * g;
+#pragma unroll
+    for (int ch = 0; ch < kChunks; ++ch) kf[ch] = ks.k_chunk(off, ch);
+    if (kHasV) {
+#pragma unroll
+      for (int x = 0; x < 16; ++x) vf[x] = vs.v_row(key, x, lane);
+    }
+  }
+  __syncthreads();
+  for (; t < n; t += KW) {
+    const int key_after = first_key(t + 2 * KW);
+    const uint32_t off_next = ks.row_offset(key_next + j) + 16 * g;
+    f32x16 s;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) s[x] = 0.f;
+#pragma unroll
+    for (int ch = 0; ch < kChunks; ++ch) {
+      const f32x4 qf = *reinterpret_cast<const f32x4*>(lds + (ch * 64 + lane) * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[e], s, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);  // the reload stays behind its fragment's last use, so it can take its registers
+      kf[ch] = ks.k_chunk(off_next, ch);
+    }
+    // keys of this tile that exist: fewer than 32 at the end of a sequence whose length is not a multiple of the tile,
+    // none in the later tiles of a partial last key block
+    const int valid = L - key;
     if (valid < kTileKF) {
 #pragma unroll
       for (int x = 0; x < 16; ++x)
         if (8 * (x / 4) + 4 * g + (x % 4) >= valid) s[x] = -__builtin_inff();
     }
-
     float mx = s[0];
 #pragma unroll
     for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
@@ -99,79 +136,114 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnArgs a) {
       part += s[x];
     }
     lsum = lsum * alpha + part;
-
     if (kHasV) {
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) {
+        for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
-        for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
+          for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int x = 0; x < 16; ++x) {
-          const int key = 8 * (x / 4) + 4 * g + (x % 4);
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vlds[key * D + 32 * dt + j], s[x], o[dt], 0, 0, 0);
-        }
+      for (int x = 0; x < 16; ++x) {
+#pragma unroll
+        for (int dt = 0; dt < kV; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[x][dt], s[x], o[dt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        vf[x] = vs.v_row(key_next, x, lane);
       }
     }
+    key = key_next;
+    key_next = __builtin_amdgcn_readfirstlane(key_after);
   }
 
+  // Merge the waves' parts: O = sum_w O_w 2^(M_w - M) / sum_w l_w 2^(M_w - M), M = max_w M_w.
   const float ltot = lsum + other_half_f(lsum);
-  const int row = row0 + j;
-  if (row >= L) return;  // partial last query tile
-  if (a.lse != nullptr && g == 0) a.lse[(int64_t)bh * a.L + row] = (M + log2f(ltot)) * 0.6931471805599453f;
+  __syncthreads();  // everyone is done with the query fragments
+  if (g == 0) {
+    stat_m[wave][j] = M;
+    stat_l[wave][j] = ltot;
+  }
   if (kHasV) {
-    const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
-    float* orow = static_cast<float*>(a.o) + b * a.o_sb + h * a.o_sh + (int64_t)row * a.o_sl;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int v = 0; v < 16; ++v) {
+      VRow w;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        f32x4 w;
+      for (int dt = 0; dt < kV; ++dt) w[dt] = o[dt][v];
+      const int piece = 8 * (v / 4) + 4 * g + (v % 4);  // columns kV * piece .. + kV - 1 of row j
+      *reinterpret_cast<VRow*>(lds + ((wave * 32 + j) * 32 + (piece ^ j)) * sizeof(VRow)) = w;
+    }
+  }
+  __syncthreads();
+  auto factors = [&](int row, float (&f)[KW], float* m) -> float {  // every wave's factor and the common maximum; returns l
+    float mm = stat_m[0][row], l = 0.f;
 #pragma unroll
-        for (int x = 0; x < 4; ++x) w[x] = o[dt][4 * q4 + x] * inv;
-        *reinterpret_cast<f32x4*>(orow + 32 * dt + 8 * q4 + 4 * g) = w;
+    for (int w = 1; w < KW; ++w) mm = fmaxf(mm, stat_m[w][row]);
+#pragma unroll
+    for (int w = 0; w < KW; ++w) {
+      f[w] = exp2f(stat_m[w][row] - mm);
+      l += stat_l[w][row] * f[w];
+    }
+    *m = mm;
+    return l;
+  };
+  if (a.lse != nullptr && tid < 32 && row0 + tid < L) {
+    float f[KW], m;
+    const float l = factors(tid, f, &m);
+    a.lse[(int64_t)bh * a.L + row0 + tid] = (m + log2f(l)) * 0.6931471805599453f;
+  }
+  if (kHasV) {
+    for (int id = tid; id < 32 * 32; id += NT) {
+      const int row = id >> 5, piece = id & 31;
+      if (row0 + row >= L) break;  // partial last query tile (rows ascend with id)
+      float f[KW], m;
+      const float l = factors(row, f, &m);
+      const float inv = l > 0.f ? 1.0f / l : 0.f;
+      VRow acc;
+#pragma unroll
+      for (int dt = 0; dt < kV; ++dt) acc[dt] = 0.f;
+#pragma unroll
+      for (int w = 0; w < KW; ++w) {
+        const VRow part = *reinterpret_cast<const VRow*>(lds + ((w * 32 + row) * 32 + (piece ^ row)) * sizeof(VRow));
+#pragma unroll
+        for (int dt = 0; dt < kV; ++dt) acc[dt] += part[dt] * f[w];
       }
+#pragma unroll
+      for (int dt = 0; dt < kV; ++dt) acc[dt] *= inv;
+      float* orow = static_cast<float*>(a.o) + b * a.o_sb + h * a.o_sh + (int64_t)(row0 + row) * a.o_sl;
+      *reinterpret_cast<VRow*>(orow + kV * piece) = acc;
+    }
   }
 }
 
-int dense_qtile_f32(int L) {
-  if (L <= 0) return 0;
-  if (L % 128 == 0) return 128;
-  if (L % 64 == 0) return 64;
-  if (L % 32 == 0) return 32;
-  return L >= 256 ? 128 : L >= 64 ? 64 : 32;  // partial last tile
-}
-
-template <int D, int NW, Mode MODE>
+template <int D, int KW, Mode MODE>
 static hipError_t launch_one_f32(const AttnArgs& a, hipStream_t s) {
   const int64_t total = (int64_t)a.B * a.Hq * a.n_qtiles;
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_f32_kernel<D, NW, MODE>), dim3((unsigned)total), dim3(NW * 64), 0, s, a);
+  hipLaunchKernelGGL((attn_f32_kernel<D, KW, MODE>), dim3((unsigned)total), dim3(KW * 64), 0, s, a);
   return hipGetLastError();
 }
 
+// Waves per work-group: a compute unit holds eight waves of this kernel, as two work-groups of four or one of eight.
+// Eight where there are no more work-groups than compute units (short sequences: the keys split eight ways), else four.
 template <int D, Mode MODE>
-static hipError_t launch_by_qtile_f32(int qtile, const AttnArgs& a, hipStream_t s) {
-  switch (qtile) {
-    case 128: return launch_one_f32<D, 4, MODE>(a, s);
-    case 64: return launch_one_f32<D, 2, MODE>(a, s);
-    case 32: return launch_one_f32<D, 1, MODE>(a, s);
-  }
-  return hipErrorInvalidValue;
+static hipError_t launch_by_fill_f32(const AttnArgs& a, hipStream_t s) {
+  if ((int64_t)a.B * a.Hq * a.n_qtiles <= 256) return launch_one_f32<D, 8, MODE>(a, s);
+  return launch_one_f32<D, 4, MODE>(a, s);
 }
 
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {
-  const int qtile = (mode == Mode::kSparse) ? block_q : dense_qtile_f32(a.L);
-  if (qtile == 0) return hipErrorInvalidValue;
-  a.n_qtiles = (a.L + qtile - 1) / qtile;
+  if (a.L <= 0 || (mode == Mode::kSparse && block_q % 32 != 0)) return hipErrorInvalidValue;
+  a.block_q = block_q;
+  a.n_qtiles = (a.L + 31) / 32;
   if (D == 128) {
-    if (mode == Mode::kDense) return launch_by_qtile_f32<128, Mode::kDense>(qtile, a, s);
-    if (mode == Mode::kSparse) return launch_by_qtile_f32<128, Mode::kSparse>(qtile, a, s);
-    return launch_by_qtile_f32<128, Mode::kStats>(qtile, a, s);
+    if (mode == Mode::kDense) return launch_by_fill_f32<128, Mode::kDense>(a, s);
+    if (mode == Mode::kSparse) return launch_by_fill_f32<128, Mode::kSparse>(a, s);
+    return launch_by_fill_f32<128, Mode::kStats>(a, s);
   }
   if (D == 64) {
-    if (mode == Mode::kDense) return launch_by_qtile_f32<64, Mode::kDense>(qtile, a, s);
-    if (mode == Mode::kSparse) return launch_by_qtile_f32<64, Mode::kSparse>(qtile, a, s);
-    return launch_by_qtile_f32<64, Mode::kStats>(qtile, a, s);
+    if (mode == Mode::kDense) return launch_by_fill_f32<64, Mode::kDense>(a, s);
+    if (mode == Mode::kSparse) return launch_by_fill_f32<64, Mode::kSparse>(a, s);
+    return launch_by_fill_f32<64, Mode::kStats>(a, s);
   }
   return hipErrorInvalidValue;
 }

@@ -25,10 +25,11 @@ struct AttnArgs {
   int32_t nqb, cap_per_head, block_k;
   int32_t n_qtiles;        // query tiles per head = ceil(L / rows per work-group)
   float scale_log2;        // log2(e) / sqrt(D)
-  // kDensePool only (nqb and block_k then describe the pooled blocks)
+  int32_t block_q;         // rows per query block (kDensePool and the fp32 sparse kernel)
+  // kDensePool only (nqb, block_q and block_k then describe the pooled blocks)
   float* slab;             // scratch: one slab of (rows per work-group) x slab_cols floats per work-group of the launch
   float* apool;            // [B, Hq, nqb, nkb] pooled scores
-  int32_t slab_cols, nkb, block_q;
+  int32_t slab_cols, nkb;
 };
 
 // Arguments of the pooled-score kernels (Section 3.3: A' = avgpool(A, block)). The keys pooled are
@@ -158,8 +159,7 @@ hipError_t launch_valu_rate(float* scratch, int iters, int op, hipStream_t s);
 // exp2, and optionally one LDS operand read each; same launch shape and matrix work as launch_mfma_rate.
 hipError_t launch_mix_rate(float* scratch, int iters, int vector_per_mfma, int lds_operands, hipStream_t s);
 
-// Rows per work-group the dense / stats kernels use for this L (0 if L is unsupported).
+// Rows per work-group the bf16 dense / stats kernels use for this L (0 if L is unsupported).
 int dense_qtile_bf16(int L);
-int dense_qtile_f32(int L);
 
 }  // namespace sparsed

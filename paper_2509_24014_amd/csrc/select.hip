@@ -201,15 +201,20 @@ void pool_bf16_kernel(const PoolArgs a) {
 }
 
 // ---------------------------------------------------------------------------- pooled scores, fp32
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) void pool_f32_kernel(const PoolArgs a) {
-  constexpr int NT = NW * 64;
-  using T = TileF32<D>;
-  __shared__ __attribute__((aligned(16))) float klds[T::kKFloats];
-  __shared__ float wsum[NW];
+// One work-group of eight waves per query block: RW = block_q / 32 row groups times KW = 8 / RW key groups. Wave
+// (rw, kw) sums, for its 32 rows, the key blocks kw, kw + KW, ...; the row groups' sums of a block meet in LDS (in row
+// group order), a segment of blocks at a time. K goes straight into registers, a fragment of the next tile requested
+// as soon as the one it replaces has been used (see attn_f32.hip), so there is no barrier inside a segment.
+// Bound: the fp32 matrix rate. 8 heads of 2000 x 128, 64 x 64 blocks: 238 -> 86 us (95 TFLOP/s); 2 heads of 256 x 64: 26 -> 8 us.
+template <int D, int RW>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pool_f32_kernel(const PoolArgs a) {
+  constexpr int KW = 8 / RW, kChunks = D / 8, kSeg = 512;
+  __shared__ float sums[RW][kSeg];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = wave % RW, kw = wave / RW;
+  const int j = lane & 31, g = lane >> 5;
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
   const int I = lid % a.nqb;
   const int bh = lid / a.nqb;
@@ -222,50 +227,74 @@ __global__ __launch_bounds__(NW * 64) void pool_f32_kernel(const PoolArgs a) {
     L = len < a.L ? len : a.L;
     key_len = L - a.key_begin < key_len ? L - a.key_begin : key_len;
   }
-  if (I * (32 * NW) >= L || key_len <= 0) return;  // uniform over the work-group
-  const float* qbase = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
-  const float* kbase = static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)a.key_begin * a.k.sl;
-  const int row0 = I * (32 * NW) + wave * 32;
-
-  QFragF32<D> qf;
-  qf.load(qbase, row0, L, a.q.sl, lane);
+  if (I * (32 * RW) >= L || key_len <= 0) return;  // uniform over the work-group
+  const SlabF32<D> ks{reinterpret_cast<const char*>(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)a.key_begin * a.k.sl),
+                      (uint32_t)(a.k.sl * 4), key_len};
+  const int row = I * (32 * RW) + rw * 32 + j;
+  f32x4 qf[kChunks], kf[kChunks];
+  {
+    const float* qrow = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh + (int64_t)(row < L ? row : L - 1) * a.q.sl + 4 * g;
+#pragma unroll
+    for (int ch = 0; ch < kChunks; ++ch) qf[ch] = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
+  }
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
-  const float lse2 = (row0 + j < L) ? a.lse[(int64_t)bh * a.L + row0 + j] * 1.4426950408889634f : __builtin_inff();
+  const float lse2 = row < L ? a.lse[(int64_t)bh * a.L + row] * 1.4426950408889634f : __builtin_inff();
   float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0;
-  const int rows_here = (L - I * (32 * NW) < 32 * NW) ? L - I * (32 * NW) : 32 * NW;  // query rows that exist
-  const int g = lane >> 5;
-
-  const int tiles_per_block = a.block_k / kTileKF;
-  const int n_tiles = (key_len + kTileKF - 1) / kTileKF;
+  const int rows_here = (L - I * (32 * RW) < 32 * RW) ? L - I * (32 * RW) : 32 * RW;  // query rows that exist
+  const int nkb = (key_len + a.block_k - 1) / a.block_k;
   const float c = a.scale_log2;
-  float acc = 0.f;  // thread 0: running sum of the current key block
-  for (int t = 0; t < n_tiles; ++t) {
-    const int valid = key_len - t * kTileKF < kTileKF ? key_len - t * kTileKF : kTileKF;  // keys of this tile that exist (>= 1)
-    __syncthreads();
-    T::template stage<NT>(kbase + (int64_t)t * kTileKF * a.k.sl, a.k.sl, klds, T::kKStride, tid, valid);
-    __syncthreads();
-    f32x16 s = logits_tile_f32<D>(klds, qf, lane);
-    if (valid < kTileKF) {
+
+  int J = kw, key = kw * a.block_k;  // block and first key of the tile to come
+  {
+    const uint32_t off = ks.row_offset(key + j) + 16 * g;
 #pragma unroll
-      for (int x = 0; x < 16; ++x)
-        if (8 * (x / 4) + 4 * g + (x % 4) >= valid) s[x] = -__builtin_inff();
-    }
-    float part = 0.f;
+    for (int ch = 0; ch < kChunks; ++ch) kf[ch] = ks.k_chunk(off, ch);
+  }
+  for (int seg = 0; seg < nkb; seg += kSeg) {
+    const int seg_end = seg + kSeg < nkb ? seg + kSeg : nkb;
+    float acc = 0.f;  // this lane's share of block J
+    while (J < seg_end) {
+      const int left = (J + 1) * a.block_k < key_len ? (J + 1) * a.block_k - key : key_len - key;  // keys of the block from `key` on (>= 1)
+      const bool last = left <= kTileKF;                                                           // last tile of its block
+      const int key_next = last ? (J + KW) * a.block_k : key + kTileKF;  // (past the last block: the last row, repeated)
+      const uint32_t off_next = ks.row_offset(key_next + j) + 16 * g;
+      f32x16 s;
 #pragma unroll
-    for (int x = 0; x < 16; ++x) part += exp2f(__builtin_fmaf(s[x], c, -lse2));
-    part = wave_sum_f(part);
-    if (lane == 0) wsum[wave] = part;
-    __syncthreads();
-    if (tid == 0) {
+      for (int x = 0; x < 16; ++x) s[x] = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) acc += wsum[w];
-      if ((t + 1) % tiles_per_block == 0 || t == n_tiles - 1) {  // key block complete (the last one may be partial)
-        const int J = t / tiles_per_block;
-        const int keys_here = key_len - J * a.block_k < a.block_k ? key_len - J * a.block_k : a.block_k;
-        arow[J] = acc * (1.0f / (float)(rows_here * keys_here));  // mean over the entries that exist
+      for (int ch = 0; ch < kChunks; ++ch) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[ch][e], s, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // the reload stays behind its fragment's last use, so it can take its registers
+        kf[ch] = ks.k_chunk(off_next, ch);
+      }
+      if (left < kTileKF) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x)
+          if (8 * (x / 4) + 4 * g + (x % 4) >= left) s[x] = -__builtin_inff();
+      }
+      float part = 0.f;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) part += exp2f(__builtin_fmaf(s[x], c, -lse2));
+      acc += part;
+      key = key_next;
+      if (last) {
+        acc = wave_sum_f(acc);
+        if (lane == 0) sums[rw][J - seg] = acc;
         acc = 0.f;
+        J += KW;
       }
     }
+    __syncthreads();
+    for (int x = tid; x < seg_end - seg; x += 512) {
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < RW; ++w) tot += sums[w][x];
+      const int first = (seg + x) * a.block_k;
+      const int keys_here = key_len - first < a.block_k ? key_len - first : a.block_k;
+      arow[seg + x] = tot * (1.0f / (float)(rows_here * keys_here));  // mean over the entries that exist
+    }
+    __syncthreads();  // the sums may be overwritten
   }
 }
 
@@ -537,9 +566,9 @@ static hipError_t launch_pool_f32_d(int block_q, const PoolArgs& a, hipStream_t 
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)total);
   switch (block_q) {
-    case 128: hipLaunchKernelGGL((pool_f32_kernel<D, 4>), grid, dim3(256), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((pool_f32_kernel<D, 2>), grid, dim3(128), 0, s, a); break;
-    case 32: hipLaunchKernelGGL((pool_f32_kernel<D, 1>), grid, dim3(64), 0, s, a); break;
+    case 128: hipLaunchKernelGGL((pool_f32_kernel<D, 4>), grid, dim3(512), 0, s, a); break;
+    case 64: hipLaunchKernelGGL((pool_f32_kernel<D, 2>), grid, dim3(512), 0, s, a); break;
+    case 32: hipLaunchKernelGGL((pool_f32_kernel<D, 1>), grid, dim3(512), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
