@@ -35,7 +35,7 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
   const int qt = lid % a.n_qtiles;
-  const int bh = lid / a.n_qtiles;
+  const int bh = batch_head_at(lid / a.n_qtiles, a.B, a.Hq, a.Hkv, a.seq_lens);
   const int b = bh / a.Hq, h = bh % a.Hq;
   const int hk = h / (a.Hq / a.Hkv);
   int L = a.L;  // length of this batch element

@@ -52,7 +52,7 @@ void pool_bf16_kernel(const PoolArgs a) {
   const int lid = xcd_remap(blockIdx.x, gridDim.x);
   const int groups_per_head = (a.nqb + kBlocksPerGroup - 1) / kBlocksPerGroup;
   const int gq = lid % groups_per_head;  // which run of 32 * NW rows of the head
-  const int bh = lid / groups_per_head;
+  const int bh = batch_head_at(lid / groups_per_head, a.B, a.Hq, a.Hkv, a.seq_lens);
   const int b = bh / a.Hq, h = bh % a.Hq;
   const int hk = h / (a.Hq / a.Hkv);
   const int first_wave = (wave / QBW) * QBW;            // first wave of this wave's query block
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int j = lane & 31, g = lane >> 5;
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
   const int I = lid % a.nqb;
-  const int bh = lid / a.nqb;
+  const int bh = batch_head_at(lid / a.nqb, a.B, a.Hq, a.Hkv, a.seq_lens);
   const int b = bh / a.Hq, h = bh % a.Hq;
   const int hk = h / (a.Hq / a.Hkv);
 

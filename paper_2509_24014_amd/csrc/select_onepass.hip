@@ -68,7 +68,7 @@ void pool1p_bf16_kernel(const PoolArgs a) {
 
   for (int unit = xcd_remap(blockIdx.x, gridDim.x); unit < units; unit += gridDim.x) {
     const int gq = unit % groups_per_head;
-    const int bh = unit / groups_per_head;
+    const int bh = batch_head_at(unit / groups_per_head, a.B, a.Hq, a.Hkv, a.seq_lens);
     const int b = bh / a.Hq, h = bh % a.Hq;
     const int hk = h / (a.Hq / a.Hkv);
     int L = a.L;  // length of this batch element
