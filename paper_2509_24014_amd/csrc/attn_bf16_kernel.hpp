@@ -287,11 +287,6 @@ __global__ __launch_bounds__(NW * 64)
     const int off = 4 * ((KB == 2 * kTileK ? 0 : (ln >> 5) * QT) + (ln & 31));
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), slab_rsrc, off, (col * QT + wave * 32) * 4, 0);
   };
-  // lanes 0-31: the pair sum of x, lanes 32-63: the pair sum of y
-  auto two_pair_sums = [&](float x, float y) -> float {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  };
   // after sub-tile 2t+1 (sum `part`): key tile t is complete. P = t & 1.
   auto park_tile = [&](const int P, const bool maybe_last, int t, float part) {
     if (KB == kTileK / 2) {
@@ -486,6 +481,7 @@ __global__ __launch_bounds__(NW * 64)
   if constexpr (kPool) {
     // A'[I, J] over the group's query blocks: a lane weighs the same four rows of every column, the lanes of a query
     // block (8, 16 or 32) are summed with DPP row operations in a fixed order. Four columns in flight per wave.
+    wait_vector_memory();  // this wave's parked sums have been written
     __syncthreads();  // all parked sums and weights of the group are written (and the staging slices read)
     constexpr int kLanes = QT / 4, kCols = 64 / kLanes, kUnroll = 4;  // lanes per column, columns per wave load
     const int li = lane_e % kLanes, sub_col = lane_e / kLanes;

@@ -4,16 +4,25 @@
 //   A'[I, J] = 1 / (rows x keys) * sum_{r in I} (1 / Z_r) * sum_{j in J} exp(s_rj - m_r),   Z_r = sum_j exp(s_rj - m_r)
 //
 // The normaliser Z_r of a query row is known only after its last key, so the per-row block sums
-// E[r, J] = sum_{j in J} exp(s_rj - m_r) are parked in a scratch slab that belongs to the work-group
-// (128 x nkb floats: O(L) per work-group, never O(L^2) in total), and weighted by 1 / Z_r and summed
-// over the rows of the query block once the row is complete. Work-groups are persistent: each walks the
-// units (128 consecutive rows of a head: one, two or four query blocks) wg, wg + G, ... and reuses its slab.
+// E[r, J] = sum_{j in J} exp(s_rj - m_r) are parked in a scratch slab that belongs to the work-group (columns J of 128
+// floats: O(L) per work-group, never O(L^2) in total; a wave stores two columns' worth of its 32 rows at a time) and,
+// once the rows are complete, weighted by 1 / Z_r and summed over the rows of each query block. Work-groups are
+// persistent: each walks the units (128 consecutive rows of a head: one, two or four query blocks) wg, wg + G, ... and
+// reuses its slab.
 //
 // Reference m_r: the maximum logit of the row's first 32 keys. It is never above the row's true maximum, so
 // nothing underflows that the two-pass form (reference = log-sum-exp) would keep. A later logit more than
 // 100 octaves above it (never, on real attention logits) is caught by the overflow test on every 32-key
-// sub-tile and handled out of line: the reference is raised, and the row's running sums, its staged block
-// sums and the ones already in the slab are rescaled.
+// sub-tile and handled out of line: the reference is raised, and the row's running sums and its parked block
+// sums are rescaled.
+//
+// Bound: the vector unit. A 32-key sub-tile is 8 matrix instructions (256 cycles at head dim 128) and 16 fma, 16 exp2 and
+// 16 adds, and an exp2 takes as long as 3.5 to 3.9 fma (about 380 cycles together). The slab is read and written
+// by one work-group only, so its order is kept by work-group fences; the columns are read back as whole 16-byte pieces,
+// eight in flight per wave.
+// 32 heads of 16384 x 128, 64 x 64 blocks: 2.52 -> 2.19 ms (1.00 PFLOP/s); 3 samples (3000, 2100, 1200) x 8 heads of 64: 62 ->
+// 39 us. (Before: block sums staged in LDS row by row, a cache write-back at the end of every unit, four reads in flight in
+// the closing pass, 48 to 76 bytes of spills.)
 //
 // Matrix work, K tile copies, fragment layouts and the 32-key software pipeline are those of pool_bf16_kernel
 // (select.hip); exponentials, sums and weights are fp32 throughout, summed in a fixed order.
@@ -24,49 +33,38 @@ namespace sparsed {
 
 namespace {
 
-[[maybe_unused]] constexpr int kChunk = 8;    // block sums staged per row before they go to the slab (32 contiguous bytes per row)
-[[maybe_unused]] constexpr int kChunkLd = 8;  // floats per staged row (no padding: one staging store per key block is too rare for its bank conflicts to count)
 [[maybe_unused]] constexpr float kOverflow = 1.2676506e30f;  // 2^100: a 32-key partial sum at or above this triggers the re-reference path
 
-// Work-groups per compute unit the kernel is built for: two K tiles + staging is just under a quarter of the LDS.
+// Work-groups per compute unit the kernel is built for: two K tiles are under a quarter of the LDS.
 constexpr int groups_per_cu(int) { return 4; }
 
 }  // namespace
 
 // QBW: waves per query block. A work-group is always NW = 4 waves = 128 consecutive rows of a head: one query block of
 // 128 rows, two of 64 or four of 32, which share its K tiles and its slab.
+// The lane number and the kernel's arguments are worked out / read again where they are used late (fresh_lane,
+// fresh_kernel_args): 128 registers a lane are all that four waves per SIMD leave, and a spill in the tile loop waits
+// for the copies in flight.
 template <int D, int NW, int BK, int QBW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 4 ? 4 : NW >= 2 ? 2 : 1, NW >= 4 ? 4 : NW >= 2 ? 2 : 1)))
-void pool1p_bf16_kernel(const PoolArgs a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pool1p_bf16_kernel(const PoolArgs) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
+  static_assert(NW == 4, "four waves per SIMD, 128 rows per slab column");
   constexpr int NT = NW * 64, QT = 32 * NW;
   constexpr int kKBytes = KLayout<D>::kTileBytes;
-  constexpr int kSubPerBlock = BK / 32;  // 32-key sub-tiles per key block: 1, 2 or 4
   __shared__ __attribute__((aligned(1024))) char kbuf0[kKBytes];
   __shared__ __attribute__((aligned(1024))) char kbuf1[kKBytes];
-  __shared__ __attribute__((aligned(16))) float chunk[NW][32][kChunkLd];
-  __shared__ float inv_z[QT];
-  // key blocks per segment of the closing pass: the per-wave partial sums of one segment fit the first K buffer
-  constexpr int kSeg = (kKBytes / (NW * 4) >= 1024) ? 1024 : (kKBytes / (NW * 4)) & ~63;
-  static_assert(kSeg >= 64 && kSeg * NW * 4 <= kKBytes, "segment of partial sums must fit a K buffer");
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j = lane & 31, g = lane >> 5;
-  const int ld = a.slab_ld;  // floats per slab row: nkb rounded up to a whole chunk
-  float* const slab = a.slab + (int64_t)blockIdx.x * QT * ld + (int64_t)wave * 32 * ld;  // this wave's 32 rows
+  __shared__ __attribute__((aligned(16))) float inv_z[QT];
   static_assert(NW % QBW == 0, "whole query blocks per work-group");
   constexpr int kBlocksPerGroup = NW / QBW, kBlockRows = 32 * QBW;
-  const int groups_per_head = (a.nqb + kBlocksPerGroup - 1) / kBlocksPerGroup;
-  const int units = a.B * a.Hq * groups_per_head;  // a unit: QT consecutive rows of one head
-  const float c = a.scale_log2;
 
-  TileDma<D, NT, false> kdma;
-  kdma.init(a.k.sl, wave, lane);
-  KFragAddr<D> kaddr;
-  kaddr.init(lane);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  for (int unit = xcd_remap(blockIdx.x, gridDim.x); unit < units; unit += gridDim.x) {
+  int unit = xcd_remap(blockIdx.x, gridDim.x), units = 0;  // a unit: QT consecutive rows of one head
+  do {
+    const KernelArgs<PoolArgs>& a = fresh_kernel_args<PoolArgs>();
+    const int lane = fresh_lane();
+    const int groups_per_head = (a.nqb + kBlocksPerGroup - 1) / kBlocksPerGroup;
+    units = a.B * a.Hq * groups_per_head;
     const int gq = unit % groups_per_head;
     const int bh = batch_head_at(unit / groups_per_head, a.B, a.Hq, a.Hkv, a.seq_lens);
     const int b = bh / a.Hq, h = bh % a.Hq;
@@ -77,36 +75,37 @@ void pool1p_bf16_kernel(const PoolArgs a) {
       L = len < a.L ? len : a.L;
     }
     if (gq * QT >= L) continue;  // rows this sample does not have (uniform over the work-group)
-    const int key_len = L;
     const __bf16* qbase = static_cast<const __bf16*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
     const __bf16* kbase = static_cast<const __bf16*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh;
     const int row0 = gq * QT + wave * 32;
+    const float c = a.scale_log2;
 
+    TileDma<D, NT, false> kdma;
+    kdma.init(a.k.sl, wave, lane);
+    KFragAddr<D> kaddr;
+    kaddr.init(lane);
     QFrag<D, 1> qf;
-    qf.load(qbase, row0, L, a.q.sl, lane);
-    const int last_blk = (key_len - 1) / kTileK;                 // last 64-key tile that exists
-    const int tail_keys = key_len - last_blk * kTileK;           // keys in it
+    const int last_blk = (L - 1) / kTileK;              // last 64-key tile that exists
+    const int tail_keys = L - last_blk * kTileK;        // keys in it
     const int n = last_blk + 1;
-    const int nkb_here = (key_len + BK - 1) / BK;                // key blocks this sample has
-    auto keys_of = [&](int blk) -> int { return blk == last_blk ? tail_keys : kTileK; };
-    auto keys_at = [&](int tile) -> int { return tile < n ? keys_of(tile) : 0; };
-    const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(kbase, ((int64_t)(key_len - 1) * a.k.sl + D) * 2);
-    const int32_t k_tile_bytes = (int32_t)(kTileK * a.k.sl * 2);
+    auto keys_at = [&](int tile) -> int { return tile >= n ? 0 : tile == last_blk ? tail_keys : kTileK; };
+    const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(kbase, ((int64_t)(L - 1) * a.k.sl + D) * 2);
+    const int64_t k_sl = a.k.sl;
+    const int32_t k_tile_bytes = (int32_t)(kTileK * k_sl * 2);
     auto copy_k_any = [&](int tile, char* dst) {  // any tile: past the end repeats the last one, which may be partial
       const int blk = tile < n ? tile : n - 1;
-      if (blk == last_blk && tail_keys < kTileK) kdma.issue_partial(krsrc, blk * k_tile_bytes, dst, wave, lane, a.k.sl, tail_keys);
+      if (blk == last_blk && tail_keys < kTileK) kdma.issue_partial(krsrc, blk * k_tile_bytes, dst, wave, fresh_lane(), k_sl, tail_keys);
       else kdma.issue(krsrc, blk * k_tile_bytes, dst, wave);
     };
 
     f32x16 s_even[1], s_odd[1];
-    float M = 0.f;     // reference of this lane's row, in octaves (log2 units)
-    float lsum = 0.f;  // this lane's share of Z_r
-    float eacc = 0.f;  // this lane's share of the block sum in progress
-    int sub = 0;       // 32-key sub-tiles summed so far
+    float M = 0.f;                  // reference of this lane's row, in octaves (log2 units)
+    float lsum = 0.f;               // this lane's share of Z_r
+    float carry = 0.f, hold = 0.f;  // its share of the sub-tile before the one being summed / of the block before the one being completed
 
     // masked: apply `valid`, the number of keys of the sub-tile that exist (>= 32: all, <= 0: none)
     auto mask_sub = [&](f32x16(&s)[1], int valid) {
-      const int mine = valid - 8 * g;  // register x of lane (j, g) holds key 16*(x/8) + 8*g + x%8
+      const int mine = valid - 8 * (fresh_lane() >> 5);  // register x of lane (j, g) holds key 16*(x/8) + 8*g + x%8
 #pragma unroll
       for (int x = 0; x < 16; ++x)
         if (16 * (x >> 3) + (x & 7) >= mine) s[0][x] = -__builtin_inff();
@@ -121,55 +120,50 @@ void pool1p_bf16_kernel(const PoolArgs a) {
       float part = 0.f;
 #pragma unroll
       for (int x = 0; x < 16; ++x) part += __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -M));
+      asm volatile("" : "+v"(part));  // keep the vector work inside the block that holds the matrix work
       return part;
     };
-    // A block sum is complete: both halves of the row are added and staged; a full chunk (or the last block) goes to the slab.
-    auto finish_block = [&](int J) {
-      const float e = pair_sum(eacc);
-      eacc = 0.f;
-      if (J >= nkb_here) return;  // the empty second half of a partial last tile with 32-key blocks
-      const int slot = J & (kChunk - 1);
-      if (g == 0) chunk[wave][j][slot] = e;
-      if (slot == kChunk - 1 || J == nkb_here - 1) {
-        const int r = lane >> 1, half = lane & 1;
-        const u32x4 w = *reinterpret_cast<const u32x4*>(&chunk[wave][r][half * 4]);
-        *reinterpret_cast<u32x4*>(slab + (int64_t)r * ld + (J & ~(kChunk - 1)) + half * 4) = w;
+    // The slab: columns J of QT floats, stored two at a time (both halves of a wave), or once per two tiles with 128-key blocks.
+    float* const slab = a.slab + (int64_t)blockIdx.x * QT * a.slab_ld;
+    const __amdgpu_buffer_rsrc_t slab_rsrc = make_rsrc(slab, (int64_t)QT * a.slab_ld * 4);
+    auto park_store = [&](int col, float v) {
+      const int ln = fresh_lane();
+      const int off = 4 * ((BK == 2 * kTileK ? 0 : (ln >> 5) * QT) + (ln & 31));
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), slab_rsrc, off, (col * QT + wave * 32) * 4, 0);
+    };
+    // after sub-tile 2t+1 (sum `part`): key tile t is complete. P = t & 1.
+    auto park_tile = [&](const int P, const bool maybe_last, int t, float part) {
+      if (BK == kTileK / 2) {
+        park_store(2 * t, two_pair_sums(carry, part));
+        return;
+      }
+      const float e = carry + part;
+      if (BK == kTileK) {
+        if (P) park_store(t - 1, two_pair_sums(hold, e));
+        else if (maybe_last && t == n - 1) park_store(t, two_pair_sums(e, 0.f));
+        else hold = e;
+      } else {
+        if (P) park_store(t >> 1, pair_sum(hold + e));
+        else if (maybe_last && t == n - 1) park_store(t >> 1, pair_sum(e));
+        else hold = e;
       }
     };
-    // Out of line: some 32-key partial sum overflowed the reference. Raise the reference of the rows concerned to
-    // their new maximum and rescale everything they have accumulated so far (J_done block sums are complete).
-    auto re_reference = [&](const f32x16(&s)[1], int J_done) {
-      const float mx = row_max(s);
-      const float Mn = fmaxf(M, mx);
+    // Out of line: some partial sum overflowed the reference. Raise the reference of the rows concerned to their new
+    // maximum, rescale everything they have accumulated (tiles_done key tiles are complete), redo the sub-tile's sum.
+    auto re_reference = [&](const f32x16(&s)[1], float& part, int tiles_done) {
+      const float Mn = fmaxf(M, row_max(s));
       const float alpha = __builtin_amdgcn_exp2f(M - Mn);  // <= 1; exactly 1 where nothing changes
       M = Mn;
       lsum *= alpha;
-      eacc *= alpha;
-      if (g == 0 && alpha != 1.0f) {
-        const int staged_from = J_done & ~(kChunk - 1);
-        for (int J = staged_from; J < J_done; ++J) chunk[wave][j][J - staged_from] *= alpha;
-        float* row = slab + (int64_t)j * ld;
-        for (int J = 0; J < staged_from; ++J) {
-          const float v = __hip_atomic_load(row + J, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          row[J] = v * alpha;
-        }
-      }
+      carry *= alpha;
+      hold *= alpha;
+      const int cols = BK == kTileK / 2 ? 2 * tiles_done : BK == kTileK ? tiles_done & ~1 : tiles_done >> 1;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // this wave's parked sums have been written
+      if (alpha < 1.0f)  // (not for a NaN: the row is lost anyway)
+        for (int J = fresh_lane() >> 5; J < cols; J += 2) slab[(int64_t)J * QT + wave * 32 + (fresh_lane() & 31)] *= alpha;
+      part = exp_sum(s);
     };
-    // One 32-key sub-tile: exponentials against the row reference, summed per lane.
-    auto expsum_sub = [&](f32x16(&s)[1], const bool masked, int valid) {
-      if (masked) mask_sub(s, valid);
-      float part = exp_sum(s);
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0, 0)) {  // wave-uniform, practically never taken
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");           // this wave's slab stores are complete
-        re_reference(s, sub / kSubPerBlock);
-        part = exp_sum(s);
-      }
-      asm volatile("" : "+v"(part));  // keep the vector work inside the block that holds the matrix work
-      lsum += part;
-      eacc += part;
-      ++sub;
-      if (sub % kSubPerBlock == 0) finish_block(sub / kSubPerBlock - 1);
-    };
+    auto overflowed = [&](float part) -> bool { return __builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0; };
 
     // Tile step t (LDS parity P = t & 1) = sub-tiles 2t+1 and 2t+2. On entry S(2t+1) is in s_odd, K(t+1) in
     // kbuf[1-P]; kbuf[P] is free and receives K(t+2). Tiles past the end are phantoms (a repeated copy, every key
@@ -181,24 +175,34 @@ void pool1p_bf16_kernel(const PoolArgs a) {
     if (MASKED) copy_k_any((T) + 2, kb_free);                                                      \
     else kdma.issue(krsrc, ((T) + 2 < n ? (T) + 2 : n - 1) * k_tile_bytes, kb_free, wave);         \
     logits_sub<D, 1, false>(kb_next, 0, kaddr, qf, s_even);                                        \
-    expsum_sub(s_odd, (MASKED), keys_at(T) - 32);                                                  \
+    if (MASKED) mask_sub(s_odd, keys_at(T) - 32);                                                  \
+    float part = exp_sum(s_odd);                                                                   \
     sched_substep_interleave<D, 1, false>();                                                       \
+    if (__builtin_expect(overflowed(part), 0)) re_reference(s_odd, part, (T));                     \
+    lsum += part;                                                                                  \
+    park_tile((P), (MASKED), (T), part);                                                           \
     __builtin_amdgcn_sched_barrier(0);                                                             \
     logits_sub<D, 1, false>(kb_next, 1, kaddr, qf, s_odd);                                         \
-    if ((T) + 1 < n) expsum_sub(s_even, (MASKED), keys_at((T) + 1));                               \
+    if (MASKED) mask_sub(s_even, keys_at((T) + 1));                                                \
+    part = exp_sum(s_even);                                                                        \
     sched_substep_interleave<D, 1, false>();                                                       \
+    if (__builtin_expect(overflowed(part), 0)) re_reference(s_even, part, (T) + 1);                \
+    lsum += part;                                                                                  \
+    carry = part;                                                                                  \
     __syncthreads();                                                                               \
   }
 
     // prologue: K(0), K(1) (a repeat of K(0) for a one-tile range) into LDS; S(0); reference and sums of sub-tile 0
     copy_k_any(0, kbuf0);
     copy_k_any(1, kbuf1);
+    qf.load(qbase, row0, L, a.q.sl, lane);
     __syncthreads();
     logits_sub<D, 1, true>(kbuf0, 0, kaddr, qf, s_even);
     logits_sub<D, 1, true>(kbuf0, 1, kaddr, qf, s_odd);
     mask_sub(s_even, keys_at(0));
     M = row_max(s_even);  // at least one key exists, so this is finite
-    expsum_sub(s_even, false, 32);
+    carry = exp_sum(s_even);
+    lsum = carry;
     __syncthreads();  // everyone is done with K(0) before tile step 0 lets K(2) overwrite it
 
     const int steady_reach = (tail_keys < kTileK) ? 4 : 2;
@@ -216,48 +220,46 @@ void pool1p_bf16_kernel(const PoolArgs a) {
       }
     }
 #undef SPARSED_POOL1P_STEP
-    if (sub % kSubPerBlock != 0) finish_block(sub / kSubPerBlock);  // a last key block cut short by the end of the keys
 
     // The rows are complete: 1 / Z_r (0 for rows past the end), the row log-sum-exp for later users, and then
-    // A'[I, J] = sum_r E[r, J] / Z_r over the rows of the block, divided by the entries that exist.
+    // A'[I, J] = sum_r E[r, J] / Z_r over the rows of the block, divided by the entries that exist: a lane weighs the same
+    // four rows of every column, and the lanes of a query block (8, 16 or 32) are summed in a fixed order.
+    const KernelArgs<PoolArgs>& ae = fresh_kernel_args<PoolArgs>();
+    const int lane_e = fresh_lane();
     const float ltot = pair_sum(lsum);
-    if (g == 0) {
-      const bool exists = row0 + j < L;
-      inv_z[wave * 32 + j] = exists ? 1.0f / ltot : 0.f;
-      if (a.lse_out != nullptr && exists) a.lse_out[(int64_t)bh * a.L + row0 + j] = (M + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+    if (lane_e < 32) {
+      const bool exists = row0 + lane_e < L;
+      inv_z[wave * 32 + lane_e] = exists ? 1.0f / ltot : 0.f;
+      if (ae.lse_out != nullptr && exists) ae.lse_out[(int64_t)bh * ae.L + row0 + lane_e] = (M + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // this wave's slab stores are complete before it reads them back
-    __syncthreads();
-    float* const partial = reinterpret_cast<float*>(kbuf0);  // [NW][kSeg] (the K buffers are idle now)
-    for (int seg = 0; seg < nkb_here; seg += kSeg) {
-      const int seg_n = nkb_here - seg < kSeg ? nkb_here - seg : kSeg;
-      for (int x = lane; x < seg_n; x += 64) {
-        float acc = 0.f;
-        const float* col = slab + seg + x;
-#pragma unroll 4
-        for (int r = 0; r < 32; ++r)
-          acc += __hip_atomic_load(col + (int64_t)r * ld, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * inv_z[wave * 32 + r];
-        partial[wave * kSeg + x] = acc;
-      }
-      __syncthreads();
+    wait_vector_memory();  // this wave's parked sums have been written
+    __syncthreads();  // all parked sums and weights of the group are written
+    constexpr int kLanes = QT / 4, kCols = 64 / kLanes, kUnroll = 8;  // lanes per column, columns per wave load
+    const int li = lane_e % kLanes, sub_col = lane_e / kLanes;
+    const f32x4v w = *reinterpret_cast<const f32x4v*>(&inv_z[4 * li]);
+    const int I = gq * kBlocksPerGroup + 4 * li / kBlockRows;
+    const int rows_here = L - I * kBlockRows < kBlockRows ? L - I * kBlockRows : kBlockRows;
+    const bool writes = (4 * li + 4) % kBlockRows == 0 && rows_here > 0;  // the last lane of a query block that exists
+    float* const arow = ae.apool + ((int64_t)bh * ae.nqb + I) * ae.out_stride;
+    const int nkb_here = (L + BK - 1) / BK;  // key blocks this sample has
+    for (int J0 = wave * (kCols * kUnroll); J0 < nkb_here; J0 += NW * kCols * kUnroll) {
+      f32x4v e[kUnroll];
 #pragma unroll
-      for (int qb = 0; qb < kBlocksPerGroup; ++qb) {  // the query blocks of the group, each summed over its own waves
-        const int I = gq * kBlocksPerGroup + qb;
-        if (I >= a.nqb || I * kBlockRows >= L) break;  // a block the head (or this sample) does not have
-        float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride;
-        const int rows_here = (L - I * kBlockRows < kBlockRows) ? L - I * kBlockRows : kBlockRows;  // query rows that exist
-        for (int x = tid; x < seg_n; x += NT) {
-          float tot = 0.f;
-#pragma unroll
-          for (int w = 0; w < QBW; ++w) tot += partial[(qb * QBW + w) * kSeg + x];
-          const int J = seg + x;
-          const int keys_here = key_len - J * BK < BK ? key_len - J * BK : BK;
-          arow[J] = tot * (1.0f / (float)(rows_here * keys_here));  // mean over the entries that exist
-        }
+      for (int u = 0; u < kUnroll; ++u) {
+        const int J = J0 + u * kCols + sub_col;
+        e[u] = *reinterpret_cast<const f32x4v*>(slab + (int64_t)(J < nkb_here ? J : nkb_here - 1) * QT + 4 * li);
       }
-      __syncthreads();  // the partial sums (and, after the last segment, the K buffers) may be overwritten
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int J = J0 + u * kCols + sub_col;
+        float x = e[u][0] * w[0] + e[u][1] * w[1] + e[u][2] * w[2] + e[u][3] * w[3];
+        x = lane_group_sum_to_last(x, kBlockRows / 4);
+        const int keys_here = L - J * BK < BK ? L - J * BK : BK;
+        if (writes && J < nkb_here) arow[J] = x * (1.0f / (float)(rows_here * keys_here));  // mean over the entries that exist
+      }
     }
-  }
+    __syncthreads();  // the K buffers, the weights and the slab are free for the next unit
+  } while ((unit += gridDim.x) < units);
 #endif
 }
 
