@@ -43,11 +43,13 @@ struct PoolArgs {
   const int32_t* seq_lens; // optional [B] per-sample lengths (only with the whole-sequence key range)
   int32_t nqb, block_k;
   int32_t key_begin, key_len;
+  int32_t key_len2;        // > 0: a second range, the key_len2 tokens behind the first, pooled into column out_col0 + 1 (a
+                           // grid of two rows; both parts of the block that holds the prefill boundary in one launch)
   int32_t out_stride, out_col0;
   float scale_log2;        // log2(e) / sqrt(D)
   // one-pass form only (pool1p_bf16_kernel; whole key range, lse unused):
-  float* slab;             // scratch, one slab of block_q x slab_ld floats per work-group of the launch
-  int32_t slab_ld;         // floats per slab row: the key-block count rounded up to a multiple of 16
+  float* slab;             // scratch, one slab of 128 x slab_ld floats per work-group of the launch
+  int32_t slab_ld;         // columns of a slab: the key-block count rounded up to a multiple of 16
   float* lse_out;          // optional [B, Hq, L]: receives the row log-sum-exp
 };
 

@@ -59,15 +59,18 @@ void pool_bf16_kernel(const PoolArgs a) {
   const int I = gq * kBlocksPerGroup + wave / QBW;      // this wave's query block
 
   // length of this batch element (per-sample lengths shorten the whole-sequence key range with it)
-  int L = a.L, key_len = a.key_len;
+  int L = a.L;
+  const int second = blockIdx.y;  // which of the launch's key ranges
+  const int key_begin = second ? a.key_begin + a.key_len : a.key_begin;
+  int key_len = second ? a.key_len2 : a.key_len;
   if (a.seq_lens != nullptr) {
     const int len = a.seq_lens[b];
     L = len < a.L ? len : a.L;
-    key_len = L - a.key_begin < key_len ? L - a.key_begin : key_len;
+    key_len = L - key_begin < key_len ? L - key_begin : key_len;
   }
   if (gq * (32 * NW) >= L || key_len <= 0) return;  // uniform over the work-group
   const __bf16* qbase = static_cast<const __bf16*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
-  const __bf16* kbase = static_cast<const __bf16*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)a.key_begin * a.k.sl;
+  const __bf16* kbase = static_cast<const __bf16*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)key_begin * a.k.sl;
   const int row0 = gq * (32 * NW) + wave * 32;
   // a query block of the group that the head (or this sample) does not have: its waves run along with all-zero terms
   const bool block_exists = I < a.nqb && I * kBlockRows < L;
@@ -76,7 +79,7 @@ void pool_bf16_kernel(const PoolArgs a) {
   qf.load(qbase, row0, L, a.q.sl, lane);
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
   const float lse2 = (row0 + j < L) ? a.lse[(int64_t)bh * a.L + row0 + j] * 1.4426950408889634f : __builtin_inff();
-  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0;
+  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0 + second;
   const int rows_here = (L - I * kBlockRows < kBlockRows) ? L - I * kBlockRows : kBlockRows;  // query rows of the block that exist
   const int last_blk = (key_len - 1) / kTileK;
   const int tail_keys = key_len - last_blk * kTileK;  // keys that exist in the last key block of the range
@@ -221,14 +224,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int b = bh / a.Hq, h = bh % a.Hq;
   const int hk = h / (a.Hq / a.Hkv);
 
-  int L = a.L, key_len = a.key_len;  // length of this batch element
+  int L = a.L;                    // length of this batch element
+  const int second = blockIdx.y;  // which of the launch's key ranges
+  const int key_begin = second ? a.key_begin + a.key_len : a.key_begin;
+  int key_len = second ? a.key_len2 : a.key_len;
   if (a.seq_lens != nullptr) {
     const int len = a.seq_lens[b];
     L = len < a.L ? len : a.L;
-    key_len = L - a.key_begin < key_len ? L - a.key_begin : key_len;
+    key_len = L - key_begin < key_len ? L - key_begin : key_len;
   }
   if (I * (32 * RW) >= L || key_len <= 0) return;  // uniform over the work-group
-  const SlabF32<D> ks{reinterpret_cast<const char*>(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)a.key_begin * a.k.sl),
+  const SlabF32<D> ks{reinterpret_cast<const char*>(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)key_begin * a.k.sl),
                       (uint32_t)(a.k.sl * 4), key_len};
   const int row = I * (32 * RW) + rw * 32 + j;
   f32x4 qf[kChunks], kf[kChunks];
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
   const float lse2 = row < L ? a.lse[(int64_t)bh * a.L + row] * 1.4426950408889634f : __builtin_inff();
-  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0;
+  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0 + second;
   const int rows_here = (L - I * (32 * RW) < 32 * RW) ? L - I * (32 * RW) : 32 * RW;  // query rows that exist
   const int nkb = (key_len + a.block_k - 1) / a.block_k;
   const float c = a.scale_log2;
@@ -570,7 +576,7 @@ static hipError_t launch_pool_bf16_d(int block_q, const PoolArgs& a, hipStream_t
   const int blocks_per_group = 128 / block_q;
   const int64_t total = (int64_t)a.B * a.Hq * ((a.nqb + blocks_per_group - 1) / blocks_per_group);
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)total), block(256);
+  const dim3 grid((unsigned)total, a.key_len2 > 0 ? 2 : 1), block(256);
   switch (block_q) {
     case 128:
       if (a.block_k == 32) hipLaunchKernelGGL((pool_bf16_kernel<D, 4, true, 4>), grid, block, 0, s, a);
@@ -598,7 +604,7 @@ template <int D>
 static hipError_t launch_pool_f32_d(int block_q, const PoolArgs& a, hipStream_t s) {
   const int64_t total = (int64_t)a.B * a.Hq * a.nqb;
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)total);
+  const dim3 grid((unsigned)total, a.key_len2 > 0 ? 2 : 1);
   switch (block_q) {
     case 128: hipLaunchKernelGGL((pool_f32_kernel<D, 4>), grid, dim3(512), 0, s, a); break;
     case 64: hipLaunchKernelGGL((pool_f32_kernel<D, 2>), grid, dim3(512), 0, s, a); break;
