@@ -11,9 +11,13 @@
 // Per tile step t a wave computes  S(t+1) = K(t+1)[half] Q^T  interleaved with the softmax of S(t),
 // then  O += P(t) V(t)[half].  K(t+2) and V(t+1) are copied global -> LDS meanwhile; one barrier per tile.
 // The last step or two (TAIL) copy and multiply nothing past the end of the list (the last barrier would wait for it, and
-// a list of
-// 13 tiles moved three tiles of 29 for nothing. 32 heads of 2000 x 128, 32 x 32 blocks, half kept: 76.5 -> 71.5 us); a partial last
-// key block is masked in the last step (the last two with 128-key blocks), the only ones that apply key counts.
+// a list of 13 tiles moved three tiles of 29 for nothing. 32 heads of 2000 x 128, 32 x 32 blocks, half kept: 76.5 -> 71.5 us);
+// a partial last key block is masked in the last steps, the only ones that apply key counts.
+// Query blocks of 32 rows (RW = 1): a wave copies and reads its own key half only, so nothing is shared until the merge, and
+// the tile loop has no barrier. One K and one V buffer (a wave refills its half as soon as its reads are done) instead of two
+// of each put four query blocks on a compute unit, two waves per SIMD, where two blocks fitted: the second wave covers
+// what the shorter lead of the copies leaves open. 32 heads of 2000 x 128, 32 x 32 blocks, half kept: 71.5 -> 60.9 us (469
+// -> 551 TFLOP/s).
 // Listed blocks of 128 keys are walked as two tiles, listed blocks of 32 keys are paired up two to a tile
 // (see the notes at `tile_shift` / `half_blocks` below).
 #include "kernels.hpp"
@@ -23,15 +27,15 @@ namespace sparsed {
 
 // KB: keys per listed block (32, 64 or 128), a compile-time choice so that the common 64 pays nothing for the others.
 template <int D, int RW, int KB>
-__global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(RW >= 2 ? 2 : 1, RW >= 2 ? 2 : 1))) void attn_bf16_splitk_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_splitk_kernel(const AttnArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
   constexpr int NW = 2 * RW, NT = NW * 64, QT = 32 * RW;
   constexpr int kKBytes = KLayout<D>::kTileBytes, kVBytes = VLayout<D>::kTileBytes;
   constexpr float kOverflow = 1.152921504606847e18f;  // 2^60: a 16-key partial sum at or above this re-references the row
   __shared__ __attribute__((aligned(1024))) char kbuf0[kKBytes];
-  __shared__ __attribute__((aligned(1024))) char kbuf1[kKBytes];
+  __shared__ __attribute__((aligned(1024))) char kbuf1[RW == 1 ? 16 : kKBytes];
   __shared__ __attribute__((aligned(1024))) char vbuf0[kVBytes];
-  __shared__ __attribute__((aligned(1024))) char vbuf1[kVBytes];
+  __shared__ __attribute__((aligned(1024))) char vbuf1[RW == 1 ? 16 : kVBytes];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -224,7 +228,80 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(RW >= 
     __syncthreads();                                                                               \
   }
 
-  if (n > 0) {
+  // RW = 1. On entry: S(t) in S_CUR, K(t+1) on its way to this wave's half of kbuf0, then V(t) to its half of vbuf0.
+  // The waits count what was issued later: a tile copy and a block number.
+  auto wait_copy = [&](bool all) {
+    constexpr int kPer = TileDma<D, NT, false>::kPerWave;
+    if (all) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPer + 1) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto reads_done = [&]() {  // this wave's LDS reads have returned: what they read may be overwritten
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#define SPARSED_PRIVATE_STEP(TAIL, T, S_CUR, S_NEXT)                                               \
+  {                                                                                                \
+    const int blk_new = col_at((T) + 4);                                                           \
+    const int valid = !(TAIL) ? 32 : valid_in((T), blk0);                                          \
+    float part;                                                                                    \
+    if (!(TAIL) || (T) + 1 < n) {                                                                  \
+      wait_copy(false); /* K(t+1) */                                                               \
+      logits_sub<D, 1, false>(kbuf0, kh, kaddr, qf, S_NEXT);                                       \
+    }                                                                                              \
+    softmax_half(S_CUR, part, (TAIL), valid);                                                      \
+    sched_substep_interleave<D, 1, false>();                                                       \
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0, 0)) re_reference(S_CUR, part);  \
+    lsum += part;                                                                                  \
+    reads_done();                                                                                  \
+    if (!(TAIL)) kdma.issue(krsrc, __builtin_amdgcn_readfirstlane(blk2) * k_tile_bytes, kbuf0, wave);     \
+    else if ((T) + 2 < n) copy_k(blk2, kbuf0);                                                     \
+    wait_copy((TAIL) && (T) + 2 >= n); /* V(t) */                                                  \
+    pv_sub<D, 1, true>(vbuf0, kh, vaddr, p, o);                                                    \
+    reads_done();                                                                                  \
+    if (!(TAIL)) vdma.issue(vrsrc, __builtin_amdgcn_readfirstlane(blk1) * v_tile_bytes, vbuf0, wave);     \
+    else if ((T) + 1 < n) copy_v(blk1, vbuf0);                                                     \
+    blk0 = blk1;                                                                                   \
+    blk1 = blk2;                                                                                   \
+    blk2 = blk3;                                                                                   \
+    blk3 = blk_new;                                                                                \
+  }
+
+  if constexpr (RW == 1) if (n > 0) {
+    copy_k(blk0, kbuf0);
+    qf.load(qbase, row0, L, a.q.sl, lane);
+    wait_vector_memory();
+    logits_sub<D, 1, true>(kbuf0, kh, kaddr, qf, s_a);
+    reads_done();
+    if (n > 1) copy_k(blk1, kbuf0);
+    copy_v(blk0, vbuf0);
+    {
+      f32x16 first[1] = {s_a[0]};  // the first tile fixes the reference, as below
+      mask_half(first, valid_in(0, blk0));
+      M = fmaxf(row_max(first), -1e30f);
+    }
+    int t = 0;
+    // a steady step at tile t copies K(t+2), which must exist and be whole: the last block of the list may be partial
+    // (with 128-key blocks its second tile may not exist at all); its copies have no branch, so that the compiler can
+    // count what is in flight
+    const int reach = 3 + ((tail_keys < unit || (tile_shift && !(last_blk & 1))) ? 1 + tile_shift : 0);
+    while (t + reach < n) {
+      SPARSED_PRIVATE_STEP(false, t, s_a, s_b);
+      SPARSED_PRIVATE_STEP(false, t + 1, s_b, s_a);
+      t += 2;
+    }
+    for (; t < n; ++t) {
+      if (t & 1) {
+        SPARSED_PRIVATE_STEP(true, t, s_b, s_a);
+      } else {
+        SPARSED_PRIVATE_STEP(true, t, s_a, s_b);
+      }
+    }
+  }
+#undef SPARSED_PRIVATE_STEP
+
+  if constexpr (RW > 1) if (n > 0) {
     copy_k(blk0, kbuf0);
     if (n > 1) copy_k(blk1, kbuf1);
     copy_v(blk0, vbuf0);
@@ -263,6 +340,7 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(RW >= 
   float* const xchg = reinterpret_cast<float*>(rw == 0 ? kbuf0 : kbuf1);   // the accumulator
   float* const xchg2 = reinterpret_cast<float*>(rw == 0 ? vbuf0 : vbuf1);  // reference maximum and sum
   const float ltot_mine = pair_sum(lsum);
+  if (RW == 1) __syncthreads();  // the exchange overlaps the other wave's halves
   if (kh == 1) {
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
