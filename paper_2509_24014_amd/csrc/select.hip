@@ -312,7 +312,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Bound: latency. The descent is a chain of up to 32 compare - count - branch steps; a row of up to 64 * R entries stays
 // in R registers a lane, so that a step does not wait for LDS reads. Rows longer than the widest register form (16) are
 // held in LDS (R = 0). 8192 rows of 256 entries: 40.8 -> 20.8 us;
-// 288 rows of at most 25 entries in two ranges: 12.0 -> 5.9 us; 16 rows of 8: 6.3 -> 3.4 us. (Before: every row in LDS, all 32 steps.)
+// 576 rows of at most 25 entries in two ranges: 12.0 -> 5.9 us; 16 rows of 8: 6.3 -> 3.4 us. (Before: every row in LDS, all 32 steps.)
 template <int R>
 struct TopkRow {
   uint32_t x[R > 0 ? R : 1];
