@@ -229,11 +229,16 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 
   // RW = 1. On entry: S(t) in S_CUR, K(t+1) on its way to this wave's half of kbuf0, then V(t) to its half of vbuf0.
-  // The waits count what was issued later: a tile copy and a block number.
+  // A counted wait leaves exactly one tile copy in flight, the one issued since the fence in front of it (V(t) behind
+  // K(t+1); K(t+2) behind V(t)). The block-number load is not part of any count: it has no fixed place among the copies, so
+  // counting it would let a load of the awaited tile stay in flight wherever the compiler issued it earlier. It is issued
+  // after the wait for K(t+1) and is a whole tile of work old at the next wait, so requiring it there costs nothing.
+  // (The compiler cannot tell the copies into kbuf0 from those into vbuf0 and waits for V(t) as well in front of the K reads
+  // of a step, at head dim 128 of both steps, at 64 of the first: V's copy is covered by the other wave of the SIMD.)
   auto wait_copy = [&](bool all) {
     constexpr int kPer = TileDma<D, NT, false>::kPerWave;
     if (all) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPer + 1) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPer) : "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
   auto reads_done = [&]() {  // this wave's LDS reads have returned: what they read may be overwritten
@@ -243,11 +248,11 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
   };
 #define SPARSED_PRIVATE_STEP(TAIL, T, S_CUR, S_NEXT)                                               \
   {                                                                                                \
-    const int blk_new = col_at((T) + 4);                                                           \
     const int valid = !(TAIL) ? 32 : valid_in((T), blk0);                                          \
     float part;                                                                                    \
+    if (!(TAIL) || (T) + 1 < n) wait_copy(false); /* K(t+1) */                                     \
+    const int blk_new = col_at((T) + 4);                                                           \
     if (!(TAIL) || (T) + 1 < n) {                                                                  \
-      wait_copy(false); /* K(t+1) */                                                               \
       logits_sub<D, 1, false>(kbuf0, kh, kaddr, qf, S_NEXT);                                       \
     }                                                                                              \
     softmax_half(S_CUR, part, (TAIL), valid);                                                      \
@@ -283,8 +288,8 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
     int t = 0;
     // a steady step at tile t copies K(t+2), which must exist and be whole: the last block of the list may be partial
-    // (with 128-key blocks its second tile may not exist at all); its copies have no branch, so that the compiler can
-    // count what is in flight
+    // (with 128-key blocks its second tile may not exist at all); its copies have no branch, so that
+    // a wait has exactly one of them behind it
     const int reach = 3 + ((tail_keys < unit || (tile_shift && !(last_blk & 1))) ? 1 + tile_shift : 0);
     while (t + reach < n) {
       SPARSED_PRIVATE_STEP(false, t, s_a, s_b);
