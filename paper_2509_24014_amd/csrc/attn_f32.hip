@@ -121,6 +121,12 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int x = 0; x < 16; ++x)
         if (8 * (x / 4) + 4 * g + (x % 4) >= valid) s[x] = -__builtin_inff();
+      if (kHasV && valid <= 0) {  // no key at all: the rows stand for none, and 0 times an infinity of theirs would be NaN
+#pragma unroll
+        for (int x = 0; x < 16; ++x)
+#pragma unroll
+          for (int dt = 0; dt < kV; ++dt) vf[x][dt] = 0.f;
+      }
     }
     float mx = s[0];
 #pragma unroll
