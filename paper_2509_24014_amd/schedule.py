@@ -35,12 +35,21 @@ class SparseDLayer:
         self.calls = {"dense": 0, "select": 0, "sparse": 0}
         self._lse = None
         self._workspace = None
+        self._workspace_for = None   # shape and dtype of the q it was made for
 
     def _scratch(self, q):
         if self._workspace is None:
             need = binding.select_workspace_bytes(q, self.block_q, self.block_k)
             self._workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            self._workspace_for = (q.shape, q.dtype)
         return self._workspace
+
+    def _scratch_holds_one_call(self, q):
+        """Whether the kept workspace suffices for the dense call that also selects: one that was made for another q may do
+        for the two calls only, which ask for less."""
+        workspace = self._scratch(q)
+        return (self._workspace_for == (q.shape, q.dtype)
+                or workspace.numel() >= binding.select_workspace_bytes(q, self.block_q, self.block_k))
 
     def _select(self, q, k, lse):
         self.index = binding.select_pattern(q, k, self.block_q, self.block_k, self.rho, lse_in=lse,
@@ -54,7 +63,7 @@ class SparseDLayer:
             self._select(q, k, None)  # no dense call at this step: selection runs its own statistics pass
         if t < self.n_dense:
             switch = t == self.n_dense - 1
-            if switch and q.is_cuda and q.dtype == torch.bfloat16:
+            if switch and q.is_cuda and q.dtype == torch.bfloat16 and self._scratch_holds_one_call(q):
                 # bf16: the dense kernel leaves the pooled scores the selection ranks, one Q K^T for both
                 out, self.index = binding.attn_dense_select(q, k, v, self.block_q, self.block_k, self.rho, out=out,
                                                             workspace=self._scratch(q), index=self.index)

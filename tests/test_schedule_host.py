@@ -70,3 +70,22 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("kept_bytes,calls", [(None, ["dense_select"]), (16, ["dense_select"]), (15, ["dense", "select"])])
+def test_bf16_switch_step_takes_the_two_calls_with_a_workspace_the_one_call_may_refuse(recorder, monkeypatch, kept_bytes, calls):
+    """select_workspace_bytes() always suffices for the call that does both; a kept workspace of less (the layer met a smaller
+    call first) may still do for the two calls, which ask for less."""
+    monkeypatch.setattr(binding, "attn_dense_select", lambda q, k, v, bq, bk, rho, out=None, workspace=None, index=None:
+                        recorder.append(("dense_select", workspace.numel())) or (q, ("index", 1)))
+
+    class OnGpu(torch.Tensor):
+        is_cuda = True
+
+    q = torch.zeros(1, 1, 64, 64, dtype=torch.bfloat16).as_subclass(OnGpu)
+    layer = schedule.SparseDLayer(5, 0.2, 32, 32, 0.5)
+    if kept_bytes is not None:
+        layer._workspace = torch.empty(kept_bytes, dtype=torch.uint8)
+    layer.step(q, q, q, 0)
+    assert [e[0] for e in recorder] == calls
+    assert layer.calls == {"dense": 1, "select": 1, "sparse": 0}
