@@ -281,7 +281,8 @@ def attn_dense_select(q, k, v, block_q: int, block_k: int, rho: float, out: Opti
     lib = load_library()
     B, H, L, D = q.shape
     nqb, nkb = -(-L // block_q), -(-L // block_k)
-    if out is None:
+    own_out = out is None
+    if own_out:
         out = torch.empty_like(q)
     if index is None:
         keep = kept_blocks(rho, nkb)
@@ -295,7 +296,8 @@ def attn_dense_select(q, k, v, block_q: int, block_k: int, rho: float, out: Opti
     if lse_out is not None and (lse_out.dtype != torch.float32 or not lse_out.is_contiguous() or lse_out.numel() != B * H * L):
         raise ValueError("lse_out must be contiguous fp32 [B, Hq, L]")
     if stream is not None and int(stream.cuda_stream) != int(torch.cuda.current_stream(q.device).cuda_stream):
-        for t in (workspace, index.row_ptr, index.col_idx):   # as in select_pattern
+        # as in select_pattern; the output as well where it is this call's own allocation
+        for t in (workspace, index.row_ptr, index.col_idx) + ((out,) if own_out else ()):
             t.record_stream(stream)
     ex = _Exec(_stream_ptr(stream), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                lse_out.data_ptr() if lse_out is not None else None, None,
