@@ -165,7 +165,7 @@ sparsed_status attention(Mode mode, const sparsed_tensor* q, const sparsed_tenso
   a.lse = (mode == Mode::kDense && ex) ? ex->lse_out : nullptr;
   a.B = q->B;
   a.Hq = q->H;
-  a.Hkv = k->H;
+  a.group = q->H / k->H;
   a.L = q->L;
   a.seq_lens = ex ? ex->seq_lens : nullptr;
   a.scale_log2 = scale_log2(q->D);
@@ -244,7 +244,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   p.apool = apool;
   p.B = q->B;
   p.Hq = q->H;
-  p.Hkv = k->H;
+  p.group = q->H / k->H;
   p.L = q->L;
   p.seq_lens = seq_lens;
   p.nqb = nqb;
@@ -282,7 +282,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
       a.lse = lse_buf;
       a.B = q->B;
       a.Hq = q->H;
-      a.Hkv = k->H;
+      a.group = q->H / k->H;
       a.L = q->L;
       a.seq_lens = seq_lens;
       a.scale_log2 = scale_log2(q->D);
@@ -392,7 +392,7 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
   a.lse = ex->lse_out;
   a.B = q->B;
   a.Hq = q->H;
-  a.Hkv = k->H;
+  a.group = q->H / k->H;
   a.L = q->L;
   a.seq_lens = ex->seq_lens;
   a.scale_log2 = scale_log2(q->D);

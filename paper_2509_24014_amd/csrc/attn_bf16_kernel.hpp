@@ -75,9 +75,8 @@ __global__ __launch_bounds__(NW * 64)
   if (kPool) n_units = a.B * a.Hq * a.n_qtiles;
   const int lid = xcd_remap(unit, n_units);
   const int qt = lid % a.n_qtiles;
-  const int bh = batch_head_at(lid / a.n_qtiles, a.B, a.Hq, a.Hkv, a.seq_lens);
-  const int b = bh / a.Hq, h = bh % a.Hq;
-  const int hk = h / (a.Hq / a.Hkv);
+  const Slab slab_of = slab_at(lid / a.n_qtiles, a);
+  const int b = slab_of.b, h = slab_of.h, hk = slab_of.hk, bh = b * a.Hq + h;
   // length of this batch element: the tensor's L unless the caller passed per-sample lengths
   int L = a.L;
   if (a.seq_lens != nullptr) {

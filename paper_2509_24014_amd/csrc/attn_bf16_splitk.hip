@@ -44,9 +44,8 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   const int lid = xcd_remap(blockIdx.x, gridDim.x);
   const int qt = lid % a.n_qtiles;
-  const int bh = batch_head_at(lid / a.n_qtiles, a.B, a.Hq, a.Hkv, a.seq_lens);
-  const int b = bh / a.Hq, h = bh % a.Hq;
-  const int hk = h / (a.Hq / a.Hkv);
+  const Slab slab_of = slab_at(lid / a.n_qtiles, a);
+  const int b = slab_of.b, h = slab_of.h, hk = slab_of.hk, bh = b * a.Hq + h;
   int L = a.L;  // length of this batch element
   if (a.seq_lens != nullptr) {
     const int len = a.seq_lens[b];

@@ -52,9 +52,8 @@ void pool_bf16_kernel(const PoolArgs a) {
   const int lid = xcd_remap(blockIdx.x, gridDim.x);
   const int groups_per_head = (a.nqb + kBlocksPerGroup - 1) / kBlocksPerGroup;
   const int gq = lid % groups_per_head;  // which run of 32 * NW rows of the head
-  const int bh = batch_head_at(lid / groups_per_head, a.B, a.Hq, a.Hkv, a.seq_lens);
-  const int b = bh / a.Hq, h = bh % a.Hq;
-  const int hk = h / (a.Hq / a.Hkv);
+  const Slab slab_of = slab_at(lid / groups_per_head, a);
+  const int b = slab_of.b, h = slab_of.h, hk = slab_of.hk, bh = b * a.Hq + h;
   const int first_wave = (wave / QBW) * QBW;            // first wave of this wave's query block
   const int I = gq * kBlocksPerGroup + wave / QBW;      // this wave's query block
 
@@ -220,9 +219,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int j = lane & 31, g = lane >> 5;
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
   const int I = lid % a.nqb;
-  const int bh = batch_head_at(lid / a.nqb, a.B, a.Hq, a.Hkv, a.seq_lens);
-  const int b = bh / a.Hq, h = bh % a.Hq;
-  const int hk = h / (a.Hq / a.Hkv);
+  const Slab slab_of = slab_at(lid / a.nqb, a);
+  const int b = slab_of.b, h = slab_of.h, hk = slab_of.hk, bh = b * a.Hq + h;
 
   int L = a.L;                    // length of this batch element
   const int second = blockIdx.y;  // which of the launch's key ranges

@@ -66,9 +66,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     const int groups_per_head = (a.nqb + kBlocksPerGroup - 1) / kBlocksPerGroup;
     units = a.B * a.Hq * groups_per_head;
     const int gq = unit % groups_per_head;
-    const int bh = batch_head_at(unit / groups_per_head, a.B, a.Hq, a.Hkv, a.seq_lens);
-    const int b = bh / a.Hq, h = bh % a.Hq;
-    const int hk = h / (a.Hq / a.Hkv);
+    const Slab slab_of = slab_at(unit / groups_per_head, a);
+    const int b = slab_of.b, h = slab_of.h, hk = slab_of.hk, bh = b * a.Hq + h;
     int L = a.L;  // length of this batch element
     if (a.seq_lens != nullptr) {
       const int len = a.seq_lens[b];
