@@ -45,9 +45,17 @@ namespace sparsed {
 template <int D, int NQ, int NW, Mode MODE, int KB = kTileK>
 __global__ __launch_bounds__(NW * 64)
     __attribute__((amdgpu_waves_per_eu((NQ == 1 && NW >= 4) ? (MODE == Mode::kStats ? 4 : 2) : 1,
-                                       (NQ == 1 && NW >= 4) ? (MODE == Mode::kStats ? 4 : 2) : 1))) void attn_bf16_kernel(const AttnArgs) {
+                                       (NQ == 1 && NW >= 4) ? (MODE == Mode::kStats ? 4 : 2) : 1))) void attn_bf16_kernel(const AttnArgs args_in) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
   constexpr bool kPool = MODE == Mode::kDensePool;
+  // What a mode works out again late instead of keeping it across the tile loop. The lane number in the last steps and the
+  // epilogue: pooling, and sparse at head dim 128 (1 spilled register otherwise; 32 heads of 8192 x 128, 128 x 64 blocks:
+  // 118.4 -> 116.5 us). The lane number everywhere, and the arguments: pooling only. Where a mode has the registers it is the
+  // slower choice, by 0.1 to 0.2 us of a short call (4 heads of 256 x 128, dense: 11.3 us, 11.0 without).
+  constexpr bool kLateLane = kPool || (MODE == Mode::kSparse && D == 128);
+  // Whether the rare re-reference path is laid out behind the loop. At head dim 64, where the loop is short, the hint makes it
+  // slower (28 heads of 3328 x 64, dense: 106 us with it, 104 without).
+  constexpr bool kFarReReference = kPool || D == 128;
   static_assert(!kPool || NQ == 1, "pooling parks one row per lane");
   constexpr int NT = NW * 64;
   constexpr int QT = 32 * NQ * NW;
@@ -70,8 +78,9 @@ __global__ __launch_bounds__(NW * 64)
   int unit = blockIdx.x;
   int n_units = (int)gridDim.x;
   do {
-  const KernelArgs<AttnArgs>& a = fresh_kernel_args<AttnArgs>();
-  const int lane = fresh_lane();
+  using Args = KernelArgsOr<kPool, AttnArgs>;
+  Args& a = kernel_args_now<kPool>(args_in);
+  const int lane = kPool ? fresh_lane() : (int)(threadIdx.x & 63);
   if (kPool) n_units = a.B * a.Hq * a.n_qtiles;
   const int lid = xcd_remap(unit, n_units);
   const int qt = lid % a.n_qtiles;
@@ -224,7 +233,7 @@ __global__ __launch_bounds__(NW * 64)
   // masked: apply `valid`, the number of keys of this sub-tile that exist (32 or more = all, 0 or less =
   // none: a phantom tile or the empty half of a partial last block). Unmasked steps skip the 16 selects.
   auto mask_sub = [&](f32x16(&s)[NQ], int valid) {
-    const int mine = valid - 8 * (fresh_lane() >> 5);  // register x of lane (j, g) holds key 16*(x/8) + 8*g + x%8 of the sub-tile
+    const int mine = valid - 8 * ((kPool ? fresh_lane() : lane) >> 5);  // register x of lane (j, g) holds key 16*(x/8) + 8*g + x%8 of the sub-tile
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
@@ -362,7 +371,7 @@ __global__ __launch_bounds__(NW * 64)
     if (kHasV) pv_sub<D, NQ, false>(vb_this, 0, vaddr, p_even, o);                                 \
     softmax_sub(s_odd, p_odd, part, (MASKED), valid_odd);                                          \
     sched_substep_interleave<D, NQ, kHasV>();                                                      \
-    if (__builtin_expect(overflowed(part), 0)) re_reference(s_odd, p_odd, part, (T));              \
+    if ((kFarReReference ? __builtin_expect(overflowed(part), 0) : overflowed(part))) re_reference(s_odd, p_odd, part, (T));              \
     SPARSED_ADD_PART                                                                               \
     if (kPool) park_tile((P), (MASKED), (T), part[0]);                                             \
     __builtin_amdgcn_sched_barrier(0);                                                             \
@@ -370,7 +379,7 @@ __global__ __launch_bounds__(NW * 64)
     if (kHasV) pv_sub<D, NQ, false>(vb_this, 1, vaddr, p_odd, o);                                  \
     softmax_sub(s_even, p_even, part, (MASKED), valid_even);                                       \
     sched_substep_interleave<D, NQ, kHasV>();                                                      \
-    if (__builtin_expect(overflowed(part), 0)) re_reference(s_even, p_even, part, (T) + 1);        \
+    if ((kFarReReference ? __builtin_expect(overflowed(part), 0) : overflowed(part))) re_reference(s_even, p_even, part, (T) + 1);        \
     SPARSED_ADD_PART                                                                               \
     if (kPool) carry = part[0];                                                                    \
     blk0 = blk1;                                                                                   \
@@ -421,7 +430,7 @@ __global__ __launch_bounds__(NW * 64)
       SPARSED_TILE_STEP(0, false, t);
       t += 1;
     }
-    lane_tail = fresh_lane();
+    lane_tail = late_lane<kLateLane>(lane);
     for (; t < n; ++t) {
       if (t & 1) {
         SPARSED_TILE_STEP(1, true, t);
@@ -442,12 +451,10 @@ __global__ __launch_bounds__(NW * 64)
   static_assert(32 * kRowBytes * 2 <= kKBytes && (!kHasV || 32 * kRowBytes * 2 <= kVBytes), "two waves share one buffer");
   // (The lane-derived values of this part are worked out afresh from an opaque copy of the lane number, so that
   // none of them is kept in a register, or spilled, across the tile loop.)
-  const int lane_e = fresh_lane();
-  // kPool reads its arguments again here; the other modes have scalar registers to keep them in, and a short call would wait
-  // for the read (2 samples x 8 heads of 600 x 64, dense: 12.11 us with it, 11.95 without).
-  KernelArgs<AttnArgs>* args_e = &a;
-  if constexpr (kPool) args_e = &fresh_kernel_args<AttnArgs>();
-  const KernelArgs<AttnArgs>& ae = *args_e;
+  const int lane_e = late_lane<kLateLane>(lane);
+  // (kPool reads its arguments again here; the other modes have scalar registers to keep them in, and a short call would wait
+  // for the read: 2 samples x 8 heads of 600 x 64, dense: 12.11 us with it, 11.95 without.)
+  Args& ae = kernel_args_now<kPool>(args_in);
   const int je = lane_e & 31, ge = lane_e >> 5;
   char* const stage = ((wave >> 1) == 0 ? kbuf0 : (wave >> 1) == 1 ? kbuf1 : (wave >> 1) == 2 ? vbuf0 : vbuf1) + (wave & 1) * (32 * kRowBytes);
 #pragma unroll

@@ -76,6 +76,15 @@ __device__ __forceinline__ int fresh_lane() {
   return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
 }
 
+// The lane number for use late in a kernel: worked out anew, or an opaque copy of `lane` (so that what is derived from it is
+// worked out there and not carried along).
+template <bool ANEW>
+__device__ __forceinline__ int late_lane(int lane) {
+  if constexpr (ANEW) return fresh_lane();
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
 // The kernel's argument struct (its only argument), read from the argument segment at the point of the call. Reading
 // it again where it is used late keeps two dozen scalars from living, or being spilled into vector registers, in between.
 template <typename Args>
@@ -85,6 +94,23 @@ __device__ __forceinline__ KernelArgs<Args>& fresh_kernel_args() {
   auto p = (KernelArgs<Args>*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
   return *p;
+}
+
+// The same as a compile-time choice: read again (FRESH), or the argument itself.
+template <bool FRESH, typename Args>
+struct PickKernelArgs {
+  using T = KernelArgs<Args>;
+};
+template <typename Args>
+struct PickKernelArgs<false, Args> {
+  using T = const Args;
+};
+template <bool FRESH, typename Args>
+using KernelArgsOr = typename PickKernelArgs<FRESH, Args>::T;
+template <bool FRESH, typename Args>
+__device__ __forceinline__ KernelArgsOr<FRESH, Args>& kernel_args_now(const Args& in) {
+  if constexpr (FRESH) return fresh_kernel_args<Args>();
+  else return in;
 }
 
 // Sum of one value per lane over aligned groups of 8, 16 or 32 lanes with DPP row operations (no LDS traffic); the total
