@@ -13,11 +13,12 @@
 // The last step or two (TAIL) copy and multiply nothing past the end of the list (the last barrier would wait for it, and
 // a list of 13 tiles moved three tiles of 29 for nothing. 32 heads of 2000 x 128, 32 x 32 blocks, half kept: 76.5 -> 71.5 us);
 // a partial last key block is masked in the last steps, the only ones that apply key counts.
-// Query blocks of 32 rows (RW = 1): a wave copies and reads its own key half only, so nothing is shared until the merge, and
-// the tile loop has no barrier. One K and one V buffer (a wave refills its half as soon as its reads are done) instead of two
-// of each put four query blocks on a compute unit, two waves per SIMD, where two blocks fitted: the second wave covers
-// what the shorter lead of the copies leaves open. 32 heads of 2000 x 128, 32 x 32 blocks, half kept: 71.5 -> 60.9 us (469
-// -> 551 TFLOP/s).
+// Query blocks of 32 rows (RW = 1) have two forms. Where the launch fills the chip, PRIVATE: a wave copies and reads its own key
+// half only, so nothing is shared until the merge, and the tile loop has no barrier. One K and one V buffer (a wave refills its
+// half as soon as its reads are done) instead of two of each put four query blocks on a compute unit, two waves per SIMD,
+// where two blocks fitted: the second wave covers what the shorter lead of the copies leaves open. 32 heads of 2000 x 128,
+// 32 x 32 blocks, half kept: 71.5 -> 60.9 us (469 -> 551 TFLOP/s). With no second wave there the lead is what counts, and the
+// double buffers are the better form (the rule is at launch_splitk_d).
 // Listed blocks of 128 keys are walked as two tiles, listed blocks of 32 keys are paired up two to a tile
 // (see the notes at `tile_shift` / `half_blocks` below).
 #include "kernels.hpp"
@@ -26,16 +27,18 @@
 namespace sparsed {
 
 // KB: keys per listed block (32, 64 or 128), a compile-time choice so that the common 64 pays nothing for the others.
-template <int D, int RW, int KB>
-__global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_splitk_kernel(const AttnArgs a) {
+// PRIVATE: the barrier-free form (RW = 1).
+template <int D, int RW, int KB, bool PRIVATE>
+__global__ __launch_bounds__(RW * 128)
+    __attribute__((amdgpu_waves_per_eu(RW == 1 && !PRIVATE ? 1 : 2, RW == 1 && !PRIVATE ? 1 : 2))) void attn_bf16_splitk_kernel(const AttnArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
   constexpr int NW = 2 * RW, NT = NW * 64, QT = 32 * RW;
   constexpr int kKBytes = KLayout<D>::kTileBytes, kVBytes = VLayout<D>::kTileBytes;
   constexpr float kOverflow = 1.152921504606847e18f;  // 2^60: a 16-key partial sum at or above this re-references the row
   __shared__ __attribute__((aligned(1024))) char kbuf0[kKBytes];
-  __shared__ __attribute__((aligned(1024))) char kbuf1[RW == 1 ? 16 : kKBytes];
+  __shared__ __attribute__((aligned(1024))) char kbuf1[PRIVATE ? 16 : kKBytes];
   __shared__ __attribute__((aligned(1024))) char vbuf0[kVBytes];
-  __shared__ __attribute__((aligned(1024))) char vbuf1[RW == 1 ? 16 : kVBytes];
+  __shared__ __attribute__((aligned(1024))) char vbuf1[PRIVATE ? 16 : kVBytes];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -227,7 +230,7 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
     __syncthreads();                                                                               \
   }
 
-  // RW = 1. On entry: S(t) in S_CUR, K(t+1) on its way to this wave's half of kbuf0, then V(t) to its half of vbuf0.
+  // PRIVATE. On entry: S(t) in S_CUR, K(t+1) on its way to this wave's half of kbuf0, then V(t) to its half of vbuf0.
   // A counted wait leaves exactly one tile copy in flight, the one issued since the fence in front of it (V(t) behind
   // K(t+1); K(t+2) behind V(t)). The block-number load is not part of any count: it has no fixed place among the copies, so
   // counting it would let a load of the awaited tile stay in flight wherever the compiler issued it earlier. It is issued
@@ -272,7 +275,7 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
     blk3 = blk_new;                                                                                \
   }
 
-  if constexpr (RW == 1) if (n > 0) {
+  if constexpr (PRIVATE) if (n > 0) {
     copy_k(blk0, kbuf0);
     qf.load(qbase, row0, L, a.q.sl, lane);
     wait_vector_memory();
@@ -305,7 +308,7 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 #undef SPARSED_PRIVATE_STEP
 
-  if constexpr (RW > 1) if (n > 0) {
+  if constexpr (!PRIVATE) if (n > 0) {
     copy_k(blk0, kbuf0);
     if (n > 1) copy_k(blk1, kbuf1);
     copy_v(blk0, vbuf0);
@@ -339,12 +342,13 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
   // Merge the two key halves of every row. The waves of half 1 leave their accumulator, reference
   // maximum and sum in the (now idle) K buffers, laid out [value][lane] so that both sides touch
   // consecutive words; the waves of half 0 fold them in, normalise and store.
+  static_assert(!PRIVATE || RW == 1, "a wave per key half");
   static_assert(RW <= 2, "one K buffer and one V buffer per wave of the second key half");
   static_assert(D / 32 * 16 * 64 * 4 <= kKBytes && 2 * 64 * 4 <= kVBytes, "exchange areas must fit the buffers");
   float* const xchg = reinterpret_cast<float*>(rw == 0 ? kbuf0 : kbuf1);   // the accumulator
   float* const xchg2 = reinterpret_cast<float*>(rw == 0 ? vbuf0 : vbuf1);  // reference maximum and sum
   const float ltot_mine = pair_sum(lsum);
-  if (RW == 1) __syncthreads();  // the exchange overlaps the other wave's halves
+  if (PRIVATE) __syncthreads();  // the exchange overlaps the other wave's halves
   if (kh == 1) {
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
@@ -392,26 +396,38 @@ __global__ __launch_bounds__(RW * 128) __attribute__((amdgpu_waves_per_eu(2, 2))
 #endif
 }
 
-template <int D, int RW>
+template <int D, int RW, bool PRIVATE>
 static hipError_t launch_splitk(const AttnArgs& a, hipStream_t s) {
   const int64_t total = (int64_t)a.B * a.Hq * a.n_qtiles;
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)total), block(RW * 128);
   switch (a.block_k) {
-    case 32: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 32>), grid, block, 0, s, a); break;
-    case 64: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 64>), grid, block, 0, s, a); break;
-    case 128: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 128>), grid, block, 0, s, a); break;
+    case 32: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 32, PRIVATE>), grid, block, 0, s, a); break;
+    case 64: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 64, PRIVATE>), grid, block, 0, s, a); break;
+    case 128: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 128, PRIVATE>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 // Sparse attention for query blocks of 32 or 64 rows. a.n_qtiles must be set by the caller.
+template <int D>
+static hipError_t launch_splitk_d(int block_q, const AttnArgs& a, hipStream_t s) {
+  if (block_q == 64) return launch_splitk<D, 2, false>(a, s);
+  if (block_q != 32) return hipErrorInvalidValue;
+  // Double buffers while every compute unit has at most the two work-groups that they allow: 448 work-groups, 14 tiles a row:
+  // head dim 64 11.5 us against 13.4 private, 128 18.3 against 19.2; 528 work-groups, 8 tiles: 14.4 against 10.3, 21.7 against
+  // 15.3. At head dim 128 the barriers outweigh the lead on long lists (512 work-groups, 16 tiles: 20.2 against 20.9; 25 tiles:
+  // 32.9 against 31.9; 76 tiles: 82.8 against 73.0), at 64 they do not (76 tiles: 44.2 against 46.7). The host does not know
+  // the lists; their capacity is the average length where it is exact, and an upper bound of it otherwise.
+  const bool long_lists = (int64_t)a.cap_per_head * a.block_k > (int64_t)20 * kTileK * a.nqb;
+  if ((int64_t)a.B * a.Hq * a.n_qtiles <= 512 && !(D == 128 && long_lists)) return launch_splitk<D, 1, false>(a, s);
+  return launch_splitk<D, 1, true>(a, s);
+}
+
 hipError_t launch_attn_bf16_splitk(int D, int block_q, const AttnArgs& a, hipStream_t s) {
-  if (D == 128 && block_q == 64) return launch_splitk<128, 2>(a, s);
-  if (D == 128 && block_q == 32) return launch_splitk<128, 1>(a, s);
-  if (D == 64 && block_q == 64) return launch_splitk<64, 2>(a, s);
-  if (D == 64 && block_q == 32) return launch_splitk<64, 1>(a, s);
+  if (D == 128) return launch_splitk_d<128>(block_q, a, s);
+  if (D == 64) return launch_splitk_d<64>(block_q, a, s);
   return hipErrorInvalidValue;
 }
 

@@ -26,7 +26,7 @@ def kernels(tmp_path_factory):
     with open(out) as f:
         text = f.read()
     found = {}
-    for m in re.finditer(r"^(_ZN7sparsed\d+attn_bf16_splitk_kernelILi(\d+)ELi(\d+)ELi(\d+)E\w*):(.*?)^\.Lfunc_end", text, re.M | re.S):
+    for m in re.finditer(r"^(_ZN7sparsed\d+attn_bf16_splitk_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb1E\w*):(.*?)^\.Lfunc_end", text, re.M | re.S):
         found[tuple(int(m.group(i)) for i in (2, 3, 4))] = m.group(5)
     return found
 
