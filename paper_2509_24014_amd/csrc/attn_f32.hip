@@ -228,12 +228,39 @@ static hipError_t launch_one_f32(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Waves per work-group: a compute unit holds eight waves of this kernel, as two work-groups of four or one of eight.
-// Eight where there are no more work-groups than compute units (short sequences: the keys split eight ways), else four.
+// Waves per work-group, dense and statistics: a compute unit holds eight waves of this kernel, as two work-groups of four or
+// one of eight. Eight where there are no more work-groups than compute units (short sequences: the keys split eight ways), else four.
 template <int D, Mode MODE>
 static hipError_t launch_by_fill_f32(const AttnArgs& a, hipStream_t s) {
   if ((int64_t)a.B * a.Hq * a.n_qtiles <= 256) return launch_one_f32<D, 8, MODE>(a, s);
   return launch_one_f32<D, 4, MODE>(a, s);
+}
+
+// Sparse: a short list does not feed four waves, and a work-group of fewer waves leaves its compute unit to others. The waves
+// of a SIMD take turns on its matrix core (one alone is hardly faster than two), so the time goes with waves per SIMD times
+// steps per wave, plus about one step for the prologue and the merge: the smallest of that over one, two and four waves. The
+// average list comes from the capacity, which is exact or an upper bound. Against four waves for all, at 64 columns a head,
+// 128 x 32 blocks: 1000 work-groups with one tile 16.4 -> 10.1 us, 2048 with 5 tiles 54.7 -> 38.1 us, 1152 with 6 tiles
+// (64 x 64 blocks) 36.7 -> 33.0 us. Long lists keep four.
+template <int D>
+static hipError_t launch_sparse_f32(const AttnArgs& a, hipStream_t s) {
+  const int64_t groups = (int64_t)a.B * a.Hq * a.n_qtiles;
+  if (groups <= 256) return launch_one_f32<D, 8, Mode::kSparse>(a, s);
+  const int64_t tiles = ((int64_t)a.cap_per_head * (a.block_k / kTileKF) + a.nqb - 1) / a.nqb;
+  int waves = 1;
+  int64_t least = 0;
+  for (int kw = 1; kw <= 4; kw *= 2) {
+    int64_t per_simd = (groups * kw + 1023) / 1024;
+    if (per_simd < 2) per_simd = 2;
+    const int64_t cost = per_simd * ((tiles + kw - 1) / kw + 1);
+    if (kw == 1 || cost <= least) {
+      least = cost;
+      waves = kw;
+    }
+  }
+  if (waves == 1) return launch_one_f32<D, 1, Mode::kSparse>(a, s);
+  if (waves == 2) return launch_one_f32<D, 2, Mode::kSparse>(a, s);
+  return launch_one_f32<D, 4, Mode::kSparse>(a, s);
 }
 
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {
@@ -242,12 +269,12 @@ hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_
   a.n_qtiles = (a.L + 31) / 32;
   if (D == 128) {
     if (mode == Mode::kDense) return launch_by_fill_f32<128, Mode::kDense>(a, s);
-    if (mode == Mode::kSparse) return launch_by_fill_f32<128, Mode::kSparse>(a, s);
+    if (mode == Mode::kSparse) return launch_sparse_f32<128>(a, s);
     return launch_by_fill_f32<128, Mode::kStats>(a, s);
   }
   if (D == 64) {
     if (mode == Mode::kDense) return launch_by_fill_f32<64, Mode::kDense>(a, s);
-    if (mode == Mode::kSparse) return launch_by_fill_f32<64, Mode::kSparse>(a, s);
+    if (mode == Mode::kSparse) return launch_sparse_f32<64>(a, s);
     return launch_by_fill_f32<64, Mode::kStats>(a, s);
   }
   return hipErrorInvalidValue;

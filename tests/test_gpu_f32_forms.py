@@ -66,6 +66,30 @@ def test_sparse_lists_of_any_length(bq, bk, L, D):
     assert_output_close(out, oracle.attn_sparse(q, k, v, rp.numpy(), ci.numpy(), bq, bk), torch.float32, f"sparse f32 {bq}x{bk} L={L}")
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,bq,bk,L,longest", [
+    (110, 32, 32, 600, 3),     # 2090 work-groups, 1 or 2 tiles on average: one wave each
+    (110, 64, 64, 590, 2),     # the same with two-tile blocks, the last one partial (14 keys)
+    (110, 128, 32, 600, 4),    # rows of a 128-row query block in four work-groups
+    (40, 32, 32, 600, 3),      # 760: two waves
+    (40, 128, 64, 590, 2),
+    (40, 32, 64, 600, 6),      # 760, lists of 6 tiles: four waves
+    (40, 64, 128, 530, 3),     # 680, four-tile blocks, the last one 18 keys
+])
+def test_sparse_short_lists_on_many_work_groups(H, bq, bk, L, longest, D):
+    """The number of waves that split a list follows from the work-groups and the capacity of the lists."""
+    nqb, nkb = -(-L // bq), -(-L // bk)
+    q, k, v = _qkv(1, H, H // 10, L, D, seed=L + bk + D)
+    rp, ci = random_csr(1, H, nqb, nkb, longest, seed=H + bk, device="cpu")
+    ci = ci[..., :int(rp[..., -1].max())].contiguous()   # an exact capacity (for the head with the most entries)
+    ix = sd.BlockIndex(rp.to(DEV), ci.to(DEV), bq, bk, nkb)
+    sd.index_validate(ix)
+    guard = torch.full((1, H, L + 40, D), 7.0, device=DEV)
+    out = sd.attn_sparse(q.to(DEV), k.to(DEV), v.to(DEV), ix, out=guard[:, :, :L])
+    assert (guard[:, :, L:] == 7.0).all()
+    assert_output_close(out, oracle.attn_sparse(q, k, v, rp.numpy(), ci.numpy(), bq, bk), torch.float32, f"sparse f32 {bq}x{bk} H={H}")
+
+
 @pytest.mark.parametrize("bq,L", [(32, 16500), (64, 16500), (128, 16500), (64, 16384), (128, 32800)])
 def test_pooling_over_segments(bq, L):
     """516, 512 and 1025 key blocks of 32: one segment filled exactly, a few blocks of a second one, one block of a third."""
