@@ -236,31 +236,25 @@ static hipError_t launch_by_fill_f32(const AttnArgs& a, hipStream_t s) {
   return launch_one_f32<D, 4, MODE>(a, s);
 }
 
-// Sparse: a short list does not feed four waves, and a work-group of fewer waves leaves its compute unit to others. The waves
-// of a SIMD take turns on its matrix core (one alone is hardly faster than two), so the time goes with waves per SIMD times
-// steps per wave, plus about one step for the prologue and the merge: the smallest of that over one, two and four waves. The
-// average list comes from the capacity, which is exact or an upper bound. Against four waves for all, at 64 columns a head,
-// 128 x 32 blocks: 1000 work-groups with one tile 16.4 -> 10.1 us, 2048 with 5 tiles 54.7 -> 38.1 us, 1152 with 6 tiles
-// (64 x 64 blocks) 36.7 -> 33.0 us. Long lists keep four.
+// Sparse: a short list does not feed four waves, and a work-group of one wave leaves its compute unit to seven others. Two
+// waves of a SIMD share its matrix core in about the time of 1.6 that run alone, one after the other, so the time goes with
+// the waves of the busiest SIMD (2 a pair, 1.25 for an odd one) times the steps of a wave, plus 1.5 steps of prologue and
+// epilogue for a wave that walks its list alone and 0.5 for one of four (theirs overlap). One wave where that is less; two
+// came out best only between the others. The average list comes from the capacity, which is exact or an upper bound. 544
+// calls (352 to 4080 work-groups, 1 to 16 tiles, both head dims): never slower than four waves for all, 2 % from the best of
+// one, two and four on average. At 64 columns a head, 128 x 32 blocks: 2048 work-groups with one tile 32.8 -> 17.8 us, with 5
+// tiles 54.7 -> 38.1 us, 1000 with two tiles 19.4 -> 13.5 us.
 template <int D>
 static hipError_t launch_sparse_f32(const AttnArgs& a, hipStream_t s) {
   const int64_t groups = (int64_t)a.B * a.Hq * a.n_qtiles;
   if (groups <= 256) return launch_one_f32<D, 8, Mode::kSparse>(a, s);
   const int64_t tiles = ((int64_t)a.cap_per_head * (a.block_k / kTileKF) + a.nqb - 1) / a.nqb;
-  int waves = 1;
-  int64_t least = 0;
-  for (int kw = 1; kw <= 4; kw *= 2) {
-    int64_t per_simd = (groups * kw + 1023) / 1024;
-    if (per_simd < 2) per_simd = 2;
-    const int64_t cost = per_simd * ((tiles + kw - 1) / kw + 1);
-    if (kw == 1 || cost <= least) {
-      least = cost;
-      waves = kw;
-    }
-  }
-  if (waves == 1) return launch_one_f32<D, 1, Mode::kSparse>(a, s);
-  if (waves == 2) return launch_one_f32<D, 2, Mode::kSparse>(a, s);
-  return launch_one_f32<D, 4, Mode::kSparse>(a, s);
+  auto busiest_simd = [](int64_t waves) -> int64_t {  // in quarters
+    const int64_t n = (waves + 1023) / 1024;
+    return n / 2 * 8 + n % 2 * 5;
+  };
+  const int64_t one = busiest_simd(groups) * (2 * tiles + 3), four = busiest_simd(4 * groups) * (2 * ((tiles + 3) / 4) + 1);
+  return one < four ? launch_one_f32<D, 1, Mode::kSparse>(a, s) : launch_one_f32<D, 4, Mode::kSparse>(a, s);
 }
 
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {

@@ -68,18 +68,18 @@ def test_sparse_lists_of_any_length(bq, bk, L, D):
 
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("H,bq,bk,L,longest", [
-    (110, 32, 32, 600, 3),     # 2090 work-groups, 1 or 2 tiles on average: one wave each
+    (110, 32, 32, 600, 3),     # 2090 work-groups, 1 or 2 tiles on average: one wave a list
     (110, 64, 64, 590, 2),     # the same with two-tile blocks, the last one partial (14 keys)
     (110, 128, 32, 600, 4),    # rows of a 128-row query block in four work-groups
-    (40, 32, 32, 600, 3),      # 760: two waves
-    (40, 128, 64, 590, 2),
-    (40, 32, 64, 600, 6),      # 760, lists of 6 tiles: four waves
+    (54, 32, 32, 600, 3),      # 1026
+    (40, 32, 32, 600, 3),      # 760, one or two tiles: one wave
+    (40, 32, 64, 600, 6),      # 760, 6 tiles: four waves
     (40, 64, 128, 530, 3),     # 680, four-tile blocks, the last one 18 keys
 ])
 def test_sparse_short_lists_on_many_work_groups(H, bq, bk, L, longest, D):
     """The number of waves that split a list follows from the work-groups and the capacity of the lists."""
     nqb, nkb = -(-L // bq), -(-L // bk)
-    q, k, v = _qkv(1, H, H // 10, L, D, seed=L + bk + D)
+    q, k, v = _qkv(1, H, H // 2, L, D, seed=L + bk + D)
     rp, ci = random_csr(1, H, nqb, nkb, longest, seed=H + bk, device="cpu")
     ci = ci[..., :int(rp[..., -1].max())].contiguous()   # an exact capacity (for the head with the most entries)
     ix = sd.BlockIndex(rp.to(DEV), ci.to(DEV), bq, bk, nkb)
