@@ -32,12 +32,27 @@ def _flops(cfg, keep):
     return dense, select, sparse
 
 
+def _kernel_sources():
+    """Every source that the bf16 attention kernels are compiled from: the files with their launches and what those include."""
+    import re
+    csrc = os.path.join(ROOT, "paper_2509_24014_amd", "csrc")
+    todo, found = ["attn_bf16.hip", "attn_bf16_splitk.hip"], []
+    while todo:
+        name = todo.pop(0)
+        if name in found:
+            continue
+        found.append(name)
+        with open(os.path.join(csrc, name)) as f:
+            todo += re.findall(r'^\s*#include "([^"]+)"', f.read(), flags=re.M)
+    return [os.path.join(csrc, name) for name in found]
+
+
 def _kernel_source_digest():
     """sha256 (first 16 hex digits) over the sources of the attention kernels: what a counter run was measured on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("attn_bf16.hip", "tile_bf16.hpp", "kernels.hpp"):
-        with open(os.path.join(ROOT, "paper_2509_24014_amd", "csrc", f), "rb") as fh:
+    for path in _kernel_sources():
+        with open(path, "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
