@@ -252,7 +252,6 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   p.key_begin = 0;
   p.key_len = q->L;
   p.out_stride = nkb;
-  p.out_col0 = 0;
   p.scale_log2 = scale_log2(q->D);
   hipError_t e = hipSuccess;
   const size_t rows_total = (size_t)pool1p_units(q->B, q->H, nqb, bq);  // units of the one-pass kernel: 128 rows of a head each

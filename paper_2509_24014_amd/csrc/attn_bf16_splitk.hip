@@ -1,6 +1,6 @@
 // Block-sparse bf16 attention (Eq. 3 / Eq. 4) for SMALL query blocks (32 or 64 rows).
 //
-// The general kernel (attn_bf16.hip) gives every wave 32 query rows and all the keys of a tile, so a
+// The general kernel (attn_bf16_kernel.hpp) gives every wave 32 query rows and all the keys of a tile, so a
 // 64-row query block is a work-group of two waves; its K/V double buffers fill the LDS of a compute
 // unit after two such groups, which leaves one wave per SIMD and nothing to overlap a wave's softmax
 // with. Here a query block gets twice the waves: wave (rw, kh) owns rows 32*rw .. 32*rw+31 and, of
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(RW * 128)
   kaddr.init(lane);
   vaddr.init(lane);
 
-  // block numbers of tiles t .. t+3, read with a vector load (see attn_bf16.hip); past the end: the last one
+  // block numbers of tiles t .. t+3, read with a vector load (see attn_bf16_kernel.hpp); past the end: the last one
   int opaque_zero;
   asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
   auto col_at = [&](int t) -> int {  // key TILE number of tile t of the list; with 32-key blocks: the block of this wave's half
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(RW * 128)
     blk2 = col_at(2);
     blk3 = col_at(3);
   }
-  QFrag<D, 1> qf;  // loaded after the first K/V copies have been issued (see attn_bf16.hip)
+  QFrag<D, 1> qf;  // loaded after the first K/V copies have been issued (see attn_bf16_kernel.hpp)
 
   const int64_t slab_rows = (int64_t)(a.L - 1);
   const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(kbase, (slab_rows * a.k.sl + D) * 2);
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(RW * 128)
 #pragma unroll
     for (int x = 0; x < 16; ++x) o[0][dt][x] = (o[0][dt][x] * f_mine + xchg[(dt * 16 + x) * 64 + lane] * f_other) * inv;
 
-  // whole-row stores through an LDS transpose (see the epilogue of attn_bf16.hip); the staging slice is this
+  // whole-row stores through an LDS transpose (see the epilogue of attn_bf16_kernel.hpp); the staging slice is this
   // row group's V buffer, whose two exchanged values this wave has already read
   constexpr int kRowBytes = 2 * D, kSlots = D / 8, kRowsPerStore = 64 / kSlots;
   static_assert(32 * kRowBytes <= kVBytes, "staging slice must fit a V buffer");

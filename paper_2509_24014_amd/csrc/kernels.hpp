@@ -38,14 +38,14 @@ struct AttnArgs {
 struct PoolArgs {
   TensorArg q, k;
   const float* lse;        // [B, Hq, L] natural-log sum-exp of each row over ALL L keys
-  float* apool;            // [B, Hq, nqb, out_stride]; block t of the range lands in column out_col0 + t
+  float* apool;            // [B, Hq, nqb, out_stride]; block t of the range lands in column t
   int32_t B, Hq, group, L;  // group: query heads per key/value head
-  const int32_t* seq_lens; // optional [B] per-sample lengths (only with the whole-sequence key range)
+  const int32_t* seq_lens; // optional [B] per-sample lengths (they cut the key ranges too)
   int32_t nqb, block_k;
   int32_t key_begin, key_len;
-  int32_t key_len2;        // > 0: a second range, the key_len2 tokens behind the first, pooled into column out_col0 + 1 (a
+  int32_t key_len2;        // > 0: a second range, the key_len2 tokens behind the first, pooled into column 1 (a
                            // grid of two rows; both parts of the block that holds the prefill boundary in one launch)
-  int32_t out_stride, out_col0;
+  int32_t out_stride;
   float scale_log2;        // log2(e) / sqrt(D)
   // one-pass form only (pool1p_bf16_kernel; whole key range, lse unused):
   float* slab;             // scratch, one slab of 128 x slab_ld floats per work-group of the launch

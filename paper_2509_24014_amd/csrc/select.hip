@@ -78,7 +78,7 @@ void pool_bf16_kernel(const PoolArgs a) {
   qf.load(qbase, row0, L, a.q.sl, lane);
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
   const float lse2 = (row0 + j < L) ? a.lse[(int64_t)bh * a.L + row0 + j] * 1.4426950408889634f : __builtin_inff();
-  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0 + second;
+  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + second;
   const int rows_here = (L - I * kBlockRows < kBlockRows) ? L - I * kBlockRows : kBlockRows;  // query rows of the block that exist
   const int last_blk = (key_len - 1) / kTileK;
   const int tail_keys = key_len - last_blk * kTileK;  // keys that exist in the last key block of the range
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
   const float lse2 = row < L ? a.lse[(int64_t)bh * a.L + row] * 1.4426950408889634f : __builtin_inff();
-  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + a.out_col0 + second;
+  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + second;
   const int rows_here = (L - I * (32 * RW) < 32 * RW) ? L - I * (32 * RW) : 32 * RW;  // query rows that exist
   const int nkb = (key_len + a.block_k - 1) / a.block_k;
   const float c = a.scale_log2;
