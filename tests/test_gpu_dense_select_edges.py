@@ -105,3 +105,34 @@ def test_replays_from_a_hip_graph():
         assert torch.equal(out, out_e) and torch.equal(out_layer, out_e) and torch.equal(pooled, pooled_e), f"replay {trial}"
         for ix in (index, layer.index):
             assert torch.equal(ix.col_idx, index_e.col_idx) and torch.equal(ix.row_ptr, index_e.row_ptr), f"replay {trial}: index"
+
+
+@pytest.mark.parametrize("H,L,D,bq,bk", [(100, 300, 64, 64, 64), (90, 270, 128, 32, 128), (130, 390, 64, 128, 32)])
+def test_padded_batches_over_many_units_equal_single_samples(H, L, D, bq, bk):
+    """More row tiles than resident work-groups, of which whole runs do not exist in the shorter samples: every persistent
+    work-group steps over some and reuses its slab after others. Both kernels that park block sums."""
+    rho, lens = 0.3, [L, L // 3, 0, L // 2 + 1]
+    q, k, v = _inputs(torch.bfloat16, len(lens), H, L, D)
+    sl = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    nqb, nkb = -(-L // bq), -(-L // bk)
+    one, own = (torch.full((len(lens), H, nqb, nkb), -1.0, device=DEV) for _ in range(2))
+    out = torch.full_like(q, 7.0)
+    _, ix = sd.attn_dense_select(q, k, v, bq, bk, rho, out=out, pooled_out=one, seq_lens=sl)
+    ix_own = sd.select_pattern(q, k, bq, bk, rho, pooled_out=own, seq_lens=sl)
+    for b, n in enumerate(lens):
+        assert (out[b, :, n:] == 7.0).all()
+        if n == 0:
+            assert (one[b] == -1.0).all() and (own[b] == -1.0).all()
+            assert not ix.row_ptr[b].any() and not ix_own.row_ptr[b].any()
+            continue
+        q1, k1, v1 = (t[b:b + 1, :, :n] for t in (q, k, v))
+        nq, nk = -(-n // bq), -(-n // bk)
+        p1 = torch.full((1, H, nq, nk), -1.0, device=DEV)
+        o1, ix1 = sd.attn_dense_select(q1, k1, v1, bq, bk, rho, pooled_out=p1)
+        assert torch.equal(out[b:b + 1, :, :n], o1)   # a row does not depend on its work-group
+        used = ix1.row_ptr[0, 0, -1].item()
+        for pooled, index in ((one, ix), (own, ix_own)):
+            torch.testing.assert_close(pooled[b:b + 1, :, :nq, :nk], p1, rtol=5e-6, atol=0)
+            assert (pooled[b, :, nq:] == -1.0).all() and (pooled[b, :, :, nk:] == -1.0).all()
+            assert torch.equal(index.row_ptr[b, :, :nq + 1], ix1.row_ptr[0])
+        assert torch.equal(ix.col_idx[b, :, :used], ix1.col_idx[0, :, :used])
