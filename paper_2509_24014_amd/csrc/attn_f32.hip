@@ -3,30 +3,40 @@
 // this is the path held to 1e-5 against the fp64 reference.
 //
 // One work-group owns 32 query rows of one (batch, head); its KW waves share the rows and split the keys: wave w takes
-// the 32-key tiles w, w + KW, ... of the list with its own running maximum, sum and output accumulator, and the parts
-// are merged once, through LDS, at the end. The waves need nothing from each other in between (K and V are loaded
-// straight into registers, see tile_f32.hpp), so the tile loop has no barrier, and a short sequence still spreads over
-// many waves. A fragment of the next tile is requested as soon as the fragment it replaces has been used: every load
-// has a whole tile of matrix work (8192 cycles at head dim 128) to arrive.
+// the 32-key tiles w, w + KW, ... of the list with its own reference, sum and output accumulator, and the parts
+// are merged once, through LDS, at the end. The waves need nothing from each other in between (tile_f32.hpp), so the tile
+// loop has no barrier, and a short sequence still spreads over many waves. The next tile is requested as soon as what it
+// replaces has been used: every load has most of a tile's work to arrive.
 //
-// Bound: the fp32 matrix rate (157 TFLOP/s nominal). 8 heads of 2000 x 128: dense 440 -> 167 us (98 TFLOP/s), sparse
-// (64 x 64 blocks, 20 % kept) 122 -> 50 us; 2 heads of 256 x 64: dense 33 -> 12 us, sparse 18 -> 8 us. (Before: tiles staged
-// through LDS by all waves, two barriers per tile, one LDS read per matrix instruction and operand, rows not split.)
+// Bound: the vector unit, which splits every K and V value into its three bf16 parts for 32 rows of queries (700 of the 880
+// vector instructions of a tile at head dim 128, 2 ns each, beside 96 matrix instructions of 16 ns), then what a work-group
+// spends before its first and after its last tile. 8 heads of 2000 x 128: dense 164 -> 110 us, sparse (64 x 64 blocks, 20 %
+// kept) 48 -> 37 us, pooling (select.hip) 84 -> 61 us; 2 heads of 256 x 64: dense 11.5 -> 9.3 us. (Before: the fp32 matrix
+// instruction alone.) Error against 64 bits, largest of an output over its root mean square, random inputs of both: 8 x
+// 2000 x 128 3.2e-6 -> 2.7e-6, 4 x 600 x 64 1.5e-6 -> 1.2e-6, peaked rows (logits of variance 16) 2.1e-5 -> 1.7e-5,
+// log-normal inputs (sigma 1.5 and 3) 3.5e-4 -> 9.2e-5; log-sum-exp 8.7e-6 -> 8.1e-6 where rows are peaked, the same elsewhere.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "tile_f32.hpp"
 
 namespace sparsed {
 
-template <int D, int KW, Mode MODE>
+template <int D, int KW, Mode MODE, bool SPLIT_FIRST>
 __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnArgs a) {
   constexpr int NT = KW * 64;
   constexpr bool kHasV = MODE != Mode::kStats;
-  constexpr int kChunks = D / 8, kV = D / 32;
+  constexpr int kChunks = D / 8, kSteps = D / 16, kV = D / 32;
   using VRow = typename SlabF32<D>::VRow;
-  // The query fragments ([chunk][lane], 16 bytes each) and, once the keys are done, the waves' accumulators
-  // ([wave][row][32 pieces of D/32 columns], piece i of row j at position i ^ j so that neither side has bank conflicts).
-  constexpr int kQBytes = kChunks * 64 * 16, kAccBytes = kHasV ? KW * 32 * D * 4 : 16;
-  __shared__ __attribute__((aligned(16))) char lds[kQBytes > kAccBytes ? kQBytes : kAccBytes];
+  // K through LDS (tile_f32.hpp), or straight into registers as V. Through LDS at head dim 64, where two waves per SIMD find
+  // room for their tiles beside another work-group's (2 heads of 256, dense: 10.2 us straight, 9.3 through LDS); at 128 a work-group of eight waves would fill the LDS, and
+  // nothing is left to run while it begins and ends (8 heads of 2000, dense: 115 us, straight 110).
+  constexpr bool KLDS = SPLIT_FIRST && D == 64;
+  // The query fragments ([step][part][lane], 16 bytes each), the waves' K tiles and, once the keys are done, the waves'
+  // accumulators ([wave][row][32 pieces of D/32 columns], piece i of row j at position i ^ j so that neither side has bank
+  // conflicts).
+  constexpr int kQBytes = SPLIT_FIRST ? kSteps * 3 * 64 * 16 : kChunks * 64 * 16, kKBytes = KLDS ? KW * KTileF32<D>::kBytes : 0, kAccBytes = kHasV ? KW * 32 * D * 4 : 16;
+  __shared__ __attribute__((aligned(1024))) char lds[kQBytes + kKBytes > kAccBytes ? kQBytes + kKBytes : kAccBytes];
   __shared__ float stat_m[KW][32], stat_l[KW][32];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -45,9 +55,9 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int row0 = qt * 32;
   if (row0 >= L) return;  // a query tile wholly past the end (uniform over the work-group)
 
-  const SlabF32<D> ks{reinterpret_cast<const char*>(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh), (uint32_t)(a.k.sl * 4), L};
-  const SlabF32<D> vs{reinterpret_cast<const char*>(kHasV ? static_cast<const float*>(a.v.ptr) + b * a.v.sb + hk * a.v.sh : nullptr),
-                      (uint32_t)(a.v.sl * 4), L};
+  SlabF32<D> ks, vs;
+  ks.init(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh, a.k.sl, L);
+  if (kHasV) vs.init(static_cast<const float*>(a.v.ptr) + b * a.v.sb + hk * a.v.sh, a.v.sl, L);
 
   // tiles of the list: every 32 keys (dense), or those of the listed key blocks
   const int tile_shift = (MODE == Mode::kSparse) ? (a.block_k == 128 ? 2 : a.block_k == 64 ? 1 : 0) : 0;
@@ -69,100 +79,206 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     return cols[(u >> tile_shift) + opaque_zero] * a.block_k + (u & ((1 << tile_shift) - 1)) * kTileKF;
   };
 
-  {  // query fragments into LDS: lane (j, g) of chunk c holds columns 8c + 4g .. + 3 of row j
-    const int row = row0 + j < L ? row0 + j : L - 1;
-    const float* qrow = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh + (int64_t)row * a.q.sl + 4 * g;
-    for (int c = wave; c < kChunks; c += KW)
-      *reinterpret_cast<f32x4*>(lds + (c * 64 + lane) * 16) = *reinterpret_cast<const f32x4*>(qrow + 8 * c);
-  }
-
   float M = -1e30f, lsum = 0.f;
   f32x16 o[kV];
-#pragma unroll
-  for (int dt = 0; dt < kV; ++dt)
-#pragma unroll
-    for (int x = 0; x < 16; ++x) o[dt][x] = 0.f;
-  f32x4 kf[kChunks];
-  VRow vf[16];
   const float c = a.scale_log2;
+  const float* const qhead = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
 
-  int t = wave, key = 0, key_next = 0;
-  if (t < n) {
-    key = __builtin_amdgcn_readfirstlane(first_key(t));
-    key_next = __builtin_amdgcn_readfirstlane(first_key(t + KW));
-    const uint32_t off = ks.row_offset(key + j) + 16 * g;
-#pragma unroll
-    for (int ch = 0; ch < kChunks; ++ch) kf[ch] = ks.k_chunk(off, ch);
-    if (kHasV) {
-#pragma unroll
-      for (int x = 0; x < 16; ++x) vf[x] = vs.v_row(key, x, lane);
+  // The wave's share of the tile list. SPLIT: on the bf16 matrix instruction; else on the fp32 one.
+  auto walk = [&](auto split_tag) __attribute__((always_inline)) {
+    constexpr bool SPLIT = decltype(split_tag)::value;
+    // query fragments into LDS: lane (j, g) of chunk ch holds columns 8 ch + 4g .. + 3 of row j
+    {
+      const int row = row0 + j < L ? row0 + j : L - 1;
+      const float* qrow = qhead + (int64_t)row * a.q.sl + 4 * g;
+      if constexpr (SPLIT) {
+        for (int s2 = wave; s2 < kSteps; s2 += KW) {
+          const f32x4 lo = *reinterpret_cast<const f32x4*>(qrow + 16 * s2), hi = *reinterpret_cast<const f32x4*>(qrow + 16 * s2 + 8);
+          const Split8 w = split8(lo, hi);
+          u32x4f* const dst = reinterpret_cast<u32x4f*>(lds) + s2 * 3 * 64 + lane;
+          dst[0] = w.h;
+          dst[64] = w.m;
+          dst[128] = w.l;
+        }
+      } else {
+        for (int ch = wave; ch < kChunks; ch += KW)
+          *reinterpret_cast<f32x4*>(lds + (ch * 64 + lane) * 16) = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
+      }
     }
-  }
-  __syncthreads();
-  for (; t < n; t += KW) {
-    const int key_after = first_key(t + 2 * KW);
-    const uint32_t off_next = ks.row_offset(key_next + j) + 16 * g;
-    f32x16 s;
+    M = -1e30f;
+    lsum = 0.f;
 #pragma unroll
-    for (int x = 0; x < 16; ++x) s[x] = 0.f;
+    for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
-    for (int ch = 0; ch < kChunks; ++ch) {
-      const f32x4 qf = *reinterpret_cast<const f32x4*>(lds + (ch * 64 + lane) * 16);
+      for (int x = 0; x < 16; ++x) o[dt][x] = 0.f;
+    constexpr bool VIA_LDS = SPLIT && KLDS;
+    char* const ktile = lds + (VIA_LDS ? kQBytes + wave * KTileF32<D>::kBytes : 0);
+    f32x4 kf[VIA_LDS ? 1 : kChunks];
+    VRow vf[16];
+
+    int t = wave, key = 0, key_next = 0;
+    if (t < n) {
+      key = __builtin_amdgcn_readfirstlane(first_key(t));
+      key_next = __builtin_amdgcn_readfirstlane(first_key(t + KW));
+      const uint32_t off = ks.k_offset(key, lane), voff = kHasV ? vs.v_offset(key, lane) : 0;
+      if constexpr (VIA_LDS) {
+        KTileF32<D>::copy(ks, key, ktile, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[e], s, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);  // the reload stays behind its fragment's last use, so it can take its registers
-      kf[ch] = ks.k_chunk(off_next, ch);
+        for (int ch = 0; ch < kChunks; ++ch) kf[ch] = ks.k_chunk(off, ch);
+      }
+      if (kHasV) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) vf[x] = vs.v_row(voff, x);
+      }
     }
-    // keys of this tile that exist: fewer than 32 at the end of a sequence whose length is not a multiple of the tile,
-    // none in the later tiles of a partial last key block
-    const int valid = L - key;
-    if (valid < kTileKF) {
+    __syncthreads();
+    for (; t < n; t += KW) {
+      const int key_after = first_key(t + 2 * KW);
+      const uint32_t off_next = ks.k_offset(key_next, lane), voff_next = kHasV ? vs.v_offset(key_next, lane) : 0;
+      f32x16 s;
 #pragma unroll
-      for (int x = 0; x < 16; ++x)
-        if (8 * (x / 4) + 4 * g + (x % 4) >= valid) s[x] = -__builtin_inff();
-      if (kHasV && valid <= 0) {  // no key at all: the rows stand for none, and 0 times an infinity of theirs would be NaN
+      for (int x = 0; x < 16; ++x) s[x] = 0.f;
+      if constexpr (SPLIT) {
+        // A tile's copy is followed by the V rows of the same tile, whose loads may stay in flight.
+        if constexpr (VIA_LDS) vector_memory_done_but_f<kHasV ? 16 : 0>();
+        auto chunk = [&](int ch) -> f32x4 {
+          if constexpr (VIA_LDS) return KTileF32<D>::chunk(ktile, ch, lane);
+          else return kf[ch];
+        };
+        Split8 now = split8(chunk(0), chunk(1));
+        f32x4 lo = chunk(2), hi = chunk(3);
+        __builtin_amdgcn_sched_barrier(0);  // a reload stays behind its fragment's last use, so it can take its registers
+#pragma unroll
+        for (int s2 = 0; s2 < kSteps; ++s2) {
+          if constexpr (!VIA_LDS) {
+            kf[2 * s2] = ks.k_chunk(off_next, 2 * s2);
+            kf[2 * s2 + 1] = ks.k_chunk(off_next, 2 * s2 + 1);
+          }
+          const u32x4f* const src = reinterpret_cast<const u32x4f*>(lds) + s2 * 3 * 64 + lane;
+          const Split8 qw = {src[0], src[64], src[128]};
+          Split8 next;
+          if (s2 + 1 < kSteps) next = split8(lo, hi);
+          if (s2 + 2 < kSteps) {
+            lo = chunk(2 * s2 + 4);
+            hi = chunk(2 * s2 + 5);
+          }
+          s = mfma_split(now, qw, s);
+          if (s2 + 2 < kSteps) sched_split_interleave<VIA_LDS ? 5 : 3>();
+          else if (s2 + 1 < kSteps) sched_split_interleave<3>();
+          __builtin_amdgcn_sched_barrier(0);
+          if (s2 + 1 < kSteps) now = next;
+          if (VIA_LDS && s2 == kSteps - 2) {
+            lds_reads_done_f();
+            KTileF32<D>::copy(ks, key_next, ktile, lane);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int ch = 0; ch < kChunks; ++ch) {
+          const f32x4 qf = *reinterpret_cast<const f32x4*>(lds + (ch * 64 + lane) * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[e], s, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          kf[ch] = ks.k_chunk(off_next, ch);
+        }
+      }
+      // keys of this tile that exist: fewer than 32 at the end of a sequence whose length is not a multiple of the tile,
+      // none in the later tiles of a partial last key block
+      const int valid = L - key;
+      if (valid < kTileKF) {
 #pragma unroll
         for (int x = 0; x < 16; ++x)
-#pragma unroll
-          for (int dt = 0; dt < kV; ++dt) vf[x][dt] = 0.f;
+          if (8 * (x / 4) + 4 * g + (x % 4) >= valid) s[x] = -__builtin_inff();
       }
-    }
-    float mx = s[0];
+      // The row's reference M stays within an octave of its maximum: probabilities stay at or below 2, and the output is
+      // rescaled for the few tiles that raise a row's maximum by more.
+      float mx = fmaxf(s[0], s[1]);
 #pragma unroll
-    for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
-    mx = fmaxf(mx, other_half_f(mx));
-    const float Mn = fmaxf(M, mx * c);
-    const float alpha = exp2f(M - Mn);
-    M = Mn;
-    float part = 0.f;
+      for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, s[x]), s[x + 1]);
+      mx = pair_max_f(mx) * c;
+      if (__builtin_amdgcn_ballot_w64(mx > M + 1.0f) != 0) {
+        const float Mn = fmaxf(M, mx);
+        const float alpha = __builtin_amdgcn_exp2f(M - Mn);
+        M = Mn;
+        lsum *= alpha;
+        if (kHasV) {
 #pragma unroll
-    for (int x = 0; x < 16; ++x) {
-      s[x] = exp2f(__builtin_fmaf(s[x], c, -Mn));
-      part += s[x];
-    }
-    lsum = lsum * alpha + part;
-    if (kHasV) {
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+          for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < kV; ++dt)
-#pragma unroll
-          for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
+            for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
+        }
       }
-      __builtin_amdgcn_sched_barrier(0);
+      float part = 0.f;
 #pragma unroll
       for (int x = 0; x < 16; ++x) {
-#pragma unroll
-        for (int dt = 0; dt < kV; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[x][dt], s[x], o[dt], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        vf[x] = vs.v_row(key_next, x, lane);
+        s[x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[x], c, -M));
+        part += s[x];
       }
+      lsum += part;
+      if (kHasV) {
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (SPLIT) {
+          Split8 p[2];
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[m].pair(i, s[8 * m + 2 * i], s[8 * m + 2 * i + 1]);
+          auto split_v = [&](int u) -> Split8 {  // u = m * kV + dt
+            const int m = u / kV, dt = u % kV;
+            Split8 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w.pair(i, vf[8 * m + 2 * i][dt], vf[8 * m + 2 * i + 1][dt]);
+            return w;
+          };
+          Split8 now = split_v(0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 2 * kV; ++u) {
+            Split8 next;
+            if (u + 1 < 2 * kV) next = split_v(u + 1);
+            o[u % kV] = mfma_split(now, p[u / kV], o[u % kV]);
+            if (u + 1 < 2 * kV) sched_split_interleave<0>();
+            __builtin_amdgcn_sched_barrier(0);
+            if (u % kV == kV - 2 || kV == 1) {  // every column of these eight rows has been split
+#pragma unroll
+              for (int x = 0; x < 8; ++x) vf[u / kV * 8 + x] = vs.v_row(voff_next, u / kV * 8 + x);
+            }
+            if (u + 1 < 2 * kV) now = next;
+          }
+        } else {
+#pragma unroll
+          for (int x = 0; x < 16; ++x) {
+#pragma unroll
+            for (int dt = 0; dt < kV; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[x][dt], s[x], o[dt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            vf[x] = vs.v_row(voff_next, x);
+          }
+        }
+      }
+      key = key_next;
+      key_next = __builtin_amdgcn_readfirstlane(key_after);
     }
-    key = key_next;
-    key_next = __builtin_amdgcn_readfirstlane(key_after);
+    vector_memory_done_but_f<0>();  // the last copy into LDS, of a tile past the list, has landed
+  };
+  if constexpr (!SPLIT_FIRST) {
+    walk(std::false_type{});
+  } else {
+    walk(std::true_type{});
+    float probe = 0.f * lsum;  // not a number if any sum of this wave is infinite or not a number
+    if (kHasV) {
+#pragma unroll
+      for (int dt = 0; dt < kV; ++dt)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) probe = __builtin_fmaf(o[dt][x], 0.f, probe);
+    }
+    if (__builtin_expect(__syncthreads_or(probe != probe), 0)) walk(std::false_type{});
   }
 
   // Merge the waves' parts: O = sum_w O_w 2^(M_w - M) / sum_w l_w 2^(M_w - M), M = max_w M_w.
-  const float ltot = lsum + other_half_f(lsum);
+  const float ltot = pair_sum_f(lsum);
   __syncthreads();  // everyone is done with the query fragments
   if (g == 0) {
     stat_m[wave][j] = M;
@@ -220,11 +336,11 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 }
 
-template <int D, int KW, Mode MODE>
+template <int D, int KW, Mode MODE, bool SPLIT_FIRST = true>
 static hipError_t launch_one_f32(const AttnArgs& a, hipStream_t s) {
   const int64_t total = (int64_t)a.B * a.Hq * a.n_qtiles;
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_f32_kernel<D, KW, MODE>), dim3((unsigned)total), dim3(KW * 64), 0, s, a);
+  hipLaunchKernelGGL((attn_f32_kernel<D, KW, MODE, SPLIT_FIRST>), dim3((unsigned)total), dim3(KW * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -236,14 +352,15 @@ static hipError_t launch_by_fill_f32(const AttnArgs& a, hipStream_t s) {
   return launch_one_f32<D, 4, MODE>(a, s);
 }
 
-// Sparse: a short list does not feed four waves, and a work-group of one wave leaves its compute unit to seven others. Two
-// waves of a SIMD share its matrix core in about the time of 1.6 that run alone, one after the other, so the time goes with
-// the waves of the busiest SIMD (2 a pair, 1.25 for an odd one) times the steps of a wave, plus 1.5 steps of prologue and
-// epilogue for a wave that walks its list alone and 0.5 for one of four (theirs overlap). One wave where that is less; two
-// came out best only between the others. The average list comes from the capacity, which is exact or an upper bound. 544
-// calls (352 to 4080 work-groups, 1 to 16 tiles, both head dims): never slower than four waves for all, 2 % from the best of
-// one, two and four on average. At 64 columns a head, 128 x 32 blocks: 2048 work-groups with one tile 32.8 -> 17.8 us, with 5
-// tiles 54.7 -> 38.1 us, 1000 with two tiles 19.4 -> 13.5 us.
+// Sparse: a short list does not feed four waves, and what a work-group spends around its tiles (splitting the queries,
+// merging the waves) grows with its waves. Two waves of a SIMD share its matrix core in about the time of 1.6 that run alone,
+// one after the other, so the time goes with the waves of the busiest SIMD (2 a pair, 1.25 for an odd one) times, in quarters of
+// a tile on the fp32 instruction, 4 a tile and 17 for a wave alone with its list on that instruction (its queries need no
+// splitting, and eight such work-groups fit a compute unit), 2 a step and 11 for one of two waves, 2 a step and 6 for one of
+// four. The average list comes from the capacity, which is exact or an upper bound. Fitted to 362 calls (280 to 3008
+// work-groups, 1 to 32 tiles, both head dims; the form chosen is 0.6 % from the best on average, 10 % at most): head dim 128, 2048
+// work-groups, 1, 4, 16 tiles: alone 27.3, 51.5, 143 us; two 32.8, 53.5, 129; four 38.4, 55.2, 123; 400 work-groups of
+// 16 tiles: 73, 45, 32.
 template <int D>
 static hipError_t launch_sparse_f32(const AttnArgs& a, hipStream_t s) {
   const int64_t groups = (int64_t)a.B * a.Hq * a.n_qtiles;
@@ -253,8 +370,10 @@ static hipError_t launch_sparse_f32(const AttnArgs& a, hipStream_t s) {
     const int64_t n = (waves + 1023) / 1024;
     return n / 2 * 8 + n % 2 * 5;
   };
-  const int64_t one = busiest_simd(groups) * (2 * tiles + 3), four = busiest_simd(4 * groups) * (2 * ((tiles + 3) / 4) + 1);
-  return one < four ? launch_one_f32<D, 1, Mode::kSparse>(a, s) : launch_one_f32<D, 4, Mode::kSparse>(a, s);
+  const int64_t one = busiest_simd(groups) * (4 * tiles + 17), two = busiest_simd(2 * groups) * (2 * ((tiles + 1) / 2) + 11),
+                four = busiest_simd(4 * groups) * (2 * ((tiles + 3) / 4) + 6);
+  if (four <= one && four <= two) return launch_one_f32<D, 4, Mode::kSparse>(a, s);
+  return two <= one ? launch_one_f32<D, 2, Mode::kSparse>(a, s) : launch_one_f32<D, 1, Mode::kSparse, false>(a, s);
 }
 
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {

@@ -7,6 +7,8 @@
 //                  ascending into the per-head CSR block index. One wavefront per row.
 // Pooled scores are fp32 from the logits on: the exponentials, the normaliser and every partial
 // sum, with a fixed summation order (lane, then wave tree, then waves in order).
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "tile_bf16.hpp"
 #include "tile_f32.hpp"
@@ -205,17 +207,20 @@ void pool_bf16_kernel(const PoolArgs a) {
 // ---------------------------------------------------------------------------- pooled scores, fp32
 // One work-group of eight waves per query block: RW = block_q / 32 row groups times KW = 8 / RW key groups. Wave
 // (rw, kw) sums, for its 32 rows, the key blocks kw, kw + KW, ...; the row groups' sums of a block meet in LDS (in row
-// group order), a segment of blocks at a time. K goes straight into registers, a fragment of the next tile requested
-// as soon as the one it replaces has been used (see attn_f32.hip), so there is no barrier inside a segment.
-// Bound: the fp32 matrix rate. 8 heads of 2000 x 128, 64 x 64 blocks: 238 -> 86 us (95 TFLOP/s); 2 heads of 256 x 64: 26 -> 8 us.
+// group order), a segment of blocks at a time. Products on split operands (tile_f32.hpp); every wave has its own K tile in LDS,
+// copied again as soon as its last chunk has been read, so there is no barrier inside a segment.
+// Bound: the vector unit (440 instructions a tile, 350 of them to split K). 8 heads of 2000 x 128, 64 x 64 blocks: 84 -> 61 us;
+// 2 heads of 256 x 64: 7.4 -> 6.6 us.
 template <int D, int RW>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pool_f32_kernel(const PoolArgs a) {
-  constexpr int KW = 8 / RW, kChunks = D / 8, kSeg = 512;
+  constexpr int KW = 8 / RW, kChunks = D / 8, kSteps = D / 16, kSeg = 512;
   __shared__ float sums[RW][kSeg];
+  __shared__ __attribute__((aligned(1024))) char ktiles[8 * KTileF32<D>::kBytes];  // every wave's own
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rw = wave % RW, kw = wave / RW;
+  char* const ktile = ktiles + wave * KTileF32<D>::kBytes;
   const int j = lane & 31, g = lane >> 5;
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
   const int I = lid % a.nqb;
@@ -232,15 +237,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     key_len = L - key_begin < key_len ? L - key_begin : key_len;
   }
   if (I * (32 * RW) >= L || key_len <= 0) return;  // uniform over the work-group
-  const SlabF32<D> ks{reinterpret_cast<const char*>(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)key_begin * a.k.sl),
-                      (uint32_t)(a.k.sl * 4), key_len};
+  SlabF32<D> ks;
+  ks.init(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh + (int64_t)key_begin * a.k.sl, a.k.sl, key_len);
   const int row = I * (32 * RW) + rw * 32 + j;
-  f32x4 qf[kChunks], kf[kChunks];
-  {
-    const float* qrow = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh + (int64_t)(row < L ? row : L - 1) * a.q.sl + 4 * g;
-#pragma unroll
-    for (int ch = 0; ch < kChunks; ++ch) qf[ch] = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
-  }
+  const float* const qrow = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh + (int64_t)(row < L ? row : L - 1) * a.q.sl + 4 * g;
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
   const float lse2 = row < L ? a.lse[(int64_t)bh * a.L + row] * 1.4426950408889634f : __builtin_inff();
   float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + second;
@@ -248,58 +248,118 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int nkb = (key_len + a.block_k - 1) / a.block_k;
   const float c = a.scale_log2;
 
-  int J = kw, key = kw * a.block_k;  // block and first key of the tile to come
-  {
-    const uint32_t off = ks.row_offset(key + j) + 16 * g;
+  // The wave's key blocks of all segments. SPLIT: on the bf16 matrix instruction; else on the fp32 one. Returns whether some
+  // sum of this lane is infinite or not a number.
+  auto walk = [&](auto split_tag) __attribute__((always_inline)) -> bool {
+    constexpr bool SPLIT = decltype(split_tag)::value;
+    f32x4 kf[SPLIT ? 1 : kChunks], qf[SPLIT ? 1 : kChunks];
+    Split8 qs[SPLIT ? kSteps : 1];
+    float probe = 0.f;
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int ch = 0; ch < kChunks; ++ch) kf[ch] = ks.k_chunk(off, ch);
-  }
-  for (int seg = 0; seg < nkb; seg += kSeg) {
-    const int seg_end = seg + kSeg < nkb ? seg + kSeg : nkb;
-    float acc = 0.f;  // this lane's share of block J
-    while (J < seg_end) {
-      const int left = (J + 1) * a.block_k < key_len ? (J + 1) * a.block_k - key : key_len - key;  // keys of the block from `key` on (>= 1)
-      const bool last = left <= kTileKF;                                                           // last tile of its block
-      const int key_next = last ? (J + KW) * a.block_k : key + kTileKF;  // (past the last block: the last row, repeated)
-      const uint32_t off_next = ks.row_offset(key_next + j) + 16 * g;
-      f32x16 s;
-#pragma unroll
-      for (int x = 0; x < 16; ++x) s[x] = 0.f;
-#pragma unroll
-      for (int ch = 0; ch < kChunks; ++ch) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[ch][e], s, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);  // the reload stays behind its fragment's last use, so it can take its registers
-        kf[ch] = ks.k_chunk(off_next, ch);
+      for (int s2 = 0; s2 < kSteps; ++s2) {
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(qrow + 16 * s2), hi = *reinterpret_cast<const f32x4*>(qrow + 16 * s2 + 8);
+        qs[s2] = split8(lo, hi);
       }
-      if (left < kTileKF) {
+    } else {
 #pragma unroll
-        for (int x = 0; x < 16; ++x)
-          if (8 * (x / 4) + 4 * g + (x % 4) >= left) s[x] = -__builtin_inff();
-      }
-      float part = 0.f;
-#pragma unroll
-      for (int x = 0; x < 16; ++x) part += exp2f(__builtin_fmaf(s[x], c, -lse2));
-      acc += part;
-      key = key_next;
-      if (last) {
-        acc = wave_sum_f(acc);
-        if (lane == 0) sums[rw][J - seg] = acc;
-        acc = 0.f;
-        J += KW;
-      }
+      for (int ch = 0; ch < kChunks; ++ch) qf[ch] = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
     }
-    __syncthreads();
-    for (int x = tid; x < seg_end - seg; x += 512) {
-      float tot = 0.f;
+    int J = kw, key = kw * a.block_k;  // block and first key of the tile to come
+    if constexpr (SPLIT) {
+      KTileF32<D>::copy(ks, key, ktile, lane);
+    } else {
+      const uint32_t off = ks.k_offset(key, lane);
 #pragma unroll
-      for (int w = 0; w < RW; ++w) tot += sums[w][x];
-      const int first = (seg + x) * a.block_k;
-      const int keys_here = key_len - first < a.block_k ? key_len - first : a.block_k;
-      arow[seg + x] = tot * (1.0f / (float)(rows_here * keys_here));  // mean over the entries that exist
+      for (int ch = 0; ch < kChunks; ++ch) kf[ch] = ks.k_chunk(off, ch);
     }
-    __syncthreads();  // the sums may be overwritten
-  }
+    for (int seg = 0; seg < nkb; seg += kSeg) {
+      const int seg_end = seg + kSeg < nkb ? seg + kSeg : nkb;
+      float acc = 0.f;  // this lane's share of block J
+      while (J < seg_end) {
+        const int left = (J + 1) * a.block_k < key_len ? (J + 1) * a.block_k - key : key_len - key;  // keys of the block from `key` on (>= 1)
+        const bool last = left <= kTileKF;                                                           // last tile of its block
+        const int key_next = last ? (J + KW) * a.block_k : key + kTileKF;  // (past the last block: rows that read as zeros)
+        f32x16 s;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) s[x] = 0.f;
+        if constexpr (SPLIT) {
+          vector_memory_done_but_f<0>();  // the tile is there
+          auto chunk = [&](int ch) -> f32x4 { return KTileF32<D>::chunk(ktile, ch, lane); };
+          Split8 now = split8(chunk(0), chunk(1));
+          f32x4 lo = chunk(2), hi = chunk(3);
+#pragma unroll
+          for (int s2 = 0; s2 < kSteps; ++s2) {
+            Split8 next;
+            if (s2 + 1 < kSteps) next = split8(lo, hi);
+            if (s2 + 2 < kSteps) {
+              lo = chunk(2 * s2 + 4);
+              hi = chunk(2 * s2 + 5);
+            }
+            s = mfma_split(now, qs[s2], s);
+            if (s2 + 2 < kSteps) sched_split_interleave<2>();
+            else if (s2 + 1 < kSteps) sched_split_interleave<0>();
+            __builtin_amdgcn_sched_barrier(0);
+            if (s2 + 1 < kSteps) now = next;
+            if (s2 == kSteps - 2) {
+              lds_reads_done_f();
+              KTileF32<D>::copy(ks, key_next, ktile, lane);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        } else {
+          const uint32_t off_next = ks.k_offset(key_next, lane);
+#pragma unroll
+          for (int ch = 0; ch < kChunks; ++ch) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[ch][e], s, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);  // the reload stays behind its fragment's last use, so it can take its registers
+            kf[ch] = ks.k_chunk(off_next, ch);
+          }
+        }
+        if (left < kTileKF) {
+#pragma unroll
+          for (int x = 0; x < 16; ++x)
+            if (8 * (x / 4) + 4 * g + (x % 4) >= left) s[x] = -__builtin_inff();
+        }
+        float least = 0.f, part = 0.f;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          s[x] = __builtin_fmaf(s[x], c, -lse2);
+          least = fminf(least, s[x]);
+        }
+        if (__builtin_amdgcn_ballot_w64(least < -126.f) == 0) {
+#pragma unroll
+          for (int x = 0; x < 16; ++x) part += __builtin_amdgcn_exp2f(s[x]);
+        } else {  // masked keys, or probabilities that the instruction alone would give as zero
+#pragma unroll
+          for (int x = 0; x < 16; ++x) part += exp2f(s[x]);
+        }
+        acc += part;
+        key = key_next;
+        if (last) {
+          if (SPLIT) probe = __builtin_fmaf(acc, 0.f, probe);
+          acc = wave_sum_f(acc);
+          if (lane == 0) sums[rw][J - seg] = acc;
+          acc = 0.f;
+          J += KW;
+        }
+      }
+      __syncthreads();
+      for (int x = tid; x < seg_end - seg; x += 512) {
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < RW; ++w) tot += sums[w][x];
+        const int first = (seg + x) * a.block_k;
+        const int keys_here = key_len - first < a.block_k ? key_len - first : a.block_k;
+        arow[seg + x] = tot * (1.0f / (float)(rows_here * keys_here));  // mean over the entries that exist
+      }
+      __syncthreads();  // the sums may be overwritten
+    }
+    vector_memory_done_but_f<0>();  // the last copy into LDS, of a tile past the range, has landed
+    return probe != probe;
+  };
+  if (__builtin_expect(__syncthreads_or(walk(std::true_type{})), 0)) walk(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------- per-row top-k
