@@ -1,4 +1,5 @@
-// Block-sparse bf16 attention (Eq. 3 / Eq. 4) for SMALL query blocks (32 or 64 rows).
+// bf16 attention with the keys split over the waves of a work-group: block-sparse (Eq. 3 / Eq. 4) for SMALL query blocks (32 or
+// 64 rows), and dense (Eq. 1) and sparse calls with too few rows to fill the chip (the rule is at splitk_takes).
 //
 // The general kernel (attn_bf16_kernel.hpp) gives every wave 32 query rows and all the keys of a tile, so a
 // 64-row query block is a work-group of two waves; its K/V double buffers fill the LDS of a compute
@@ -6,7 +7,7 @@
 // with. Here a query block gets twice the waves: wave (rw, kh) owns rows 32*rw .. 32*rw+31 and, of
 // every 64-key tile, only the 32 keys of half kh. The two key halves of a row keep their own running
 // maximum, sum and output accumulator (flash-decoding style) and are merged once, through LDS, at the
-// end. Same LDS footprint per group, twice the waves per compute unit.
+// end. Same LDS footprint per group, twice the waves per compute unit. With SG tile streams a row's keys are in 2 SG parts.
 //
 // Per tile step t a wave computes  S(t+1) = K(t+1)[half] Q^T  interleaved with the softmax of S(t),
 // then  O += P(t) V(t)[half].  K(t+2) and V(t+1) are copied global -> LDS meanwhile; one barrier per tile.
@@ -27,22 +28,32 @@
 namespace sparsed {
 
 // KB: keys per listed block (32, 64 or 128), a compile-time choice so that the common 64 pays nothing for the others.
-// PRIVATE: the barrier-free form (RW = 1).
-template <int D, int RW, int KB, bool PRIVATE>
-__global__ __launch_bounds__(RW * 128)
-    __attribute__((amdgpu_waves_per_eu(RW == 1 && !PRIVATE ? 1 : 2, RW == 1 && !PRIVATE ? 1 : 2))) void attn_bf16_splitk_kernel(const AttnArgs a) {
+// PRIVATE: the barrier-free form (RW = 1). SG: tile streams; stream sg walks the tiles sg, sg + SG, ... with 2 RW waves and
+// buffers of its own. LIST: sparse (the listed blocks), else dense (every tile).
+template <int D, int RW, int KB, bool PRIVATE, int SG, bool LIST>
+__global__ __launch_bounds__(RW * SG * 128)
+    __attribute__((amdgpu_waves_per_eu(RW * SG == 1 && !PRIVATE ? 1 : 2, RW * SG == 1 && !PRIVATE ? 1 : 2))) void attn_bf16_splitk_kernel(const AttnArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
-  constexpr int NW = 2 * RW, NT = NW * 64, QT = 32 * RW;
+  static_assert(LIST || KB == kTileK, "dense walks 64-key tiles");
+  constexpr int NW = 2 * RW, NT = NW * 64, QT = 32 * RW;  // waves and threads of a stream
+  constexpr int KW = 2 * SG;                              // parts that the keys of a row are split into
   constexpr int kKBytes = KLayout<D>::kTileBytes, kVBytes = VLayout<D>::kTileBytes;
   constexpr float kOverflow = 1.152921504606847e18f;  // 2^60: a 16-key partial sum at or above this re-references the row
-  __shared__ __attribute__((aligned(1024))) char kbuf0[kKBytes];
-  __shared__ __attribute__((aligned(1024))) char kbuf1[PRIVATE ? 16 : kKBytes];
-  __shared__ __attribute__((aligned(1024))) char vbuf0[kVBytes];
-  __shared__ __attribute__((aligned(1024))) char vbuf1[PRIVATE ? 16 : kVBytes];
+  __shared__ __attribute__((aligned(1024))) char kbufs0[SG * kKBytes];
+  __shared__ __attribute__((aligned(1024))) char kbufs1[PRIVATE ? 16 : SG * kKBytes];
+  __shared__ __attribute__((aligned(1024))) char vbufs0[SG * kVBytes];
+  __shared__ __attribute__((aligned(1024))) char vbufs1[PRIVATE ? 16 : SG * kVBytes];
+  __shared__ float stat_m[SG > 1 ? RW : 1][SG > 1 ? KW : 1][32], stat_l[SG > 1 ? RW : 1][SG > 1 ? KW : 1][32];
+  __shared__ float half_m[RW == 4 ? RW : 1][64], half_l[RW == 4 ? RW : 1][64];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_of_group = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sg = SG == 1 ? 0 : wave_of_group / NW, wave = SG == 1 ? wave_of_group : wave_of_group % NW;
   const int rw = wave % RW, kh = wave / RW;  // row group and key half of this wave
+  char* const kbuf0 = kbufs0 + sg * kKBytes;
+  char* const kbuf1 = kbufs1 + (PRIVATE ? 0 : sg * kKBytes);
+  char* const vbuf0 = vbufs0 + sg * kVBytes;
+  char* const vbuf1 = vbufs1 + (PRIVATE ? 0 : sg * kVBytes);
   const int j = lane & 31, g = lane >> 5;
 
   const int lid = xcd_remap(blockIdx.x, gridDim.x);
@@ -61,21 +72,27 @@ __global__ __launch_bounds__(RW * 128)
   const __bf16* vbase = static_cast<const __bf16*>(a.v.ptr) + b * a.v.sb + hk * a.v.sh;
   const int row0 = qt * QT + rw * 32;
 
-  const int32_t* rp = a.row_ptr + (int64_t)bh * (a.nqb + 1) + qt;
-  const int beg = rp[0], end = rp[1];
+  int beg = 0, end = 0;
+  if (LIST) {  // the rows of a query block may be spread over several work-groups
+    const int32_t* rp = a.row_ptr + (int64_t)bh * (a.nqb + 1) + ((qt * QT) >> __builtin_ctz(a.block_q));
+    beg = rp[0];
+    end = rp[1];
+  }
   // A listed 128-key block is two consecutive tiles. Listed 32-key blocks are paired up in list order:
   // tile t holds entries 2t and 2t + 1, one in each 32-key half, wherever in the sequence they come from
   // (the key half a wave owns is then exactly one listed block; an odd count leaves the last half empty).
   constexpr int tile_shift = KB == 2 * kTileK ? 1 : 0;
   constexpr bool half_blocks = KB == kTileK / 2;
   const int entries = end - beg;
-  const int n = half_blocks ? (entries + 1) >> 1 : entries << tile_shift;
-  const int32_t* cols = a.col_idx + (int64_t)bh * a.cap_per_head + beg;
+  const int n = !LIST ? (L + kTileK - 1) / kTileK : half_blocks ? (entries + 1) >> 1 : entries << tile_shift;
+  // steps of this wave: the same for all where they meet at barriers (streams short of a tile end with a masked repeat)
+  const int n_steps = SG == 1 ? n : PRIVATE ? (n - sg + SG - 1) / SG : (n + SG - 1) / SG;
+  const int32_t* cols = LIST ? a.col_idx + (int64_t)bh * a.cap_per_head + beg : nullptr;
   constexpr int unit = half_blocks ? kTileK / 2 : kTileK;  // keys per copy unit: a 32-key block or a 64-key tile
   const int last_blk = (L - 1) / unit;                 // last unit that exists
   const int tail_keys = L - last_blk * unit;           // keys in it
 
-  float M = 0.f, lsum = 0.f;
+  float M = SG > 1 ? -1e30f : 0.f, lsum = 0.f;  // (a stream without a tile must not set the row's reference)
   f32x16 o[1][D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt)
@@ -101,7 +118,9 @@ __global__ __launch_bounds__(RW * 128)
   // block numbers of tiles t .. t+3, read with a vector load (see attn_bf16_kernel.hpp); past the end: the last one
   int opaque_zero;
   asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
-  auto col_at = [&](int t) -> int {  // key TILE number of tile t of the list; with 32-key blocks: the block of this wave's half
+  auto col_at = [&](int step) -> int {  // key TILE number of this stream's tile at a step; with 32-key blocks: the block of this wave's half
+    const int t = step * SG + sg;
+    if (!LIST) return t < n ? t : n - 1;
     if (half_blocks) {
       const int e = 2 * t + kh;
       return cols[(e < entries ? e : (entries > 0 ? entries - 1 : 0)) + opaque_zero];  // a missing half repeats the last block, masked
@@ -197,7 +216,9 @@ __global__ __launch_bounds__(RW * 128)
     exp_half(s, part);
   };
   // keys of this wave's half that exist in tile T of the list, whose first block number is `first`
-  auto valid_in = [&](int T, int first) -> int {
+  auto valid_in = [&](int step, int first) -> int {
+    const int T = step * SG + sg;
+    if (SG > 1 && T >= n) return 0;
     const int tile0 = __builtin_amdgcn_readfirstlane(first);
     return half_blocks ? (2 * T + kh < entries ? (tile0 == last_blk ? tail_keys : 32) : 0)
                        : (tile0 > last_blk ? 0 : tile0 == last_blk ? tail_keys : kTileK) - 32 * kh;
@@ -211,18 +232,18 @@ __global__ __launch_bounds__(RW * 128)
     char* const kb_next = (P) ? kbuf0 : kbuf1;                                                     \
     char* const vb_this = (P) ? vbuf1 : vbuf0;                                                     \
     char* const vb_free = (P) ? vbuf0 : vbuf1;                                                     \
-    if (!(TAIL) || (T) + 2 < n) copy_k(blk2, kb_free);                                             \
-    if (!(TAIL) || (T) + 1 < n) copy_v(blk1, vb_free);                                             \
+    if (!(TAIL) || (T) + 2 < n_steps) copy_k(blk2, kb_free);                                       \
+    if (!(TAIL) || (T) + 1 < n_steps) copy_v(blk1, vb_free);                                       \
     const int blk_new = col_at((T) + 4);                                                           \
     const int valid = !(MASKED) ? 32 : valid_in((T), blk0);                                         \
     float part;                                                                                    \
-    if (!(TAIL) || (T) + 1 < n) logits_sub<D, 1, false>(kb_next, kh, kaddr, qf, S_NEXT);           \
+    if (!(TAIL) || (T) + 1 < n_steps) logits_sub<D, 1, false>(kb_next, kh, kaddr, qf, S_NEXT);     \
     softmax_half(S_CUR, part, (MASKED), valid);                                                    \
     sched_substep_interleave<D, 1, false>();                                                       \
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0, 0)) re_reference(S_CUR, part);  \
     lsum += part;                                                                                  \
     __builtin_amdgcn_sched_barrier(0);                                                             \
-    pv_sub<D, 1, true>(vb_this, kh, vaddr, p, o);                                                  \
+    if (SG == 1 || !(TAIL) || (T) * SG + sg < n) pv_sub<D, 1, true>(vb_this, kh, vaddr, p, o);     \
     blk0 = blk1;                                                                                   \
     blk1 = blk2;                                                                                   \
     blk2 = blk3;                                                                                   \
@@ -252,9 +273,9 @@ __global__ __launch_bounds__(RW * 128)
   {                                                                                                \
     const int valid = !(TAIL) ? 32 : valid_in((T), blk0);                                          \
     float part;                                                                                    \
-    if (!(TAIL) || (T) + 1 < n) wait_copy(false); /* K(t+1) */                                     \
+    if (!(TAIL) || (T) + 1 < n_steps) wait_copy(false); /* K(t+1) */                                     \
     const int blk_new = col_at((T) + 4);                                                           \
-    if (!(TAIL) || (T) + 1 < n) {                                                                  \
+    if (!(TAIL) || (T) + 1 < n_steps) {                                                                  \
       logits_sub<D, 1, false>(kbuf0, kh, kaddr, qf, S_NEXT);                                       \
     }                                                                                              \
     softmax_half(S_CUR, part, (TAIL), valid);                                                      \
@@ -263,25 +284,25 @@ __global__ __launch_bounds__(RW * 128)
     lsum += part;                                                                                  \
     reads_done();                                                                                  \
     if (!(TAIL)) kdma.issue(krsrc, __builtin_amdgcn_readfirstlane(blk2) * k_tile_bytes, kbuf0, wave);     \
-    else if ((T) + 2 < n) copy_k(blk2, kbuf0);                                                     \
-    wait_copy((TAIL) && (T) + 2 >= n); /* V(t) */                                                  \
+    else if ((T) + 2 < n_steps) copy_k(blk2, kbuf0);                                                     \
+    wait_copy((TAIL) && (T) + 2 >= n_steps); /* V(t) */                                                  \
     pv_sub<D, 1, true>(vbuf0, kh, vaddr, p, o);                                                    \
     reads_done();                                                                                  \
     if (!(TAIL)) vdma.issue(vrsrc, __builtin_amdgcn_readfirstlane(blk1) * v_tile_bytes, vbuf0, wave);     \
-    else if ((T) + 1 < n) copy_v(blk1, vbuf0);                                                     \
+    else if ((T) + 1 < n_steps) copy_v(blk1, vbuf0);                                                     \
     blk0 = blk1;                                                                                   \
     blk1 = blk2;                                                                                   \
     blk2 = blk3;                                                                                   \
     blk3 = blk_new;                                                                                \
   }
 
-  if constexpr (PRIVATE) if (n > 0) {
+  if constexpr (PRIVATE) if (n_steps > 0) {
     copy_k(blk0, kbuf0);
     qf.load(qbase, row0, L, a.q.sl, lane);
     wait_vector_memory();
     logits_sub<D, 1, true>(kbuf0, kh, kaddr, qf, s_a);
     reads_done();
-    if (n > 1) copy_k(blk1, kbuf0);
+    if (n_steps > 1) copy_k(blk1, kbuf0);
     copy_v(blk0, vbuf0);
     {
       f32x16 first[1] = {s_a[0]};  // the first tile fixes the reference, as below
@@ -293,12 +314,12 @@ __global__ __launch_bounds__(RW * 128)
     // (with 128-key blocks its second tile may not exist at all); its copies have no branch, so that
     // a wait has exactly one of them behind it
     const int reach = 3 + ((tail_keys < unit || (tile_shift && !(last_blk & 1))) ? 1 + tile_shift : 0);
-    while (t + reach < n) {
+    while (t + reach < n_steps) {
       SPARSED_PRIVATE_STEP(false, t, s_a, s_b);
       SPARSED_PRIVATE_STEP(false, t + 1, s_b, s_a);
       t += 2;
     }
-    for (; t < n; ++t) {
+    for (; t < n_steps; ++t) {
       if (t & 1) {
         SPARSED_PRIVATE_STEP(true, t, s_b, s_a);
       } else {
@@ -310,7 +331,7 @@ __global__ __launch_bounds__(RW * 128)
 
   if constexpr (!PRIVATE) if (n > 0) {
     copy_k(blk0, kbuf0);
-    if (n > 1) copy_k(blk1, kbuf1);
+    if (n_steps > 1) copy_k(blk1, kbuf1);
     copy_v(blk0, vbuf0);
     qf.load(qbase, row0, L, a.q.sl, lane);
     __syncthreads();
@@ -325,12 +346,12 @@ __global__ __launch_bounds__(RW * 128)
     __syncthreads();  // everyone is done with K(0) before step 0 lets K(2) overwrite it
 
     int t = 0;
-    while (t + 2 < n) {
+    while (t + 2 < n_steps) {
       SPARSED_SPLITK_STEP(0, false, false, t, s_a, s_b);
       SPARSED_SPLITK_STEP(1, false, false, t + 1, s_b, s_a);
       t += 2;
     }
-    if (n - t == 2) {  // with 128-key blocks the last two tiles may both be short (a partial last block)
+    if (n_steps - t == 2) {  // with 128-key blocks the last two tiles may both be short (a partial last block)
       SPARSED_SPLITK_STEP(0, (tile_shift != 0), true, t, s_a, s_b);
       SPARSED_SPLITK_STEP(1, true, true, t + 1, s_b, s_a);
     } else {
@@ -339,95 +360,219 @@ __global__ __launch_bounds__(RW * 128)
   }
 #undef SPARSED_SPLITK_STEP
 
-  // Merge the two key halves of every row. The waves of half 1 leave their accumulator, reference
-  // maximum and sum in the (now idle) K buffers, laid out [value][lane] so that both sides touch
-  // consecutive words; the waves of half 0 fold them in, normalise and store.
-  static_assert(!PRIVATE || RW == 1, "a wave per key half");
-  static_assert(RW <= 2, "one K buffer and one V buffer per wave of the second key half");
-  static_assert(D / 32 * 16 * 64 * 4 <= kKBytes && 2 * 64 * 4 <= kVBytes, "exchange areas must fit the buffers");
-  float* const xchg = reinterpret_cast<float*>(rw == 0 ? kbuf0 : kbuf1);   // the accumulator
-  float* const xchg2 = reinterpret_cast<float*>(rw == 0 ? vbuf0 : vbuf1);  // reference maximum and sum
-  const float ltot_mine = pair_sum(lsum);
-  if (PRIVATE) __syncthreads();  // the exchange overlaps the other wave's halves
-  if (kh == 1) {
+  if constexpr (SG > 1) {
+    // Merge the KW parts of every row. Wave `part` of a row group finishes 1/KW of the columns: every wave leaves its
+    // accumulator's groups of 8 columns with the wave that owns them, four values a lane, lane after lane, in a region of the
+    // (now idle) buffers that belongs to the owner, and the owner adds the parts up, each by its factor, normalises and stores.
+    constexpr int kGroups = D / 8, kOwn = kGroups / KW;             // groups of 8 columns, and those of a wave
+    constexpr int kRegionBytes = (KW - 1) * kOwn * 1024;
+    static_assert(RW <= 2 && (!PRIVATE || RW == 1), "a buffer per wave of a stream");
+    static_assert(kRegionBytes <= kVBytes && kVBytes <= kKBytes, "a region a buffer");
+    const int part = 2 * sg + kh;
+    auto region = [&](int p) -> char* {  // of the wave of this row group that owns part p
+      const int w = (p & 1) * RW + rw;   // its number in its stream
+      char* const bufs[4] = {kbufs0 + (p >> 1) * kKBytes, PRIVATE || RW == 1 ? vbufs0 + (p >> 1) * kVBytes : kbufs1 + (p >> 1) * kKBytes,
+                             vbufs0 + (p >> 1) * kVBytes, vbufs1 + (PRIVATE ? 0 : (p >> 1) * kVBytes)};
+      return bufs[w];
+    };
+    const float ltot_mine = pair_sum(lsum);
+    if (PRIVATE) __syncthreads();  // the regions overlap the buffers of waves that may still be reading them
+    if (g == 0) {
+      stat_m[rw][part][j] = M;
+      stat_l[rw][part][j] = ltot_mine;
+    }
+    f32x4v own[kOwn];
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int p = 0; p < KW; ++p) {
+      f32x4v v[kOwn];
 #pragma unroll
-      for (int x = 0; x < 16; ++x) xchg[(dt * 16 + x) * 64 + lane] = o[0][dt][x];
-    xchg2[lane] = M;
-    xchg2[64 + lane] = ltot_mine;
-  }
-  __syncthreads();
-  if (kh == 1) return;
-  const float M_other = xchg2[lane], l_other = xchg2[64 + lane];
-  const float Mn = fmaxf(M, M_other);
-  const float f_mine = __builtin_amdgcn_exp2f(M - Mn), f_other = __builtin_amdgcn_exp2f(M_other - Mn);
-  const float ltot = ltot_mine * f_mine + l_other * f_other;
-  const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
+      for (int i = 0; i < kOwn; ++i)
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+        for (int e = 0; e < 4; ++e) v[i][e] = o[0][(p * kOwn + i) / 4][4 * ((p * kOwn + i) % 4) + e];
+      if (p == part) {
 #pragma unroll
-    for (int x = 0; x < 16; ++x) o[0][dt][x] = (o[0][dt][x] * f_mine + xchg[(dt * 16 + x) * 64 + lane] * f_other) * inv;
+        for (int i = 0; i < kOwn; ++i) own[i] = v[i];
+      } else {
+        char* const dst = region(p) + (part < p ? part : part - 1) * (kOwn * 1024) + lane * 16;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) *reinterpret_cast<f32x4v*>(dst + i * 1024) = v[i];
+      }
+    }
+    __syncthreads();
+    float Mn = M, ltot = 0.f;
+#pragma unroll
+    for (int p = 0; p < KW; ++p) Mn = fmaxf(Mn, stat_m[rw][p][j]);
+    char* const mine = region(part);
+    {
+      const float f = __builtin_amdgcn_exp2f(M - Mn);
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i) own[i] *= f;
+    }
+#pragma unroll
+    for (int p = 0; p < KW; ++p) {
+      const float f = __builtin_amdgcn_exp2f(stat_m[rw][p][j] - Mn);
+      ltot += stat_l[rw][p][j] * f;
+      if (p != part) {
+        const char* const src = mine + (p < part ? p : p - 1) * (kOwn * 1024) + lane * 16;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) own[i] += *reinterpret_cast<const f32x4v*>(src + i * 1024) * f;
+      }
+    }
+    if (!LIST && a.lse != nullptr && part == 0 && g == 0 && row0 + j < L)
+      a.lse[(int64_t)bh * a.L + row0 + j] = (Mn + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+    const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
 
-  // whole-row stores through an LDS transpose (see the epilogue of attn_bf16_kernel.hpp); the staging slice is this
-  // row group's V buffer, whose two exchanged values this wave has already read
-  constexpr int kRowBytes = 2 * D, kSlots = D / 8, kRowsPerStore = 64 / kSlots;
-  static_assert(32 * kRowBytes <= kVBytes, "staging slice must fit a V buffer");
-  char* const stage = rw == 0 ? vbuf0 : vbuf1;
+    // stores of whole runs of a row, through an LDS transpose in the wave's own region (its slots of 16 bytes, one per group,
+    // at position slot ^ (row mod slots))
+    constexpr int kRowBytes = 16 * kOwn;
+    static_assert(32 * kRowBytes <= kRegionBytes, "staging fits the region");
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const f32x2 lo = {o[0][dt][4 * q4], o[0][dt][4 * q4 + 1]};
-      const f32x2 hi = {o[0][dt][4 * q4 + 2], o[0][dt][4 * q4 + 3]};
+    for (int i = 0; i < kOwn; ++i) {
+      const f32x2 lo = {own[i][0] * inv, own[i][1] * inv}, hi = {own[i][2] * inv, own[i][3] * inv};
       u32x2 w;
       w[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
       w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
-      *reinterpret_cast<u32x2*>(stage + j * kRowBytes + (((4 * dt + q4) ^ (j & (kSlots - 1))) << 4) + 8 * g) = w;
+      *reinterpret_cast<u32x2*>(mine + j * kRowBytes + ((i ^ (j & (kOwn - 1))) << 4) + 8 * g) = w;
     }
-  __bf16* const obase = static_cast<__bf16*>(a.o) + b * a.o_sb + h * a.o_sh;
+    __bf16* const obase = static_cast<__bf16*>(a.o) + b * a.o_sb + h * a.o_sh + part * (8 * kOwn);
 #pragma unroll
-  for (int it = 0; it < 32 / kRowsPerStore; ++it) {
-    const int r = it * kRowsPerStore + lane / kSlots, slot = lane % kSlots;
-    const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * kRowBytes + ((slot ^ (r & (kSlots - 1))) << 4));
-    const int grow = row0 + r;
-    if (grow < L) *reinterpret_cast<u32x4*>(obase + (int64_t)grow * a.o_sl + slot * 8) = w;
+    for (int it = 0; it < (32 * kOwn + 63) / 64; ++it) {
+      const int piece = it * 64 + lane, r = piece / kOwn, slot = piece % kOwn;
+      if (r < 32 && row0 + r < L) {
+        const u32x4 w = *reinterpret_cast<const u32x4*>(mine + r * kRowBytes + ((slot ^ (r & (kOwn - 1))) << 4));
+        *reinterpret_cast<u32x4*>(obase + (int64_t)(row0 + r) * a.o_sl + slot * 8) = w;
+      }
+    }
+  } else {
+    // Merge the two key halves of every row. The waves of half 1 leave their accumulator, reference
+    // maximum and sum in the (now idle) K buffers, laid out [value][lane] so that both sides touch
+    // consecutive words; the waves of half 0 fold them in, normalise and store.
+    static_assert(!PRIVATE || RW == 1, "a wave per key half");
+    static_assert(RW == 1 || RW == 2 || RW == 4, "a K buffer and a V buffer per wave of the second key half, or a buffer");
+    static_assert(D / 32 * 16 * 64 * 4 <= kKBytes && 2 * 64 * 4 <= kVBytes, "exchange areas must fit the buffers");
+    float* const xchg = reinterpret_cast<float*>(rw == 0 ? kbuf0 : RW <= 2 || rw == 1 ? kbuf1 : rw == 2 ? vbuf0 : vbuf1);  // the accumulator
+    float* const xchg_m = RW == 4 ? half_m[rw] : reinterpret_cast<float*>(rw == 0 ? vbuf0 : vbuf1);  // reference maximum
+    float* const xchg_l = RW == 4 ? half_l[rw] : xchg_m + 64;                                        // and sum
+    const float ltot_mine = pair_sum(lsum);
+    if (PRIVATE) __syncthreads();  // the exchange overlaps the other wave's halves
+    if (kh == 1) {
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) xchg[(dt * 16 + x) * 64 + lane] = o[0][dt][x];
+      xchg_m[lane] = M;
+      xchg_l[lane] = ltot_mine;
+    }
+    __syncthreads();
+    if (kh == 1) return;
+    const float M_other = xchg_m[lane], l_other = xchg_l[lane];
+    const float Mn = fmaxf(M, M_other);
+    const float f_mine = __builtin_amdgcn_exp2f(M - Mn), f_other = __builtin_amdgcn_exp2f(M_other - Mn);
+    const float ltot = ltot_mine * f_mine + l_other * f_other;
+    if (!LIST && a.lse != nullptr && g == 0 && row0 + j < L)
+      a.lse[(int64_t)bh * a.L + row0 + j] = (Mn + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
+    const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) o[0][dt][x] = (o[0][dt][x] * f_mine + xchg[(dt * 16 + x) * 64 + lane] * f_other) * inv;
+
+    // whole-row stores through an LDS transpose (see the epilogue of attn_bf16_kernel.hpp); the staging slice is this
+    // row group's V buffer, whose two exchanged values this wave has already read (with four row groups: where its exchange was)
+    constexpr int kRowBytes = 2 * D, kSlots = D / 8, kRowsPerStore = 64 / kSlots;
+    static_assert(32 * kRowBytes <= kVBytes, "staging slice must fit a V buffer");
+    char* const stage = RW == 4 ? reinterpret_cast<char*>(xchg) : rw == 0 ? vbuf0 : vbuf1;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x2 lo = {o[0][dt][4 * q4], o[0][dt][4 * q4 + 1]};
+        const f32x2 hi = {o[0][dt][4 * q4 + 2], o[0][dt][4 * q4 + 3]};
+        u32x2 w;
+        w[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+        w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
+        *reinterpret_cast<u32x2*>(stage + j * kRowBytes + (((4 * dt + q4) ^ (j & (kSlots - 1))) << 4) + 8 * g) = w;
+      }
+    __bf16* const obase = static_cast<__bf16*>(a.o) + b * a.o_sb + h * a.o_sh;
+#pragma unroll
+    for (int it = 0; it < 32 / kRowsPerStore; ++it) {
+      const int r = it * kRowsPerStore + lane / kSlots, slot = lane % kSlots;
+      const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * kRowBytes + ((slot ^ (r & (kSlots - 1))) << 4));
+      const int grow = row0 + r;
+      if (grow < L) *reinterpret_cast<u32x4*>(obase + (int64_t)grow * a.o_sl + slot * 8) = w;
+    }
   }
 #endif
 }
 
-template <int D, int RW, bool PRIVATE>
-static hipError_t launch_splitk(const AttnArgs& a, hipStream_t s) {
+template <int D, int RW, bool PRIVATE, int SG>
+static hipError_t launch_splitk(Mode mode, AttnArgs a, hipStream_t s) {
+  a.n_qtiles = (a.L + 32 * RW - 1) / (32 * RW);
   const int64_t total = (int64_t)a.B * a.Hq * a.n_qtiles;
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)total), block(RW * 128);
+  const dim3 grid((unsigned)total), block(RW * SG * 128);
+  if (mode == Mode::kDense) {
+    if constexpr (RW * SG == 1) return hipErrorInvalidValue;  // no rule takes dense there
+    else hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 64, PRIVATE, SG, false>), grid, block, 0, s, a);
+    return hipGetLastError();
+  }
   switch (a.block_k) {
-    case 32: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 32, PRIVATE>), grid, block, 0, s, a); break;
-    case 64: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 64, PRIVATE>), grid, block, 0, s, a); break;
-    case 128: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 128, PRIVATE>), grid, block, 0, s, a); break;
+    case 32: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 32, PRIVATE, SG, true>), grid, block, 0, s, a); break;
+    case 64: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 64, PRIVATE, SG, true>), grid, block, 0, s, a); break;
+    case 128: hipLaunchKernelGGL((attn_bf16_splitk_kernel<D, RW, 128, PRIVATE, SG, true>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Sparse attention for query blocks of 32 or 64 rows. a.n_qtiles must be set by the caller.
-template <int D>
-static hipError_t launch_splitk_d(int block_q, const AttnArgs& a, hipStream_t s) {
-  if (block_q == 64) return launch_splitk<D, 2, false>(a, s);
-  if (block_q != 32) return hipErrorInvalidValue;
-  // Double buffers while every compute unit has at most the two work-groups that they allow: 448 work-groups, 14 tiles a row:
-  // head dim 64 11.5 us against 13.4 private, 128 18.3 against 19.2; 528 work-groups, 8 tiles: 14.4 against 10.3, 21.7 against
-  // 15.3. At head dim 128 the barriers outweigh the lead on long lists (512 work-groups, 16 tiles: 20.2 against 20.9; 25 tiles:
-  // 32.9 against 31.9; 76 tiles: 82.8 against 73.0), at 64 they do not (76 tiles: 44.2 against 46.7). The host does not know
-  // the lists; their capacity is the average length where it is exact, and an upper bound of it otherwise.
-  const bool long_lists = (int64_t)a.cap_per_head * a.block_k > (int64_t)20 * kTileK * a.nqb;
-  if ((int64_t)a.B * a.Hq * a.n_qtiles <= 512 && !(D == 128 && long_lists)) return launch_splitk<D, 1, false>(a, s);
-  return launch_splitk<D, 1, true>(a, s);
+// Whether and how a dense or sparse call is split over the keys. What counts is how many runs of 32 query rows there are (the
+// chip holds 2048 waves of 256 registers) and how many tiles each walks. Dense, and sparse with 128-row query blocks, up to
+// 1024 runs: the general kernel's work-groups of 128 or 256 rows leave compute units idle or with one wave a SIMD. The fewer the
+// runs, the smaller the work-group's share of rows and the more parts of the keys, as long as a part has a few tiles; rows of
+// one query block in several work-groups walk the same list. Beyond, K and V copied for 32 to 128 rows instead of 128 or 256
+// cost more than the idle units (1504 runs of 94 tiles, head dim 128, dense: 146.5 us general, 164.7 split).
+// Dense, us, general -> split, (heads, tokens, head dim): (4, 2048, 64) 33.0 -> 13.6, (4, 2048, 128) 43.6 -> 19.9,
+// (8, 600, 64) 12.9 -> 8.5, (16, 600, 64) 13.1 -> 9.7, (4, 4096, 64) 61.4 -> 27.9, (8, 4096, 128) 84.0 -> 71.0,
+// (28, 600, 64) 13.5 -> 11.9. Sparse 128 x 128, 30 % kept: (4, 2048, 64) 12.4 -> 8.8, (4, 2048, 128) 15.1 -> 11.9,
+// (4, 4096, 64) 19.6 -> 13.9, (8, 3000, 64) 19.1 -> 17.0 (head dim 128: 24.0 and 23.6, with longer lists the general kernel is
+// the faster one; with lists of fewer than 8 tiles it is at 64). Sparse 32 x 32, half kept: (4, 2048, 64) 13.3 -> 9.8,
+// (4, 4096, 128) 35.6 -> 30.2. Sparse 64 x 64, 7 tiles, 256 runs: 8.2 split in two, 7.8 in four.
+bool splitk_takes(Mode mode, int D, int block_q, const AttnArgs& a) {
+  if (mode == Mode::kSparse && block_q <= 64) return true;
+  if (mode != Mode::kDense && mode != Mode::kSparse) return false;
+  const int64_t runs = (int64_t)a.B * a.Hq * ((a.L + 31) / 32);
+  if (runs <= 512) return true;
+  return runs <= 1024 && (mode == Mode::kDense || (D == 64 && (int64_t)a.cap_per_head * a.block_k >= (int64_t)8 * kTileK * a.nqb));
 }
 
-hipError_t launch_attn_bf16_splitk(int D, int block_q, const AttnArgs& a, hipStream_t s) {
-  if (D == 128) return launch_splitk_d<128>(block_q, a, s);
-  if (D == 64) return launch_splitk_d<64>(block_q, a, s);
+template <int D>
+static hipError_t launch_splitk_d(Mode mode, int block_q, const AttnArgs& a, hipStream_t s) {
+  const bool dense = mode == Mode::kDense;
+  const int64_t runs = (int64_t)a.B * a.Hq * ((a.L + 31) / 32);
+  // tiles that a row walks; the host does not know the lists: their capacity is the average length where it is exact, and an
+  // upper bound of it otherwise
+  const int64_t tiles = dense ? (a.L + kTileK - 1) / kTileK : ((int64_t)a.cap_per_head * a.block_k / kTileK + a.nqb - 1) / a.nqb;
+  if (!dense && block_q == 32) {
+    if (tiles >= (runs <= 256 ? 4 : 12) && runs <= 512) return launch_splitk<D, 1, true, 2>(mode, a, s);
+    // Double buffers while every compute unit has at most the two work-groups that they allow: 448 work-groups, 14 tiles a row:
+    // head dim 64 11.5 us against 13.4 private, 128 18.3 against 19.2; 528 work-groups, 8 tiles: 14.4 against 10.3, 21.7 against
+    // 15.3.
+    if (runs <= 512) return launch_splitk<D, 1, false, 1>(mode, a, s);
+    return launch_splitk<D, 1, true, 1>(mode, a, s);
+  }
+  if (runs <= 256 && tiles >= (dense ? 8 : 10)) return launch_splitk<D, 1, true, 2>(mode, a, s);
+  if (runs > 256 && runs <= 512 && tiles >= (!dense ? 16 : D == 64 ? 12 : 20)) return launch_splitk<D, 2, false, 2>(mode, a, s);
+  if (runs > 512 && (dense || block_q == 128)) {
+    if constexpr (D == 64) return launch_splitk<D, 4, false, 1>(mode, a, s);
+    else if (dense) return launch_splitk<D, 4, false, 1>(mode, a, s);
+  }
+  return launch_splitk<D, 2, false, 1>(mode, a, s);
+}
+
+hipError_t launch_attn_bf16_splitk(Mode mode, int D, int block_q, const AttnArgs& a, hipStream_t s) {
+  if (mode == Mode::kSparse && block_q != 32 && block_q != 64 && block_q != 128) return hipErrorInvalidValue;
+  if (D == 128) return launch_splitk_d<128>(mode, block_q, a, s);
+  if (D == 64) return launch_splitk_d<64>(mode, block_q, a, s);
   return hipErrorInvalidValue;
 }
 

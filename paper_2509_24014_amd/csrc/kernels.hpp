@@ -25,7 +25,7 @@ struct AttnArgs {
   int32_t nqb, cap_per_head, block_k;
   int32_t n_qtiles;        // query tiles per head = ceil(L / rows per work-group)
   float scale_log2;        // log2(e) / sqrt(D)
-  int32_t block_q;         // rows per query block (kDensePool and the fp32 sparse kernel)
+  int32_t block_q;         // rows per query block (sparse; kDensePool)
   // kDensePool only (nqb, block_q and block_k then describe the pooled blocks)
   float* slab;             // scratch: one slab of (rows per work-group) x slab_cols floats per work-group of the launch
   float* apool;            // [B, Hq, nqb, nkb] pooled scores
@@ -127,8 +127,10 @@ enum class Mode : int { kDense = 0, kSparse = 1, kStats = 2, kDensePool = 3 };
 // the sparse and pooled kernels; dense and stats pick their own query tile from L.
 hipError_t launch_attn_bf16(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s);
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s);
-// bf16 sparse attention for query blocks of 32 or 64 rows (two waves per 32 rows, keys of a tile split between them)
-hipError_t launch_attn_bf16_splitk(int D, int block_q, const AttnArgs& a, hipStream_t s);
+// bf16 attention with the keys split over the waves of a work-group (a.block_q set; block_q = 0 for dense), and the calls it
+// is for: sparse with query blocks of 32 or 64 rows, dense and sparse calls with few rows in all.
+bool splitk_takes(Mode mode, int D, int block_q, const AttnArgs& a);
+hipError_t launch_attn_bf16_splitk(Mode mode, int D, int block_q, const AttnArgs& a, hipStream_t s);
 // The dense call that also pools (bf16): shape of its launch for q [B, Hq, L, .] and blocks of block_q x block_k, and the
 // launch itself (a.slab of groups * rows * slab_cols floats, a.apool, a.nqb, a.nkb, a.block_q, a.block_k set by the caller).
 struct DensePoolShape {
