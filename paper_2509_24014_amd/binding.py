@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 from typing import Optional
 
@@ -53,7 +54,37 @@ class _Exec(ctypes.Structure):
                 ("seq_lens", ctypes.c_void_p)]
 
 
+# The same structs as bytes. A short call is bound by what the host does before its launch, and packing costs a fifth of
+# filling a ctypes structure (a dense step with its output given: 11.6 us on the host with ctypes structures and the stream
+# object looked up, 5.9 so, 3.2 of them the launch).
+_pack_tensor = struct.Struct("P5i4x3q").pack
+_pack_index = struct.Struct("7i4xPP").pack
+_pack_exec = struct.Struct("PPNPPPP").pack
+_DTYPES = {torch.bfloat16: SPARSED_BF16, torch.float32: SPARSED_F32}
+
 _lib = None
+_calls = None
+
+
+class _Calls:
+    """The entry points of the hot path, taking their structs as bytes (the library reads them during the call only)."""
+
+    def __init__(self, lib):
+        S, i, d = ctypes.c_char_p, ctypes.c_int32, ctypes.c_double
+        for name, args in (("attn_dense", [S] * 5), ("attn_sparse", [S] * 6), ("attn_dense_select", [S] * 4 + [i, i, d, S, S]),
+                           ("select_pattern", [S, S, i, i, d, S, S]), ("select_pattern_static", [S, S, i, i, d, S, S]),
+                           ("select_pattern_isolated", [S, S, i, i, d, i, S, S]),
+                           ("select_pattern_isolated_tokens", [S, S, i, i, d, i, S, S])):
+            call = lib["sparsed_" + name]   # a function object of its own
+            call.argtypes, call.restype = args, ctypes.c_int
+            setattr(self, name, call)
+
+
+def _entry() -> _Calls:
+    global _calls
+    if _calls is None:
+        _calls = _Calls(load_library())
+    return _calls
 
 
 def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
@@ -122,27 +153,35 @@ def _check(status: int) -> None:
         raise SparsedError(status, msg)
 
 
-def _tensor(t: torch.Tensor, name: str) -> _Tensor:
+def _tensor_bytes(t: torch.Tensor, name: str) -> bytes:
     if t.dim() != 4:
         raise ValueError(f"{name} must be [B, H, L, D]")
-    if t.dtype == torch.bfloat16:
-        dt = SPARSED_BF16
-    elif t.dtype == torch.float32:
-        dt = SPARSED_F32
-    else:
+    dt = _DTYPES.get(t.dtype)
+    if dt is None:
         raise ValueError(f"{name}: dtype {t.dtype} is not bf16 or fp32")
-    if t.stride(3) != 1:
+    B, H, L, D = t.shape
+    sb, sh, sl, sd = t.stride()
+    if sd != 1:
         raise ValueError(f"{name}: last dimension must be contiguous")
     if not t.is_cuda:
         raise ValueError(f"{name} must live on the GPU")
-    B, H, L, D = t.shape
-    return _Tensor(t.data_ptr(), dt, B, H, L, D, t.stride(0), t.stride(1), t.stride(2))
+    return _pack_tensor(t.data_ptr(), dt, B, H, L, D, sb, sh, sl)
+
+
+def _tensor(t: torch.Tensor, name: str) -> _Tensor:
+    return _Tensor.from_buffer_copy(_tensor_bytes(t, name))
+
+
+# The current stream's handle without a Python stream object around it (2.6 us); not part of torch's documented interface.
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream_ptr(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return int(torch.cuda.current_stream().cuda_stream)
 
 
 @dataclass
@@ -159,14 +198,17 @@ class BlockIndex:
     def nqb(self) -> int:
         return self.row_ptr.shape[2] - 1
 
-    def _c(self) -> _BlockIndex:
-        B, H, _ = self.row_ptr.shape
-        if self.row_ptr.dtype != torch.int32 or self.col_idx.dtype != torch.int32:
+    def _bytes(self) -> bytes:
+        row_ptr, col_idx = self.row_ptr, self.col_idx
+        B, H, rows = row_ptr.shape
+        if row_ptr.dtype != torch.int32 or col_idx.dtype != torch.int32:
             raise ValueError("block index tensors must be int32")
-        if not (self.row_ptr.is_contiguous() and self.col_idx.is_contiguous()):
+        if not (row_ptr.is_contiguous() and col_idx.is_contiguous()):
             raise ValueError("block index tensors must be contiguous")
-        return _BlockIndex(B, H, self.nqb, self.nkb, self.block_q, self.block_k, self.col_idx.shape[2],
-                           self.row_ptr.data_ptr(), self.col_idx.data_ptr())
+        return _pack_index(B, H, rows - 1, self.nkb, self.block_q, self.block_k, col_idx.shape[2], row_ptr.data_ptr(), col_idx.data_ptr())
+
+    def _c(self) -> _BlockIndex:
+        return _BlockIndex.from_buffer_copy(self._bytes())
 
 
 def version() -> int:
@@ -206,37 +248,36 @@ def _seq_lens_ptr(seq_lens, B):
 def attn_dense(q, k, v, out: Optional[torch.Tensor] = None, lse_out: Optional[torch.Tensor] = None, stream=None,
                seq_lens: Optional[torch.Tensor] = None):
     """sparsed_attn_dense: full bidirectional attention (Eq. 1). Returns ``out``."""
-    lib = load_library()
     if out is None:
         out = torch.empty_like(q)
-    ex = _Exec(_stream_ptr(stream), None, 0, lse_out.data_ptr() if lse_out is not None else None, None, None,
-               _seq_lens_ptr(seq_lens, q.shape[0]))
-    if lse_out is not None and (lse_out.dtype != torch.float32 or not lse_out.is_contiguous()
-                                or lse_out.numel() != q.shape[0] * q.shape[1] * q.shape[2]):
-        raise ValueError("lse_out must be contiguous fp32 [B, Hq, L]")
-    tq, tk, tv, to = _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out")
-    _check(lib.sparsed_attn_dense(ctypes.byref(tq), ctypes.byref(tk), ctypes.byref(tv), ctypes.byref(to), ctypes.byref(ex)))
+    lse = 0
+    if lse_out is not None:
+        if lse_out.dtype != torch.float32 or not lse_out.is_contiguous() or lse_out.numel() != q.shape[0] * q.shape[1] * q.shape[2]:
+            raise ValueError("lse_out must be contiguous fp32 [B, Hq, L]")
+        lse = lse_out.data_ptr()
+    lens = 0 if seq_lens is None else _seq_lens_ptr(seq_lens, q.shape[0])
+    tq, tk, tv, to = _tensor_bytes(q, "q"), _tensor_bytes(k, "k"), _tensor_bytes(v, "v"), _tensor_bytes(out, "out")
+    _check(_entry().attn_dense(tq, tk, tv, to, _pack_exec(_stream_ptr(stream), 0, 0, lse, 0, 0, lens)))
     return out
 
 
 def _select(q, k, block_q, block_k, rho, prefill_blocks, lse_in, workspace, pooled_out, index, stream, prefill_tokens=None,
             seq_lens=None):
-    lib = load_library()
     B, H, L, D = q.shape
     nqb, nkb = -(-L // block_q), -(-L // block_k)
-    if prefill_tokens is not None:
-        keep = kept_blocks(rho, -(-prefill_tokens // block_k)) + kept_blocks(rho, nkb - prefill_tokens // block_k)
-    elif prefill_blocks is None:
-        keep = kept_blocks(rho, nkb)
-    else:
-        keep = kept_blocks(rho, prefill_blocks) + kept_blocks(rho, nkb - prefill_blocks)
     if index is None:
+        if prefill_tokens is not None:
+            keep = kept_blocks(rho, -(-prefill_tokens // block_k)) + kept_blocks(rho, nkb - prefill_tokens // block_k)
+        elif prefill_blocks is None:
+            keep = kept_blocks(rho, nkb)
+        else:
+            keep = kept_blocks(rho, prefill_blocks) + kept_blocks(rho, nkb - prefill_blocks)
         index = BlockIndex(torch.empty(B, H, nqb + 1, dtype=torch.int32, device=q.device),
                            torch.empty(B, H, max(nqb * keep, 1), dtype=torch.int32, device=q.device), block_q, block_k, nkb)
     if workspace is None:
         tq0 = _tensor(q, "q")
         if prefill_tokens is not None:
-            need = int(lib.sparsed_select_tokens_workspace_bytes(ctypes.byref(tq0), block_q, block_k))
+            need = int(load_library().sparsed_select_tokens_workspace_bytes(ctypes.byref(tq0), block_q, block_k))
         elif lse_in is not None:
             need = select_workspace_min_bytes(q, block_q, block_k)   # the slabs of the one-pass kernel would go unused
         else:
@@ -251,19 +292,17 @@ def _select(q, k, block_q, block_k, rho, prefill_blocks, lse_in, workspace, pool
         # the kernels run on `stream`; keep the allocator from handing these blocks to later work on the current stream
         for t in (workspace, index.row_ptr, index.col_idx):
             t.record_stream(stream)
-    ex = _Exec(_stream_ptr(stream), workspace.data_ptr(), workspace.numel() * workspace.element_size(), None,
-               lse_in.data_ptr() if lse_in is not None else None, pooled_out.data_ptr() if pooled_out is not None else None,
-               _seq_lens_ptr(seq_lens, B))
-    tq, tk, ci = _tensor(q, "q"), _tensor(k, "k"), index._c()
+    lens = 0 if seq_lens is None else _seq_lens_ptr(seq_lens, B)
+    tq, tk, ci = _tensor_bytes(q, "q"), _tensor_bytes(k, "k"), index._bytes()
+    ex = _pack_exec(_stream_ptr(stream), workspace.data_ptr(), workspace.numel() * workspace.element_size(), 0,
+                    0 if lse_in is None else lse_in.data_ptr(), 0 if pooled_out is None else pooled_out.data_ptr(), lens)
+    calls = _entry()
     if prefill_tokens is not None:
-        st = lib.sparsed_select_pattern_isolated_tokens(ctypes.byref(tq), ctypes.byref(tk), block_q, block_k, float(rho),
-                                                        int(prefill_tokens), ctypes.byref(ci), ctypes.byref(ex))
+        st = calls.select_pattern_isolated_tokens(tq, tk, block_q, block_k, float(rho), int(prefill_tokens), ci, ex)
     elif prefill_blocks is None:
-        st = lib.sparsed_select_pattern(ctypes.byref(tq), ctypes.byref(tk), block_q, block_k, float(rho), ctypes.byref(ci),
-                                        ctypes.byref(ex))
+        st = calls.select_pattern(tq, tk, block_q, block_k, float(rho), ci, ex)
     else:
-        st = lib.sparsed_select_pattern_isolated(ctypes.byref(tq), ctypes.byref(tk), block_q, block_k, float(rho),
-                                                 int(prefill_blocks), ctypes.byref(ci), ctypes.byref(ex))
+        st = calls.select_pattern_isolated(tq, tk, block_q, block_k, float(rho), int(prefill_blocks), ci, ex)
     _check(st)
     return index
 
@@ -278,7 +317,6 @@ def attn_dense_select(q, k, v, block_q: int, block_k: int, rho: float, out: Opti
                       workspace=None, pooled_out=None, index: Optional[BlockIndex] = None, stream=None,
                       seq_lens: Optional[torch.Tensor] = None):
     """sparsed_attn_dense_select: the dense step and the pattern selected from its q, k in one call. Returns (out, index)."""
-    lib = load_library()
     B, H, L, D = q.shape
     nqb, nkb = -(-L // block_q), -(-L // block_k)
     own_out = out is None
@@ -299,12 +337,11 @@ def attn_dense_select(q, k, v, block_q: int, block_k: int, rho: float, out: Opti
         # as in select_pattern; the output as well where it is this call's own allocation
         for t in (workspace, index.row_ptr, index.col_idx) + ((out,) if own_out else ()):
             t.record_stream(stream)
-    ex = _Exec(_stream_ptr(stream), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-               lse_out.data_ptr() if lse_out is not None else None, None,
-               pooled_out.data_ptr() if pooled_out is not None else None, _seq_lens_ptr(seq_lens, B))
-    tq, tk, tv, to, ci = _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"), index._c()
-    _check(lib.sparsed_attn_dense_select(ctypes.byref(tq), ctypes.byref(tk), ctypes.byref(tv), ctypes.byref(to), block_q, block_k,
-                                         float(rho), ctypes.byref(ci), ctypes.byref(ex)))
+    lens = 0 if seq_lens is None else _seq_lens_ptr(seq_lens, B)
+    tq, tk, tv, to = _tensor_bytes(q, "q"), _tensor_bytes(k, "k"), _tensor_bytes(v, "v"), _tensor_bytes(out, "out")
+    ex = _pack_exec(_stream_ptr(stream), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                    0 if lse_out is None else lse_out.data_ptr(), 0, 0 if pooled_out is None else pooled_out.data_ptr(), lens)
+    _check(_entry().attn_dense_select(tq, tk, tv, to, block_q, block_k, float(rho), index._bytes(), ex))
     return out, index
 
 
@@ -315,12 +352,11 @@ def select_pattern_static(q, k, block_q: int, block_k: int, rho: float, index: B
                           stream=None, seq_lens: Optional[torch.Tensor] = None) -> BlockIndex:
     """sparsed_select_pattern_static: selection with the library's built-in scratch; allocates nothing (the caller
     brings the index to fill)."""
-    lib = load_library()
-    ex = _Exec(_stream_ptr(stream), None, 0, None, lse_in.data_ptr() if lse_in is not None else None,
-               pooled_out.data_ptr() if pooled_out is not None else None, _seq_lens_ptr(seq_lens, q.shape[0]))
-    tq, tk, ci = _tensor(q, "q"), _tensor(k, "k"), index._c()
-    _check(lib.sparsed_select_pattern_static(ctypes.byref(tq), ctypes.byref(tk), block_q, block_k, float(rho), ctypes.byref(ci),
-                                             ctypes.byref(ex)))
+    lens = 0 if seq_lens is None else _seq_lens_ptr(seq_lens, q.shape[0])
+    tq, tk, ci = _tensor_bytes(q, "q"), _tensor_bytes(k, "k"), index._bytes()
+    ex = _pack_exec(_stream_ptr(stream), 0, 0, 0, 0 if lse_in is None else lse_in.data_ptr(),
+                    0 if pooled_out is None else pooled_out.data_ptr(), lens)
+    _check(_entry().select_pattern_static(tq, tk, block_q, block_k, float(rho), ci, ex))
     return index
 
 
@@ -342,13 +378,11 @@ def select_pattern_isolated_tokens(q, k, block_q: int, block_k: int, rho: float,
 def attn_sparse(q, k, v, index: BlockIndex, out: Optional[torch.Tensor] = None, stream=None,
                 seq_lens: Optional[torch.Tensor] = None):
     """sparsed_attn_sparse: block-sparse attention with a stored pattern (Eq. 3, Eq. 4). Returns ``out``."""
-    lib = load_library()
     if out is None:
         out = torch.empty_like(q)
-    ex = _Exec(_stream_ptr(stream), None, 0, None, None, None, _seq_lens_ptr(seq_lens, q.shape[0]))
-    tq, tk, tv, to, ci = _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"), index._c()
-    _check(lib.sparsed_attn_sparse(ctypes.byref(tq), ctypes.byref(tk), ctypes.byref(tv), ctypes.byref(ci), ctypes.byref(to),
-                                   ctypes.byref(ex)))
+    lens = 0 if seq_lens is None else _seq_lens_ptr(seq_lens, q.shape[0])
+    tq, tk, tv, to = _tensor_bytes(q, "q"), _tensor_bytes(k, "k"), _tensor_bytes(v, "v"), _tensor_bytes(out, "out")
+    _check(_entry().attn_sparse(tq, tk, tv, index._bytes(), to, _pack_exec(_stream_ptr(stream), 0, 0, 0, 0, 0, lens)))
     return out
 
 
