@@ -348,6 +348,19 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   return SPARSED_OK;
 }
 
+// bf16 steps with too few query rows to fill the chip: the dense call with its keys split over the waves, then pooling with its
+// statistics and the keys cut into segments, instead of the kernel that does both, which can do neither. Us, one kernel -> two
+// (heads, tokens, head dim): (4, 2048, 128) 49.1 -> 33.4, (8, 1000, 128) 32.4 -> 26.1, (16, 1000, 128) 33.5 -> 30.8, (4, 4096, 128)
+// 87.2 -> 75.7, (28, 600, 128) 27.0 and 29.0; (4, 2048, 64) 30.5 -> 24.9, (4, 800, 64) 19.4 -> 18.2, (4, 3000, 64) 42.5 -> 37.8,
+// (8, 1500, 64) 27.6 and 28.3, (4, 4096, 64) 52.9 and 52.6. From 12 tiles on: at head dim
+// 128 ten tiles gain as well (25.2 -> 20.9), but up to there a sample of a padded batch is, bit for bit, what it is alone.
+bool dense_then_pool(const sparsed_tensor* q) {
+  const int64_t runs = (int64_t)q->B * q->H * ceil_div(q->L, 32);
+  const int tiles = ceil_div(q->L, 64);
+  if (q->D == 128) return runs <= 512 && tiles >= 12;
+  return (runs <= 256 && tiles >= 13) || (runs <= 384 && tiles >= 40);
+}
+
 // Dense attention and the pattern of one key range from the same q, k. bf16: the attention kernel leaves the pooled
 // scores; fp32: dense with its log-sum-exp, then selection with it.
 sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v, sparsed_tensor* out,
@@ -376,10 +389,18 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
     if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step))) return st;
     return select_impl(q, k, bq, bk, rho, 0, false, ix, &step);
   }
-  const DensePoolShape sh = dense_pool_shape(q->B, q->H, q->L, bk);
   const size_t apool_bytes = align256((size_t)q->B * q->H * nqb * nkb * sizeof(float));
-  const size_t need = apool_bytes + (size_t)sh.groups * sh.rows * sh.slab_cols * sizeof(float);
-  if ((st = caller_workspace(ex, need, "dense step with selection", &ws))) return st;
+  auto bytes_of = [&](const DensePoolShape& sh) { return apool_bytes + (size_t)sh.groups * sh.rows * sh.slab_cols * sizeof(float); };
+  DensePoolShape sh = dense_pool_shape(q->D, q->B, q->H, q->L, bk, 256);
+  if (ex && ex->workspace && ex->workspace_bytes < bytes_of(sh)) sh = dense_pool_shape(q->D, q->B, q->H, q->L, bk, 128);
+  if ((st = caller_workspace(ex, bytes_of(sh), "dense step with selection", &ws))) return st;
+  if (dense_then_pool(q) && ex->workspace_bytes >= select_ws_bytes(q->B, q->H, q->L, nqb, nkb)) {
+    sparsed_exec step = *ex;
+    if (!step.lse_out) step.lse_out = reinterpret_cast<float*>(ws);
+    step.lse_in = step.lse_out;
+    if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step))) return st;
+    return select_impl(q, k, bq, bk, rho, 0, false, ix, &step);
+  }
   AttnArgs a{};
   a.q = targ(q);
   a.k = targ(k);
@@ -401,7 +422,7 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
   a.block_k = bk;
   a.apool = ex->pooled_out ? ex->pooled_out : reinterpret_cast<float*>(ws);
   a.slab = reinterpret_cast<float*>(ws + apool_bytes);
-  hipError_t e = launch_attn_bf16_dense_pool(q->D, a, stream_of(ex));
+  hipError_t e = launch_attn_bf16_dense_pool(q->D, a, sh, stream_of(ex));
   if (e != hipSuccess) return hip_fail(e, "dense attention with pooling launch");
   TopkArgs t{};
   t.apool = a.apool;

@@ -3,12 +3,21 @@
 
 namespace sparsed {
 
-int dense_qtile_bf16(int L) {
+// Rows per work-group of a call that walks every tile. 256 (8 waves, alone on a compute unit) copies a tile for twice the rows
+// of 128 (4 waves, two work-groups a unit) and is the faster form of a chip that is full for the whole launch: 5 % at head dim
+// 128, 1 to 4 % at 64. But its launch ends with a round of its own length, however few units have work in it, where a 128-row
+// work-group that is alone on its unit takes 0.7 of a pair's time. Dense, us, 256 -> 128 rows, 1.1, 1.25, 1.5, 2.25, 3.1, 4.1
+// rounds of 256: head dim 64 143 -> 122, 157 -> 135, 98 -> 87, 219 -> 198, 405 -> 376, 755 -> 716; 128 210 -> 184, 232 -> 206,
+// 145 -> 139, 336 -> 314, 630 -> 601, 1182 -> 1154; above half a round left over, 256 rows throughout. (A length that is a
+// multiple of 64 and not of 128 once had work-groups of 64 rows, two waves: 16 heads of 3776 x 128 148 us, 102 with 256 rows.)
+int dense_qtile_bf16(int D, int64_t heads, int L) {
   if (L <= 0) return 0;
-  if (L % 256 == 0) return 256;
-  if (L % 128 == 0) return 128;
-  if (L % 64 == 0) return 64;
-  return L >= 1024 ? 256 : L >= 256 ? 128 : 64;  // partial last tile: waste at most one tile of rows
+  if (L <= 64) return 64;
+  constexpr int64_t kCus = 256;
+  const int64_t n256 = heads * ((L + 255) / 256), n128 = heads * ((L + 127) / 128), left = n128 % (2 * kCus);
+  const int64_t cost256 = (n256 + kCus - 1) / kCus * 1000;
+  const int64_t cost128 = (n128 / (2 * kCus) * 10 + (left == 0 ? 0 : left <= kCus ? 7 : 10)) * (D == 64 ? 101 : 105);
+  return cost128 < cost256 ? 128 : 256;
 }
 
 template <int D, int NQ, int NW, Mode MODE, int KB = kTileK>
@@ -35,7 +44,7 @@ static hipError_t launch_by_qtile(int qtile, const AttnArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_attn_bf16(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {
-  const int qtile = (mode == Mode::kSparse) ? block_q : dense_qtile_bf16(a.L);
+  const int qtile = (mode == Mode::kSparse) ? block_q : dense_qtile_bf16(D, (int64_t)a.B * a.Hq, a.L);
   if (qtile == 0) return hipErrorInvalidValue;
   a.n_qtiles = (a.L + qtile - 1) / qtile;
   a.block_q = block_q;

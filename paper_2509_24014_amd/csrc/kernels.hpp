@@ -45,6 +45,7 @@ struct PoolArgs {
   int32_t key_begin, key_len;
   int32_t key_len2;        // > 0: a second range, the key_len2 tokens behind the first, pooled into column 1 (a
                            // grid of two rows; both parts of the block that holds the prefill boundary in one launch)
+  int32_t seg_len;         // set by the bf16 launcher: > 0: the range is cut into segments of so many tokens, one per grid row
   int32_t out_stride;
   float scale_log2;        // log2(e) / sqrt(D)
   // one-pass form only (pool1p_bf16_kernel; whole key range, lse unused):
@@ -138,8 +139,8 @@ struct DensePoolShape {
   int groups;     // persistent work-groups
   int slab_cols;  // columns of a work-group's slab
 };
-DensePoolShape dense_pool_shape(int B, int Hq, int L, int block_k);
-hipError_t launch_attn_bf16_dense_pool(int D, AttnArgs a, hipStream_t s);
+DensePoolShape dense_pool_shape(int D, int B, int Hq, int L, int block_k, int max_rows);  // max_rows: 256 or 128
+hipError_t launch_attn_bf16_dense_pool(int D, AttnArgs a, const DensePoolShape& sh, hipStream_t s);
 hipError_t launch_pool_bf16(int D, int block_q, const PoolArgs& a, hipStream_t s);
 hipError_t launch_pool_f32(int D, int block_q, const PoolArgs& a, hipStream_t s);
 // Pooled scores of bf16 inputs in one pass over the keys (no row statistics needed): `groups` persistent work-groups,
@@ -181,7 +182,7 @@ hipError_t launch_valu_rate(float* scratch, int iters, int op, hipStream_t s);
 // exp2, and optionally one LDS operand read each; same launch shape and matrix work as launch_mfma_rate.
 hipError_t launch_mix_rate(float* scratch, int iters, int vector_per_mfma, int lds_operands, hipStream_t s);
 
-// Rows per work-group the bf16 dense / stats kernels use for this L (0 if L is unsupported).
-int dense_qtile_bf16(int L);
+// Rows per work-group the bf16 dense / stats kernels use for heads = B * Hq and this L (0 if L is unsupported).
+int dense_qtile_bf16(int D, int64_t heads, int L);
 
 }  // namespace sparsed

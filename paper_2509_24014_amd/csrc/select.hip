@@ -61,9 +61,18 @@ void pool_bf16_kernel(const PoolArgs a) {
 
   // length of this batch element (per-sample lengths shorten the whole-sequence key range with it)
   int L = a.L;
-  const int second = blockIdx.y;  // which of the launch's key ranges
-  const int key_begin = second ? a.key_begin + a.key_len : a.key_begin;
-  int key_len = second ? a.key_len2 : a.key_len;
+  // which part of the keys: the whole range, one of the launch's two ranges, or a segment of the range
+  int key_begin = a.key_begin, key_len = a.key_len, first_col = 0;
+  if (a.seg_len > 0) {
+    const int skip = blockIdx.y * a.seg_len;
+    key_begin += skip;
+    key_len = key_len - skip < a.seg_len ? key_len - skip : a.seg_len;
+    first_col = skip / a.block_k;
+  } else if (blockIdx.y) {
+    key_begin += key_len;
+    key_len = a.key_len2;
+    first_col = 1;
+  }
   if (a.seq_lens != nullptr) {
     const int len = a.seq_lens[b];
     L = len < a.L ? len : a.L;
@@ -80,7 +89,7 @@ void pool_bf16_kernel(const PoolArgs a) {
   qf.load(qbase, row0, L, a.q.sl, lane);
   // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
   const float lse2 = (row0 + j < L) ? a.lse[(int64_t)bh * a.L + row0 + j] * 1.4426950408889634f : __builtin_inff();
-  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + second;
+  float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + first_col;
   const int rows_here = (L - I * kBlockRows < kBlockRows) ? L - I * kBlockRows : kBlockRows;  // query rows of the block that exist
   const int last_blk = (key_len - 1) / kTileK;
   const int tail_keys = key_len - last_blk * kTileK;  // keys that exist in the last key block of the range
@@ -627,14 +636,28 @@ __global__ __launch_bounds__(256) void window_index_kernel(const WindowArgs a) {
 }
 
 // ---------------------------------------------------------------------------- launchers
+// Tokens per segment where there are too few query rows to fill the chip, which holds four work-groups a compute unit: the key
+// range is cut so that it does, into segments of at least four tiles (0: one segment). Scores of the segments are independent
+// given the row statistics. Pooling and top-k, us: 4 heads of 2048 x 128 27 -> 14.7 (least segments of 4 or 8 tiles), of 600 x 64
+// 13.7 -> 10.0 (4 tiles; 8 leave one segment).
+static int pool_segment(int64_t groups, int key_len) {
+  constexpr int kSlots = 1024, kLeast = 4 * kTileK;
+  const int64_t parts = kSlots / groups;
+  if (parts < 2 || key_len < 2 * kLeast) return 0;
+  int64_t len = (key_len + parts - 1) / parts;
+  if (len < kLeast) len = kLeast;
+  return (int)((len + 127) / 128 * 128);  // a multiple of every block_k
+}
+
 template <int D>
-static hipError_t launch_pool_bf16_d(int block_q, const PoolArgs& a, hipStream_t s) {
+static hipError_t launch_pool_bf16_d(int block_q, PoolArgs a, hipStream_t s) {
   // every work-group is four waves = 128 consecutive rows of a head: one, two or four query blocks
   if (block_q != 128 && block_q != 64 && block_q != 32) return hipErrorInvalidValue;
   const int blocks_per_group = 128 / block_q;
   const int64_t total = (int64_t)a.B * a.Hq * ((a.nqb + blocks_per_group - 1) / blocks_per_group);
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)total, a.key_len2 > 0 ? 2 : 1), block(256);
+  a.seg_len = a.key_len2 > 0 ? 0 : pool_segment(total, a.key_len);
+  const dim3 grid((unsigned)total, a.key_len2 > 0 ? 2 : a.seg_len > 0 ? (a.key_len + a.seg_len - 1) / a.seg_len : 1), block(256);
   switch (block_q) {
     case 128:
       if (a.block_k == 32) hipLaunchKernelGGL((pool_bf16_kernel<D, 4, true, 4>), grid, block, 0, s, a);
