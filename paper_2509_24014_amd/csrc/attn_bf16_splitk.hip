@@ -115,51 +115,65 @@ __global__ __launch_bounds__(RW * SG * 128)
   kaddr.init(lane);
   vaddr.init(lane);
 
-  // block numbers of tiles t .. t+3, read with a vector load (see attn_bf16_kernel.hpp); past the end: the last one
-  int opaque_zero;
-  asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
-  auto col_at = [&](int step) -> int {  // key TILE number of this stream's tile at a step; with 32-key blocks: the block of this wave's half
-    const int t = step * SG + sg;
-    if (!LIST) return t < n ? t : n - 1;
-    if (half_blocks) {
+  // Block numbers of this stream's next 64 steps, one a lane; a step reads the ones it needs from there. (A load a step, even
+  // four tiles ahead, is waited for by count, and the count takes the copies in flight with it.) Past the end: the last one.
+  int list_base = 0;
+  auto list_from = [&](int from) -> int {
+    const int t = (from + lane) * SG + sg;
+    if (half_blocks) {  // the block of this wave's half of the tile; a missing half repeats the last block, masked
       const int e = 2 * t + kh;
-      return cols[(e < entries ? e : (entries > 0 ? entries - 1 : 0)) + opaque_zero];  // a missing half repeats the last block, masked
+      return cols[e < entries ? e : entries - 1];
     }
-    const int idx = t < n ? t : (n > 0 ? n - 1 : 0);
-    return (cols[(idx >> tile_shift) + opaque_zero] << tile_shift) + (idx & tile_shift);
+    const int idx = t < n ? t : n - 1;
+    return (cols[idx >> tile_shift] << tile_shift) + (idx & tile_shift);
   };
-  int blk0 = 0, blk1 = 0, blk2 = 0, blk3 = 0;
-  if (n > 0) {
-    blk0 = col_at(0);
-    blk1 = col_at(1);
-    blk2 = col_at(2);
-    blk3 = col_at(3);
-  }
+  int list = LIST && n > 0 ? list_from(0) : 0;
+  auto blk_at = [&](int step) -> int {  // key TILE number of this stream's tile at a step; with 32-key blocks: the block of this wave's half
+    if (!LIST) {
+      const int t = step * SG + sg;
+      return t < n ? t : n - 1;
+    }
+    return __builtin_amdgcn_readlane(list, step - list_base);
+  };
+  // before steps that need the numbers up to step `last`
+  auto reach_list = [&](int t, int last) {
+    if (LIST && last - list_base > 63) {
+      list_base = t;
+      list = list_from(t);
+      asm volatile("" : "+v"(list));
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), in a form that the compiler counts: no wait is left for the reads
+    }
+  };
   QFrag<D, 1> qf;  // loaded after the first K/V copies have been issued (see attn_bf16_kernel.hpp)
 
   const int64_t slab_rows = (int64_t)(a.L - 1);
-  const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(kbase, (slab_rows * a.k.sl + D) * 2);
-  const __amdgpu_buffer_rsrc_t vrsrc = make_rsrc(vbase, (slab_rows * a.v.sl + D) * 2);
+  auto rsrc_of = [](const void* base, int64_t bytes) {
+    if constexpr (PRIVATE) return untracked_rsrc(base, bytes);
+    else return make_rsrc(base, bytes);
+  };
+  const auto krsrc = rsrc_of(kbase, (slab_rows * a.k.sl + D) * 2);
+  const auto vrsrc = rsrc_of(vbase, (slab_rows * a.v.sl + D) * 2);
   const int32_t k_tile_bytes = (int32_t)(unit * a.k.sl * 2), v_tile_bytes = (int32_t)(unit * a.v.sl * 2);  // bytes per copy unit
   // (the second tile of a partial 128-key block may lie wholly past the end: any real tile is copied, all keys masked)
+  // a whole unit
+  auto copy_whole_k = [&](int ub, char* dst) { kdma.issue(krsrc, ub * k_tile_bytes, dst, wave); };
+  auto copy_whole_v = [&](int ub, char* dst) { vdma.issue(vrsrc, ub * v_tile_bytes, dst, wave); };
   auto copy_k = [&](int blk, char* dst) {
-    const int rb = __builtin_amdgcn_readfirstlane(blk);
-    const int ub = rb < last_blk ? rb : last_blk;
+    const int ub = blk < last_blk ? blk : last_blk;
     if (ub == last_blk && tail_keys < unit) {
       if (half_blocks) kdma.issue_partial_half(krsrc, ub * k_tile_bytes, dst, wave, lane, a.k.sl, tail_keys);
       else kdma.issue_partial(krsrc, ub * k_tile_bytes, dst, wave, lane, a.k.sl, tail_keys);
     } else {
-      kdma.issue(krsrc, ub * k_tile_bytes, dst, wave);
+      copy_whole_k(ub, dst);
     }
   };
   auto copy_v = [&](int blk, char* dst) {
-    const int rb = __builtin_amdgcn_readfirstlane(blk);
-    const int ub = rb < last_blk ? rb : last_blk;
+    const int ub = blk < last_blk ? blk : last_blk;
     if (ub == last_blk && tail_keys < unit) {
       if (half_blocks) vdma.issue_partial_half(vrsrc, ub * v_tile_bytes, dst, wave, lane, a.v.sl, tail_keys);
       else vdma.issue_partial(vrsrc, ub * v_tile_bytes, dst, wave, lane, a.v.sl, tail_keys);
     } else {
-      vdma.issue(vrsrc, ub * v_tile_bytes, dst, wave);
+      copy_whole_v(ub, dst);
     }
   };
 
@@ -215,11 +229,11 @@ __global__ __launch_bounds__(RW * SG * 128)
       for (int x = 0; x < 16; ++x) o[0][dt][x] *= alpha;
     exp_half(s, part);
   };
-  // keys of this wave's half that exist in tile T of the list, whose first block number is `first`
-  auto valid_in = [&](int step, int first) -> int {
+  // keys of this wave's half that exist in its stream's tile at a step
+  auto valid_in = [&](int step) -> int {
     const int T = step * SG + sg;
     if (SG > 1 && T >= n) return 0;
-    const int tile0 = __builtin_amdgcn_readfirstlane(first);
+    const int tile0 = blk_at(step);
     return half_blocks ? (2 * T + kh < entries ? (tile0 == last_blk ? tail_keys : 32) : 0)
                        : (tile0 > last_blk ? 0 : tile0 == last_blk ? tail_keys : kTileK) - 32 * kh;
   };
@@ -232,10 +246,9 @@ __global__ __launch_bounds__(RW * SG * 128)
     char* const kb_next = (P) ? kbuf0 : kbuf1;                                                     \
     char* const vb_this = (P) ? vbuf1 : vbuf0;                                                     \
     char* const vb_free = (P) ? vbuf0 : vbuf1;                                                     \
-    if (!(TAIL) || (T) + 2 < n_steps) copy_k(blk2, kb_free);                                       \
-    if (!(TAIL) || (T) + 1 < n_steps) copy_v(blk1, vb_free);                                       \
-    const int blk_new = col_at((T) + 4);                                                           \
-    const int valid = !(MASKED) ? 32 : valid_in((T), blk0);                                         \
+    if (!(TAIL) || (T) + 2 < n_steps) copy_k(blk_at((T) + 2), kb_free);                            \
+    if (!(TAIL) || (T) + 1 < n_steps) copy_v(blk_at((T) + 1), vb_free);                            \
+    const int valid = !(MASKED) ? 32 : valid_in(T);                                               \
     float part;                                                                                    \
     if (!(TAIL) || (T) + 1 < n_steps) logits_sub<D, 1, false>(kb_next, kh, kaddr, qf, S_NEXT);     \
     softmax_half(S_CUR, part, (MASKED), valid);                                                    \
@@ -244,20 +257,15 @@ __global__ __launch_bounds__(RW * SG * 128)
     lsum += part;                                                                                  \
     __builtin_amdgcn_sched_barrier(0);                                                             \
     if (SG == 1 || !(TAIL) || (T) * SG + sg < n) pv_sub<D, 1, true>(vb_this, kh, vaddr, p, o);     \
-    blk0 = blk1;                                                                                   \
-    blk1 = blk2;                                                                                   \
-    blk2 = blk3;                                                                                   \
-    blk3 = blk_new;                                                                                \
     __syncthreads();                                                                               \
   }
 
   // PRIVATE. On entry: S(t) in S_CUR, K(t+1) on its way to this wave's half of kbuf0, then V(t) to its half of vbuf0.
   // A counted wait leaves exactly one tile copy in flight, the one issued since the fence in front of it (V(t) behind
-  // K(t+1); K(t+2) behind V(t)). The block-number load is not part of any count: it has no fixed place among the copies, so
-  // counting it would let a load of the awaited tile stay in flight wherever the compiler issued it earlier. It is issued
-  // after the wait for K(t+1) and is a whole tile of work old at the next wait, so requiring it there costs nothing.
-  // (The compiler cannot tell the copies into kbuf0 from those into vbuf0 and waits for V(t) as well in front of the K reads
-  // of a step, at head dim 128 of both steps, at 64 of the first: V's copy is covered by the other wave of the SIMD.)
+  // K(t+1); K(t+2) behind V(t)). The copies are issued so that the compiler does not count them: it cannot tell those into
+  // kbuf0 from those into vbuf0 and would wait for V(t) in front of the K reads of a step as well, half a step after it was
+  // asked for (32 heads of 2000 x 128, 32 x 32 blocks, half kept: 57.9 ->
+  // 55.9 us with the list read from registers; 32 heads of 7428 x 128, 32 x 128 blocks, 12 tiles a row: 183 -> 169).
   auto wait_copy = [&](bool all) {
     constexpr int kPer = TileDma<D, NT, false>::kPerWave;
     if (all) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -271,10 +279,9 @@ __global__ __launch_bounds__(RW * SG * 128)
   };
 #define SPARSED_PRIVATE_STEP(TAIL, T, S_CUR, S_NEXT)                                               \
   {                                                                                                \
-    const int valid = !(TAIL) ? 32 : valid_in((T), blk0);                                          \
+    const int valid = !(TAIL) ? 32 : valid_in(T);                                                \
     float part;                                                                                    \
     if (!(TAIL) || (T) + 1 < n_steps) wait_copy(false); /* K(t+1) */                                     \
-    const int blk_new = col_at((T) + 4);                                                           \
     if (!(TAIL) || (T) + 1 < n_steps) {                                                                  \
       logits_sub<D, 1, false>(kbuf0, kh, kaddr, qf, S_NEXT);                                       \
     }                                                                                              \
@@ -283,30 +290,26 @@ __global__ __launch_bounds__(RW * SG * 128)
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0, 0)) re_reference(S_CUR, part);  \
     lsum += part;                                                                                  \
     reads_done();                                                                                  \
-    if (!(TAIL)) kdma.issue(krsrc, __builtin_amdgcn_readfirstlane(blk2) * k_tile_bytes, kbuf0, wave);     \
-    else if ((T) + 2 < n_steps) copy_k(blk2, kbuf0);                                                     \
+    if (!(TAIL)) copy_whole_k(blk_at((T) + 2), kbuf0);                                             \
+    else if ((T) + 2 < n_steps) copy_k(blk_at((T) + 2), kbuf0);                                                     \
     wait_copy((TAIL) && (T) + 2 >= n_steps); /* V(t) */                                                  \
     pv_sub<D, 1, true>(vbuf0, kh, vaddr, p, o);                                                    \
     reads_done();                                                                                  \
-    if (!(TAIL)) vdma.issue(vrsrc, __builtin_amdgcn_readfirstlane(blk1) * v_tile_bytes, vbuf0, wave);     \
-    else if ((T) + 1 < n_steps) copy_v(blk1, vbuf0);                                                     \
-    blk0 = blk1;                                                                                   \
-    blk1 = blk2;                                                                                   \
-    blk2 = blk3;                                                                                   \
-    blk3 = blk_new;                                                                                \
+    if (!(TAIL)) copy_whole_v(blk_at((T) + 1), vbuf0);                                             \
+    else if ((T) + 1 < n_steps) copy_v(blk_at((T) + 1), vbuf0);                                                     \
   }
 
   if constexpr (PRIVATE) if (n_steps > 0) {
-    copy_k(blk0, kbuf0);
+    copy_k(blk_at(0), kbuf0);
     qf.load(qbase, row0, L, a.q.sl, lane);
     wait_vector_memory();
     logits_sub<D, 1, true>(kbuf0, kh, kaddr, qf, s_a);
     reads_done();
-    if (n_steps > 1) copy_k(blk1, kbuf0);
-    copy_v(blk0, vbuf0);
+    if (n_steps > 1) copy_k(blk_at(1), kbuf0);
+    copy_v(blk_at(0), vbuf0);
     {
       f32x16 first[1] = {s_a[0]};  // the first tile fixes the reference, as below
-      mask_half(first, valid_in(0, blk0));
+      mask_half(first, valid_in(0));
       M = fmaxf(row_max(first), -1e30f);
     }
     int t = 0;
@@ -315,11 +318,13 @@ __global__ __launch_bounds__(RW * SG * 128)
     // a wait has exactly one of them behind it
     const int reach = 3 + ((tail_keys < unit || (tile_shift && !(last_blk & 1))) ? 1 + tile_shift : 0);
     while (t + reach < n_steps) {
+      reach_list(t, t + 3);
       SPARSED_PRIVATE_STEP(false, t, s_a, s_b);
       SPARSED_PRIVATE_STEP(false, t + 1, s_b, s_a);
       t += 2;
     }
     for (; t < n_steps; ++t) {
+      reach_list(t, t + 2);
       if (t & 1) {
         SPARSED_PRIVATE_STEP(true, t, s_b, s_a);
       } else {
@@ -330,9 +335,9 @@ __global__ __launch_bounds__(RW * SG * 128)
 #undef SPARSED_PRIVATE_STEP
 
   if constexpr (!PRIVATE) if (n > 0) {
-    copy_k(blk0, kbuf0);
-    if (n_steps > 1) copy_k(blk1, kbuf1);
-    copy_v(blk0, vbuf0);
+    copy_k(blk_at(0), kbuf0);
+    if (n_steps > 1) copy_k(blk_at(1), kbuf1);
+    copy_v(blk_at(0), vbuf0);
     qf.load(qbase, row0, L, a.q.sl, lane);
     __syncthreads();
     logits_sub<D, 1, true>(kbuf0, kh, kaddr, qf, s_a);
@@ -340,17 +345,19 @@ __global__ __launch_bounds__(RW * SG * 128)
       // The first tile fixes the reference: the maximum over the keys of this wave's half that exist. A half
       // with no such key (a short first block) starts from a floor that the first real key re-references.
       f32x16 first[1] = {s_a[0]};
-      mask_half(first, valid_in(0, blk0));
+      mask_half(first, valid_in(0));
       M = fmaxf(row_max(first), -1e30f);
     }
     __syncthreads();  // everyone is done with K(0) before step 0 lets K(2) overwrite it
 
     int t = 0;
     while (t + 2 < n_steps) {
+      reach_list(t, t + 3);
       SPARSED_SPLITK_STEP(0, false, false, t, s_a, s_b);
       SPARSED_SPLITK_STEP(1, false, false, t + 1, s_b, s_a);
       t += 2;
     }
+    reach_list(t, t + 2);
     if (n_steps - t == 2) {  // with 128-key blocks the last two tiles may both be short (a partial last block)
       SPARSED_SPLITK_STEP(0, (tile_shift != 0), true, t, s_a, s_b);
       SPARSED_SPLITK_STEP(1, true, true, t + 1, s_b, s_a);

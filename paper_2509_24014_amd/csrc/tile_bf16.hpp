@@ -171,6 +171,33 @@ struct VLayout {
 // Permutation of the K rows fed to the first product: swap bits 2 and 3.
 __device__ __forceinline__ int krow_perm(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
 
+// The same descriptor as make_rsrc's (below) as four words. Copies through it are written out, so that the compiler does not
+// know that they are in flight and what they write: the caller waits for them itself before any read of the tile, and for
+// its reads before it asks for another. They return nothing in registers, and what they need is read when they are
+// issued. A kernel uses one kind or the other: both set m0, and the compiler may keep a value there between its own.
+typedef u32x4 UntrackedRsrc;
+__device__ __forceinline__ UntrackedRsrc untracked_rsrc(const void* base, int64_t bytes) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  UntrackedRsrc r;
+  r[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+  r[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xffffu));
+  r[2] = bytes > 0x7fffffff ? 0x7fffffffu : (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
+  r[3] = 0x00020000u;
+  return r;
+}
+
+// 16 bytes a lane, global -> LDS: lane i of the wave deposits its bytes at dst + 16 i.
+__device__ __forceinline__ void lds_load_16(__amdgpu_buffer_rsrc_t rsrc, char* dst, int32_t lane_offset, int32_t offset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (SPARSED_LDS void*)dst, 16, lane_offset, offset, 0, 0);
+}
+__device__ __forceinline__ void lds_load_16(const UntrackedRsrc& rsrc, char* dst, int32_t lane_offset, int32_t offset) {
+  const uint32_t at = (uint32_t)(uintptr_t)(SPARSED_LDS char*)dst;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(lane_offset), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(offset))
+               : "memory");
+}
+
 // Direct global -> LDS copy of one [64][D] bf16 tile by NT threads (NT/64 waves). Per-lane byte
 // offsets into the global tile are precomputed once (they depend on the row stride and the lane
 // only); per tile a wave issues kPerWave 16-byte-per-lane loads, each filling one KB of LDS.
@@ -217,7 +244,8 @@ struct TileDma {
   // Same copy for a tile of which only the first `rows` rows exist (the last key block of a sequence
   // whose length is not a multiple of the tile): the missing rows are fetched from the last row
   // that exists, so every address stays inside the tensor; their logits are masked by the caller.
-  __device__ __forceinline__ void issue_partial(__amdgpu_buffer_rsrc_t rsrc, int32_t tile_byte_offset, char* lds_tile,
+  template <typename Rsrc>
+  __device__ __forceinline__ void issue_partial(Rsrc rsrc, int32_t tile_byte_offset, char* lds_tile,
                                                 int wave_in_group, int lane, int64_t stride_l, int rows) const {
     // Worked out afresh at every call on purpose (the lane number is made opaque): these few integer
     // operations run a handful of times per work-group, whereas per-lane offsets hoisted out of the
@@ -231,7 +259,7 @@ struct TileDma {
       source_of(wl, lane, &row, &chunk);
       if (row >= rows) row = rows - 1;
       char* dst = lds_tile + lds_piece_offset(wl);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (SPARSED_LDS void*)dst, 16, row * row_bytes + chunk * 16, tile_byte_offset, 0, 0);
+      lds_load_16(rsrc, dst, row * row_bytes + chunk * 16, tile_byte_offset);
     }
   }
   // 32-key blocks: a tile is put together from two independent 32-row halves. With at least two waves
@@ -247,7 +275,8 @@ struct TileDma {
     }
   }
   // the same for a 32-key block of which only the first `rows` rows exist (the last block of a sequence)
-  __device__ __forceinline__ void issue_partial_half(__amdgpu_buffer_rsrc_t rsrc, int32_t block_byte_offset, char* lds_tile,
+  template <typename Rsrc>
+  __device__ __forceinline__ void issue_partial_half(Rsrc rsrc, int32_t block_byte_offset, char* lds_tile,
                                                      int wave_in_group, int lane, int64_t stride_l, int rows) const {
     asm volatile("" : "+v"(lane));  // worked out afresh at every call, as in issue_partial
     const int32_t row_bytes = (int32_t)(stride_l * 2);
@@ -259,20 +288,21 @@ struct TileDma {
       row &= 31;  // row within the half
       if (row >= rows) row = rows - 1;
       char* dst = lds_tile + lds_piece_offset(wl);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (SPARSED_LDS void*)dst, 16, row * row_bytes + chunk * 16, block_byte_offset, 0, 0);
+      lds_load_16(rsrc, dst, row * row_bytes + chunk * 16, block_byte_offset);
     }
   }
   // rsrc: buffer descriptor of the (batch, head) slab; tile_byte_offset: wave-uniform byte offset of
   // the tile's first row in it; lds_tile: LDS address of the tile. The buffer form of the direct
   // load is used because the compiler accounts for it on the vector-memory counter only; the
   // global_load form makes it wait for ALL outstanding LDS reads at every later use of one.
-  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rsrc, int32_t tile_byte_offset, char* lds_tile,
+  template <typename Rsrc>
+  __device__ __forceinline__ void issue(Rsrc rsrc, int32_t tile_byte_offset, char* lds_tile,
                                         int wave_in_group) const {
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) {
       char* dst = lds_tile + lds_piece_offset(wave_in_group * kPerWave + u);
-      if (kUniformStep) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (SPARSED_LDS void*)dst, 16, goff[0], tile_byte_offset + u * step, 0, 0);
-      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (SPARSED_LDS void*)dst, 16, goff[u], tile_byte_offset, 0, 0);
+      if (kUniformStep) lds_load_16(rsrc, dst, goff[0], tile_byte_offset + u * step);
+      else lds_load_16(rsrc, dst, goff[u], tile_byte_offset);
     }
   }
 };
