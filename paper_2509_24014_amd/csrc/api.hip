@@ -381,20 +381,24 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
     return fail(SPARSED_ERR_INDEX, "cap_per_head %d < nqb*k = %lld", ix->cap_per_head, (long long)nqb * keep);
 
   char* ws = nullptr;
-  if (q->dtype != SPARSED_BF16) {
+  const bool bf16 = q->dtype == SPARSED_BF16;
+  const size_t statistics_bytes = align256((size_t)q->B * q->H * q->L * sizeof(float));
+  if (!bf16) {
     if ((st = caller_workspace(ex, select_ws_bytes(q->B, q->H, q->L, nqb, nkb), "dense step with selection", &ws))) return st;
-    sparsed_exec step = *ex;
-    if (!step.lse_out) step.lse_out = reinterpret_cast<float*>(ws);  // where the selection would put its own statistics
-    step.lse_in = step.lse_out;
-    if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step))) return st;
-    return select_impl(q, k, bq, bk, rho, 0, false, ix, &step);
+    if (!dense_pool_pays_f32(q->D, (int64_t)q->B * q->H, q->L, bq, bk)) {
+      sparsed_exec step = *ex;
+      if (!step.lse_out) step.lse_out = reinterpret_cast<float*>(ws);  // where the selection would put its own statistics
+      step.lse_in = step.lse_out;
+      if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step))) return st;
+      return select_impl(q, k, bq, bk, rho, 0, false, ix, &step);
+    }
   }
   const size_t apool_bytes = align256((size_t)q->B * q->H * nqb * nkb * sizeof(float));
   auto bytes_of = [&](const DensePoolShape& sh) { return apool_bytes + (size_t)sh.groups * sh.rows * sh.slab_cols * sizeof(float); };
   DensePoolShape sh = dense_pool_shape(q->D, q->B, q->H, q->L, bk, 256);
   if (ex && ex->workspace && ex->workspace_bytes < bytes_of(sh)) sh = dense_pool_shape(q->D, q->B, q->H, q->L, bk, 128);
-  if ((st = caller_workspace(ex, bytes_of(sh), "dense step with selection", &ws))) return st;
-  if (dense_then_pool(q) && ex->workspace_bytes >= select_ws_bytes(q->B, q->H, q->L, nqb, nkb)) {
+  if (bf16 && (st = caller_workspace(ex, bytes_of(sh), "dense step with selection", &ws))) return st;
+  if (bf16 && dense_then_pool(q) && ex->workspace_bytes >= select_ws_bytes(q->B, q->H, q->L, nqb, nkb)) {
     sparsed_exec step = *ex;
     if (!step.lse_out) step.lse_out = reinterpret_cast<float*>(ws);
     step.lse_in = step.lse_out;
@@ -420,9 +424,9 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
   a.nkb = nkb;
   a.block_q = bq;
   a.block_k = bk;
-  a.apool = ex->pooled_out ? ex->pooled_out : reinterpret_cast<float*>(ws);
-  a.slab = reinterpret_cast<float*>(ws + apool_bytes);
-  hipError_t e = launch_attn_bf16_dense_pool(q->D, a, sh, stream_of(ex));
+  a.apool = ex->pooled_out ? ex->pooled_out : reinterpret_cast<float*>(ws + (bf16 ? 0 : statistics_bytes));
+  if (bf16) a.slab = reinterpret_cast<float*>(ws + apool_bytes);
+  hipError_t e = bf16 ? launch_attn_bf16_dense_pool(q->D, a, sh, stream_of(ex)) : launch_attn_f32_dense_pool(q->D, a, stream_of(ex));
   if (e != hipSuccess) return hip_fail(e, "dense attention with pooling launch");
   TopkArgs t{};
   t.apool = a.apool;

@@ -22,25 +22,47 @@
 
 namespace sparsed {
 
-template <int D, int KW, Mode MODE, bool SPLIT_FIRST>
-__global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnArgs a) {
-  constexpr int NT = KW * 64;
+// Pooling (kDensePool). The step at which the pattern is selected needs A'[I, J], the mean of the probabilities over query block
+// I and key block J, beside the attention output, and the tile loop already forms the sums of a row's probabilities. A
+// work-group is then a query block, RW = block_q / 32 row groups times KW = 8 / RW key groups; a wave takes whole key
+// blocks and parks, per row and block, the sum and the reference it is relative to in LDS. When the rows are complete, the
+// parts' references and sums are known to all, and the work-group weighs and adds up its parked sums. Against the dense call
+// and a pooling kernel that computes every logit again (short fp32 schedules, switch step and top-k): 8 heads of 2000 x 128,
+// 64 x 64 blocks 174 -> 121 us; 2 of 256 x 64, 32 x 32 blocks 18.1 -> 13.3 us.
+template <int D, int RW>
+struct PoolLdsF32 {
+  static constexpr int kBytes = 157 * 1024;  // a compute unit's, less the statistics
+  static constexpr int kUsed = RW * (D / 16) * 3 * 64 * 16 + (D == 64 ? 8 * KTileF32<D>::kBytes : 0);  // queries, K tiles
+  static constexpr int kBlocks = (kBytes - kUsed) / (RW * 32 * 8);                                       // key blocks that can be parked
+};
+
+template <int D, int KW, Mode MODE, bool SPLIT_FIRST, int RW = 1>
+__global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnArgs a) {
+  constexpr bool kPool = MODE == Mode::kDensePool;
+  static_assert(RW == 1 || kPool, "several row groups: only where a work-group is a query block");
+  constexpr int NW = RW * KW, NT = NW * 64;
   constexpr bool kHasV = MODE != Mode::kStats;
   constexpr int kChunks = D / 8, kSteps = D / 16, kV = D / 32;
   using VRow = typename SlabF32<D>::VRow;
   // K through LDS (tile_f32.hpp), or straight into registers as V. Through LDS at head dim 64, where two waves per SIMD find
-  // room for their tiles beside another work-group's (2 heads of 256, dense: 10.2 us straight, 9.3 through LDS); at 128 a work-group of eight waves would fill the LDS, and
-  // nothing is left to run while it begins and ends (8 heads of 2000, dense: 115 us, straight 110).
+  // room for their tiles beside another work-group's (2 heads of 256, dense: 10.2 us straight, 9.3 through LDS); at 128 a
+  // work-group of eight waves would fill the LDS, and nothing is left to run while it begins and ends (8 heads of 2000, dense:
+  // 115 us, straight 110).
   constexpr bool KLDS = SPLIT_FIRST && D == 64;
-  // The query fragments ([step][part][lane], 16 bytes each), the waves' K tiles and, once the keys are done, the waves'
-  // accumulators ([wave][row][32 pieces of D/32 columns], piece i of row j at position i ^ j so that neither side has bank
-  // conflicts).
-  constexpr int kQBytes = SPLIT_FIRST ? kSteps * 3 * 64 * 16 : kChunks * 64 * 16, kKBytes = KLDS ? KW * KTileF32<D>::kBytes : 0, kAccBytes = kHasV ? KW * 32 * D * 4 : 16;
-  __shared__ __attribute__((aligned(1024))) char lds[kQBytes + kKBytes > kAccBytes ? kQBytes + kKBytes : kAccBytes];
-  __shared__ float stat_m[KW][32], stat_l[KW][32];
+  // The query fragments ([row group][step][part][lane], 16 bytes each), the waves' K tiles, the parked sums ([block][row], sum
+  // and reference) and, once the keys are done, the waves' accumulators ([wave][row][32 pieces of D/32 columns], piece i of
+  // row j at position i ^ j so that neither side has bank conflicts).
+  constexpr int kQBytes = SPLIT_FIRST ? kSteps * 3 * 64 * 16 : kChunks * 64 * 16;  // of a row group
+  constexpr int kKBytes = KLDS ? NW * KTileF32<D>::kBytes : 0, kAccBytes = kHasV ? NW * 32 * D * 4 : 16;
+  constexpr int kTileBytes = RW * kQBytes + kKBytes > kAccBytes ? RW * kQBytes + kKBytes : kAccBytes;
+  __shared__ __attribute__((aligned(1024))) char lds[kPool ? PoolLdsF32<D, RW>::kBytes : kTileBytes];
+  static_assert(!kPool || (kTileBytes <= PoolLdsF32<D, RW>::kBytes && RW * kQBytes + kKBytes == PoolLdsF32<D, RW>::kUsed), "layout");
+  f32x2f* const parked = reinterpret_cast<f32x2f*>(lds + (kPool ? PoolLdsF32<D, RW>::kUsed : 0));
+  __shared__ float stat_m[NW][32], stat_l[NW][32];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = RW == 1 ? 0 : wave % RW, kw = RW == 1 ? wave : wave / RW;  // row group and key group of this wave
   const int j = lane & 31, g = lane >> 5;
 
   const int lid = xcd_remap_f(blockIdx.x, gridDim.x);
@@ -52,15 +74,15 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int len = a.seq_lens[b];
     L = len < a.L ? len : a.L;
   }
-  const int row0 = qt * 32;
-  if (row0 >= L) return;  // a query tile wholly past the end (uniform over the work-group)
+  const int wg_row0 = qt * (32 * RW), row0 = wg_row0 + rw * 32;
+  if (wg_row0 >= L) return;  // a query tile wholly past the end (uniform over the work-group)
 
   SlabF32<D> ks, vs;
   ks.init(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh, a.k.sl, L);
   if (kHasV) vs.init(static_cast<const float*>(a.v.ptr) + b * a.v.sb + hk * a.v.sh, a.v.sl, L);
 
   // tiles of the list: every 32 keys (dense), or those of the listed key blocks
-  const int tile_shift = (MODE == Mode::kSparse) ? (a.block_k == 128 ? 2 : a.block_k == 64 ? 1 : 0) : 0;
+  const int tile_shift = (MODE == Mode::kSparse || kPool) ? (a.block_k == 128 ? 2 : a.block_k == 64 ? 1 : 0) : 0;
   int n;
   const int32_t* cols = nullptr;
   if (MODE == Mode::kSparse) {
@@ -73,7 +95,15 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
   int opaque_zero;  // keeps the list reads on the vector path: a scalar load would share its counter with the LDS reads
   asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
+  // kPool: a wave's tiles are those of the key blocks kw, kw + KW, ..., numbered kw, kw + KW, ... as if they were every KW-th
+  // tile; a partial last block counts as a whole one (its last tiles may hold no key)
+  const int nkb = kPool ? (n + (1 << tile_shift) - 1) >> tile_shift : 0;
+  if (kPool) n = ((nkb - kw + KW - 1) / KW << tile_shift) * KW;  // (no tile: at most zero)
   auto first_key = [&](int t) -> int {  // of tile t of the list; past the end: of the last one (a harmless repeat)
+    if (kPool) {
+      const int i = (t < n ? t : n - 1) / KW;  // this wave's i-th tile
+      return (((kw + (i >> tile_shift) * KW) << tile_shift) + (i & ((1 << tile_shift) - 1))) * kTileKF;
+    }
     const int u = t < n ? t : n - 1;
     if (MODE != Mode::kSparse) return u * kTileKF;
     return cols[(u >> tile_shift) + opaque_zero] * a.block_k + (u & ((1 << tile_shift) - 1)) * kTileKF;
@@ -84,6 +114,8 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const float c = a.scale_log2;
   const float* const qhead = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
 
+  char* const qlds = lds + rw * kQBytes;
+
   // The wave's share of the tile list. SPLIT: on the bf16 matrix instruction; else on the fp32 one.
   auto walk = [&](auto split_tag) __attribute__((always_inline)) {
     constexpr bool SPLIT = decltype(split_tag)::value;
@@ -92,17 +124,17 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       const int row = row0 + j < L ? row0 + j : L - 1;
       const float* qrow = qhead + (int64_t)row * a.q.sl + 4 * g;
       if constexpr (SPLIT) {
-        for (int s2 = wave; s2 < kSteps; s2 += KW) {
+        for (int s2 = kw; s2 < kSteps; s2 += KW) {
           const f32x4 lo = *reinterpret_cast<const f32x4*>(qrow + 16 * s2), hi = *reinterpret_cast<const f32x4*>(qrow + 16 * s2 + 8);
           const Split8 w = split8(lo, hi);
-          u32x4f* const dst = reinterpret_cast<u32x4f*>(lds) + s2 * 3 * 64 + lane;
+          u32x4f* const dst = reinterpret_cast<u32x4f*>(qlds) + s2 * 3 * 64 + lane;
           dst[0] = w.h;
           dst[64] = w.m;
           dst[128] = w.l;
         }
       } else {
-        for (int ch = wave; ch < kChunks; ch += KW)
-          *reinterpret_cast<f32x4*>(lds + (ch * 64 + lane) * 16) = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
+        for (int ch = kw; ch < kChunks; ch += KW)
+          *reinterpret_cast<f32x4*>(qlds + (ch * 64 + lane) * 16) = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
       }
     }
     M = -1e30f;
@@ -112,11 +144,12 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int x = 0; x < 16; ++x) o[dt][x] = 0.f;
     constexpr bool VIA_LDS = SPLIT && KLDS;
-    char* const ktile = lds + (VIA_LDS ? kQBytes + wave * KTileF32<D>::kBytes : 0);
+    char* const ktile = lds + (VIA_LDS ? RW * kQBytes + wave * KTileF32<D>::kBytes : 0);
+    float block_sum = 0.f;  // kPool: this lane's share of the key block in progress
     f32x4 kf[VIA_LDS ? 1 : kChunks];
     VRow vf[16];
 
-    int t = wave, key = 0, key_next = 0;
+    int t = kw, key = 0, key_next = 0;
     if (t < n) {
       key = __builtin_amdgcn_readfirstlane(first_key(t));
       key_next = __builtin_amdgcn_readfirstlane(first_key(t + KW));
@@ -156,7 +189,7 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
             kf[2 * s2] = ks.k_chunk(off_next, 2 * s2);
             kf[2 * s2 + 1] = ks.k_chunk(off_next, 2 * s2 + 1);
           }
-          const u32x4f* const src = reinterpret_cast<const u32x4f*>(lds) + s2 * 3 * 64 + lane;
+          const u32x4f* const src = reinterpret_cast<const u32x4f*>(qlds) + s2 * 3 * 64 + lane;
           const Split8 qw = {src[0], src[64], src[128]};
           Split8 next;
           if (s2 + 1 < kSteps) next = split8(lo, hi);
@@ -178,7 +211,7 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       } else {
 #pragma unroll
         for (int ch = 0; ch < kChunks; ++ch) {
-          const f32x4 qf = *reinterpret_cast<const f32x4*>(lds + (ch * 64 + lane) * 16);
+          const f32x4 qf = *reinterpret_cast<const f32x4*>(qlds + (ch * 64 + lane) * 16);
 #pragma unroll
           for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ch][e], qf[e], s, 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
@@ -204,6 +237,7 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const float alpha = __builtin_amdgcn_exp2f(M - Mn);
         M = Mn;
         lsum *= alpha;
+        if (kPool) block_sum *= alpha;
         if (kHasV) {
 #pragma unroll
           for (int dt = 0; dt < kV; ++dt)
@@ -218,6 +252,16 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         part += s[x];
       }
       lsum += part;
+      if (kPool) {
+        block_sum += part;
+        const int i = t / KW;
+        if (((i + 1) & ((1 << tile_shift) - 1)) == 0) {  // the last tile of its block
+          const float e = pair_sum_f(block_sum);
+          const f32x2f v = {e, M};
+          if (g == 0) parked[(kw + (i >> tile_shift) * KW) * (RW * 32) + rw * 32 + j] = v;
+          block_sum = 0.f;
+        }
+      }
       if (kHasV) {
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (SPLIT) {
@@ -279,10 +323,54 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
   // Merge the waves' parts: O = sum_w O_w 2^(M_w - M) / sum_w l_w 2^(M_w - M), M = max_w M_w.
   const float ltot = pair_sum_f(lsum);
+  auto factors = [&](int group, int row, float (&f)[KW], float* m) -> float {  // every part's factor and the common maximum; returns l
+    float mm = stat_m[group][row], l = 0.f;
+#pragma unroll
+    for (int w = 1; w < KW; ++w) mm = fmaxf(mm, stat_m[w * RW + group][row]);
+#pragma unroll
+    for (int w = 0; w < KW; ++w) {
+      f[w] = exp2f(stat_m[w * RW + group][row] - mm);
+      l += stat_l[w * RW + group][row] * f[w];
+    }
+    *m = mm;
+    return l;
+  };
   __syncthreads();  // everyone is done with the query fragments
   if (g == 0) {
     stat_m[wave][j] = M;
     stat_l[wave][j] = ltot;
+  }
+  if constexpr (kPool) {
+    // A'[I, J] = sum over the rows of E 2^(M_parked - M) / l, divided by the entries that exist. A wave takes a key block (two
+    // with 32 rows) at a time, a lane one row of it, or two; the lanes are added up in a fixed order.
+    __syncthreads();
+    constexpr int kRowsPerLane = RW == 4 ? 2 : 1;
+    float ref[kRowsPerLane], weight[kRowsPerLane];
+    int at[kRowsPerLane];
+#pragma unroll
+    for (int u = 0; u < kRowsPerLane; ++u) {
+      at[u] = RW == 1 ? j : lane + 64 * u;
+      float f[KW];
+      const float l = factors(at[u] >> 5, at[u] & 31, f, &ref[u]);
+      weight[u] = wg_row0 + at[u] < L ? 1.0f / l : 0.f;
+    }
+    const int rows_here = L - wg_row0 < 32 * RW ? L - wg_row0 : 32 * RW;
+    float* const arow = a.apool + ((int64_t)bh * a.nqb + qt) * a.nkb;
+    constexpr int kAtOnce = RW == 1 ? 2 : 1;
+    for (int J0 = wave * kAtOnce; J0 < nkb; J0 += NW * kAtOnce) {
+      const int J = J0 + (RW == 1 ? g : 0);
+      float x = 0.f;
+#pragma unroll
+      for (int u = 0; u < kRowsPerLane; ++u) {
+        const f32x2f v = parked[(J < nkb ? J : nkb - 1) * (RW * 32) + at[u]];
+        x += v[0] * exp2f(v[1] - ref[u]) * weight[u];
+      }
+#pragma unroll
+      for (int d = RW == 1 ? 16 : 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+      const int keys_here = L - J * a.block_k < a.block_k ? L - J * a.block_k : a.block_k;
+      if ((RW == 1 ? j : lane) == 0 && J < nkb) arow[J] = x * (1.0f / (float)(rows_here * keys_here));
+    }
+    __syncthreads();  // the accumulators may take the parked sums' place
   }
   if (kHasV) {
 #pragma unroll
@@ -295,42 +383,30 @@ __global__ __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
   }
   __syncthreads();
-  auto factors = [&](int row, float (&f)[KW], float* m) -> float {  // every wave's factor and the common maximum; returns l
-    float mm = stat_m[0][row], l = 0.f;
-#pragma unroll
-    for (int w = 1; w < KW; ++w) mm = fmaxf(mm, stat_m[w][row]);
-#pragma unroll
-    for (int w = 0; w < KW; ++w) {
-      f[w] = exp2f(stat_m[w][row] - mm);
-      l += stat_l[w][row] * f[w];
-    }
-    *m = mm;
-    return l;
-  };
-  if (a.lse != nullptr && tid < 32 && row0 + tid < L) {
+  if (a.lse != nullptr && tid < 32 * RW && wg_row0 + tid < L) {
     float f[KW], m;
-    const float l = factors(tid, f, &m);
-    a.lse[(int64_t)bh * a.L + row0 + tid] = (m + log2f(l)) * 0.6931471805599453f;
+    const float l = factors(tid >> 5, tid & 31, f, &m);
+    a.lse[(int64_t)bh * a.L + wg_row0 + tid] = (m + log2f(l)) * 0.6931471805599453f;
   }
   if (kHasV) {
-    for (int id = tid; id < 32 * 32; id += NT) {
-      const int row = id >> 5, piece = id & 31;
-      if (row0 + row >= L) break;  // partial last query tile (rows ascend with id)
+    for (int id = tid; id < RW * 32 * 32; id += NT) {
+      const int group = id >> 10, row = (id >> 5) & 31, piece = id & 31;
+      if (wg_row0 + group * 32 + row >= L) break;  // partial last query tile (rows ascend with id)
       float f[KW], m;
-      const float l = factors(row, f, &m);
+      const float l = factors(group, row, f, &m);
       const float inv = l > 0.f ? 1.0f / l : 0.f;
       VRow acc;
 #pragma unroll
       for (int dt = 0; dt < kV; ++dt) acc[dt] = 0.f;
 #pragma unroll
       for (int w = 0; w < KW; ++w) {
-        const VRow part = *reinterpret_cast<const VRow*>(lds + ((w * 32 + row) * 32 + (piece ^ row)) * sizeof(VRow));
+        const VRow part = *reinterpret_cast<const VRow*>(lds + (((w * RW + group) * 32 + row) * 32 + (piece ^ row)) * sizeof(VRow));
 #pragma unroll
         for (int dt = 0; dt < kV; ++dt) acc[dt] += part[dt] * f[w];
       }
 #pragma unroll
       for (int dt = 0; dt < kV; ++dt) acc[dt] *= inv;
-      float* orow = static_cast<float*>(a.o) + b * a.o_sb + h * a.o_sh + (int64_t)(row0 + row) * a.o_sl;
+      float* orow = static_cast<float*>(a.o) + b * a.o_sb + h * a.o_sh + (int64_t)(wg_row0 + group * 32 + row) * a.o_sl;
       *reinterpret_cast<VRow*>(orow + kV * piece) = acc;
     }
   }
@@ -374,6 +450,48 @@ static hipError_t launch_sparse_f32(const AttnArgs& a, hipStream_t s) {
                 four = busiest_simd(4 * groups) * (2 * ((tiles + 3) / 4) + 6);
   if (four <= one && four <= two) return launch_one_f32<D, 4, Mode::kSparse>(a, s);
   return two <= one ? launch_one_f32<D, 2, Mode::kSparse>(a, s) : launch_one_f32<D, 1, Mode::kSparse, false>(a, s);
+}
+
+template <int D, int RW>
+static hipError_t launch_pool_rw_f32(const AttnArgs& a, hipStream_t s) {
+  const int64_t total = (int64_t)a.B * a.Hq * a.n_qtiles;
+  if (total <= 0 || total > 0x7fffffff || a.nkb > PoolLdsF32<D, RW>::kBlocks) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((attn_f32_kernel<D, 8 / RW, Mode::kDensePool, true, RW>), dim3((unsigned)total), dim3(512), 0, s, a);
+  return hipGetLastError();
+}
+template <int D>
+static hipError_t launch_pool_d_f32(const AttnArgs& a, hipStream_t s) {
+  switch (a.block_q) {
+    case 32: return launch_pool_rw_f32<D, 1>(a, s);
+    case 64: return launch_pool_rw_f32<D, 2>(a, s);
+    case 128: return launch_pool_rw_f32<D, 4>(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+hipError_t launch_attn_f32_dense_pool(int D, AttnArgs a, hipStream_t s) {
+  if (a.L <= 0 || !a.apool || (a.block_k != 32 && a.block_k != 64 && a.block_k != 128)) return hipErrorInvalidValue;
+  a.n_qtiles = a.nqb;  // a work-group is a query block
+  if (D == 128) return launch_pool_d_f32<128>(a, s);
+  if (D == 64) return launch_pool_d_f32<64>(a, s);
+  return hipErrorInvalidValue;
+}
+
+template <int D>
+static int parked_blocks_f32(int block_q) {
+  return block_q == 32 ? PoolLdsF32<D, 1>::kBlocks : block_q == 64 ? PoolLdsF32<D, 2>::kBlocks : PoolLdsF32<D, 4>::kBlocks;
+}
+// Whether the kernel above takes a call: its sums must fit the LDS, and its coarser work-groups must cost less than computing the
+// logits a second time. In tiles that a wave walks, times the rounds of the chip: FUSED here; DENSE in the dense call, whose
+// waves split a query tile's keys four or eight ways whatever block_q; a pooling kernel walks as many tiles as this one, in half the
+// time each. Of 152 calls (1 to 32 heads of 130 to 4000 tokens) none is slower for it by more than 1 %; where it is left, four
+// heads of 600 x 128, 128 x 64 blocks, 56.2 us so and 64.3 in one kernel (10 tiles here, 3 there).
+bool dense_pool_pays_f32(int D, int64_t heads, int L, int block_q, int block_k) {
+  const int nkb = (L + block_k - 1) / block_k, rw = block_q / 32, kw = 8 / rw;
+  if (nkb > (D == 128 ? parked_blocks_f32<128>(block_q) : parked_blocks_f32<64>(block_q))) return false;
+  const int64_t tiles = (L + 31) / 32, groups = heads * ((L + block_q - 1) / block_q), dense_groups = heads * tiles;
+  const int64_t fused = (int64_t)((nkb + kw - 1) / kw) * (block_k / 32) * ((groups + 255) / 256);
+  const int64_t dense = dense_groups <= 256 ? (tiles + 7) / 8 : (tiles + 3) / 4 * ((dense_groups + 511) / 512);
+  return fused <= 2 * dense + 1;
 }
 
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {

@@ -141,6 +141,10 @@ struct DensePoolShape {
 };
 DensePoolShape dense_pool_shape(int D, int B, int Hq, int L, int block_k, int max_rows);  // max_rows: 256 or 128
 hipError_t launch_attn_bf16_dense_pool(int D, AttnArgs a, const DensePoolShape& sh, hipStream_t s);
+// The same for fp32 (a.apool, a.nqb, a.nkb, a.block_q, a.block_k set by the caller; no scratch), and whether it is the form for
+// a call with heads = B * Hq (else: the dense call with its log-sum-exp, then pooling with it).
+hipError_t launch_attn_f32_dense_pool(int D, AttnArgs a, hipStream_t s);
+bool dense_pool_pays_f32(int D, int64_t heads, int L, int block_q, int block_k);
 hipError_t launch_pool_bf16(int D, int block_q, const PoolArgs& a, hipStream_t s);
 hipError_t launch_pool_f32(int D, int block_q, const PoolArgs& a, hipStream_t s);
 // Pooled scores of bf16 inputs in one pass over the keys (no row statistics needed): `groups` persistent work-groups,

@@ -63,8 +63,8 @@ class SparseDLayer:
             self._select(q, k, None)  # no dense call at this step: selection runs its own statistics pass
         if t < self.n_dense:
             switch = t == self.n_dense - 1
-            if switch and q.is_cuda and q.dtype == torch.bfloat16 and self._scratch_holds_one_call(q):
-                # bf16: the dense kernel leaves the pooled scores the selection ranks, one Q K^T for both
+            if switch and q.is_cuda and self._scratch_holds_one_call(q):
+                # one call for both, so that the dense kernel can leave the pooled scores the selection ranks
                 out, self.index = binding.attn_dense_select(q, k, v, self.block_q, self.block_k, self.rho, out=out,
                                                             workspace=self._scratch(q), index=self.index)
                 self.calls["dense"] += 1
