@@ -254,6 +254,15 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   p.out_stride = nkb;
   p.scale_log2 = scale_log2(q->D);
   hipError_t e = hipSuccess;
+  const size_t rows = (size_t)q->B * q->H * nqb;
+  float* part = nullptr;  // per row the score of the boundary block's prefill keys and that of its generation keys
+  int32_t *rows_tmp = nullptr, *counts = nullptr;
+  if (straddle >= 0) {
+    char* extra = ws + base_bytes;
+    part = reinterpret_cast<float*>(extra);
+    rows_tmp = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)));
+    counts = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)) + align256(rows * (size_t)(nkb + 1) * sizeof(int32_t)));
+  }
   const size_t rows_total = (size_t)pool1p_units(q->B, q->H, nqb, bq);  // units of the one-pass kernel: 128 rows of a head each
   // How many one-pass slabs the scratch behind `need` has room for.
   const size_t ws_bytes = fixed_scratch ? fixed_scratch_bytes : ex->workspace_bytes;
@@ -263,15 +272,13 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   if (slabs > rows_total) slabs = rows_total;
   const size_t slabs_needed = rows_total < (size_t)kOnepassMinGroups ? rows_total : (size_t)kOnepassMinGroups;
   if (!lse && bf16 && slabs >= slabs_needed) {
-    // 1 + 2. no log-sum-exp handed over: pooled scores A' (and the row log-sum-exp) in one pass over the keys
+    // 1 + 2. no log-sum-exp handed over: pooled scores A' (those of the two parts of the boundary block too) in one pass
     p.slab = reinterpret_cast<float*>(ws + need);
     p.slab_ld = onepass_slab_ld(nkb);
-    p.lse_out = lse_buf;
+    p.part = part;
+    p.boundary = boundary_token;
     e = launch_pool1p_bf16(q->D, bq, p, (int)slabs, s);
     if (e != hipSuccess) return hip_fail(e, "one-pass pooled-score launch");
-    lse = lse_buf;
-    p.slab = nullptr;
-    p.lse_out = nullptr;
   } else {
     // 1. row log-sum-exp of Eq. 1's logits, unless the caller passes the one attn_dense produced
     if (!lse) {
@@ -293,26 +300,18 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
     p.lse = lse;
     e = bf16 ? launch_pool_bf16(q->D, bq, p, s) : launch_pool_f32(q->D, bq, p, s);
     if (e != hipSuccess) return hip_fail(e, "pooled-score launch");
-  }
-  p.lse = lse;
-  const size_t rows = (size_t)q->B * q->H * nqb;
-  float* part = nullptr;
-  int32_t *rows_tmp = nullptr, *counts = nullptr;
-  if (straddle >= 0) {
-    // the block that holds the boundary once more, pooled over its prefill keys and over its generation keys
-    char* extra = ws + base_bytes;
-    part = reinterpret_cast<float*>(extra);
-    rows_tmp = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)));
-    counts = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)) + align256(rows * (size_t)(nkb + 1) * sizeof(int32_t)));
-    const int block_end = (straddle + 1) * bk < q->L ? (straddle + 1) * bk : q->L;
-    PoolArgs pa = p;
-    pa.apool = part;
-    pa.out_stride = 2;
-    pa.key_begin = straddle * bk;
-    pa.key_len = boundary_token - straddle * bk;
-    pa.key_len2 = block_end - boundary_token;  // both parts in one launch (each is a tile or two: 6.4 us of latency apiece)
-    e = bf16 ? launch_pool_bf16(q->D, bq, pa, s) : launch_pool_f32(q->D, bq, pa, s);
-    if (e != hipSuccess) return hip_fail(e, "pooled-score launch (the two parts of the boundary block)");
+    if (straddle >= 0) {
+      // the block that holds the boundary once more, pooled over its prefill keys and over its generation keys
+      const int block_end = (straddle + 1) * bk < q->L ? (straddle + 1) * bk : q->L;
+      PoolArgs pa = p;
+      pa.apool = part;
+      pa.out_stride = 2;
+      pa.key_begin = straddle * bk;
+      pa.key_len = boundary_token - straddle * bk;
+      pa.key_len2 = block_end - boundary_token;  // both parts in one launch (each is a tile or two: 6.4 us of latency apiece)
+      e = bf16 ? launch_pool_bf16(q->D, bq, pa, s) : launch_pool_f32(q->D, bq, pa, s);
+      if (e != hipSuccess) return hip_fail(e, "pooled-score launch (the two parts of the boundary block)");
+    }
   }
   // 3. per-row top-k into the CSR index
   TopkArgs t{};

@@ -51,7 +51,8 @@ struct PoolArgs {
   // one-pass form only (pool1p_bf16_kernel; whole key range, lse unused):
   float* slab;             // scratch, one slab of 128 x slab_ld floats per work-group of the launch
   int32_t slab_ld;         // columns of a slab: the key-block count rounded up to a multiple of 16
-  float* lse_out;          // optional [B, Hq, L]: receives the row log-sum-exp
+  float* part;             // optional [B, Hq, nqb, 2]: the key block that holds the key token `boundary`, pooled over its keys
+  int32_t boundary;        // before that token and over the others (rows of samples that end before the token: not written)
 };
 
 // Arguments of the per-row top-k kernel (Eq. 6): one wavefront per pooled row.
