@@ -260,7 +260,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   if (straddle >= 0) {
     char* extra = ws + base_bytes;
     part = reinterpret_cast<float*>(extra);
-    rows_tmp = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)));
+    if (!places_rows_itself(nqb, nkb)) rows_tmp = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)));
     counts = reinterpret_cast<int32_t*>(extra + align256(rows * 2 * sizeof(float)) + align256(rows * (size_t)(nkb + 1) * sizeof(int32_t)));
   }
   const size_t rows_total = (size_t)pool1p_units(q->B, q->H, nqb, bq);  // units of the one-pass kernel: 128 rows of a head each
@@ -338,7 +338,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   t.counts = counts;
   e = launch_topk(t, s);
   if (e != hipSuccess) return hip_fail(e, "top-k launch");
-  if (straddle >= 0) {
+  if (rows_tmp != nullptr) {
     // rows differ in length (the boundary block may be kept by both ranges): build the CSR from the fixed-stride rows
     CompactArgs c{rows_tmp, counts, ix->row_ptr, ix->col_idx, q->B * q->H, nqb, keep, ix->cap_per_head};
     e = launch_compact(c, s);

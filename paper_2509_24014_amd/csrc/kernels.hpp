@@ -66,8 +66,8 @@ struct TopkArgs {
   int32_t cap_per_head;
   // Prefill boundary inside key block `straddle` (else straddle < 0): that block enters the first range
   // with score part[2r] (its prefill keys) and the second with part[2r+1] (its generation keys); it is
-  // listed once even if both keep it, so rows differ in length: entries go to rows_tmp [rows, keep_lo +
-  // keep_hi] and counts [rows], and compact_kernel builds the CSR from them.
+  // listed once even if both keep it, so rows differ in length. Without rows_tmp (places_rows_itself) the kernel writes
+  // the CSR; else entries go to rows_tmp [rows, keep_lo + keep_hi] and counts [rows], and compact_kernel builds it.
   // Per-sample lengths (optional): sample b ranks the key blocks it has, ceil(len/block_k) of them, with its own
   // counts kept_blocks(rho, size of each of its ranges), and its query blocks past ceil(len/block_q) get empty rows.
   const int32_t* seq_lens;
@@ -155,6 +155,8 @@ int pool1p_groups(int block_q);
 // Units of work of that launch: runs of 128 consecutive rows of one head (one, two or four query blocks).
 int64_t pool1p_units(int B, int Hq, int nqb, int block_q);
 hipError_t launch_topk(const TopkArgs& a, hipStream_t s);
+// Whether launch_topk is to write the CSR itself (rows_tmp null) where rows differ in length, or staged rows for launch_compact.
+bool places_rows_itself(int nqb, int nkb);
 hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
 hipError_t launch_validate(const ValidateArgs& a, hipStream_t s);
 hipError_t launch_window_index(const WindowArgs& a, hipStream_t s);

@@ -468,32 +468,65 @@ __global__ __launch_bounds__(64) void topk_kernel(const TopkArgs a) {
     return (int)x;
   };
   if (a.straddle >= 0) {
-    // Prefill boundary at key token a.boundary, inside key block a.straddle. Rows differ in length, so they are
-    // staged at a fixed stride (the host's keep_lo + keep_hi) with their lengths; compact_kernel builds the CSR.
+    // Prefill boundary at key token a.boundary, inside key block a.straddle. A row is one entry shorter where both of its
+    // ranges keep that block, so its place depends on the rows before it. Either the wave works out which of those are
+    // short (rows_tmp null, see places_rows_itself), or the rows are staged at a fixed stride (the host's keep_lo + keep_hi)
+    // with their lengths and compact_kernel builds the CSR.
     int L = a.L;  // length of this batch element
     if (a.seq_lens != nullptr) {
       const int len = a.seq_lens[bh / a.heads_per_batch];
       L = len < a.L ? len : a.L;
     }
     const int nkb_b = L > 0 ? (L + a.block_k - 1) / a.block_k : 0, nqb_b = L > 0 ? (L + a.block_q - 1) / a.block_q : 0;
-    int32_t* tmp = a.rows_tmp + (int64_t)r * keep;
-    if (I >= nqb_b) {  // a query block this sample does not have: an empty row
-      if (lane == 0) a.counts[r] = 0;
-      return;
-    }
-    if (L <= a.boundary) {
-      // a sample no longer than the prefill: one range over the key blocks it has, none of them split
-      row.load(nkb_b, [&](int J) { return src[J]; });
-      const int keep_b = kept(nkb_b);
-      row.emit(0, nkb_b, keep_b, tmp);
-      if (lane == 0) a.counts[r] = keep_b;
-      return;
-    }
     // The ranked row has nkb_b + 1 entries: blocks before the one that holds the boundary, that block's
     // prefill part, its generation part, the blocks after it. Entries [0, Js] are the prefill range.
+    // A sample no longer than the prefill has one range over the key blocks it has, none of them split.
     const int Js = a.straddle, nv = nkb_b + 1;
-    const int keep_lo = kept(Js + 1), keep_hi = kept(nkb_b - Js), keep_b = keep_lo + keep_hi;
+    const bool one_range = L <= a.boundary;
+    const int keep_lo = kept(one_range ? nkb_b : Js + 1), keep_hi = one_range ? 0 : kept(nkb_b - Js), keep_b = keep_lo + keep_hi;
     const uint32_t* part = reinterpret_cast<const uint32_t*>(a.part) + (int64_t)r * 2;
+    int32_t* tmp = nullptr;
+    int begin = 0;
+    auto finish = [&](int n) {  // the row has n entries
+      if (lane != 0) return;
+      if (R == 0 || R > 4 || a.rows_tmp != nullptr) {
+        a.counts[r] = n;
+        return;
+      }
+      int32_t* rp = a.row_ptr + (int64_t)bh * (a.nqb + 1);
+      rp[I] = begin;
+      if (I == a.nqb - 1) rp[a.nqb] = begin + n;
+    };
+    if (R == 0 || R > 4 || a.rows_tmp != nullptr) {
+      tmp = a.rows_tmp + (int64_t)r * keep;
+    } else {
+      // A lane per earlier row (at most 64): both parts of its boundary block are kept if, in their range, fewer entries than
+      // it keeps rank before them. The first part is the last of its range, so equal entries rank before it; the second
+      // part is the first of its.
+      const int earlier = I < nqb_b ? I : nqb_b;
+      int before_lo = 0, before_hi = 0;
+      if (!one_range && lane < earlier) {
+        const uint32_t* mine = src + (int64_t)(lane - I) * a.nkb;
+        const uint32_t p_lo = part[2 * (lane - I)], p_hi = part[2 * (lane - I) + 1];
+#pragma unroll 8
+        for (int J = 0; J < Js; ++J) before_lo += mine[J] >= p_lo;
+#pragma unroll 8
+        for (int J = Js + 1; J < nkb_b; ++J) before_hi += mine[J] > p_hi;
+      }
+      const bool is_short = !one_range && lane < earlier && before_lo < keep_lo && before_hi < keep_hi;
+      begin = earlier * keep_b - __builtin_popcountll(__ballot(is_short));
+      tmp = a.col_idx + (int64_t)bh * a.cap_per_head + begin;
+    }
+    if (I >= nqb_b) {  // a query block this sample does not have: an empty row
+      finish(0);
+      return;
+    }
+    if (one_range) {
+      row.load(nkb_b, [&](int J) { return src[J]; });
+      row.emit(0, nkb_b, keep_b, tmp);
+      finish(keep_b);
+      return;
+    }
     row.load(nv, [&](int v) { return v == Js ? part[0] : v == Js + 1 ? part[1] : src[v < Js ? v : v - 1]; });
     int32_t* sel = reinterpret_cast<int32_t*>(lds + (R > 0 ? 0 : nv));  // the kept entries of both ranges
     row.emit(0, Js + 1, keep_lo, sel);
@@ -506,7 +539,7 @@ __global__ __launch_bounds__(64) void topk_kernel(const TopkArgs a) {
       const int v = sel[t];
       tmp[t - ((dup && t > keep_lo) ? 1 : 0)] = v > Js ? v - 1 : v;
     }
-    if (lane == 0) a.counts[r] = keep_b - (dup ? 1 : 0);
+    finish(keep_b - (dup ? 1 : 0));
     return;
   }
   if (a.seq_lens != nullptr) {
@@ -700,6 +733,12 @@ hipError_t launch_pool_f32(int D, int block_q, const PoolArgs& a, hipStream_t s)
   if (D == 64) return launch_pool_f32_d<64>(block_q, a, s);
   return hipErrorInvalidValue;
 }
+
+// A lane per earlier row: up to 64 rows a head; rows in at most four registers a lane. A wave then reads the scores of all the
+// rows before its own, which is quicker than a second launch everywhere here. Whole selection (statistics given) with head dim
+// 64, us, staged and compacted -> placed: 4 heads of 64 rows x 64 blocks 39.7 -> 32.3, 64 x 128 78.1 -> 70.0, 4 x 4 20.0 -> 17.3;
+// 32 heads 48 x 192 268 -> 262, 64 x 128 140.0 -> 138.4 (64-row blocks) and 402.5 -> 402.4 (128-row blocks).
+bool places_rows_itself(int nqb, int nkb) { return nqb <= 64 && nkb < 256; }
 
 hipError_t launch_topk(const TopkArgs& a, hipStream_t s) {
   if (a.rows <= 0) return hipErrorInvalidValue;

@@ -43,3 +43,46 @@ def test_both_selections_keep_the_same_blocks(bq, bk, L, D):
     # 1e-5 of themselves; neighbours in a ranking of n random scores that spread by s of themselves lie within that of each
     # other in about n * 1e-5 / s < 1 % of the rows (n <= 42, s >= 0.05).
     assert differ <= 0.01 * rows + 1, (differ, rows)
+
+
+# query blocks and key blocks on both sides of what a row places for itself (64 rows, 255 blocks)
+@pytest.mark.parametrize("nqb,nkb", [(1, 4), (2, 2), (63, 63), (64, 64), (64, 255), (64, 256), (65, 65), (16, 255), (17, 64)])
+@pytest.mark.parametrize("rho", [0.05, 0.5, 1.0])
+def test_rows_lie_behind_one_another_and_match_the_ranking(nqb, nkb, rho):
+    L = nkb * 32 - 3
+    bq = next((b for b in (32, 64, 128) if -(-L // b) <= nqb), 128)
+    nqb = -(-L // bq)
+    D, H = 64, 2
+    g = torch.Generator().manual_seed(nqb * 1000 + nkb)
+    q = torch.randn(2, H, L, D, generator=g).to(torch.bfloat16).to(DEV)
+    k = torch.randn(2, H, L, D, generator=g).to(torch.bfloat16).to(DEV)
+    k[:, :, 32:64] = k[:, :, :32] if L >= 64 else k[:, :, 32:64]  # equal blocks: ties
+    lens = torch.tensor([L, max(1, L // 3)], dtype=torch.int32, device=DEV)
+    token = (nkb // 2) * 32 + 17
+    if token >= L:
+        token = 17
+    pooled = torch.zeros(2, H, nqb, nkb, dtype=torch.float32, device=DEV)
+    ix = sd.select_pattern_isolated_tokens(q, k, bq, 32, rho, token, seq_lens=lens, pooled_out=pooled)
+    sd.index_validate(ix)
+    js = token // 32
+    for b, n in enumerate(lens.tolist()):
+        blocks, qblocks = -(-n // 32), -(-n // bq)
+        for h in range(H):
+            rows = _rows(ix, h, b)
+            assert ix.row_ptr[b, h, 0] == 0 and len(rows) == nqb
+            for i, row in enumerate(rows):
+                if i >= qblocks:
+                    assert row == []
+                    continue
+                scores = pooled[b, h, i, :blocks].cpu()
+                order = lambda s: torch.sort(-s, stable=True).indices.tolist()
+                if n <= token:
+                    assert row == sorted(order(scores)[:sd.kept_blocks(rho, blocks)])
+                    continue
+                lo, hi = sd.kept_blocks(rho, js + 1), sd.kept_blocks(rho, blocks - js)
+                # the parts' own scores stay inside the selection: of each range, the blocks other than the boundary's that it
+                # keeps are the best ones, `keep` of them or, where the boundary's part is among the kept, one fewer
+                first, second = [j for j in row if j < js], [j for j in row if j > js]
+                assert first == sorted(order(scores[:js])[:len(first)]) and len(first) in (lo, lo - 1), (b, h, i)
+                assert second == sorted(js + 1 + j for j in order(scores[js + 1:])[:len(second)]) and len(second) in (hi, hi - 1)
+                assert (js in row) == (len(first) == lo - 1 or len(second) == hi - 1)
