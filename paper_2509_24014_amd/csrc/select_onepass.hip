@@ -45,20 +45,22 @@ constexpr int groups_per_cu(int) { return 4; }
 // The lane number and the kernel's arguments are worked out / read again where they are used late (fresh_lane,
 // fresh_kernel_args): 128 registers a lane are all that four waves per SIMD leave, and a spill in the tile loop waits
 // for the copies in flight.
-template <int D, int NW, int BK, int QBW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pool1p_bf16_kernel(const PoolArgs) {
+// KS: runs that the keys are cut into, four waves each; all with the same rows.
+template <int D, int KS, int BK, int QBW>
+__global__ __launch_bounds__(KS * 256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pool1p_bf16_kernel(const PoolArgs) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub (the body uses device-only types)
-  static_assert(NW == 4, "four waves per SIMD, 128 rows per slab column");
-  constexpr int NT = NW * 64, QT = 32 * NW;
+  constexpr int NW = 4, NT = NW * 64, QT = 32 * NW;  // waves and threads of a run, rows of a slab column
   constexpr int kKBytes = KLayout<D>::kTileBytes;
-  __shared__ __attribute__((aligned(1024))) char kbuf0[kKBytes];
-  __shared__ __attribute__((aligned(1024))) char kbuf1[kKBytes];
-  __shared__ __attribute__((aligned(16))) float inv_z[QT];
+  __shared__ __attribute__((aligned(1024))) char kbuf0[KS * kKBytes];  // run r: its tile at r * kKBytes, which is part of kaddr
+  __shared__ __attribute__((aligned(1024))) char kbuf1[KS * kKBytes];
+  __shared__ __attribute__((aligned(16))) float inv_z[KS * QT];
+  __shared__ float run_max[KS > 1 ? KS * QT : 1], run_sum[KS > 1 ? KS * QT : 1];  // reference and sum of a row in each run
   __shared__ float part_sum[2][NW];  // a wave's share of the two parts of the boundary's key block
   static_assert(NW % QBW == 0, "whole query blocks per work-group");
   constexpr int kBlocksPerGroup = NW / QBW, kBlockRows = 32 * QBW;
 
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_of_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wave_of_all % NW, run = KS > 1 ? wave_of_all / NW : 0;
 
   int unit = xcd_remap(blockIdx.x, gridDim.x), units = 0;  // a unit: QT consecutive rows of one head
   do {
@@ -84,14 +86,23 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     kdma.init(a.k.sl, wave, lane);
     KFragAddr<D> kaddr;
     kaddr.init(lane);
+    if (KS > 1)
+#pragma unroll
+      for (int i = 0; i < KFragAddr<D>::kBases; ++i) kaddr.base[i] += run * kKBytes;
     QFrag<D, 1> qf;
-    const int last_blk = (L - 1) / kTileK;              // last 64-key tile that exists
-    const int tail_keys = L - last_blk * kTileK;        // keys in it
-    const int n = last_blk + 1;
+    // This run's tiles: tile0 and the n - 1 behind it (an even tile0: a run's columns are its own and begin with a pair).
+    const int n_all = (L - 1) / kTileK + 1;             // 64-key tiles that exist
+    const int n_first = KS == 1 ? n_all : n_all < 2 ? n_all : ((n_all + 3) >> 2) * 2;  // tiles of the first run, no fewer than of the second
+    const int tile0 = run * n_first, n = run == 0 ? n_first : n_all - n_first;
+    const int last_blk = n - 1;
+    const int tail_keys = tile0 + n == n_all ? L - (n_all - 1) * kTileK : kTileK;  // keys in the last of them
     auto keys_at = [&](int tile) -> int { return tile >= n ? 0 : tile == last_blk ? tail_keys : kTileK; };
-    const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(kbase, ((int64_t)(L - 1) * a.k.sl + D) * 2);
+    const int first_key = n > 0 ? tile0 * kTileK : 0;
+    const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(kbase + first_key * a.k.sl, ((int64_t)(L - 1 - first_key) * a.k.sl + D) * 2);
     const int64_t k_sl = a.k.sl;
     const int32_t k_tile_bytes = (int32_t)(kTileK * k_sl * 2);
+    char* const kdst0 = kbuf0 + run * kKBytes;
+    char* const kdst1 = kbuf1 + run * kKBytes;
     auto copy_k_any = [&](int tile, char* dst) {  // any tile: past the end repeats the last one, which may be partial
       const int blk = tile < n ? tile : n - 1;
       if (blk == last_blk && tail_keys < kTileK) kdma.issue_partial(krsrc, blk * k_tile_bytes, dst, wave, fresh_lane(), k_sl, tail_keys);
@@ -124,8 +135,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
       return part;
     };
     // The slab: columns J of QT floats, stored two at a time (both halves of a wave), or once per two tiles with 128-key blocks.
-    float* const slab = a.slab + (int64_t)blockIdx.x * QT * a.slab_ld;
-    const __amdgpu_buffer_rsrc_t slab_rsrc = make_rsrc(slab, (int64_t)QT * a.slab_ld * 4);
+    const int col0 = BK == kTileK / 2 ? 2 * tile0 : BK == kTileK ? tile0 : tile0 >> 1;  // this run's first column
+    float* const slab = a.slab + ((int64_t)blockIdx.x * a.slab_ld + col0) * QT;
+    const __amdgpu_buffer_rsrc_t slab_rsrc = make_rsrc(slab, (int64_t)QT * (a.slab_ld - col0) * 4);
     auto park_store = [&](int col, float v) {
       const int ln = fresh_lane();
       const int off = 4 * ((BK == 2 * kTileK ? 0 : (ln >> 5) * QT) + (ln & 31));
@@ -170,7 +182,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     // masked); MASKED steps (the last few) count the keys that exist in each sub-tile.
 #define SPARSED_POOL1P_STEP(P, MASKED, T)                                                          \
   {                                                                                                \
-    char* const kb_free = (P) ? kbuf1 : kbuf0;                                                     \
+    char* const kb_free = (P) ? kdst1 : kdst0;                                                     \
     char* const kb_next = (P) ? kbuf0 : kbuf1;                                                     \
     if (MASKED) copy_k_any((T) + 2, kb_free);                                                      \
     else kdma.issue(krsrc, ((T) + 2 < n ? (T) + 2 : n - 1) * k_tile_bytes, kb_free, wave);         \
@@ -193,16 +205,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   }
 
     // prologue: K(0), K(1) (a repeat of K(0) for a one-tile range) into LDS; S(0); reference and sums of sub-tile 0
-    copy_k_any(0, kbuf0);
-    copy_k_any(1, kbuf1);
-    qf.load(qbase, row0, L, a.q.sl, lane);
+    if (KS == 1 || n > 0) {
+      copy_k_any(0, kdst0);
+      copy_k_any(1, kdst1);
+      qf.load(qbase, row0, L, a.q.sl, lane);
+    }
     __syncthreads();
-    logits_sub<D, 1, true>(kbuf0, 0, kaddr, qf, s_even);
-    logits_sub<D, 1, true>(kbuf0, 1, kaddr, qf, s_odd);
-    mask_sub(s_even, keys_at(0));
-    M = row_max(s_even);  // at least one key exists, so this is finite
-    carry = exp_sum(s_even);
-    lsum = carry;
+    if (KS == 1 || n > 0) {
+      logits_sub<D, 1, true>(kbuf0, 0, kaddr, qf, s_even);
+      logits_sub<D, 1, true>(kbuf0, 1, kaddr, qf, s_odd);
+      mask_sub(s_even, keys_at(0));
+      M = row_max(s_even);  // at least one key exists, so this is finite
+      if (KS > 1 && run > 0) M = fmaxf(M, -1e30f);  // (keys of logit -inf behind others: their sums are 0)
+      carry = exp_sum(s_even);
+      lsum = carry;
+    }
     __syncthreads();  // everyone is done with K(0) before tile step 0 lets K(2) overwrite it
 
     const int steady_reach = (tail_keys < kTileK) ? 4 : 2;
@@ -220,6 +237,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
       }
     }
 #undef SPARSED_POOL1P_STEP
+    if (KS > 1)
+      for (t = n > 0 ? n : 0; t < n_first; ++t) __syncthreads();  // a shorter run keeps step
 
     // The rows are complete: 1 / Z_r (0 for rows past the end), and then
     // A'[I, J] = sum_r E[r, J] / Z_r over the rows of the block, divided by the entries that exist: a lane weighs the same
@@ -227,21 +246,36 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     const KernelArgs<PoolArgs>& ae = fresh_kernel_args<PoolArgs>();
     const int lane_e = fresh_lane();
     const float ltot = pair_sum(lsum);
+    float weight = 1.0f / ltot;
+    if (KS > 1) {
+      // 1 / Z_r against this run's reference, Z_r from both runs' sums. A run without a sum has no say in the common reference.
+      const int at = wave * 32 + (lane_e & 31);
+      if (lane_e < 32) {
+        run_max[run * QT + at] = M;
+        run_sum[run * QT + at] = ltot;
+      }
+      __syncthreads();
+      const float m0 = run_sum[at] == 0.f ? -3e38f : run_max[at], m1 = run_sum[QT + at] == 0.f ? -3e38f : run_max[QT + at];
+      const float m = fmaxf(m0, m1);
+      const float a0 = __builtin_amdgcn_exp2f(m0 - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
+      weight = (run ? a1 : a0) / (run_sum[at] * a0 + run_sum[QT + at] * a1);
+    }
     const bool splits = ae.part != nullptr && L > ae.boundary;
     if (splits) {
       // The key block that holds the prefill boundary once more, its keys before the boundary and the others apart: one or two
       // tiles against the row statistics that are at hand here, instead of a launch that reads Q and the statistics again.
       // 3 samples (3000, 2100, 1200) x 8 heads of 64, 128 x 128 blocks, 30 % kept: 73.2 -> 68.5 us with
       // the sparse step (the launch: 8.3 us).
-      const int tile0 = ae.boundary / BK * BK / kTileK, tile1 = (ae.boundary / BK * BK + BK - 1) / kTileK;
+      const int begin = ae.boundary / BK * BK / kTileK, end = (ae.boundary / BK * BK + BK - 1) / kTileK;
+      const bool mine = KS == 1 || (begin >= n_first) == (run == 1);  // the run that has the block
       float before = 0.f, behind = 0.f;
-      for (int tile = tile0; tile <= tile1 && tile < n; ++tile) {
-        copy_k_any(tile, kbuf0);
+      for (int tile = begin; tile <= end && tile < n_all; ++tile) {
+        if (mine) copy_k_any(tile - tile0, kdst0);
         __syncthreads();
 #pragma unroll 1
         for (int sub = 0; sub < 2; ++sub) {
           const int key0 = tile * kTileK + 32 * sub;
-          if (BK < kTileK && (key0 & ~(BK - 1)) != ae.boundary / BK * BK) continue;  // the other block of the tile
+          if (!mine || (BK < kTileK && (key0 & ~(BK - 1)) != ae.boundary / BK * BK)) continue;  // (the other block of the tile)
           logits_sub<D, 1, false>(kbuf0, sub, kaddr, qf, s_even);
           int first = key0 + 8 * (lane_e >> 5);  // key of register 0
           asm volatile("" : "+v"(first));  // the comparisons below stay here: sixteen masks at once do not fit
@@ -255,17 +289,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
         }
         __syncthreads();  // the tile may be overwritten
       }
-      const float z = row0 + (lane_e & 31) < L ? 1.0f / ltot : 0.f;
+      const float z = row0 + (lane_e & 31) < L ? weight : 0.f;
       before = lane_group_sum_to_last(pair_sum(before) * z, 32);
       behind = lane_group_sum_to_last(pair_sum(behind) * z, 32);
-      if (lane_e == 31) {
+      if (lane_e == 31 && mine) {
         part_sum[0][wave] = before;
         part_sum[1][wave] = behind;
       }
     }
     if (lane_e < 32) {
       const bool exists = row0 + lane_e < L;
-      inv_z[wave * 32 + lane_e] = exists ? 1.0f / ltot : 0.f;
+      inv_z[run * QT + wave * 32 + lane_e] = exists ? weight : 0.f;
     }
     wait_vector_memory();  // this wave's parked sums have been written
     __syncthreads();  // all parked sums and weights of the group are written
@@ -280,22 +314,27 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     }
     constexpr int kLanes = QT / 4, kCols = 64 / kLanes, kUnroll = 8;  // lanes per column, columns per wave load
     const int li = lane_e % kLanes, sub_col = lane_e / kLanes;
-    const f32x4v w = *reinterpret_cast<const f32x4v*>(&inv_z[4 * li]);
+    const f32x4v w0 = *reinterpret_cast<const f32x4v*>(&inv_z[4 * li]);
+    f32x4v w1 = w0;
+    if (KS > 1) w1 = *reinterpret_cast<const f32x4v*>(&inv_z[(KS - 1) * QT + 4 * li]);
+    const int col1 = n_first * kTileK / BK;  // the second run's first column
+    const float* const all = slab - (int64_t)col0 * QT;
     const int I = gq * kBlocksPerGroup + 4 * li / kBlockRows;
     const int rows_here = L - I * kBlockRows < kBlockRows ? L - I * kBlockRows : kBlockRows;
     const bool writes = (4 * li + 4) % kBlockRows == 0 && rows_here > 0;  // the last lane of a query block that exists
     float* const arow = ae.apool + ((int64_t)bh * ae.nqb + I) * ae.out_stride;
     const int nkb_here = (L + BK - 1) / BK;  // key blocks this sample has
-    for (int J0 = wave * (kCols * kUnroll); J0 < nkb_here; J0 += NW * kCols * kUnroll) {
+    for (int J0 = wave_of_all * (kCols * kUnroll); J0 < nkb_here; J0 += KS * NW * kCols * kUnroll) {
       f32x4v e[kUnroll];
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const int J = J0 + u * kCols + sub_col;
-        e[u] = *reinterpret_cast<const f32x4v*>(slab + (int64_t)(J < nkb_here ? J : nkb_here - 1) * QT + 4 * li);
+        e[u] = *reinterpret_cast<const f32x4v*>(all + (int64_t)(J < nkb_here ? J : nkb_here - 1) * QT + 4 * li);
       }
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const int J = J0 + u * kCols + sub_col;
+        const f32x4v w = KS > 1 && J >= col1 ? w1 : w0;
         float x = e[u][0] * w[0] + e[u][1] * w[1] + e[u][2] * w[2] + e[u][3] * w[3];
         x = lane_group_sum_to_last(x, kBlockRows / 4);
         const int keys_here = L - J * BK < BK ? L - J * BK : BK;
@@ -314,16 +353,35 @@ int64_t pool1p_units(int B, int Hq, int nqb, int block_q) {
   return (int64_t)B * Hq * ((nqb + per - 1) / per);
 }
 
-template <int D, int QBW>
+template <int D, int KS, int QBW>
 static hipError_t launch_pool1p_bk(const PoolArgs& a, int groups, hipStream_t s) {
-  const dim3 grid((unsigned)groups), block(256);
+  const dim3 grid((unsigned)groups), block(KS * 256);
   switch (a.block_k) {
-    case 32: hipLaunchKernelGGL((pool1p_bf16_kernel<D, 4, 32, QBW>), grid, block, 0, s, a); break;
-    case 64: hipLaunchKernelGGL((pool1p_bf16_kernel<D, 4, 64, QBW>), grid, block, 0, s, a); break;
-    case 128: hipLaunchKernelGGL((pool1p_bf16_kernel<D, 4, 128, QBW>), grid, block, 0, s, a); break;
+    case 32: hipLaunchKernelGGL((pool1p_bf16_kernel<D, KS, 32, QBW>), grid, block, 0, s, a); break;
+    case 64: hipLaunchKernelGGL((pool1p_bf16_kernel<D, KS, 64, QBW>), grid, block, 0, s, a); break;
+    case 128: hipLaunchKernelGGL((pool1p_bf16_kernel<D, KS, 128, QBW>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <int D, int KS>
+static hipError_t launch_pool1p_q(int block_q, const PoolArgs& a, int groups, hipStream_t s) {
+  if (block_q == 128) return launch_pool1p_bk<D, KS, 4>(a, groups, s);
+  if (block_q == 64) return launch_pool1p_bk<D, KS, 2>(a, groups, s);
+  return launch_pool1p_bk<D, KS, 1>(a, groups, s);
+}
+
+// Two key runs: the same number of waves in flight, half as many units at a time and each in half the time. By rounds of the
+// chip, 1024 units at a time or 512, where the last round of whole units is at most half full and rounds are few; and with at
+// most a unit a compute unit, where it is twice the waves, if the runs are long enough to pay for merging them (24 tiles).
+// Selections, one run -> two, us. 32 heads of 128: 6000 tokens (1504 units) 441 -> 353, 8192 (2048) 590 -> 608, 4096 (1024)
+// 158 -> 167, 3000 (768) 96 -> 131; 2 heads of 8192 (128) 88 -> 76, 8 heads of 3000 (192) 42 -> 40, of 1000 (64) 21 -> 21, of 600
+// (40) 17 -> 20. Head dim 64: 311 -> 245, 441 -> 441, 112 -> 119, 71 -> 94; 78 -> 65, 37 -> 34, 18 -> 18, 15 -> 16.
+static int key_runs(const PoolArgs& a, int64_t units) {
+  const int64_t rounds = (units + 1023) / 1024, half_rounds = (units + 511) / 512;
+  if (units > 1024) return rounds <= 6 && half_rounds < 2 * rounds ? 2 : 1;
+  return units <= 256 && a.L > 23 * kTileK ? 2 : 1;
 }
 
 // One-pass pooled scores over the whole key range of every sample. a.slab holds `groups` slabs of
@@ -333,14 +391,13 @@ hipError_t launch_pool1p_bf16(int D, int block_q, const PoolArgs& a, int groups,
   const int64_t units = pool1p_units(a.B, a.Hq, a.nqb, block_q);
   if (units <= 0 || units > 0x7fffffff || groups < 1 || a.slab == nullptr || a.slab_ld < a.out_stride) return hipErrorInvalidValue;
   if (groups > units) groups = (int)units;
-  if (D == 128) {
-    if (block_q == 128) return launch_pool1p_bk<128, 4>(a, groups, s);
-    if (block_q == 64) return launch_pool1p_bk<128, 2>(a, groups, s);
-    return launch_pool1p_bk<128, 1>(a, groups, s);
-  } else if (D == 64) {
-    if (block_q == 128) return launch_pool1p_bk<64, 4>(a, groups, s);
-    if (block_q == 64) return launch_pool1p_bk<64, 2>(a, groups, s);
-    return launch_pool1p_bk<64, 1>(a, groups, s);
+  if (key_runs(a, units) == 2) {
+    if (groups > 512) groups = 512;  // two a compute unit
+    if (D == 128) return launch_pool1p_q<128, 2>(block_q, a, groups, s);
+    if (D == 64) return launch_pool1p_q<64, 2>(block_q, a, groups, s);
+  } else {
+    if (D == 128) return launch_pool1p_q<128, 1>(block_q, a, groups, s);
+    if (D == 64) return launch_pool1p_q<64, 1>(block_q, a, groups, s);
   }
   return hipErrorInvalidValue;
 }

@@ -1,0 +1,52 @@
+"""One-pass pooled scores with the keys in one run and in two: calls on both sides of the rule that chooses (units of 128 rows:
+up to 256 and 24 key tiles or more, or a last round of 1024 that is at most half full), and tile counts at which the second run is
+shorter than the first. Scores against the pooling kernel that is given the row statistics."""
+import pytest
+import torch
+
+import paper_2509_24014_amd as sd
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("B,H,L,D,bq,bk", [
+    (1, 2, 1472, 64, 64, 64), (1, 2, 1473, 64, 128, 128),                # 23 and 24 tiles
+    (1, 2, 1537, 128, 32, 32), (1, 1, 1660, 128, 64, 128), (1, 2, 1700, 128, 128, 64), (2, 2, 1728, 64, 32, 32),  # 25 to 27 tiles
+    (1, 20, 1600, 64, 128, 64),                                            # 260 units: one run
+    (1, 342, 300, 64, 32, 128), (1, 1025, 100, 64, 128, 32), (2, 513, 70, 128, 64, 64),   # 1026 units: two runs of 4, 1 and 0 tiles
+    (1, 769, 250, 64, 128, 64), (1, 770, 190, 128, 128, 64),              # 1538 units: one run
+])
+def test_scores_of_both_forms(B, H, L, D, bq, bk):
+    g = torch.Generator(device=DEV).manual_seed(L)
+    q = (torch.randn(B, H, L, D, generator=g, device=DEV) * 0.6).to(torch.bfloat16)
+    k = (torch.randn(B, 1, L, D, generator=g, device=DEV) * 0.6).to(torch.bfloat16)
+    nqb, nkb = -(-L // bq), -(-L // bk)
+    lse, out = torch.zeros(B, H, L, dtype=torch.float32, device=DEV), torch.zeros(B, H, nqb, nkb, device=DEV)
+    want = torch.zeros_like(out)
+    for lens in (None, torch.tensor([L] + [max(1, L * 2 // 5)] * (B - 1), dtype=torch.int32, device=DEV)):
+        ix = sd.select_pattern(q, k, bq, bk, 0.3, pooled_out=out, seq_lens=lens)
+        sd.index_validate(ix)
+        sd.attn_dense(q, k, k, seq_lens=lens, lse_out=lse)
+        sd.select_pattern(q, k, bq, bk, 0.3, pooled_out=want, lse_in=lse, seq_lens=lens)
+        # each is within 5e-6 of the exact score (the bar of the pooling kernels)
+        for b in range(B):
+            n = L if lens is None else int(lens[b])
+            x, y = out[b, :, :-(-n // bq), :-(-n // bk)], want[b, :, :-(-n // bq), :-(-n // bk)]
+            assert torch.isfinite(x).all() and ((x - y).abs() <= 1e-5 * y).all(), ((x - y).abs() / y).max()
+
+
+@pytest.mark.parametrize("D,where", [(64, 100), (64, 1500), (128, 40), (128, 1000), (128, 1599)])
+def test_a_logit_far_above_the_others_in_either_run(D, where):
+    """One key whose logits are 150 to 300 octaves above every other key's: the references of the runs differ by as much, and
+    all of the weight is in one column."""
+    L, b = 1600, 64
+    q = torch.ones(1, 1, L, D, device=DEV, dtype=torch.bfloat16)
+    q[:, :, 800:] = 2
+    k = torch.full((1, 1, L, D), -0.25, device=DEV, dtype=torch.bfloat16)
+    k[:, :, where] = 104 * D ** -0.5   # logits (104 + sqrt(D) / 4) times 1 and 2 above the others
+    out = torch.zeros(1, 1, L // b, L // b, device=DEV)
+    sd.select_pattern(q, k, b, b, 0.3, pooled_out=out)
+    want = torch.zeros_like(out)
+    want[..., where // b] = 1 / b
+    assert torch.allclose(out, want, rtol=5e-6, atol=1e-30)
