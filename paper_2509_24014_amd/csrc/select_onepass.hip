@@ -21,7 +21,7 @@
 // by one work-group only, so its order is kept by work-group fences; the columns are read back as whole 16-byte pieces,
 // eight in flight per wave.
 // 32 heads of 16384 x 128, 64 x 64 blocks: 2.52 -> 2.19 ms (1.00 PFLOP/s); 3 samples (3000, 2100, 1200) x 8 heads of 64: 62 ->
-// 39 us. (Before: block sums staged in LDS row by row, a cache write-back at the end of every unit, four reads in flight in
+// 39 us (41 with the two parts of a boundary block, which were a launch of 8.6). (Before: block sums staged in LDS row by row, a cache write-back at the end of every unit, four reads in flight in
 // the closing pass, 48 to 76 bytes of spills.)
 //
 // Matrix work, K tile copies, fragment layouts and the 32-key software pipeline are those of pool_bf16_kernel
@@ -40,7 +40,7 @@ constexpr int groups_per_cu(int) { return 4; }
 
 }  // namespace
 
-// QBW: waves per query block. A work-group is always NW = 4 waves = 128 consecutive rows of a head: one query block of
+// QBW: waves per query block. A work-group always has 128 consecutive rows of a head, four waves: one query block of
 // 128 rows, two of 64 or four of 32, which share its K tiles and its slab.
 // The lane number and the kernel's arguments are worked out / read again where they are used late (fresh_lane,
 // fresh_kernel_args): 128 registers a lane are all that four waves per SIMD leave, and a spill in the tile loop waits
