@@ -425,8 +425,16 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
   a.block_k = bk;
   a.apool = ex->pooled_out ? ex->pooled_out : reinterpret_cast<float*>(ws + (bf16 ? 0 : statistics_bytes));
   if (bf16) a.slab = reinterpret_cast<float*>(ws + apool_bytes);
+  const bool ranked = !bf16 && ranks_own_rows_f32((int64_t)q->B * q->H, nqb, nkb, bq);
+  if (ranked) {
+    a.row_ptr_out = ix->row_ptr;
+    a.col_idx_out = ix->col_idx;
+    a.cap_per_head = ix->cap_per_head;
+    a.rho = rho;
+  }
   hipError_t e = bf16 ? launch_attn_bf16_dense_pool(q->D, a, sh, stream_of(ex)) : launch_attn_f32_dense_pool(q->D, a, stream_of(ex));
   if (e != hipSuccess) return hip_fail(e, "dense attention with pooling launch");
+  if (ranked) return SPARSED_OK;
   TopkArgs t{};
   t.apool = a.apool;
   t.row_ptr = ix->row_ptr;

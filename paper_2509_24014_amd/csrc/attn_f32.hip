@@ -19,6 +19,7 @@
 
 #include "kernels.hpp"
 #include "tile_f32.hpp"
+#include "topk_row.hpp"
 
 namespace sparsed {
 
@@ -36,9 +37,11 @@ struct PoolLdsF32 {
   static constexpr int kBlocks = (kBytes - kUsed) / (RW * 32 * 8);                                       // key blocks that can be parked
 };
 
-template <int D, int KW, Mode MODE, bool SPLIT_FIRST, int RW = 1>
+// RANKS (kDensePool): the work-group also ranks the row it has pooled and writes its part of the index (ranks_own_rows_f32).
+template <int D, int KW, Mode MODE, bool SPLIT_FIRST, int RW = 1, bool RANKS = false>
 __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnArgs a) {
   constexpr bool kPool = MODE == Mode::kDensePool;
+  static_assert(!RANKS || kPool, "the rows ranked are the pooled ones");
   static_assert(RW == 1 || kPool, "several row groups: only where a work-group is a query block");
   constexpr int NW = RW * KW, NT = NW * 64;
   constexpr bool kHasV = MODE != Mode::kStats;
@@ -75,7 +78,19 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     L = len < a.L ? len : a.L;
   }
   const int wg_row0 = qt * (32 * RW), row0 = wg_row0 + rw * 32;
-  if (wg_row0 >= L) return;  // a query tile wholly past the end (uniform over the work-group)
+  // RANKS: the place of row qt, every row of a sample keeping as many blocks
+  auto place_row = [&](int keep) {
+    const KernelArgs<AttnArgs>& ae = fresh_kernel_args<AttnArgs>();
+    const int rows = L > 0 ? (L + 32 * RW - 1) / (32 * RW) : 0;  // query blocks of the sample; those behind them are empty
+    if (tid != 0) return;
+    int32_t* const rp = ae.row_ptr_out + (int64_t)bh * (ae.nqb + 1);
+    rp[qt] = (qt < rows ? qt : rows) * keep;
+    if (qt == ae.nqb - 1) rp[ae.nqb] = rows * keep;
+  };
+  if (wg_row0 >= L) {  // a query tile wholly past the end (uniform over the work-group)
+    if (RANKS) place_row(L > 0 ? kept_blocks_of(a.rho, (L + a.block_k - 1) / a.block_k) : 0);
+    return;
+  }
 
   SlabF32<D> ks, vs;
   ks.init(static_cast<const float*>(a.k.ptr) + b * a.k.sb + hk * a.k.sh, a.k.sl, L);
@@ -335,6 +350,8 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     *m = mm;
     return l;
   };
+  TopkRow<4> row;
+  row.lane = lane;
   __syncthreads();  // everyone is done with the query fragments
   if (g == 0) {
     stat_m[wave][j] = M;
@@ -368,7 +385,15 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
       for (int d = RW == 1 ? 16 : 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
       const int keys_here = L - J * a.block_k < a.block_k ? L - J * a.block_k : a.block_k;
-      if ((RW == 1 ? j : lane) == 0 && J < nkb) arow[J] = x * (1.0f / (float)(rows_here * keys_here));
+      if ((RW == 1 ? j : lane) == 0 && J < nkb) {
+        x *= 1.0f / (float)(rows_here * keys_here);
+        arow[J] = x;
+        if (RANKS) parked[J * (RW * 32)][0] = x;  // (this wave alone has read the block's sums)
+      }
+    }
+    if (RANKS) {
+      __syncthreads();
+      if (wave == 0) row.load(nkb, [&](int J) { return __float_as_uint(parked[J * (RW * 32)][0]); });
     }
     __syncthreads();  // the accumulators may take the parked sums' place
   }
@@ -408,6 +433,15 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
       for (int dt = 0; dt < kV; ++dt) acc[dt] *= inv;
       float* orow = static_cast<float*>(a.o) + b * a.o_sb + h * a.o_sh + (int64_t)(wg_row0 + group * 32 + row) * a.o_sl;
       *reinterpret_cast<VRow*>(orow + kV * piece) = acc;
+    }
+  }
+  if constexpr (RANKS) {
+    // The row's kept blocks, from the scores in the first wave's registers.
+    const KernelArgs<AttnArgs>& ae = fresh_kernel_args<AttnArgs>();
+    if (wave == 0) {
+      const int keep = kept_blocks_of(ae.rho, nkb);
+      row.emit(0, nkb, keep, ae.col_idx_out + (int64_t)bh * ae.cap_per_head + (int64_t)qt * keep);
+      place_row(keep);
     }
   }
 }
@@ -456,6 +490,13 @@ template <int D, int RW>
 static hipError_t launch_pool_rw_f32(const AttnArgs& a, hipStream_t s) {
   const int64_t total = (int64_t)a.B * a.Hq * a.n_qtiles;
   if (total <= 0 || total > 0x7fffffff || a.nkb > PoolLdsF32<D, RW>::kBlocks) return hipErrorInvalidValue;
+  if constexpr (RW <= 2) {
+    if (a.row_ptr_out != nullptr) {
+      if (a.nkb > 256) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((attn_f32_kernel<D, 8 / RW, Mode::kDensePool, true, RW, true>), dim3((unsigned)total), dim3(512), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((attn_f32_kernel<D, 8 / RW, Mode::kDensePool, true, RW>), dim3((unsigned)total), dim3(512), 0, s, a);
   return hipGetLastError();
 }
@@ -493,6 +534,12 @@ bool dense_pool_pays_f32(int D, int64_t heads, int L, int block_q, int block_k) 
   const int64_t dense = dense_groups <= 256 ? (tiles + 7) / 8 : (tiles + 3) / 4 * ((dense_groups + 511) / 512);
   return fused <= 2 * dense + 1;
 }
+
+// One wave ranks while the rest of its compute unit, which holds one such work-group, waits: about as long as a launch takes, so
+// it is for calls of one round of the chip. Switch step, us, launch of its own -> ranked here, (heads, tokens, head dim) and
+// blocks: (2, 256, 64) 32 x 32 13.5 -> 12.8, (8, 100, 64) 32 x 32 11.4 -> 10.3, (28, 100, 128) 64 x 64 17.7 -> 16.4, (8, 2000, 128)
+// 64 x 64 115.5 -> 114.3; with two rounds (28, 600, 64) 32 x 32 45.6 and 47.6; 128-row blocks 22.4 and 22.5, 103.3 and 106.4.
+bool ranks_own_rows_f32(int64_t heads, int nqb, int nkb, int block_q) { return block_q <= 64 && heads * nqb <= 256 && nkb <= 256; }
 
 hipError_t launch_attn_f32(Mode mode, int D, int block_q, AttnArgs a, hipStream_t s) {
   if (a.L <= 0 || (mode == Mode::kSparse && block_q % 32 != 0)) return hipErrorInvalidValue;

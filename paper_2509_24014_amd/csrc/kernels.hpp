@@ -30,6 +30,10 @@ struct AttnArgs {
   float* slab;             // scratch: one slab of (rows per work-group) x slab_cols floats per work-group of the launch
   float* apool;            // [B, Hq, nqb, nkb] pooled scores
   int32_t slab_cols, nkb;
+  // kDensePool of fp32 only: where the kept blocks go if the kernel ranks its rows itself (ranks_own_rows), else null; the
+  // capacity per head is cap_per_head
+  int32_t *row_ptr_out, *col_idx_out;
+  double rho;
 };
 
 // Arguments of the pooled-score kernels (Section 3.3: A' = avgpool(A, block)). The keys pooled are
@@ -123,6 +127,17 @@ __device__ __forceinline__ Slab slab_at(int pos, const Args& a) {
   return alternate ? Slab{y, x * group + rest - y * group, x} : Slab{x, rest, y};
 }
 
+// The kernel's argument struct (its only argument), read from the argument segment at the point of the call. Reading
+// it again where it is used late keeps two dozen scalars from living, or being spilled into vector registers, in between.
+template <typename Args>
+using KernelArgs = const __attribute__((address_space(4))) Args;
+template <typename Args>
+__device__ __forceinline__ KernelArgs<Args>& fresh_kernel_args() {
+  auto p = (KernelArgs<Args>*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
 enum class Mode : int { kDense = 0, kSparse = 1, kStats = 2, kDensePool = 3 };
 
 // Launchers. Each returns the HIP error of the launch. block_q selects the work-group shape for
@@ -146,6 +161,8 @@ hipError_t launch_attn_bf16_dense_pool(int D, AttnArgs a, const DensePoolShape& 
 // a call with heads = B * Hq (else: the dense call with its log-sum-exp, then pooling with it).
 hipError_t launch_attn_f32_dense_pool(int D, AttnArgs a, hipStream_t s);
 bool dense_pool_pays_f32(int D, int64_t heads, int L, int block_q, int block_k);
+// Whether that launch is to rank the rows as well (a.row_ptr_out, a.col_idx_out, a.cap_per_head and a.rho set), or launch_topk after it.
+bool ranks_own_rows_f32(int64_t heads, int nqb, int nkb, int block_q);
 hipError_t launch_pool_bf16(int D, int block_q, const PoolArgs& a, hipStream_t s);
 hipError_t launch_pool_f32(int D, int block_q, const PoolArgs& a, hipStream_t s);
 // Pooled scores of bf16 inputs in one pass over the keys (no row statistics needed): `groups` persistent work-groups,

@@ -85,17 +85,6 @@ __device__ __forceinline__ int late_lane(int lane) {
   return lane;
 }
 
-// The kernel's argument struct (its only argument), read from the argument segment at the point of the call. Reading
-// it again where it is used late keeps two dozen scalars from living, or being spilled into vector registers, in between.
-template <typename Args>
-using KernelArgs = const __attribute__((address_space(4))) Args;
-template <typename Args>
-__device__ __forceinline__ KernelArgs<Args>& fresh_kernel_args() {
-  auto p = (KernelArgs<Args>*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return *p;
-}
-
 // The same as a compile-time choice: read again (FRESH), or the argument itself.
 template <bool FRESH, typename Args>
 struct PickKernelArgs {

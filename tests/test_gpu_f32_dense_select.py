@@ -98,3 +98,33 @@ def test_infinite_values(bq):
 @pytest.mark.parametrize("bq,bk", [(32, 64), (64, 32), (128, 128)])
 def test_lengths_per_sample(bq, bk):
     _check(*_qkv(3, 4, 2, 700, 64, seed=bq), bq, bk, lens=[700, 333, 1])
+
+
+# One wave ranks the row that its work-group has just pooled, with at most 256 work-groups, 256 key blocks and 64 rows a block;
+# beyond, a launch of its own does.
+@pytest.mark.parametrize("nkb,bq,bk,D", [(1, 32, 32, 64), (2, 128, 128, 128), (63, 32, 32, 64), (64, 64, 32, 128), (65, 32, 32, 128),
+                                         (42, 32, 32, 128), (43, 32, 32, 128), (130, 64, 32, 64), (256, 32, 32, 64), (257, 32, 32, 64)])
+@pytest.mark.parametrize("rho", [0.05, 0.5, 1.0])
+def test_kept_blocks_are_the_highest_of_the_returned_scores(nkb, bq, bk, D, rho):
+    L = nkb * bk - 3
+    B, H = (3, 2) if nkb < 60 else (1, 1)   # 6 times 42 work-groups rank, 6 times 43 do not; one sample of 256 does
+    g = torch.Generator().manual_seed(nkb)
+    q, k, v = (torch.randn(B, H, L, D, generator=g).cuda() for _ in range(3))
+    if nkb > 2:
+        k[:, :, bk:2 * bk] = k[:, :, :bk]   # equal blocks: ties
+    nqb = -(-L // bq)
+    lens = torch.tensor([L, max(1, L // 2), 1] if B == 3 else [L * 2 // 3], dtype=torch.int32, device="cuda")
+    for seq_lens in (None, lens):
+        pooled = torch.zeros(B, H, nqb, nkb, dtype=torch.float32, device="cuda")
+        index = sd.BlockIndex(torch.full((B, H, nqb + 1), -7, dtype=torch.int32, device="cuda"),
+                              torch.full((B, H, nqb * sd.kept_blocks(rho, nkb)), -7, dtype=torch.int32, device="cuda"), bq, bk, nkb)
+        sd.attn_dense_select(q, k, v, bq, bk, rho, pooled_out=pooled, index=index, seq_lens=seq_lens)
+        rp, ci, scores = index.row_ptr.cpu(), index.col_idx.cpu(), pooled.cpu()
+        for b in range(B):
+            n = L if seq_lens is None else int(lens[b])
+            blocks, rows = -(-n // bk), -(-n // bq)
+            keep = sd.kept_blocks(rho, blocks)
+            assert rp[b, 0].tolist() == [min(i, rows) * keep for i in range(nqb + 1)]
+            assert torch.equal(rp[b], rp[b, :1].expand(H, -1))
+            best = torch.sort(-scores[b, :, :rows, :blocks], dim=2, stable=True).indices[..., :keep].sort(dim=2).values
+            assert torch.equal(ci[b, :, :rows * keep].view(H, rows, keep).long(), best)
