@@ -163,7 +163,10 @@ __device__ __forceinline__ int krow_perm(int i) { return (i & ~12) | ((i & 4) <<
 // The same descriptor as make_rsrc's (below) as four words. Copies through it are written out, so that the compiler does not
 // know that they are in flight and what they write: the caller waits for them itself before any read of the tile, and for
 // its reads before it asks for another. They return nothing in registers, and what they need is read when they are
-// issued. A kernel uses one kind or the other: both set m0, and the compiler may keep a value there between its own.
+// issued. What the compiler would otherwise see to is in the blocks themselves: five wait states between a vector
+// instruction that writes a scalar register (a spilled one is restored by such an instruction) and a load that reads it, one
+// between a write of m0 and a load that uses it. A kernel uses one kind of copy or the other: both set m0, which the compiler
+// reserves (it cannot be named as overwritten), and it may keep a value there between its own.
 typedef u32x4 UntrackedRsrc;
 __device__ __forceinline__ UntrackedRsrc untracked_rsrc(const void* base, int64_t bytes) {
   const uint64_t p = reinterpret_cast<uint64_t>(base);
@@ -181,10 +184,34 @@ __device__ __forceinline__ void lds_load_16(__amdgpu_buffer_rsrc_t rsrc, char* d
 }
 __device__ __forceinline__ void lds_load_16(const UntrackedRsrc& rsrc, char* dst, int32_t lane_offset, int32_t offset) {
   const uint32_t at = (uint32_t)(uintptr_t)(SPARSED_LDS char*)dst;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
                : "s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(lane_offset), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(offset))
                : "memory");
+}
+// Four of them in one block, to dst, dst + PIECE, ...: a row of bytes each that begins `step` further on, at one lane offset.
+template <int PIECE>
+__device__ __forceinline__ void lds_load_16_x4(const UntrackedRsrc& rsrc, char* dst, int32_t lane_offset, int32_t offset, int32_t step) {
+  const uint32_t at = (uint32_t)(uintptr_t)(SPARSED_LDS char*)dst;
+  int32_t from = __builtin_amdgcn_readfirstlane(offset);
+#define SPARSED_NEXT_COPY "\n\ts_add_u32 m0, m0, %5\n\ts_add_u32 %0, %0, %4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds" SPARSED_NEXT_COPY SPARSED_NEXT_COPY SPARSED_NEXT_COPY
+               : "+&s"(from)
+               : "s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(lane_offset), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(step)), "i"(PIECE)
+               : "memory", "scc");
+#undef SPARSED_NEXT_COPY
+}
+// The same from one place, at a lane offset each.
+template <int PIECE>
+__device__ __forceinline__ void lds_load_16_x4(const UntrackedRsrc& rsrc, char* dst, const int32_t* lane_offset, int32_t offset) {
+  const uint32_t at = (uint32_t)(uintptr_t)(SPARSED_LDS char*)dst;
+#define SPARSED_NEXT_COPY(V) "\n\ts_add_u32 m0, m0, %7\n\ts_nop 0\n\tbuffer_load_dwordx4 " V ", %1, %2 offen lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %3, %1, %2 offen lds" SPARSED_NEXT_COPY("%4") SPARSED_NEXT_COPY("%5") SPARSED_NEXT_COPY("%6")
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)at)), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(offset)), "v"(lane_offset[0]),
+                 "v"(lane_offset[1]), "v"(lane_offset[2]), "v"(lane_offset[3]), "i"(PIECE)
+               : "memory", "scc");
+#undef SPARSED_NEXT_COPY
 }
 
 // Direct global -> LDS copy of one [64][D] bf16 tile by NT threads (NT/64 waves). Per-lane byte
@@ -287,6 +314,17 @@ struct TileDma {
   template <typename Rsrc>
   __device__ __forceinline__ void issue(Rsrc rsrc, int32_t tile_byte_offset, char* lds_tile,
                                         int wave_in_group) const {
+    if constexpr (__is_same(Rsrc, UntrackedRsrc)) {
+      constexpr int kPiece = IS_V ? 1024 : KLayout<D>::kPieceBytes;
+      static_assert(kPerWave % 4 == 0, "blocks of four");
+#pragma unroll
+      for (int u = 0; u < kPerWave; u += 4) {
+        char* dst = lds_tile + lds_piece_offset(wave_in_group * kPerWave + u);
+        if constexpr (kUniformStep) lds_load_16_x4<kPiece>(rsrc, dst, goff[0], tile_byte_offset + u * step, step);
+        else lds_load_16_x4<kPiece>(rsrc, dst, goff + u, tile_byte_offset);
+      }
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) {
       char* dst = lds_tile + lds_piece_offset(wave_in_group * kPerWave + u);
