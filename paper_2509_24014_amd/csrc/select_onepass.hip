@@ -255,10 +255,31 @@ __global__ __launch_bounds__(KS * 256) __attribute__((amdgpu_waves_per_eu(4, 4))
         run_sum[run * QT + at] = ltot;
       }
       __syncthreads();
-      const float m0 = run_sum[at] == 0.f ? -3e38f : run_max[at], m1 = run_sum[QT + at] == 0.f ? -3e38f : run_max[QT + at];
-      const float m = fmaxf(m0, m1);
+      const float l0 = run_sum[at], l1 = run_sum[QT + at];
+      const float m0 = l0 == 0.f ? -3e38f : run_max[at], m1 = l1 == 0.f ? -3e38f : run_max[QT + at];
+      const float m = fmaxf(m0, m1), mine = run ? m1 : m0;
       const float a0 = __builtin_amdgcn_exp2f(m0 - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
-      weight = (run ? a1 : a0) / (run_sum[at] * a0 + run_sum[QT + at] * a1);
+      weight = (run ? a1 : a0) / (l0 * a0 + l1 * a1);
+      // A run's later logits may lie up to 100 octaves above its reference before that is raised, so its sums can count beside
+      // the other run's where the factor between the references alone is near or below the smallest float. Rows whose
+      // references are that far apart (out of line, practically never) take it in two steps, their parked sums right here.
+      const bool apart = l0 != 0.f && l1 != 0.f && fabsf(m0 - m1) > 100.f;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(apart) != 0, 0)) {
+        const float h = __builtin_amdgcn_exp2f(0.5f * (mine - m)), h0 = __builtin_amdgcn_exp2f(0.5f * (m0 - m)),
+                    h1 = __builtin_amdgcn_exp2f(0.5f * (m1 - m));
+        if (apart) {
+          weight = 1.0f / (l0 * h0 * h0 + l1 * h1 * h1);
+          M = m;
+        }
+        const int cols = BK == kTileK / 2 ? 2 * n : BK == kTileK ? n : (n + 1) >> 1;
+        wait_vector_memory();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // this wave's parked sums have been written
+        if (apart && mine < m)
+          for (int J = lane_e >> 5; J < cols; J += 2) {
+            float* const e = slab + (int64_t)J * QT + at;
+            *e = *e * h * h;
+          }
+      }
     }
     const bool splits = ae.part != nullptr && L > ae.boundary;
     if (splits) {

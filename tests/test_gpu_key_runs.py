@@ -50,3 +50,46 @@ def test_a_logit_far_above_the_others_in_either_run(D, where):
     want = torch.zeros_like(out)
     want[..., where // b] = 1 / b
     assert torch.allclose(out, want, rtol=5e-6, atol=1e-30)
+
+
+@pytest.mark.parametrize("D,bq,bk", [(64, 64, 64), (128, 128, 128), (64, 32, 32), (128, 64, 128)])
+@pytest.mark.parametrize("run,low,high", [(0, -130, -35), (1, -130, -35), (1, -180, -90), (0, -180, -90), (1, -250, -155)])
+def test_scores_of_a_run_whose_reference_is_far_below(run, low, high, D, bq, bk):
+    """One run begins 130 octaves or more below the other, its reference with it, and climbs by 90 to 95, too little for the
+    reference to be raised: the factor between the references is below the smallest float, the scores are not. Also the two
+    parts of a boundary block among the keys that climb."""
+    L = 1601 if bk < 128 else 1600 + 65   # the first run is 14 tiles, keys 0 .. 895
+    octaves = torch.zeros(L)
+    begin = 896 * run
+    octaves[begin:L if run else 896] = low
+    octaves[begin + 400:begin + 600] = high
+    q, k = torch.zeros(1, 2, L, D), torch.zeros(1, 2, L, D)
+    q[..., 0] = 8
+    k[0, :, :, 0] = octaves / 1.4426950408889634 * D ** 0.5 / 8
+    q, k = q.bfloat16().to(DEV), k.bfloat16().to(DEV)
+    nqb, nkb = -(-L // bq), -(-L // bk)
+    p = torch.softmax(q[0, 0, :1].double() @ k[0, 0].double().t() / D ** 0.5, 1)[0]
+    want = torch.stack([p[J * bk:(J + 1) * bk].mean() for J in range(nkb)])
+    out = torch.zeros(1, 2, nqb, nkb, device=DEV)
+    ix = sd.select_pattern(q, k, bq, bk, 0.5, pooled_out=out)
+    # arguments of up to 250 octaves are carried to 2^-24 of that, at three roundings: 250 * 3 * 2^-24 * ln 2 = 3.1e-5
+    held = want > 1e-34
+    assert held.sum() >= nkb // 2 and ((out.double() - want).abs() / want)[..., held].max() < 4e-5
+    assert (out[..., ~held] < 1e-33).all()
+    keep = sd.kept_blocks(0.5, nkb)
+    cut = want.sort(descending=True).values[keep - 1]
+    if cut > 1e-34:
+        assert (want[ix.col_idx.view(1, 2, nqb, keep).long()] >= cut * (1 - 1e-4)).all()
+    token = begin + 500 + 5   # inside a key block, among the keys that climb
+    js = token // bk
+    parts = [p[js * bk:token].mean(), p[token:(js + 1) * bk].mean()]
+    ix = sd.select_pattern_isolated_tokens(q, k, bq, bk, 0.5, token)
+    sd.index_validate(ix)
+    first = torch.cat([want[:js], parts[0][None]])
+    kept = sd.kept_blocks(0.5, js + 1)
+    rows = ix.row_ptr[0, 0].tolist()
+    for I in range(nqb):
+        row = ix.col_idx[0, 0, rows[I]:rows[I + 1]].tolist()
+        mine = [j for j in row if j < js]
+        floor = first.sort(descending=True).values[kept - 1]
+        assert all(want[j] >= floor * (1 - 1e-4) for j in mine)
