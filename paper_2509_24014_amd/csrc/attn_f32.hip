@@ -260,12 +260,21 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
             for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
         }
       }
-      float part = 0.f;
+      float part = 0.f, least = 0.f;
 #pragma unroll
       for (int x = 0; x < 16; ++x) {
-        s[x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[x], c, -M));
-        part += s[x];
+        s[x] = __builtin_fmaf(s[x], c, -M);
+        if (kHasV) least = fminf(least, s[x]);
       }
+      if (!kHasV || __builtin_expect(__builtin_amdgcn_ballot_w64(least < -126.f) == 0, 1)) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) s[x] = __builtin_amdgcn_exp2f(s[x]);
+      } else {  // masked keys, or probabilities that the instruction alone would give as zero
+#pragma unroll
+        for (int x = 0; x < 16; ++x) s[x] = exp2f(s[x]);
+      }
+#pragma unroll
+      for (int x = 0; x < 16; ++x) part += s[x];
       lsum += part;
       if (kPool) {
         block_sum += part;

@@ -128,3 +128,23 @@ def test_kept_blocks_are_the_highest_of_the_returned_scores(nkb, bq, bk, D, rho)
             assert torch.equal(rp[b], rp[b, :1].expand(H, -1))
             best = torch.sort(-scores[b, :, :rows, :blocks], dim=2, stable=True).indices[..., :keep].sort(dim=2).values
             assert torch.equal(ci[b, :, :rows * keep].view(H, rows, keep).long(), best)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bq,H", [(64, 2), (128, 40)])   # head counts at which one kernel does both
+def test_scores_below_the_smallest_normal_number_are_ranked(bq, H, D):
+    """Blocks whose probabilities lie 130 to 146 octaves below the row's largest, the later the larger: their scores are subnormal
+    numbers, and the largest of them is kept, not the first."""
+    L, bk = 512, 64
+    q, k, v = _qkv(1, H, H, L, D, seed=bq + D, scale=0.01)
+    q[..., 0], k[..., 0] = 8.0, 0.0
+    k[:, :, 256:, 0] = -torch.linspace(146, 130, 256) * math.log(2) * D ** 0.5 / 8
+    pooled = torch.zeros(1, H, L // bq, 8, device=DEV)
+    _, ix = sd.attn_dense_select(q.to(DEV), k.to(DEV), v.to(DEV), bq, bk, 0.625, pooled_out=pooled)
+    p = torch.softmax(q.double() @ k.double().transpose(2, 3) / math.sqrt(D), 3)
+    want = p.view(1, H, L // bq, bq, 8, bk).mean((3, 5))
+    # a subnormal number is a multiple of 2^-149: the mean is rounded there once, its terms (relative to a row's reference, up to
+    # 2^9 times as large) before; and the arguments as in every row
+    assert ((pooled.cpu().double() - want).abs() <= 2.0 ** -148 + 2e-3 * want).all()
+    assert (want[..., 7] > 2.0 ** -143).all()
+    assert (ix.col_idx.cpu().view(1, H, L // bq, 5) == torch.tensor([0, 1, 2, 3, 7])).all()
