@@ -62,6 +62,7 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
   static_assert(!kPool || (kTileBytes <= PoolLdsF32<D, RW>::kBytes && RW * kQBytes + kKBytes == PoolLdsF32<D, RW>::kUsed), "layout");
   f32x2f* const parked = reinterpret_cast<f32x2f*>(lds + (kPool ? PoolLdsF32<D, RW>::kUsed : 0));
   __shared__ float stat_m[NW][32], stat_l[NW][32];
+  __shared__ int verdicts[SPLIT_FIRST ? NW : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -130,6 +131,8 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
   const float* const qhead = static_cast<const float*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
 
   char* const qlds = lds + rw * kQBytes;
+  bool queries_outside = false;  // some query value of this wave's share (SplitRange)
+  uint32_t v_top = 0;            // bits of the largest |V| of tiles with probabilities below 2^-108 (tile_f32.hpp)
 
   // The wave's share of the tile list. SPLIT: on the bf16 matrix instruction; else on the fp32 one.
   auto walk = [&](auto split_tag) __attribute__((always_inline)) {
@@ -139,14 +142,18 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
       const int row = row0 + j < L ? row0 + j : L - 1;
       const float* qrow = qhead + (int64_t)row * a.q.sl + 4 * g;
       if constexpr (SPLIT) {
+        SplitRange range;
         for (int s2 = kw; s2 < kSteps; s2 += KW) {
           const f32x4 lo = *reinterpret_cast<const f32x4*>(qrow + 16 * s2), hi = *reinterpret_cast<const f32x4*>(qrow + 16 * s2 + 8);
           const Split8 w = split8(lo, hi);
+          range.add(lo);
+          range.add(hi);
           u32x4f* const dst = reinterpret_cast<u32x4f*>(qlds) + s2 * 3 * 64 + lane;
           dst[0] = w.h;
           dst[64] = w.m;
           dst[128] = w.l;
         }
+        queries_outside = __builtin_amdgcn_ballot_w64(range.outside()) != 0;
       } else {
         for (int ch = kw; ch < kChunks; ch += KW)
           *reinterpret_cast<f32x4*>(qlds + (ch * 64 + lane) * 16) = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);
@@ -266,12 +273,23 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
         s[x] = __builtin_fmaf(s[x], c, -M);
         if (kHasV) least = fminf(least, s[x]);
       }
-      if (!kHasV || __builtin_expect(__builtin_amdgcn_ballot_w64(least < -126.f) == 0, 1)) {
+      if (!kHasV || __builtin_expect(__builtin_amdgcn_ballot_w64(least < (SPLIT ? -108.f : -126.f)) == 0, 1)) {
 #pragma unroll
         for (int x = 0; x < 16; ++x) s[x] = __builtin_amdgcn_exp2f(s[x]);
       } else {  // masked keys, or probabilities that the instruction alone would give as zero
 #pragma unroll
         for (int x = 0; x < 16; ++x) s[x] = exp2f(s[x]);
+        if constexpr (SPLIT && kHasV) {
+          float top = 0.f;
+#pragma unroll
+          for (int x = 0; x < 16; ++x)
+#pragma unroll
+            for (int dt = 0; dt < kV; ++dt) top = fmaxf(top, fabsf(vf[x][dt]));
+#pragma unroll
+          for (int d = 32; d >= 1; d >>= 1) top = fmaxf(top, __shfl_xor(top, d, 64));
+          const uint32_t bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(top));
+          v_top = bits > v_top ? bits : v_top;
+        }
       }
 #pragma unroll
       for (int x = 0; x < 16; ++x) part += s[x];
@@ -335,14 +353,38 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     walk(std::false_type{});
   } else {
     walk(std::true_type{});
-    float probe = 0.f * lsum;  // not a number if any sum of this wave is infinite or not a number
+    // Whether this wave's results may show what the parts do not carry (tile_f32.hpp), and, for all waves together, whether any
+    // sum is not zero. In doubled bits less one, zero comes last and what is not finite before it.
+    constexpr int kRepeat = 1, kHasSums = 2, kHasKeys = 4;
+    bool repeat = queries_outside || !(lsum < __builtin_inff());
+    uint32_t low = ~0u, high = 0;
     if (kHasV) {
 #pragma unroll
       for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
-        for (int x = 0; x < 16; ++x) probe = __builtin_fmaf(o[dt][x], 0.f, probe);
+        for (int x = 0; x < 16; ++x) {
+          const uint32_t u = (__float_as_uint(o[dt][x]) << 1) - 1u;
+          low = u < low ? u : low;
+          high = u > high ? u : high;
+        }
+      const float good = fmaxf(0x1p-90f, __uint_as_float(v_top) * 0x1p-92f);  // the least sum that is good
+      repeat = repeat || low < (__float_as_uint(good) << 1) - 1u;
+      if (__builtin_expect(high >= 0xff000000u - 1u, 0)) {
+        float probe = 0.f;  // not a number if any sum is infinite or not a number
+#pragma unroll
+        for (int dt = 0; dt < kV; ++dt)
+#pragma unroll
+          for (int x = 0; x < 16; ++x) probe = __builtin_fmaf(o[dt][x], 0.f, probe);
+        repeat = repeat || probe != probe || good >= 0x1p-60f;
+      }
     }
-    if (__builtin_expect(__syncthreads_or(probe != probe), 0)) walk(std::false_type{});
+    int verdict = (__builtin_amdgcn_ballot_w64(repeat) != 0 ? kRepeat : 0) | (__builtin_amdgcn_ballot_w64(low != ~0u) != 0 ? kHasSums : 0) |
+                  (kHasV && __builtin_amdgcn_ballot_w64(lsum > 0.f) != 0 ? kHasKeys : 0);
+    if (lane == 0) verdicts[wave] = verdict;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) verdict |= verdicts[w];
+    if (__builtin_expect((verdict & kRepeat) || (verdict & (kHasSums | kHasKeys)) == kHasKeys, 0)) walk(std::false_type{});
   }
 
   // Merge the waves' parts: O = sum_w O_w 2^(M_w - M) / sum_w l_w 2^(M_w - M), M = max_w M_w.

@@ -259,18 +259,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const float c = a.scale_log2;
 
   // The wave's key blocks of all segments. SPLIT: on the bf16 matrix instruction; else on the fp32 one. Returns whether some
-  // sum of this lane is infinite or not a number.
+  // sum of this lane is infinite or not a number, or the logits may be short of bits (tile_f32.hpp).
   auto walk = [&](auto split_tag) __attribute__((always_inline)) -> bool {
     constexpr bool SPLIT = decltype(split_tag)::value;
     f32x4 kf[SPLIT ? 1 : kChunks], qf[SPLIT ? 1 : kChunks];
     Split8 qs[SPLIT ? kSteps : 1];
     float probe = 0.f;
     if constexpr (SPLIT) {
+      SplitRange range;
 #pragma unroll
       for (int s2 = 0; s2 < kSteps; ++s2) {
         const f32x4 lo = *reinterpret_cast<const f32x4*>(qrow + 16 * s2), hi = *reinterpret_cast<const f32x4*>(qrow + 16 * s2 + 8);
         qs[s2] = split8(lo, hi);
+        range.add(lo);
+        range.add(hi);
       }
+      if (range.outside()) probe = __builtin_nanf("");
     } else {
 #pragma unroll
       for (int ch = 0; ch < kChunks; ++ch) qf[ch] = *reinterpret_cast<const f32x4*>(qrow + 8 * ch);

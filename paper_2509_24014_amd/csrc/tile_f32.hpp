@@ -11,9 +11,17 @@
 // to at most 2^-17 of the whole (h h, h m, m h, m m, h l, l h); the three left out are below 2^-26 of it, a quarter of half
 // an fp32 unit in the last place. Six bf16 instructions take 192 cycles for what the fp32 one takes 512, and their sums are
 // rounded less often: error against 64 bits see attn_f32.hip. An operand that is infinite, not a number or beyond the
-// largest bf16 number splits into parts that are not numbers; a work-group that ends with a sum that is not finite does its
-// work again on the fp32 instruction, so such inputs give what they give there. The instruction takes parts below 2^-126 as
-// zero: a value is carried to 2^-26 of itself or to 2^-126, whichever is more.
+// largest bf16 number splits into parts that are not numbers; and parts end at 2^-133, so a value is carried to 2^-26 of itself
+// or to 2^-134, whichever is more. A work-group whose results either may show does its work again on the fp32 instruction, so
+// such inputs give what they give there. It can tell at little cost:
+//   logits  A query value below 2^-108 (and not zero) is short of bits, and one of 2^80 or more would show that a key value is
+//           (SplitRange, where the queries are split); with neither, a logit is off by 2^-47 at most.
+//   output  Probabilities add up to 2^-134 of an error for every value of V. A sum below 2^-90 (and not zero) may show it; so
+//           may one where every sum of the work-group is zero. Probabilities below 2^-108 of the row's largest are short of bits
+//           themselves; a tile that has any notes the largest value of V there, and the least sum that is good rises to 2^-92
+//           of it (2^16 keys that are off by 2^-134 each, 2^-26 of the sum). A sum of zero may be a column of zeros and is
+//           taken as it is, unless V has values of 2^32 or more at such probabilities.
+// What remains: a column of V whose values are all below 2^-126, beside larger columns, gives zeros.
 //
 // K and V go from global memory straight into the registers that feed the matrix cores: the vector memory path delivers
 // them with room to spare, and nothing is gained by passing a tile through LDS (and a barrier) to reorder it. Both products
@@ -85,6 +93,21 @@ __device__ __forceinline__ Split8 split8(f32x4 lo, f32x4 hi) {
   w.pair(3, hi[2], hi[3]);
   return w;
 }
+// Whether values lie where their three parts stand for them to 2^-26 and products with parts that are cut off stay small.
+struct SplitRange {
+  static constexpr uint32_t kLeast = (127u - 108u) << 24;  // 2^-108, doubled bits
+  uint32_t low = ~0u;                                      // least doubled bits less one: zero comes last
+  float high = 0.f;
+  __device__ __forceinline__ void add(f32x4 v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t u = (__float_as_uint(v[e]) << 1) - 1u;
+      low = u < low ? u : low;
+      high = fmaxf(high, fabsf(v[e]));
+    }
+  }
+  __device__ __forceinline__ bool outside() const { return low < kLeast - 1u || !(high < 0x1p80f); }
+};
 // acc += A . B, the six products of the parts that matter, smallest first
 __device__ __forceinline__ f32x16 mfma_split(const Split8& a, const Split8& b, f32x16 acc) {
   auto mul = [&](const u32x4f& x, const u32x4f& y) {

@@ -93,3 +93,82 @@ def test_every_form_of_the_sparse_launch(H, keep, D):
     s = (q @ k.transpose(2, 3)).double() / math.sqrt(D)
     want = torch.softmax(s.masked_fill(~mask, -math.inf), dim=3) @ v.double()
     assert (out - want).abs().max() < 1e-5
+
+
+def _sparse_index(H, L, keep, seed):
+    n = -(-L // 64)
+    sel = torch.rand(1, H, n, n, generator=torch.Generator().manual_seed(seed)).topk(keep, 3).indices.sort(3).values
+    ix = sd.BlockIndex((torch.arange(n + 1, dtype=torch.int32) * keep).expand(1, H, n + 1).contiguous().to(DEV),
+                       sel.to(torch.int32).reshape(1, H, -1).contiguous().to(DEV), 64, 64, n)
+    mask = torch.zeros(1, H, n, n, dtype=torch.bool).scatter_(3, sel, True)
+    return ix, mask.repeat_interleave(64, 2).repeat_interleave(64, 3)[:, :, :L, :L]
+
+
+def _all_calls(q, k, v, keep=3):
+    """(output, exact output, sum of the magnitudes in it) of the dense, the dense and selecting and the sparse call."""
+    H, L, D = q.shape[1:]
+    qd, kd, vd = (t.to(DEV) for t in (q, k, v))
+    s = q.double() @ k.double().transpose(2, 3) / math.sqrt(D)
+    ix, mask = _sparse_index(H, L, keep, seed=L)
+    for got, logits in ((sd.attn_dense(qd, kd, vd), s), (sd.attn_dense_select(qd, kd, vd, 64, 64, 0.3)[0], s),
+                        (sd.attn_sparse(qd, kd, vd, ix), s.masked_fill(~mask, -math.inf))):
+        p = torch.softmax(logits, dim=3)
+        yield got.cpu().double(), p @ v.double(), p @ v.double().abs()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,L,keep", [(2, 300, 3), (20, 480, 3), (70, 480, 1)])   # 8 and 4 waves; with 1050 work-groups the sparse lists
+@pytest.mark.parametrize("e", [-95, -112, -118, -124, -130, -140])
+def test_small_values_keep_their_bits(e, H, L, keep, D):
+    """Values of V far below what three bf16 parts can hold in full (a part ends at 2^-133): to 1e-5 of the sum of magnitudes, as any
+    others, or to the resolution of subnormal numbers, 2^-149 (terms relative to sums of up to 2^9, and the result)."""
+    q, k, v = _qkv(H, L, D, seed=L + D)
+    v = (v * 2.0 ** -64) * 2.0 ** (e + 64)
+    for got, want, size in _all_calls(q, k, v, keep):
+        assert ((got - want).abs() <= 1e-5 * size + 2.0 ** -147).all()
+    v[..., 1::2] = torch.randn(v[..., 1::2].shape, generator=torch.Generator().manual_seed(e))   # beside ordinary columns
+    if e >= -118:
+        for got, want, size in _all_calls(q, k, v, keep):
+            assert ((got - want).abs() <= 1e-5 * size).all()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,L", [(2, 300), (20, 480)])
+@pytest.mark.parametrize("e", [100, 112, 120, 125, -112, -125])
+def test_logits_of_small_and_large_factors(e, H, L, D):
+    q, k, v = _qkv(H, L, D, seed=L + D)
+    q, k = q * 2.0 ** -e, k * 2.0 ** e
+    for got, want, size in _all_calls(q, k, v):
+        assert ((got - want).abs() <= 1e-5 * size).all()
+    p = _exact(q, k, v)[2]
+    n = -(-L // 64)
+    lse = torch.logsumexp(q.double() @ k.double().transpose(2, 3) / math.sqrt(D), dim=3).float().contiguous().to(DEV)
+    pooled = torch.zeros(1, H, n, n, device=DEV)
+    sd.select_pattern(q.to(DEV), k.to(DEV), 64, 64, 0.3, lse_in=lse, pooled_out=pooled)
+    whole = L // 64
+    want = p[:, :, :whole * 64, :whole * 64].view(1, H, whole, 64, whole, 64).mean((3, 5))
+    assert ((pooled.cpu().double()[:, :, :whole, :whole] - want).abs() <= 5e-6 * want).all()
+
+
+@pytest.mark.parametrize("octaves,e", [(60, 60), (100, 100), (115, 113), (125, 124), (130, 125), (140, 126)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_large_values_at_small_probabilities(octaves, e, D):
+    """One key far below the others whose values are as far above: its share of the sums is of their size."""
+    q, k, v = _qkv(2, 300, D, seed=D)
+    q[..., 0], k[..., 0] = 8.0, 0.0
+    q[..., 1:], k[..., 1:] = q[..., 1:] * 0.01, k[..., 1:] * 0.01
+    k[0, :, 70, 0] = -octaves * math.log(2) * D ** 0.5 / 8
+    v[0, :, 70] = 2.0 ** e
+    for got, want, size in _all_calls(q, k, v, keep=5):
+        # a subnormal probability is a multiple of 2^-149; its logit is carried to 2^-24 of 140 octaves at three roundings
+        assert ((got - want).abs() <= 3e-5 * size + 2.0 ** (e - 149)).all()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_columns_and_heads_of_zeros(D):
+    q, k, v = _qkv(2, 300, D, seed=D)
+    v[..., D // 2:] = 0
+    v[:, 1] = 0
+    for got, want, size in _all_calls(q, k, v):
+        assert not got[..., D // 2:].any() and not got[:, 1].any()
+        assert ((got - want).abs() <= 1e-5 * size).all()
