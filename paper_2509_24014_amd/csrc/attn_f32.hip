@@ -246,7 +246,11 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
       if (valid < kTileKF) {
 #pragma unroll
         for (int x = 0; x < 16; ++x)
-          if (8 * (x / 4) + 4 * g + (x % 4) >= valid) s[x] = -__builtin_inff();
+          if (8 * (x / 4) + 4 * g + (x % 4) >= valid) {
+            s[x] = -__builtin_inff();
+            // (a row past the end mostly reads as zeros, but where a few rows are 16 MB and more apart its offset wraps)
+            if (kHasV) vf[x] = VRow{};
+          }
       }
       // The row's reference M stays within an octave of its maximum: probabilities stay at or below 2, and the output is
       // rescaled for the few tiles that raise a row's maximum by more.

@@ -134,8 +134,9 @@ __device__ __forceinline__ void sched_split_interleave() {
 }
 
 // A (batch, head) slab of K or V and this lane's way of reading 32-key tiles of it, through a buffer descriptor that ends with
-// the slab: rows at or past its end (a tile at the end of the sequence, or wholly past it) read as zeros; the caller masks
-// their logits. Offsets stay below 2^32: a slab is below 2^31 bytes, and a tile begins at most a key block past its end.
+// the slab: rows at or past its end (a tile at the end of the sequence, or wholly past it) read as zeros, unless the rows are so
+// far apart that their 32-bit offsets wrap; they then read as something inside the slab. The caller masks their logits and
+// clears their V.
 template <int D>
 struct SlabF32 {
   __amdgpu_buffer_rsrc_t rsrc;

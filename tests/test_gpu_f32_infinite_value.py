@@ -25,3 +25,25 @@ def test_tiles_past_the_end_add_nothing_to_an_infinite_row(L, bk, D):
     p = torch.softmax(q.double() @ k.double().transpose(2, 3) / math.sqrt(D), dim=3)
     want = p @ v.double().nan_to_num(posinf=0.0, neginf=0.0)
     assert (out[..., 2:] - want[..., 2:]).abs().max() < 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L,stride", [(5, 2**27 - 64), (17, 2**25 - 64)])
+def test_rows_far_apart_with_anything_between_them(L, stride, D):
+    """Rows half a GB or 128 MB apart: the offsets of rows past the end wrap around 32 bits and land between those that exist."""
+    store = torch.full(((L - 1) * stride + D,), math.nan, device=DEV)
+    far = store.as_strided((1, 1, L, D), (store.numel() // 4 * 4, store.numel() // 4 * 4, stride, 1))
+    g = torch.Generator().manual_seed(L)
+    q, k, v = (torch.randn(1, 1, L, D, generator=g).to(DEV) for _ in range(3))
+    want = torch.softmax(q.double() @ k.double().transpose(2, 3).contiguous() / math.sqrt(D), dim=3)
+    for which in range(2):
+        far.copy_(v if which else k)
+        kk, vv = (k, far) if which else (far, v)
+        ix = sd.BlockIndex(torch.tensor([[[0, 1]]], dtype=torch.int32, device=DEV), torch.zeros(1, 1, 1, dtype=torch.int32, device=DEV), 128, 128, 1)
+        pooled = torch.zeros(1, 1, 1, 1, device=DEV)
+        for out in (sd.attn_dense(q, kk, vv), sd.attn_sparse(q, kk, vv, ix), sd.attn_dense_select(q, kk, vv, 128, 128, 1.0, pooled_out=pooled)[0]):
+            assert (out.double() - want @ v.double()).abs().max() < 1e-5
+        assert abs(pooled.item() * L - 1) < 1e-5
+        pooled.zero_()
+        sd.select_pattern(q, kk, 128, 128, 1.0, pooled_out=pooled)
+        assert abs(pooled.item() * L - 1) < 1e-5
