@@ -240,6 +240,12 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
           kf[ch] = ks.k_chunk(off_next, ch);
         }
       }
+      // this lane's least logit, of keys that do not exist as well (rows that mostly read as zeros)
+      float least = fminf(s[0], s[1]);
+      if (kHasV) {
+#pragma unroll
+        for (int x = 2; x < 16; x += 2) least = fminf(fminf(least, s[x]), s[x + 1]);
+      }
       // keys of this tile that exist: fewer than 32 at the end of a sequence whose length is not a multiple of the tile,
       // none in the later tiles of a partial last key block
       const int valid = L - key;
@@ -248,7 +254,7 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
         for (int x = 0; x < 16; ++x)
           if (8 * (x / 4) + 4 * g + (x % 4) >= valid) {
             s[x] = -__builtin_inff();
-            // (a row past the end mostly reads as zeros, but where a few rows are 16 MB and more apart its offset wraps)
+            // (a row past the end mostly reads as zeros, but where rows are 16 MB and more apart its offset wraps)
             if (kHasV) vf[x] = VRow{};
           }
       }
@@ -271,16 +277,13 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
             for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
         }
       }
-      float part = 0.f, least = 0.f;
+      float part = 0.f;
 #pragma unroll
-      for (int x = 0; x < 16; ++x) {
-        s[x] = __builtin_fmaf(s[x], c, -M);
-        if (kHasV) least = fminf(least, s[x]);
-      }
-      if (!kHasV || __builtin_expect(__builtin_amdgcn_ballot_w64(least < (SPLIT ? -108.f : -126.f)) == 0, 1)) {
+      for (int x = 0; x < 16; ++x) s[x] = __builtin_fmaf(s[x], c, -M);
+      if (!kHasV || __builtin_expect(__builtin_amdgcn_ballot_w64(__builtin_fmaf(least, c, -M) < (SPLIT ? -108.f : -126.f)) == 0, 1)) {
 #pragma unroll
         for (int x = 0; x < 16; ++x) s[x] = __builtin_amdgcn_exp2f(s[x]);
-      } else {  // masked keys, or probabilities that the instruction alone would give as zero
+      } else {  // probabilities that the instruction alone would give as zero, or that three parts do not hold whole
 #pragma unroll
         for (int x = 0; x < 16; ++x) s[x] = exp2f(s[x]);
         if constexpr (SPLIT && kHasV) {
@@ -353,46 +356,60 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     }
     vector_memory_done_but_f<0>();  // the last copy into LDS, of a tile past the list, has landed
   };
+  auto leave_statistics = [&]() {
+    const float ltot = pair_sum_f(lsum);
+    if (g == 0) {
+      stat_m[wave][j] = M;
+      stat_l[wave][j] = ltot;
+    }
+  };
   if constexpr (!SPLIT_FIRST) {
     walk(std::false_type{});
+    leave_statistics();
+    __syncthreads();  // everyone is done with the query fragments
   } else {
     walk(std::true_type{});
     // Whether this wave's results may show what the parts do not carry (tile_f32.hpp), and, for all waves together, whether any
-    // sum is not zero. In doubled bits less one, zero comes last and what is not finite before it.
+    // sum is not zero.
     constexpr int kRepeat = 1, kHasSums = 2, kHasKeys = 4;
-    bool repeat = queries_outside || !(lsum < __builtin_inff());
-    uint32_t low = ~0u, high = 0;
+    float least = __builtin_inff(), probe = 0.f * lsum;  // probe: not a number if any sum is infinite or not a number
+    bool small = false, sums = false;
     if (kHasV) {
 #pragma unroll
       for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
         for (int x = 0; x < 16; ++x) {
-          const uint32_t u = (__float_as_uint(o[dt][x]) << 1) - 1u;
-          low = u < low ? u : low;
-          high = u > high ? u : high;
+          probe = __builtin_fmaf(o[dt][x], 0.f, probe);
+          least = fminf(least, fabsf(o[dt][x]));
         }
       const float good = fmaxf(0x1p-90f, __uint_as_float(v_top) * 0x1p-92f);  // the least sum that is good
-      repeat = repeat || low < (__float_as_uint(good) << 1) - 1u;
-      if (__builtin_expect(high >= 0xff000000u - 1u, 0)) {
-        float probe = 0.f;  // not a number if any sum is infinite or not a number
+      small = least < good;
+      sums = least > 0.f;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 0.f) != 0, 0)) {  // the least of those that are not zero
+        float next = __builtin_inff();
 #pragma unroll
         for (int dt = 0; dt < kV; ++dt)
 #pragma unroll
-          for (int x = 0; x < 16; ++x) probe = __builtin_fmaf(o[dt][x], 0.f, probe);
-        repeat = repeat || probe != probe || good >= 0x1p-60f;
+          for (int x = 0; x < 16; ++x) next = fminf(next, o[dt][x] == 0.f ? __builtin_inff() : fabsf(o[dt][x]));
+        small = next < good || (least == 0.f && good >= 0x1p-60f);
+        sums = next < __builtin_inff();
       }
     }
-    int verdict = (__builtin_amdgcn_ballot_w64(repeat) != 0 ? kRepeat : 0) | (__builtin_amdgcn_ballot_w64(low != ~0u) != 0 ? kHasSums : 0) |
-                  (kHasV && __builtin_amdgcn_ballot_w64(lsum > 0.f) != 0 ? kHasKeys : 0);
+    int verdict = (queries_outside || __builtin_amdgcn_ballot_w64(small || probe != probe) != 0 ? kRepeat : 0) |
+                  (__builtin_amdgcn_ballot_w64(sums) != 0 ? kHasSums : 0) | (kHasV && __builtin_amdgcn_ballot_w64(lsum > 0.f) != 0 ? kHasKeys : 0);
     if (lane == 0) verdicts[wave] = verdict;
-    __syncthreads();
+    leave_statistics();
+    __syncthreads();  // everyone is done with the query fragments
 #pragma unroll
     for (int w = 0; w < NW; ++w) verdict |= verdicts[w];
-    if (__builtin_expect((verdict & kRepeat) || (verdict & (kHasSums | kHasKeys)) == kHasKeys, 0)) walk(std::false_type{});
+    if (__builtin_expect((verdict & kRepeat) || (verdict & (kHasSums | kHasKeys)) == kHasKeys, 0)) {
+      walk(std::false_type{});
+      leave_statistics();
+      __syncthreads();
+    }
   }
 
   // Merge the waves' parts: O = sum_w O_w 2^(M_w - M) / sum_w l_w 2^(M_w - M), M = max_w M_w.
-  const float ltot = pair_sum_f(lsum);
   auto factors = [&](int group, int row, float (&f)[KW], float* m) -> float {  // every part's factor and the common maximum; returns l
     float mm = stat_m[group][row], l = 0.f;
 #pragma unroll
@@ -407,15 +424,9 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
   };
   TopkRow<4> row;
   row.lane = lane;
-  __syncthreads();  // everyone is done with the query fragments
-  if (g == 0) {
-    stat_m[wave][j] = M;
-    stat_l[wave][j] = ltot;
-  }
   if constexpr (kPool) {
     // A'[I, J] = sum over the rows of E 2^(M_parked - M) / l, divided by the entries that exist. A wave takes a key block (two
     // with 32 rows) at a time, a lane one row of it, or two; the lanes are added up in a fixed order.
-    __syncthreads();
     constexpr int kRowsPerLane = RW == 4 ? 2 : 1;
     float ref[kRowsPerLane], weight[kRowsPerLane];
     int at[kRowsPerLane];
