@@ -148,7 +148,7 @@ size_t select_tokens_extra_bytes(int B, int Hq, int nqb, int nkb) {
 }
 
 sparsed_status attention(Mode mode, const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v,
-                         const sparsed_block_index* ix, sparsed_tensor* out, const sparsed_exec* ex) {
+                         const sparsed_block_index* ix, sparsed_tensor* out, const sparsed_exec* ex, float* row_stat = nullptr) {
   sparsed_status st;
   if ((st = check_tensor(q, "q")) || (st = check_tensor(k, "k")) || (st = check_tensor(v, "v")) || (st = check_tensor(out, "out")))
     return st;
@@ -163,6 +163,7 @@ sparsed_status attention(Mode mode, const sparsed_tensor* q, const sparsed_tenso
   a.o_sh = out->stride_h;
   a.o_sl = out->stride_l;
   a.lse = (mode == Mode::kDense && ex) ? ex->lse_out : nullptr;
+  a.row_stat = row_stat;
   a.B = q->B;
   a.Hq = q->H;
   a.group = q->H / k->H;
@@ -187,10 +188,12 @@ sparsed_status attention(Mode mode, const sparsed_tensor* q, const sparsed_tenso
 }
 
 // boundary_token >= 0: isolated selection whose prefill / generation boundary is that key token and lies
-// strictly inside a key block (prefill_blocks is then ignored).
+// strictly inside a key block (prefill_blocks is then ignored). row_stat: statistics that a dense call left (AttnArgs), instead of
+// a log-sum-exp.
 sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int32_t bq, int32_t bk, double rho,
                            int32_t prefill_blocks, bool isolated, sparsed_block_index* ix, const sparsed_exec* ex,
-                           int32_t boundary_token = -1, char* fixed_scratch = nullptr, size_t fixed_scratch_bytes = 0) {
+                           int32_t boundary_token = -1, char* fixed_scratch = nullptr, size_t fixed_scratch_bytes = 0,
+                           const float* row_stat = nullptr) {
   sparsed_status st;
   if ((st = check_tensor(q, "q")) || (st = check_tensor(k, "k")) || (st = check_qk(q, k, "k"))) return st;
   if ((st = check_blocks(q, bq, bk))) return st;
@@ -271,7 +274,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
   if (slabs > (size_t)pool1p_groups(bq)) slabs = (size_t)pool1p_groups(bq);
   if (slabs > rows_total) slabs = rows_total;
   const size_t slabs_needed = rows_total < (size_t)kOnepassMinGroups ? rows_total : (size_t)kOnepassMinGroups;
-  if (!lse && bf16 && slabs >= slabs_needed) {
+  if (!lse && !row_stat && bf16 && slabs >= slabs_needed) {
     // 1 + 2. no log-sum-exp handed over: pooled scores A' (those of the two parts of the boundary block too) in one pass
     p.slab = reinterpret_cast<float*>(ws + need);
     p.slab_ld = onepass_slab_ld(nkb);
@@ -281,7 +284,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
     if (e != hipSuccess) return hip_fail(e, "one-pass pooled-score launch");
   } else {
     // 1. row log-sum-exp of Eq. 1's logits, unless the caller passes the one attn_dense produced
-    if (!lse) {
+    if (!lse && !row_stat) {
       AttnArgs a{};
       a.q = targ(q);
       a.k = targ(k);
@@ -298,6 +301,7 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
     }
     // 2. pooled scores A'
     p.lse = lse;
+    p.row_stat = row_stat;
     e = bf16 ? launch_pool_bf16(q->D, bq, p, s) : launch_pool_f32(q->D, bq, p, s);
     if (e != hipSuccess) return hip_fail(e, "pooled-score launch");
     if (straddle >= 0) {
@@ -397,12 +401,14 @@ sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* 
   DensePoolShape sh = dense_pool_shape(q->D, q->B, q->H, q->L, bk, 256);
   if (ex && ex->workspace && ex->workspace_bytes < bytes_of(sh)) sh = dense_pool_shape(q->D, q->B, q->H, q->L, bk, 128);
   if (bf16 && (st = caller_workspace(ex, bytes_of(sh), "dense step with selection", &ws))) return st;
-  if (bf16 && dense_then_pool(q) && ex->workspace_bytes >= select_ws_bytes(q->B, q->H, q->L, nqb, nkb)) {
+  // (the row statistics behind what the selection uses itself: from 3 key blocks on, and there are more, that fits `bytes_of`)
+  const size_t select_bytes = select_ws_bytes(q->B, q->H, q->L, nqb, nkb);
+  if (bf16 && dense_then_pool(q) && ex->workspace_bytes >= select_bytes + 2 * statistics_bytes) {
+    float* const row_stat = reinterpret_cast<float*>(ws + select_bytes);
     sparsed_exec step = *ex;
-    if (!step.lse_out) step.lse_out = reinterpret_cast<float*>(ws);
-    step.lse_in = step.lse_out;
-    if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step))) return st;
-    return select_impl(q, k, bq, bk, rho, 0, false, ix, &step);
+    step.lse_in = nullptr;
+    if ((st = attention(Mode::kDense, q, k, v, nullptr, out, &step, row_stat))) return st;
+    return select_impl(q, k, bq, bk, rho, 0, false, ix, &step, -1, nullptr, 0, row_stat);
   }
   AttnArgs a{};
   a.q = targ(q);

@@ -18,6 +18,7 @@ struct AttnArgs {
   void* o;
   int64_t o_sb, o_sh, o_sl;
   float* lse;              // optional [B, Hq, L]: natural-log sum-exp of each row's scaled logits
+  float* row_stat;         // optional [B, Hq, L, 2] (dense calls that splitk_takes): a row's reference in octaves, and 1 / its sum against that
   const int32_t* row_ptr;  // sparse only: [B, Hq, nqb + 1]
   const int32_t* col_idx;  // sparse only: [B, Hq, cap_per_head]
   int32_t B, Hq, group, L;  // group: query heads per key/value head
@@ -42,6 +43,7 @@ struct AttnArgs {
 struct PoolArgs {
   TensorArg q, k;
   const float* lse;        // [B, Hq, L] natural-log sum-exp of each row over ALL L keys
+  const float* row_stat;   // bf16: instead of lse, as AttnArgs::row_stat
   float* apool;            // [B, Hq, nqb, out_stride]; block t of the range lands in column t
   int32_t B, Hq, group, L;  // group: query heads per key/value head
   const int32_t* seq_lens; // optional [B] per-sample lengths (they cut the key ranges too)

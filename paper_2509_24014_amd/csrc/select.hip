@@ -88,8 +88,20 @@ void pool_bf16_kernel(const PoolArgs a) {
 
   QFrag<D, 1> qf;
   qf.load(qbase, row0, L, a.q.sl, lane);
-  // a query row past L (partial last query block) gets an infinite normaliser: all its terms are 0
-  const float lse2 = (row0 + j < L) ? a.lse[(int64_t)bh * a.L + row0 + j] * 1.4426950408889634f : __builtin_inff();
+  // What a term is relative to, and what the sums of a row are weighed by: its log-sum-exp and 1, or its reference and 1 / its sum
+  // where the dense call left those (the log-sum-exp, rounded to fp32, is off by 2^-24 of its size: 4 heads of 2048 x 128, scores
+  // to 4e-7 of themselves with it, to 5e-8 so). A query row past L (partial last query block): infinitely far, all its terms are 0.
+  float ref = __builtin_inff(), weight = 1.f;
+  if (row0 + j < L) {
+    const int64_t at = (int64_t)bh * a.L + row0 + j;
+    if (a.row_stat != nullptr) {
+      const f32x2 stat = *reinterpret_cast<const f32x2*>(a.row_stat + 2 * at);
+      ref = stat[0];
+      weight = stat[1];
+    } else {
+      ref = a.lse[at] * 1.4426950408889634f;
+    }
+  }
   float* arow = a.apool + ((int64_t)bh * a.nqb + I) * a.out_stride + first_col;
   const int rows_here = (L - I * kBlockRows < kBlockRows) ? L - I * kBlockRows : kBlockRows;  // query rows of the block that exist
   const int last_blk = (key_len - 1) / kTileK;
@@ -124,7 +136,8 @@ void pool_bf16_kernel(const PoolArgs a) {
     }
     float part = 0.f;
 #pragma unroll
-    for (int x = 0; x < 16; ++x) part += __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -lse2));
+    for (int x = 0; x < 16; ++x) part += __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -ref));
+    part *= weight;
     asm volatile("" : "+v"(part));  // keep the vector work inside the block that holds the matrix work
     return part;
   };

@@ -113,3 +113,24 @@ def test_a_workspace_of_the_smaller_shape_still_serves():
     assert (got.float() - want.float()).abs().max() < MAX
     with pytest.raises(sd.SparsedError):
         sd.attn_dense_select(q, k, v, bq, bk, 0.2, workspace=torch.empty(need - 256, dtype=torch.uint8, device=DEV))
+
+
+@pytest.mark.parametrize("H,L,D", [(4, 2048, 128), (8, 1000, 128), (4, 1000, 64), (16, 1000, 128), (4, 1000, 128)])
+@pytest.mark.parametrize("offset", [0, 14, 100])
+def test_scores_of_a_switch_step_as_two_kernels_keep_their_bits(H, L, D, offset):
+    """Logits with a common offset of up to 70 (100 octaves): a score is as good as without, where the row statistics go from the one
+    kernel to the other as where one kernel does both."""
+    q, k, v = _qkv(1, H, H, L, D, seed=L + D)
+    q, k = q * 0.5, k * 0.5
+    q[..., 0], k[..., 0] = 8, offset / 8 * D ** 0.5 / 1.4426950408889634
+    nb = -(-L // 64)
+    pooled = torch.zeros(1, H, nb, nb, device=DEV)
+    sd.attn_dense_select(q, k, v, 64, 64, 0.2, pooled_out=pooled)
+    p = _rows(q, k, v, 0, 0, torch.arange(L, device=DEV))[2]
+    pad = lambda x: torch.nn.functional.pad(x, (0, nb * 64 - L, 0, nb * 64 - L)).view(nb, 64, nb, 64).sum((1, 3))  # noqa: E731
+    want = pad(p) / pad(torch.ones_like(p))
+    # arguments are differences to the row's reference of some ten octaves, of fp32 logits that carry 2^-24 of up to 100 octaves each
+    # (an error of its own for every pair, averaged over 4096): 100 * 2^-24 * ln 2 / sqrt(4096) = 6e-8, and the sums' own 1e-7;
+    # a reference that were rounded like the logits would be off by 100 * 2^-24 * ln 2 = 4e-6 for a whole row
+    error = ((pooled[0, 0].double() - want) / want)[:L // 64, :L // 64]
+    assert error.pow(2).mean().sqrt() < 2.5e-7, error.pow(2).mean().sqrt()
