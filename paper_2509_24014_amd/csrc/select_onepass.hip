@@ -164,15 +164,20 @@ __global__ __launch_bounds__(KS * 256) __attribute__((amdgpu_waves_per_eu(4, 4))
     // maximum, rescale everything they have accumulated (tiles_done key tiles are complete), redo the sub-tile's sum.
     auto re_reference = [&](const f32x16(&s)[1], float& part, int tiles_done) {
       const float Mn = fmaxf(M, row_max(s));
-      const float alpha = __builtin_amdgcn_exp2f(M - Mn);  // <= 1; exactly 1 where nothing changes
+      // 2^(M - Mn) in two factors: the sums are up to 2^100, so that what is left of them counts where the one factor were zero
+      const float half = __builtin_amdgcn_exp2f(0.5f * (M - Mn));  // <= 1; exactly 1 where nothing changes
       M = Mn;
-      lsum *= alpha;
-      carry *= alpha;
-      hold *= alpha;
+      auto rescaled = [&](float x) -> float { return x * half * half; };
+      lsum = rescaled(lsum);
+      carry = rescaled(carry);
+      hold = rescaled(hold);
       const int cols = BK == kTileK / 2 ? 2 * tiles_done : BK == kTileK ? tiles_done & ~1 : tiles_done >> 1;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // this wave's parked sums have been written
-      if (alpha < 1.0f)  // (not for a NaN: the row is lost anyway)
-        for (int J = fresh_lane() >> 5; J < cols; J += 2) slab[(int64_t)J * QT + wave * 32 + (fresh_lane() & 31)] *= alpha;
+      if (half < 1.0f)  // (not for a NaN: the row is lost anyway)
+        for (int J = fresh_lane() >> 5; J < cols; J += 2) {
+          float* const e = slab + (int64_t)J * QT + wave * 32 + (fresh_lane() & 31);
+          *e = rescaled(*e);
+        }
       part = exp_sum(s);
     };
     auto overflowed = [&](float part) -> bool { return __builtin_amdgcn_ballot_w64(!(part < kOverflow)) != 0; };

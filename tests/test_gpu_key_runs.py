@@ -93,3 +93,26 @@ def test_scores_of_a_run_whose_reference_is_far_below(run, low, high, D, bq, bk)
         mine = [j for j in row if j < js]
         floor = first.sort(descending=True).values[kept - 1]
         assert all(want[j] >= floor * (1 - 1e-4) for j in mine)
+
+
+@pytest.mark.parametrize("D,bq,bk", [(64, 64, 64), (128, 128, 128), (64, 32, 32)])
+@pytest.mark.parametrize("L", [700, 1700])   # one run of keys, two
+@pytest.mark.parametrize("start", [-130, -150, -185])
+def test_parked_sums_far_above_a_reference_that_is_raised(start, L, D, bq, bk):
+    """Within one run: keys far below the others, then some 95 octaves above those, then the others: the reference is raised by 130
+    octaves or more, and the sums parked so far by 2^95 relative to it still count."""
+    octaves = torch.zeros(L)
+    octaves[:64], octaves[64:192], octaves[192:320] = start, start + 90, start + 95
+    q, k = torch.zeros(1, 1, L, D), torch.zeros(1, 1, L, D)
+    q[..., 0] = 8
+    k[0, 0, :, 0] = octaves / 1.4426950408889634 * D ** 0.5 / 8
+    q, k = q.bfloat16().to(DEV), k.bfloat16().to(DEV)
+    nkb = -(-L // bk)
+    p = torch.softmax(q[0, 0, :1].double() @ k[0, 0].double().t() / D ** 0.5, 1)[0]
+    want = torch.stack([p[J * bk:(J + 1) * bk].mean() for J in range(nkb)])
+    out = torch.zeros(1, 1, -(-L // bq), nkb, device=DEV)
+    sd.select_pattern(q, k, bq, bk, 0.5, pooled_out=out)
+    held = want > 1e-34
+    # arguments of up to 185 octaves, three roundings: 185 * 3 * 2^-24 * ln 2 = 2.3e-5
+    assert held[64 // bk + (bk == 128)] and ((out.double() - want).abs() / want)[..., held].max() < 3e-5
+    assert (out[..., ~held] < 1e-33).all()
