@@ -319,8 +319,8 @@ __global__ __launch_bounds__(NW * 64)
   auto re_reference = [&](const f32x16(&s)[NQ], bf16x8(&p)[NQ][2], float(&part)[NQ], int tiles_done) {
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) {
-      const float Mn = fmaxf(M[nq], row_max(s, nq));
-      const float alpha = __builtin_amdgcn_exp2f(M[nq] - Mn);  // <= 1; exactly 1 where nothing changes
+      const float Mn = fmaxf(M[nq], row_max(s, nq)), by = M[nq] - Mn;
+      const float alpha = __builtin_amdgcn_exp2f(by);  // <= 1; exactly 1 where nothing changes
       M[nq] = Mn;
       lsum[nq] *= alpha;
 #pragma unroll
@@ -328,12 +328,17 @@ __global__ __launch_bounds__(NW * 64)
 #pragma unroll
         for (int x = 0; x < 16; ++x) o[nq][dt][x] *= alpha;
       if (kPool) {
-        carry *= alpha;
-        hold *= alpha;
+        // (in two factors: a parked sum may be 2^60, so that what is left of it counts where alpha is zero)
+        const float half = __builtin_amdgcn_exp2f(0.5f * by);
+        carry = carry * half * half;
+        hold = hold * half * half;
         const int cols = KB == kTileK / 2 ? 2 * tiles_done : KB == kTileK ? tiles_done & ~1 : tiles_done >> 1;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // this wave's parked sums have been written
-        if (alpha < 1.0f)  // (not for a NaN: the row is lost anyway)
-          for (int J = fresh_lane() >> 5; J < cols; J += 2) slab[(int64_t)J * QT + wave * 32 + (fresh_lane() & 31)] *= alpha;
+        if (half < 1.0f)  // (not for a NaN: the row is lost anyway)
+          for (int J = fresh_lane() >> 5; J < cols; J += 2) {
+            float* const e = slab + (int64_t)J * QT + wave * 32 + (fresh_lane() & 31);
+            *e = *e * half * half;
+          }
       }
     }
     exp_sub(s, p, part);

@@ -127,3 +127,26 @@ def test_schedule_switch_step_equals_dense_then_select():
     _, col_idx, apool, _ = oracle.select_pattern(q, k, 64, 64, 0.2)
     keep = oracle.kept_blocks(0.2, 16)
     compare_index(layer.index.col_idx.cpu().numpy(), col_idx, apool.reshape(-1, 16), keep)
+
+
+@pytest.mark.parametrize("D,bq,bk", [(64, 64, 64), (128, 128, 128), (64, 32, 32), (128, 64, 128)])
+@pytest.mark.parametrize("H,L", [(1, 700), (1, 1700), (60, 700)])   # one kernel of 128 rows a work-group; two kernels; 256 rows
+@pytest.mark.parametrize("start", [-131, -145])
+def test_parked_sums_far_above_a_reference_that_is_raised(start, H, L, D, bq, bk):
+    """Keys far below the others, then some 55 octaves above those, then the others: the reference is raised by 130 octaves or more,
+    and the sums parked so far by 2^55 relative to it still count."""
+    octaves = torch.zeros(L)
+    octaves[:64], octaves[64:192], octaves[192:320] = start, start + 50, start + 55
+    q, k = torch.zeros(1, H, L, D), torch.zeros(1, H, L, D)
+    q[..., 0] = 8
+    k[0, :, :, 0] = octaves / 1.4426950408889634 * D ** 0.5 / 8
+    q, k = q.bfloat16().to(DEV), k.bfloat16().to(DEV)
+    nkb = -(-L // bk)
+    p = torch.softmax(q[0, 0, :1].double() @ k[0, 0].double().t() / D ** 0.5, 1)[0]
+    want = torch.stack([p[J * bk:(J + 1) * bk].mean() for J in range(nkb)])
+    out = torch.zeros(1, H, -(-L // bq), nkb, device=DEV)
+    sd.attn_dense_select(q, k, k, bq, bk, 0.5, pooled_out=out)
+    held = want > 1e-34
+    # arguments of up to 145 octaves, three roundings: 145 * 3 * 2^-24 * ln 2 = 1.8e-5
+    assert held[256 // bk - 1] and ((out.double() - want).abs() / want)[..., held].max() < 3e-5
+    assert (out[..., ~held] < 1e-33).all()
