@@ -343,7 +343,7 @@ __global__ __launch_bounds__(KS * 256) __attribute__((amdgpu_waves_per_eu(4, 4))
     const f32x4v w0 = *reinterpret_cast<const f32x4v*>(&inv_z[4 * li]);
     f32x4v w1 = w0;
     if (KS > 1) w1 = *reinterpret_cast<const f32x4v*>(&inv_z[(KS - 1) * QT + 4 * li]);
-    const int col1 = n_first * kTileK / BK;  // the second run's first column
+    const int col1 = (n_first * kTileK + BK - 1) / BK;  // the second run's first column
     const float* const all = slab - (int64_t)col0 * QT;
     const int I = gq * kBlocksPerGroup + 4 * li / kBlockRows;
     const int rows_here = L - I * kBlockRows < kBlockRows ? L - I * kBlockRows : kBlockRows;

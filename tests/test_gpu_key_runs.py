@@ -116,3 +116,19 @@ def test_parked_sums_far_above_a_reference_that_is_raised(start, L, D, bq, bk):
     # arguments of up to 185 octaves, three roundings: 185 * 3 * 2^-24 * ln 2 = 2.3e-5
     assert held[64 // bk + (bk == 128)] and ((out.double() - want).abs() / want)[..., held].max() < 3e-5
     assert (out[..., ~held] < 1e-33).all()
+
+
+@pytest.mark.parametrize("bk", [32, 64, 128])
+@pytest.mark.parametrize("n", [1, 40, 64, 65, 100, 130])
+def test_a_sample_of_a_tile_or_two_beside_a_long_one(n, bk):
+    """The long sample takes two runs; the first run of a sample of one tile is that tile, half a block of 128."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q, k = ((torch.randn(2, 2, 2300, 64, generator=g, device=DEV) * 0.6).to(torch.bfloat16) for _ in range(2))
+    out = torch.full((2, 2, 36, -(-2300 // bk)), 7.0, device=DEV)
+    sd.select_pattern(q, k, 64, bk, 0.3, pooled_out=out, seq_lens=torch.tensor([2300, n], dtype=torch.int32, device=DEV))
+    p = torch.softmax(q[1, :, :n].double() @ k[1, :, :n].double().transpose(1, 2).contiguous() / 8, 2)
+    for I in range(-(-n // 64)):
+        for J in range(-(-n // bk)):
+            want = p[:, I * 64:(I + 1) * 64, J * bk:(J + 1) * bk].mean((1, 2))
+            assert ((out[1, :, I, J].double() - want).abs() <= 5e-6 * want).all(), (I, J)
+    assert (out[1, :, -(-n // 64):] == 7.0).all() and (out[1, :, :, -(-n // bk):] == 7.0).all()
