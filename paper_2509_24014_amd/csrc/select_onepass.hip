@@ -398,16 +398,22 @@ static hipError_t launch_pool1p_q(int block_q, const PoolArgs& a, int groups, hi
   return launch_pool1p_bk<D, KS, 1>(a, groups, s);
 }
 
-// Two key runs: the same number of waves in flight, half as many units at a time and each in half the time. By rounds of the
-// chip, 1024 units at a time or 512, where the last round of whole units is at most half full and rounds are few; and with at
-// most a unit a compute unit, where it is twice the waves, if the runs are long enough to pay for merging them (24 tiles).
-// Selections, one run -> two, us. 32 heads of 128: 6000 tokens (1504 units) 441 -> 353, 8192 (2048) 590 -> 608, 4096 (1024)
-// 158 -> 167, 3000 (768) 96 -> 131; 2 heads of 8192 (128) 88 -> 76, 8 heads of 3000 (192) 42 -> 40, of 1000 (64) 21 -> 21, of 600
-// (40) 17 -> 20. Head dim 64: 311 -> 245, 441 -> 441, 112 -> 119, 71 -> 94; 78 -> 65, 37 -> 34, 18 -> 18, 15 -> 16.
-static int key_runs(const PoolArgs& a, int64_t units) {
-  const int64_t rounds = (units + 1023) / 1024, half_rounds = (units + 511) / 512;
-  if (units > 1024) return rounds <= 6 && half_rounds < 2 * rounds ? 2 : 1;
-  return units <= 256 && a.L > 23 * kTileK ? 2 : 1;
+// Two key runs: the same number of waves in flight, half as many units at a time and each in half the time. It pays with at most a
+// unit a compute unit, where it is twice the waves, and where one to three whole rounds of the chip (1024 units) leave
+// a last one that is at most half full, but not empty, if the runs are long enough for what merging them costs every unit. Selections, two runs
+// against one, by 128-row units and tokens. Head dim 64, up to 256 units: 1500 0.95, 2000 to 3000 0.92, longer 0.86; 1025 to 1280:
+// 250 to 1000 1.23, 1000 to 2000 0.92, longer 0.88; to 1536 1.05, 0.93, 0.84; a round more 1.27, 0.98, 0.93; two more 1.23, 1.02,
+// 0.93; three more 1.0 at best. Head dim 128: 1.01, 0.96, 0.89; 1.1, 1.02, 0.94; 1.1, 0.93, 0.85; a round more 1.33, 1.11, 1.05 and
+// (from 2305 units) 1.26, 1.01, 0.96; two more 1.0 at best. 257 to 1024 units: 1.0 to 1.4 (32 heads of 3000 x 128 96 -> 131 us). With
+// lengths per sample the rounds are not known, and with fewer slabs than a round they are others.
+static int key_runs(int D, const PoolArgs& a, int64_t units, int groups) {
+  const int tiles = (a.L + kTileK - 1) / kTileK;
+  if (units <= 256) return tiles >= (D == 64 ? 24 : 30) ? 2 : 1;
+  if (units <= 1024 || groups < 1024 || a.seq_lens != nullptr) return 1;
+  const int64_t full = (units - 1) / 1024, left = units - full * 1024;
+  if (left <= 64 || left > 512 || full > (D == 64 ? 3 : 2)) return 1;  // (a few units more than a round: 1.05 to 1.14)
+  if (D == 64 || left > 256) return tiles >= 16 * full ? 2 : 1;
+  return full == 1 && tiles >= 32 ? 2 : 1;
 }
 
 // One-pass pooled scores over the whole key range of every sample. a.slab holds `groups` slabs of
@@ -417,7 +423,7 @@ hipError_t launch_pool1p_bf16(int D, int block_q, const PoolArgs& a, int groups,
   const int64_t units = pool1p_units(a.B, a.Hq, a.nqb, block_q);
   if (units <= 0 || units > 0x7fffffff || groups < 1 || a.slab == nullptr || a.slab_ld < a.out_stride) return hipErrorInvalidValue;
   if (groups > units) groups = (int)units;
-  if (key_runs(a, units) == 2) {
+  if (key_runs(D, a, units, groups) == 2) {
     if (groups > 512) groups = 512;  // two a compute unit
     if (D == 128) return launch_pool1p_q<128, 2>(block_q, a, groups, s);
     if (D == 64) return launch_pool1p_q<64, 2>(block_q, a, groups, s);

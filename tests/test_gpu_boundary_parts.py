@@ -16,7 +16,8 @@ def _rows(ix, h, b=0):
 
 
 @pytest.mark.parametrize("bq,bk,L,D", [(32, 32, 333, 64), (64, 64, 500, 128), (128, 128, 901, 64), (32, 128, 700, 128),
-                                       (128, 32, 420, 128), (64, 32, 390, 64), (128, 64, 1281, 128)])
+                                       (128, 32, 420, 128), (64, 32, 390, 64), (128, 64, 1281, 128),
+                                       (64, 64, 1500, 64), (128, 128, 2250, 128)])   # these two with the keys in two runs
 def test_both_selections_keep_the_same_blocks(bq, bk, L, D):
     g = torch.Generator().manual_seed(L)
     q = torch.randn(2, 4, L, D, generator=g).to(torch.bfloat16).to(DEV)

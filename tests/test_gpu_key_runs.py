@@ -1,6 +1,6 @@
 """One-pass pooled scores with the keys in one run and in two: calls on both sides of the rule that chooses (units of 128 rows:
-up to 256 and 24 key tiles or more, or a last round of 1024 that is at most half full), and tile counts at which the second run is
-shorter than the first. Scores against the pooling kernel that is given the row statistics."""
+up to 256 of 24 key tiles or more, 30 at head dim 128, or a last round of 1024 that is at most half full if the units are long), and tile
+counts at which the second run is shorter than the first. Scores against the pooling kernel that is given the row statistics."""
 import pytest
 import torch
 
@@ -12,10 +12,13 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("B,H,L,D,bq,bk", [
     (1, 2, 1472, 64, 64, 64), (1, 2, 1473, 64, 128, 128),                # 23 and 24 tiles
-    (1, 2, 1537, 128, 32, 32), (1, 1, 1660, 128, 64, 128), (1, 2, 1700, 128, 128, 64), (2, 2, 1728, 64, 32, 32),  # 25 to 27 tiles
+    (1, 2, 1856, 128, 32, 32), (1, 1, 1857, 128, 64, 128), (1, 2, 2200, 128, 128, 64), (1, 2, 1728, 64, 32, 32),  # 29, 30, 35, 27 tiles
+    (3, 2, 2300, 128, 32, 64), (4, 1, 1500, 64, 64, 128),                  # with lengths per sample: runs of 8, 7 and of 6, 4 tiles and so on
+    (3, 4, 2200, 128, 128, 128), (2, 2, 1600, 64, 64, 32),                 # and of samples of 1 or 2 tiles (below)
     (1, 20, 1600, 64, 128, 64),                                            # 260 units: one run
-    (1, 342, 300, 64, 32, 128), (1, 1025, 100, 64, 128, 32), (2, 513, 70, 128, 64, 64),   # 1026 units: two runs of 4, 1 and 0 tiles
-    (1, 769, 250, 64, 128, 64), (1, 770, 190, 128, 128, 64),              # 1538 units: one run
+    (1, 94, 2000, 64, 32, 128), (1, 87, 2300, 128, 128, 32), (1, 130, 1025, 64, 64, 64),  # 1504, 1566 and 1170 units
+    (1, 165, 1000, 128, 64, 64), (1, 129, 1000, 128, 128, 64), (1, 240, 1020, 64, 64, 128),  # 1320 (two runs), 1032 and 1920 (one)
+    (1, 342, 300, 64, 32, 128), (1, 769, 250, 64, 128, 64), (1, 770, 190, 128, 128, 64),  # 1026 and 1538 units of 3 to 5 tiles: one run
 ])
 def test_scores_of_both_forms(B, H, L, D, bq, bk):
     g = torch.Generator(device=DEV).manual_seed(L)
@@ -24,7 +27,10 @@ def test_scores_of_both_forms(B, H, L, D, bq, bk):
     nqb, nkb = -(-L // bq), -(-L // bk)
     lse, out = torch.zeros(B, H, L, dtype=torch.float32, device=DEV), torch.zeros(B, H, nqb, nkb, device=DEV)
     want = torch.zeros_like(out)
-    for lens in (None, torch.tensor([L] + [max(1, L * 2 // 5)] * (B - 1), dtype=torch.int32, device=DEV)):
+    for lens in (None, torch.tensor([L] + [max(1, L * 2 // 5)] * (B - 1), dtype=torch.int32, device=DEV),
+                 torch.tensor([L, 64, 65, 130][:B], dtype=torch.int32, device=DEV)):   # runs of 1 and 0, 2 and 0, 2 and 1 tiles
+        out.zero_()
+        want.zero_()
         ix = sd.select_pattern(q, k, bq, bk, 0.3, pooled_out=out, seq_lens=lens)
         sd.index_validate(ix)
         sd.attn_dense(q, k, k, seq_lens=lens, lse_out=lse)
@@ -36,13 +42,13 @@ def test_scores_of_both_forms(B, H, L, D, bq, bk):
             assert torch.isfinite(x).all() and ((x - y).abs() <= 1e-5 * y).all(), ((x - y).abs() / y).max()
 
 
-@pytest.mark.parametrize("D,where", [(64, 100), (64, 1500), (128, 40), (128, 1000), (128, 1599)])
+@pytest.mark.parametrize("D,where", [(64, 100), (64, 1500), (128, 40), (128, 1000), (128, 2299)])
 def test_a_logit_far_above_the_others_in_either_run(D, where):
     """One key whose logits are 150 to 300 octaves above every other key's: the references of the runs differ by as much, and
     all of the weight is in one column."""
-    L, b = 1600, 64
+    L, b = 2304, 64
     q = torch.ones(1, 1, L, D, device=DEV, dtype=torch.bfloat16)
-    q[:, :, 800:] = 2
+    q[:, :, 1152:] = 2
     k = torch.full((1, 1, L, D), -0.25, device=DEV, dtype=torch.bfloat16)
     k[:, :, where] = 104 * D ** -0.5   # logits (104 + sqrt(D) / 4) times 1 and 2 above the others
     out = torch.zeros(1, 1, L // b, L // b, device=DEV)
@@ -58,10 +64,10 @@ def test_scores_of_a_run_whose_reference_is_far_below(run, low, high, D, bq, bk)
     """One run begins 130 octaves or more below the other, its reference with it, and climbs by 90 to 95, too little for the
     reference to be raised: the factor between the references is below the smallest float, the scores are not. Also the two
     parts of a boundary block among the keys that climb."""
-    L = 1601 if bk < 128 else 1600 + 65   # the first run is 14 tiles, keys 0 .. 895
+    L = 2305 if bk < 128 else 2304 + 65   # 37 or 38 tiles, the first run 20 of them, keys 0 .. 1279
     octaves = torch.zeros(L)
-    begin = 896 * run
-    octaves[begin:L if run else 896] = low
+    begin = 1280 * run
+    octaves[begin:L if run else 1280] = low
     octaves[begin + 400:begin + 600] = high
     q, k = torch.zeros(1, 2, L, D), torch.zeros(1, 2, L, D)
     q[..., 0] = 8
@@ -96,7 +102,7 @@ def test_scores_of_a_run_whose_reference_is_far_below(run, low, high, D, bq, bk)
 
 
 @pytest.mark.parametrize("D,bq,bk", [(64, 64, 64), (128, 128, 128), (64, 32, 32)])
-@pytest.mark.parametrize("L", [700, 1700])   # one run of keys, two
+@pytest.mark.parametrize("L", [700, 2300])   # one run of keys, two
 @pytest.mark.parametrize("start", [-130, -150, -185])
 def test_parked_sums_far_above_a_reference_that_is_raised(start, L, D, bq, bk):
     """Within one run: keys far below the others, then some 95 octaves above those, then the others: the reference is raised by 130
