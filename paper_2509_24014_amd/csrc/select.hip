@@ -605,17 +605,38 @@ __global__ __launch_bounds__(256) void window_index_kernel(const WindowArgs a) {
 }
 
 // ---------------------------------------------------------------------------- launchers
-// Tokens per segment where there are too few query rows to fill the chip, which holds four work-groups a compute unit: the key
-// range is cut so that it does, into segments of at least four tiles (0: one segment). Scores of the segments are independent
-// given the row statistics. Pooling and top-k, us: 4 heads of 2048 x 128 27 -> 14.7 (least segments of 4 or 8 tiles), of 600 x 64
-// 13.7 -> 10.0 (4 tiles; 8 leave one segment).
-static int pool_segment(int64_t groups, int key_len) {
-  constexpr int kSlots = 1024, kLeast = 4 * kTileK;
-  const int64_t parts = kSlots / groups;
-  if (parts < 2 || key_len < 2 * kLeast) return 0;
-  int64_t len = (key_len + parts - 1) / parts;
-  if (len < kLeast) len = kLeast;
-  return (int)((len + 127) / 128 * 128);  // a multiple of every block_k
+// Tokens per segment where there are too few query rows to fill the chip: the key range is cut into segments, four tiles or
+// more each (0: one segment), whose scores are independent given the row statistics. What a launch takes, in hundredths of a
+// microsecond, is a fixed part and a part per tile of a segment, by the work-groups of the busiest compute unit, one to four
+// (fitted to 2300 calls with and without segments, to 5 %); the number of segments is the one that takes least. Pooling and top-k,
+// us: 4 heads of 2048 x 128 27 -> 14.7 (7 segments), of 600 x 64 13.7 -> 10.0 (2); where the units nearly fill the chip, segments
+// pay by the work-groups they leave on the busiest unit: 300 units of 2000 tokens 0.82 (head dim 64), 0.92 (128) of the time, 450
+// units of 1000 tokens, head dim 128, 1.09, and are left whole.
+static int pool_segment(int D, int64_t groups, int key_len, int block_k) {
+  constexpr int kCus = 256, kLeast = 4 * kTileK;
+  struct Line {
+    int fixed, per_tile;
+  };
+  static constexpr Line kLines[2][2][4] = {  // [head dim 128][key blocks of 32]
+      {{{740, 49}, {810, 74}, {830, 105}, {860, 138}}, {{730, 69}, {790, 92}, {860, 124}, {840, 163}}},
+      {{{770, 57}, {840, 98}, {990, 153}, {1120, 199}}, {{770, 74}, {880, 110}, {900, 172}, {1180, 213}}}};
+  auto cost = [&](int64_t parts, int len) -> int64_t {
+    const int64_t k = (groups * parts - 1) / kCus;
+    if (k > 3) return INT64_MAX;
+    const Line& c = kLines[D == 128][block_k == 32][k];
+    return c.fixed + (int64_t)c.per_tile * ((len + kTileK - 1) / kTileK);
+  };
+  if (groups > 2 * kCus) return 0;
+  int64_t least = cost(1, key_len);
+  int best = 0;
+  for (int parts = 2; parts <= 4 * kCus / groups && key_len > kLeast; ++parts) {
+    int len = (key_len + parts - 1) / parts;
+    len = (len + 127) / 128 * 128;  // a multiple of every block_k
+    if (len < kLeast) break;
+    const int64_t c = cost((key_len + len - 1) / len, len);
+    if (c * 100 < least * 99) least = c, best = len;
+  }
+  return best;
 }
 
 template <int D>
@@ -625,7 +646,7 @@ static hipError_t launch_pool_bf16_d(int block_q, PoolArgs a, hipStream_t s) {
   const int blocks_per_group = 128 / block_q;
   const int64_t total = (int64_t)a.B * a.Hq * ((a.nqb + blocks_per_group - 1) / blocks_per_group);
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
-  a.seg_len = a.key_len2 > 0 ? 0 : pool_segment(total, a.key_len);
+  a.seg_len = a.key_len2 > 0 ? 0 : pool_segment(D, total, a.key_len, a.block_k);
   const dim3 grid((unsigned)total, a.key_len2 > 0 ? 2 : a.seg_len > 0 ? (a.key_len + a.seg_len - 1) / a.seg_len : 1), block(256);
   switch (block_q) {
     case 128:
