@@ -405,11 +405,11 @@ static hipError_t launch_pool1p_q(int block_q, const PoolArgs& a, int groups, hi
 // 250 to 1000 1.23, 1000 to 2000 0.92, longer 0.88; to 1536 1.05, 0.93, 0.84; a round more 1.27, 0.98, 0.93; two more 1.23, 1.02,
 // 0.93; three more 1.0 at best. Head dim 128: 1.01, 0.96, 0.89; 1.1, 1.02, 0.94; 1.1, 0.93, 0.85; a round more 1.33, 1.11, 1.05 and
 // (from 2305 units) 1.26, 1.01, 0.96; two more 1.0 at best. 257 to 1024 units: 1.0 to 1.4 (32 heads of 3000 x 128 96 -> 131 us). With
-// lengths per sample the rounds are not known, and with fewer slabs than a round they are others.
+// fewer slabs than a round the rounds are others; with lengths per sample they are a guess (0.97 on average, 0.79 to 1.18).
 static int key_runs(int D, const PoolArgs& a, int64_t units, int groups) {
   const int tiles = (a.L + kTileK - 1) / kTileK;
   if (units <= 256) return tiles >= (D == 64 ? 24 : 30) ? 2 : 1;
-  if (units <= 1024 || groups < 1024 || a.seq_lens != nullptr) return 1;
+  if (units <= 1024 || groups < 1024) return 1;
   const int64_t full = (units - 1) / 1024, left = units - full * 1024;
   if (left <= 64 || left > 512 || full > (D == 64 ? 3 : 2)) return 1;  // (a few units more than a round: 1.05 to 1.14)
   if (D == 64 || left > 256) return tiles >= 16 * full ? 2 : 1;
