@@ -14,7 +14,7 @@ DensePoolShape dense_pool_shape(int D, int B, int Hq, int L, int block_k, int ma
   DensePoolShape s;
   constexpr int kCus = 256;
   const bool alone = (int64_t)B * Hq * ((L + 127) / 128) <= kCus;
-  const bool small = D == 128 ? alone && L <= 512 : alone || dense_qtile_bf16(D, (int64_t)B * Hq, L) <= 128;
+  const bool small = D == 128 ? alone && L <= 512 : alone || dense_qtile_bf16(D, (int64_t)B * Hq, L, false) <= 128;
   s.rows = max_rows < 256 || small ? 128 : 256;
   const int64_t units = (int64_t)B * Hq * ((L + s.rows - 1) / s.rows), resident = s.rows == 256 ? kCus : 2 * kCus;
   s.groups = (int)(units < resident ? units : resident);

@@ -208,7 +208,8 @@ hipError_t launch_valu_rate(float* scratch, int iters, int op, hipStream_t s);
 // exp2, and optionally one LDS operand read each; same launch shape and matrix work as launch_mfma_rate.
 hipError_t launch_mix_rate(float* scratch, int iters, int vector_per_mfma, int lds_operands, hipStream_t s);
 
-// Rows per work-group the bf16 dense / stats kernels use for heads = B * Hq and this L (0 if L is unsupported).
-int dense_qtile_bf16(int D, int64_t heads, int L);
+// Rows per work-group the bf16 dense / stats kernels use for heads = B * Hq and this L (0 if L is unsupported); padded: the samples
+// have lengths of their own.
+int dense_qtile_bf16(int D, int64_t heads, int L, bool padded);
 
 }  // namespace sparsed
