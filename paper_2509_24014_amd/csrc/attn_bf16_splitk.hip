@@ -572,7 +572,13 @@ static hipError_t launch_splitk_d(Mode mode, int block_q, const AttnArgs& a, hip
     return launch_splitk<D, 1, true, 1>(mode, a, s);
   }
   if (runs <= 256 && tiles >= (dense ? 8 : 10)) return launch_splitk<D, 1, true, 2>(mode, a, s);
-  if (runs > 256 && runs <= 512 && tiles >= (!dense ? 16 : D == 64 ? 12 : 20)) return launch_splitk<D, 2, false, 2>(mode, a, s);
+  // An index with room for every block says nothing of the length of its lists, and eight waves a work-group lose more on short ones
+  // than they gain on long ones. Against four waves, lists of less than 6 tiles and of 14 and more: 64 x 64 blocks 1.18 (up to 1.46) and
+  // 0.95 of the time, 64 x 128 1.13 (up to 1.37) and 0.88, 128 x 64 1.17 and 1.02; 128 x 128 blocks gain (general kernel 1, eight
+  // waves 0.84 and 0.68).
+  const bool any_length = !dense && (block_q == 64 || a.block_k < 128) &&
+                          (int64_t)a.cap_per_head >= (int64_t)a.nqb * ((a.L + a.block_k - 1) / a.block_k);
+  if (runs > 256 && runs <= 512 && !any_length && tiles >= (!dense ? 16 : D == 64 ? 12 : 20)) return launch_splitk<D, 2, false, 2>(mode, a, s);
   if (runs > 512 && (dense || block_q == 128)) {
     if constexpr (D == 64) return launch_splitk<D, 4, false, 1>(mode, a, s);
     else if (dense) return launch_splitk<D, 4, false, 1>(mode, a, s);
