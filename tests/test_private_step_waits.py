@@ -1,4 +1,4 @@
-"""Counted waits of the barrier-free loop of the 32-row sparse kernel, read from the assembly hipcc makes of it here.
+"""Counted waits of the barrier-free loop of the split-key kernel, read from the assembly hipcc makes of every form of it here.
 
 A counted wait in inline assembly is a promise about what was issued after the copy it waits for. What was issued between
 the fence in front of it and the wait itself is certain: one tile copy, D / 16 loads of a wave. A wait that leaves more than
@@ -30,15 +30,24 @@ def assembly(tmp_path_factory):
 @pytest.fixture(scope="module")
 def kernels(assembly):
     found = {}
-    for m in re.finditer(r"^(_ZN7sparsed\d+attn_bf16_splitk_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb1E\w*):(.*?)^\.Lfunc_end", assembly, re.M | re.S):
-        found[tuple(int(m.group(i)) for i in (2, 3, 4))] = m.group(5)
+    for m in re.finditer(r"^_ZN7sparsed\d+attn_bf16_splitk_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb1ELi(\d+)ELb(\d)E\w*:(.*?)^\.Lfunc_end",
+                         assembly, re.M | re.S):
+        key = tuple(int(m.group(i)) for i in range(1, 6))   # head dim, row groups, keys a block, tile streams, lists or every tile
+        assert key not in found
+        found[key] = m.group(6)
     return found
 
 
-@pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("block_k", [32, 64, 128])
-def test_counted_waits_leave_only_the_copy_issued_since_the_fence(kernels, D, block_k):
-    body = kernels[(D, 1, block_k)]
+FORMS = [(D, 1, block_k, streams, 1) for D in (64, 128) for block_k in (32, 64, 128) for streams in (1, 2)] + [(D, 1, 64, 2, 0) for D in (64, 128)]
+
+
+def test_every_barrier_free_form_is_looked_at(kernels):
+    assert sorted(kernels) == sorted(FORMS)
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_counted_waits_leave_only_the_copy_issued_since_the_fence(kernels, form):
+    D, body = form[0], kernels[form]
     waits = [int(n) for n in re.findall(r"#ASMSTART\s+s_waitcnt vmcnt\((\d+)\)", body)]
     counted = [n for n in waits if n > 0]
     assert len(counted) >= 4, "two counted waits in each of the two steady steps"
