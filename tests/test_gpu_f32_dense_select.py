@@ -60,11 +60,12 @@ def test_every_block_size(H, L, bq, bk, D):
     _check(*_qkv(1, H, 1 if H == 3 else H, L, D, seed=L + bq + bk), bq, bk)
 
 
-@pytest.mark.parametrize("D,bq,L", [(128, 32, 8600), (128, 64, 7100), (128, 128, 2100), (64, 64, 5300)])
-def test_around_the_blocks_that_fit(D, bq, L):
-    """Key blocks of 32: a little under and over what the LDS holds (over: the dense call and a pooling kernel)."""
-    for n in (L - 300, L):
-        _check(*_qkv(1, 1, 1, n, D, seed=n), bq, 32, rho=0.05)
+@pytest.mark.parametrize("D,bq,H,fit", [(128, 32, 1, 532), (128, 64, 1, 218), (128, 128, 16, 61), (64, 32, 1, 324), (64, 64, 1, 138), (64, 128, 16, 45)])
+def test_around_the_blocks_that_fit(D, bq, H, fit):
+    """As many key blocks as the LDS holds sums of, and one more (the dense call and a pooling kernel), at head counts for which the
+    rule on costs takes the one kernel."""
+    for n in (fit, fit + 1):
+        _check(*_qkv(1, H, H, 32 * n - 5, D, seed=n), bq, 32, rho=0.05)
 
 
 @pytest.mark.parametrize("bq,bk", [(32, 32), (64, 128), (128, 64)])

@@ -68,13 +68,19 @@ def test_sparse_lists_of_any_length(bq, bk, L, D):
 
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("H,bq,bk,L,longest", [
-    (110, 32, 32, 600, 3),     # 2090 work-groups, 1 or 2 tiles on average: one wave a list
+    (110, 32, 32, 600, 3),     # 2090 work-groups, 3 tiles on average: four waves a list, some without a tile
     (110, 64, 64, 590, 2),     # the same with two-tile blocks, the last one partial (14 keys)
     (110, 128, 32, 600, 4),    # rows of a 128-row query block in four work-groups
     (54, 32, 32, 600, 3),      # 1026
-    (40, 32, 32, 600, 3),      # 760, one or two tiles: one wave
-    (40, 32, 64, 600, 6),      # 760, 6 tiles: four waves
+    (40, 32, 32, 600, 3),      # 760
+    (40, 32, 64, 600, 6),      # 760, 8 tiles
     (40, 64, 128, 530, 3),     # 680, four-tile blocks, the last one 18 keys
+    (64, 32, 32, 1024, 1),     # 2048, at most one tile: one wave a list
+    (62, 32, 32, 1010, 4),     # 1984, 3 tiles on average, the last one 18 keys: one wave
+    (62, 64, 32, 1000, 3),     # the same with two work-groups a query block
+    (62, 128, 64, 1010, 1),    # and with four, two-tile blocks
+    (62, 64, 64, 1010, 3),     # 5 tiles on average: two waves
+    (62, 128, 128, 1010, 1),   # one four-tile block, the last one 114 keys: two waves
 ])
 def test_sparse_short_lists_on_many_work_groups(H, bq, bk, L, longest, D):
     """The number of waves that split a list follows from the work-groups and the capacity of the lists."""

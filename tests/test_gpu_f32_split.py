@@ -77,9 +77,12 @@ def test_inputs_of_very_different_size(H, L, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("H,keep", [(8, 1), (8, 7), (40, 1), (40, 7), (70, 1), (70, 2), (70, 7)])
+@pytest.mark.parametrize("H,keep", [(8, 1), (8, 7),                           # 240 work-groups: eight waves a list
+                                    (40, 1), (40, 7), (70, 2), (70, 7),       # 1200 and 2100: four
+                                    (64, 1), (67, 1),                         # 1920 and 2010, two tiles: one
+                                    (64, 2), (64, 3), (70, 1)])               # and four, six, 2100 and two: two
 def test_every_form_of_the_sparse_launch(H, keep, D):
-    """240, 1200 and 2100 work-groups with lists of 1 to 14 tiles: one, two, four and eight waves a list."""
+    """240 to 2100 work-groups with lists of 2 to 14 tiles: one, two, four and eight waves a list."""
     L, bq, bk = 950, 64, 64
     nqb, nkb = 15, 15
     q, k, v = _qkv(H, L, D, seed=H + keep)
