@@ -367,11 +367,11 @@ __global__ __launch_bounds__(RW * SG * 128)
   }
 #undef SPARSED_SPLITK_STEP
 
-  auto row_results = [&](float reference, float ltot, float inv) {  // of this lane's row
+  auto row_results = [&](float reference, float ltot) {  // of this lane's row
     if (LIST || g != 0 || row0 + j >= L) return;
     const int64_t at = (int64_t)bh * a.L + row0 + j;
     if (a.lse != nullptr) a.lse[at] = (reference + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
-    if (a.row_stat != nullptr) *reinterpret_cast<f32x2*>(a.row_stat + 2 * at) = f32x2{reference, inv};
+    if (a.row_stat != nullptr) *reinterpret_cast<f32x2*>(a.row_stat + 2 * at) = f32x2{reference, 1.0f / ltot};  // (not a number where the sum is not)
   };
   if constexpr (SG > 1) {
     // Merge the KW parts of every row. Wave `part` of a row group finishes 1/KW of the columns: every wave leaves its
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(RW * SG * 128)
       }
     }
     const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
-    if (part == 0) row_results(Mn, ltot, inv);
+    if (part == 0) row_results(Mn, ltot);
 
     // stores of whole runs of a row, through an LDS transpose in the wave's own region (its slots of 16 bytes, one per group,
     // at position slot ^ (row mod slots))
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(RW * SG * 128)
     const float f_mine = __builtin_amdgcn_exp2f(M - Mn), f_other = __builtin_amdgcn_exp2f(M_other - Mn);
     const float ltot = ltot_mine * f_mine + l_other * f_other;
     const float inv = ltot > 0.f ? 1.0f / ltot : 0.f;
-    row_results(Mn, ltot, inv);
+    row_results(Mn, ltot);
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll

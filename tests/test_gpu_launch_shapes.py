@@ -134,3 +134,15 @@ def test_scores_of_a_switch_step_as_two_kernels_keep_their_bits(H, L, D, offset)
     # a reference that were rounded like the logits would be off by 100 * 2^-24 * ln 2 = 4e-6 for a whole row
     error = ((pooled[0, 0].double() - want) / want)[:L // 64, :L // 64]
     assert error.pow(2).mean().sqrt() < 2.5e-7, error.pow(2).mean().sqrt()
+
+
+@pytest.mark.parametrize("L", [500, 1000])   # one kernel, two
+def test_scores_of_rows_with_an_infinite_logit_are_not_numbers(L):
+    q, k, v = _qkv(1, 2, 2, L, 128, seed=L)
+    q[0, 0] = q[0, 0].abs()
+    k[0, 0, 40, 2] = math.inf
+    nb = -(-L // 64)
+    pooled = torch.zeros(1, 2, nb, nb, device=DEV)
+    out, _ = sd.attn_dense_select(q, k, v, 64, 64, 0.2, pooled_out=pooled)
+    assert pooled[0, 0].isnan().all() and out[0, 0].isnan().all()
+    assert torch.isfinite(pooled[0, 1]).all() and torch.isfinite(out[0, 1]).all()
