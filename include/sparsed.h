@@ -43,8 +43,17 @@
  *    (the paper pools with L // block_size and is silent on a remainder).
  *  - Arithmetic: bf16 tensors are multiplied on the bf16 matrix cores with
  *    fp32 accumulation, softmax in fp32, probabilities rounded to bf16 before
- *    the product with V. fp32 tensors use fp32 matrix cores throughout.
+ *    the product with V. fp32 tensors: fp32 accumulation, fp32 softmax, products as
+ *    good as fp32 ones; they run on the bf16 matrix cores with every operand as the sum
+ *    of three bf16 parts, or on the fp32 matrix cores where the parts would not do
+ *    (infinities, NaN, values beyond 3.3e38 or so small that their low parts would be
+ *    cut off, about 2^-108). One thing is lost there: a column of V whose values are all
+ *    below 2^-126 beside larger columns of the same head gives zeros.
  *    Pooled scores for selection are fp32 from the logits on, for either dtype.
+ *  - A call repeated with the same arguments gives the same bits. How a row's keys are
+ *    divided over the chip follows from B, H, L and the capacity of the index, and the
+ *    order of its sums with it: a sample of a batch, or a head of several, may differ in
+ *    rounding from the same sample or head alone.
  */
 #ifndef SPARSED_H
 #define SPARSED_H
@@ -159,9 +168,10 @@ sparsed_status sparsed_select_pattern(const sparsed_tensor* q, const sparsed_ten
 
 /*
  * The switch step in one call (Algorithm 1 nests the selection under the full-attention branch): the dense
- * attention of sparsed_attn_dense and, from the same q and k, the pattern of sparsed_select_pattern. For bf16 inputs
- * the attention kernel leaves the pooled scores itself (its softmax already forms every block's row sums), so
- * Q K^T and the exponentials are computed once instead of twice; for fp32 it is the two calls in turn. Same outputs
+ * attention of sparsed_attn_dense and, from the same q and k, the pattern of sparsed_select_pattern. The attention
+ * kernel leaves the pooled scores itself (its softmax already forms every block's row sums), so that Q K^T and the
+ * exponentials are computed once instead of twice, but where two kernels are the quicker: bf16 calls with few query rows,
+ * fp32 calls whose block sums do not fit the LDS or whose query blocks fill the chip badly. Same outputs
  * as the two calls up to fp32 summation order. Arguments and limits are those of the two calls; ex->lse_out and
  * ex->pooled_out are optional, ex->lse_in is ignored. Needs ex->workspace; sparsed_select_workspace_bytes()
  * always suffices.

@@ -356,7 +356,8 @@ sparsed_status select_impl(const sparsed_tensor* q, const sparsed_tensor* k, int
 // (heads, tokens, head dim): (4, 2048, 128) 49.1 -> 33.4, (8, 1000, 128) 32.4 -> 26.1, (16, 1000, 128) 33.5 -> 30.8, (4, 4096, 128)
 // 87.2 -> 75.7, (28, 600, 128) 27.0 and 29.0; (4, 2048, 64) 30.5 -> 24.9, (4, 800, 64) 19.4 -> 18.2, (4, 3000, 64) 42.5 -> 37.8,
 // (8, 1500, 64) 27.6 and 28.3, (4, 4096, 64) 52.9 and 52.6. From 12 tiles on: at head dim
-// 128 ten tiles gain as well (25.2 -> 20.9), but up to there a sample of a padded batch is, bit for bit, what it is alone.
+// 128 ten tiles gain as well (25.2 -> 20.9), but up to there the switch step of a padded batch gives every sample, bit for bit, what it
+// gives the sample alone (longer ones, and the other calls, may differ in rounding: how keys are divided follows from the whole call).
 bool dense_then_pool(const sparsed_tensor* q) {
   const int64_t runs = (int64_t)q->B * q->H * ceil_div(q->L, 32);
   const int tiles = ceil_div(q->L, 64);
@@ -364,8 +365,8 @@ bool dense_then_pool(const sparsed_tensor* q) {
   return (runs <= 256 && tiles >= 13) || (runs <= 384 && tiles >= 40);
 }
 
-// Dense attention and the pattern of one key range from the same q, k. bf16: the attention kernel leaves the pooled
-// scores; fp32: dense with its log-sum-exp, then selection with it.
+// Dense attention and the pattern of one key range from the same q, k: the attention kernel leaves the pooled scores, or (bf16 calls of
+// few rows, fp32 calls that dense_pool_pays_f32 turns down) the dense call leaves its row statistics and a selection follows.
 sparsed_status dense_select_impl(const sparsed_tensor* q, const sparsed_tensor* k, const sparsed_tensor* v, sparsed_tensor* out,
                                  int32_t bq, int32_t bk, double rho, sparsed_block_index* ix, const sparsed_exec* ex) {
   sparsed_status st;

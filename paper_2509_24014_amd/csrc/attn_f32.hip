@@ -1,6 +1,7 @@
 // fp32 flash-attention forward for gfx950: dense (Eq. 1), block-sparse (Eq. 3 / Eq. 4) and the
-// statistics-only pass. fp32 inputs, fp32 matrix cores (32x32x2), fp32 softmax, fp32 output:
-// this is the path held to 1e-5 against the fp64 reference.
+// statistics-only pass. fp32 inputs, fp32 softmax, fp32 output; products on the bf16 matrix instruction with operands split in
+// three (tile_f32.hpp), or on the fp32 one (32x32x2): where the parts would not do, and for lists that one wave walks.
+// This is the path held to 1e-5 against the fp64 reference.
 //
 // One work-group owns 32 query rows of one (batch, head); its KW waves share the rows and split the keys: wave w takes
 // the 32-key tiles w, w + KW, ... of the list with its own reference, sum and output accumulator, and the parts

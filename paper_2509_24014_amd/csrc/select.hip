@@ -1,8 +1,8 @@
 // Pattern selection for gfx950 (Section 3.3; Algorithm 1's per-query-block loop; Eq. 6):
 //   pool_*_kernel  A'[I, J] = mean over the block_q x block_k rectangle of the softmax
 //                  probabilities of Eq. 1 (every row normalised over all L keys, via the row
-//                  log-sum-exp computed by the statistics pass). One work-group per query block
-//                  walks all key tiles once; the L x L matrix never exists.
+//                  log-sum-exp of the statistics pass, or what a dense call left). A work-group walks
+//                  all key tiles, or those of a segment, once; the L x L matrix never exists.
 //   topk_kernel    per pooled row, the k largest entries (ties: lower block index), written
 //                  ascending into the per-head CSR block index. One wavefront per row.
 // Pooled scores are fp32 from the logits on: the exponentials, the normaliser and every partial

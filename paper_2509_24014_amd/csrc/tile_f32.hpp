@@ -3,7 +3,7 @@
 //
 // Same transposed formulation as the bf16 kernels: S^T[key, query] = K . Q^T puts one query in
 // each lane (lane = 32*g + j holds query j; register v holds key row 8*(v/4) + 4*g + (v%4) of the
-// 32-key tile). Everything stays fp32: inputs, both products, softmax.
+// 32-key tile). Inputs, accumulators and softmax are fp32, and the products as good as fp32 ones:
 //
 // Products. The fp32 matrix instruction contracts 2 columns in 64 cycles, the bf16 one 16 in 32. An fp32 value is the sum of
 // three bf16 values to 2^-26 of itself (each the nearest to what the ones before it leave, all of them exact differences),
