@@ -9,13 +9,15 @@
 // loop has no barrier, and a short sequence still spreads over many waves. The next tile is requested as soon as what it
 // replaces has been used: every load has most of a tile's work to arrive.
 //
-// Bound: the vector unit, which splits every K and V value into its three bf16 parts for 32 rows of queries (700 of the 880
-// vector instructions of a tile at head dim 128, 2 ns each, beside 96 matrix instructions of 16 ns), then what a work-group
-// spends before its first and after its last tile. 8 heads of 2000 x 128: dense 164 -> 110 us, sparse (64 x 64 blocks, 20 %
-// kept) 48 -> 37 us, pooling (select.hip) 84 -> 61 us; 2 heads of 256 x 64: dense 11.5 -> 9.3 us. (Before: the fp32 matrix
-// instruction alone.) Error against 64 bits, largest of an output over its root mean square, random inputs of both: 8 x
-// 2000 x 128 3.2e-6 -> 2.7e-6, 4 x 600 x 64 1.5e-6 -> 1.2e-6, peaked rows (logits of variance 16) 2.1e-5 -> 1.7e-5,
-// log-normal inputs (sigma 1.5 and 3) 3.5e-4 -> 9.2e-5; log-sum-exp 8.7e-6 -> 8.1e-6 where rows are peaked, the same elsewhere.
+// Bound: the vector unit, which splits every K and V value into its three bf16 parts for 32 rows of queries (700 of the 890
+// vector instructions of a tile at head dim 128, 2 ns each), and the matrix cores (96 instructions of 16 ns), which hardly
+// overlap: 60 % and 42 % busy in a dense call of 8 heads of 2000 x 128; then what a work-group spends before its first and after
+// its last tile. 8 heads of 2000 x 128: dense 164 -> 111 us, sparse (64 x 64 blocks, 20 % kept) 48 -> 37 us, pooling (select.hip)
+// 84 -> 61 us; 2 heads of 256 x 64: dense 11.5 -> 9.4 us. (Before: the fp32 matrix instruction alone. Of these times 1 to 3 %
+// are the looks at values that three parts do not hold, see tile_f32.hpp.) Error against 64 bits, largest of an output over its
+// root mean square, random inputs of both: 8 x 2000 x 128 3.2e-6 -> 2.7e-6, 4 x 600 x 64 1.5e-6 -> 1.2e-6, peaked rows (logits of
+// variance 16) 2.1e-5 -> 1.7e-5, log-normal inputs (sigma 1.5 and 3) 3.5e-4 -> 9.0e-5; log-sum-exp 8.7e-6 -> 8.1e-6 where rows are
+// peaked, the same elsewhere.
 #include <type_traits>
 
 #include "kernels.hpp"
