@@ -368,7 +368,7 @@ __global__ __launch_bounds__(RW * SG * 128)
 #undef SPARSED_SPLITK_STEP
 
   auto row_results = [&](float reference, float ltot) {  // of this lane's row
-    if (LIST || g != 0 || row0 + j >= L) return;
+    if (LIST || (a.lse == nullptr && a.row_stat == nullptr) || g != 0 || row0 + j >= L) return;
     const int64_t at = (int64_t)bh * a.L + row0 + j;
     if (a.lse != nullptr) a.lse[at] = (reference + __builtin_amdgcn_logf(ltot)) * 0.6931471805599453f;
     if (a.row_stat != nullptr) *reinterpret_cast<f32x2*>(a.row_stat + 2 * at) = f32x2{reference, 1.0f / ltot};  // (not a number where the sum is not)
