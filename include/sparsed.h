@@ -47,8 +47,7 @@
  *    good as fp32 ones; they run on the bf16 matrix cores with every operand as the sum
  *    of three bf16 parts, or on the fp32 matrix cores where the parts would not do
  *    (infinities, NaN, values beyond 3.3e38 or so small that their low parts would be
- *    cut off, about 2^-108). One thing is lost there: a column of V whose values are all
- *    below 2^-126 beside larger columns of the same head gives zeros.
+ *    cut off, about 2^-108).
  *    Pooled scores for selection are fp32 from the logits on, for either dtype.
  *  - A call repeated with the same arguments gives the same bits. How a row's keys are
  *    divided over the chip follows from B, H, L and the capacity of the index, and the

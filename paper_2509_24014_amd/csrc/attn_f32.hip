@@ -372,11 +372,9 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     __syncthreads();  // everyone is done with the query fragments
   } else {
     walk(std::true_type{});
-    // Whether this wave's results may show what the parts do not carry (tile_f32.hpp), and, for all waves together, whether any
-    // sum is not zero.
-    constexpr int kRepeat = 1, kHasSums = 2, kHasKeys = 4;
+    // Whether this wave's results may show what the parts do not carry (tile_f32.hpp).
     float least = __builtin_inff(), probe = 0.f * lsum;  // probe: not a number if any sum is infinite or not a number
-    bool small = false, sums = false;
+    bool small = false;
     if (kHasV) {
 #pragma unroll
       for (int dt = 0; dt < kV; ++dt)
@@ -387,7 +385,6 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
         }
       const float good = fmaxf(0x1p-90f, __uint_as_float(v_top) * 0x1p-92f);  // the least sum that is good
       small = least < good;
-      sums = least > 0.f;
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 0.f) != 0, 0)) {  // the least of those that are not zero
         float next = __builtin_inff();
 #pragma unroll
@@ -395,17 +392,27 @@ __global__ __launch_bounds__(RW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
           for (int x = 0; x < 16; ++x) next = fminf(next, o[dt][x] == 0.f ? __builtin_inff() : fabsf(o[dt][x]));
         small = next < good || (least == 0.f && good >= 0x1p-60f);
-        sums = next < __builtin_inff();
+        // zeros are good where V is zero: its values again, for any that are small and not zero
+        SplitRange range;
+        for (int t = kw; t < n; t += KW) {
+          const uint32_t off = vs.v_offset(__builtin_amdgcn_readfirstlane(first_key(t)), lane);
+#pragma unroll 4
+          for (int x = 0; x < 16; ++x) {
+            const VRow w = vs.v_row(off, x);
+#pragma unroll
+            for (int dt = 0; dt < kV; ++dt) range.add_low(w[dt]);
+          }
+        }
+        small |= range.below();
       }
     }
-    int verdict = (queries_outside || __builtin_amdgcn_ballot_w64(small || probe != probe) != 0 ? kRepeat : 0) |
-                  (__builtin_amdgcn_ballot_w64(sums) != 0 ? kHasSums : 0) | (kHasV && __builtin_amdgcn_ballot_w64(lsum > 0.f) != 0 ? kHasKeys : 0);
+    int verdict = queries_outside || __builtin_amdgcn_ballot_w64(small || probe != probe) != 0 ? 1 : 0;
     if (lane == 0) verdicts[wave] = verdict;
     leave_statistics();
     __syncthreads();  // everyone is done with the query fragments
 #pragma unroll
     for (int w = 0; w < NW; ++w) verdict |= verdicts[w];
-    if (__builtin_expect((verdict & kRepeat) || (verdict & (kHasSums | kHasKeys)) == kHasKeys, 0)) {
+    if (__builtin_expect(verdict, 0)) {
       walk(std::false_type{});
       leave_statistics();
       __syncthreads();

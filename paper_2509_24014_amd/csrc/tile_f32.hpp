@@ -16,12 +16,12 @@
 // such inputs give what they give there. It can tell at little cost:
 //   logits  A query value below 2^-108 (and not zero) is short of bits, and one of 2^80 or more would show that a key value is
 //           (SplitRange, where the queries are split); with neither, a logit is off by 2^-47 at most.
-//   output  Probabilities add up to 2^-134 of an error for every value of V. A sum below 2^-90 (and not zero) may show it; so
-//           may one where every sum of the work-group is zero. Probabilities below 2^-108 of the row's largest are short of bits
-//           themselves; a tile that has any notes the largest value of V there, and the least sum that is good rises to 2^-92
-//           of it (2^16 keys that are off by 2^-134 each, 2^-26 of the sum). A sum of zero may be a column of zeros and is
-//           taken as it is, unless V has values of 2^32 or more at such probabilities.
-// What remains: a column of V whose values are all below 2^-126, beside larger columns, gives zeros.
+//   output  Probabilities add up to 2^-134 of an error for every value of V. A sum below 2^-90 (and not zero) may show it.
+//           Probabilities below 2^-108 of the row's largest are short of bits themselves; a tile that has any notes the largest
+//           value of V there, and the least sum that is good rises to 2^-92 of it (2^16 keys that are off by 2^-134 each, 2^-26
+//           of the sum). A sum of zero is good where V is zero: a wave with one reads its V again and asks for a repeat if a value
+//           is below 2^-108 and not zero, or may be 2^32 or more at such probabilities. Dense calls with columns of zeros, 8
+//           heads of 2000 x 128: 109 -> 124 us, 2 of 256 x 64 9.1 -> 10.0; V all zeros, which used to be a repeat, 218 -> 109, 16.2 -> 10.1.
 //
 // K and V go from global memory straight into the registers that feed the matrix cores: the vector memory path delivers
 // them with room to spare, and nothing is gained by passing a tile through LDS (and a barrier) to reorder it. Both products
@@ -98,15 +98,19 @@ struct SplitRange {
   static constexpr uint32_t kLeast = (127u - 108u) << 24;  // 2^-108, doubled bits
   uint32_t low = ~0u;                                      // least doubled bits less one: zero comes last
   float high = 0.f;
+  __device__ __forceinline__ void add_low(float v) {
+    const uint32_t u = (__float_as_uint(v) << 1) - 1u;
+    low = u < low ? u : low;
+  }
   __device__ __forceinline__ void add(f32x4 v) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const uint32_t u = (__float_as_uint(v[e]) << 1) - 1u;
-      low = u < low ? u : low;
+      add_low(v[e]);
       high = fmaxf(high, fabsf(v[e]));
     }
   }
-  __device__ __forceinline__ bool outside() const { return low < kLeast - 1u || !(high < 0x1p80f); }
+  __device__ __forceinline__ bool below() const { return low < kLeast - 1u; }
+  __device__ __forceinline__ bool outside() const { return below() || !(high < 0x1p80f); }
 };
 // acc += A . B, the six products of the parts that matter, smallest first
 __device__ __forceinline__ f32x16 mfma_split(const Split8& a, const Split8& b, f32x16 acc) {

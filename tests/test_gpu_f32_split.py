@@ -135,6 +135,22 @@ def test_small_values_keep_their_bits(e, H, L, keep, D):
             assert ((got - want).abs() <= 1e-5 * size).all()
 
 
+@pytest.mark.parametrize("H,L,keep", [(2, 300, 3), (20, 480, 8), (5, 2100, 30)])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("e", [-127, -132, -140])
+def test_small_columns_beside_ordinary_and_empty_ones(e, H, L, keep, D):
+    """A few columns of V below the smallest normal number, at -140 below the smallest part too: their sums are right to the resolution of
+    subnormal numbers and not zeros; columns of zeros, more of them in one head, stay zeros."""
+    q, k, v = _qkv(H, L, D, seed=L + D)
+    v[..., 3::16] = (v[..., 3::16] * 2.0 ** -64) * 2.0 ** (e + 64)
+    v[..., 8::16] = 0.0
+    v[:, 0, :, 1::2] = 0.0
+    for got, want, size in _all_calls(q, k, v, keep):
+        assert ((got - want).abs() <= 1e-5 * size + 2.0 ** -147).all()
+        assert (got[..., 8::16] == 0).all()
+        assert (got[:, 1:, :, 3::16].abs().amax((2, 3)) > 2.0 ** (e - 8)).all()
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("H,L", [(2, 300), (20, 480)])
 @pytest.mark.parametrize("e", [100, 112, 120, 125, -112, -125])
